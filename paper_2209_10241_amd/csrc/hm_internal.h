@@ -334,6 +334,9 @@ struct hm_graph {
   unsigned long long hs5_mask = 0;
   uint64_t n5 = 0;
   bool order5_built = false;
+  // bit tensors of the order-5 dense path (3 x n_nodes^2 x words), built on
+  // first use on small hypergraphs with bit rows
+  uint32_t* dense5 = nullptr;
   // raw counters of the sampled counting calls (kHistCopies copies of 256),
   // then the tail and head of their work queue (the two words after one
   // unused); zero between calls

@@ -96,6 +96,29 @@ def test_unbiased_over_seeds(hm):
     assert np.all(np.abs(z) < 4.5), np.abs(z).max()
 
 
+@pytest.mark.parametrize("n_nodes,n_edges", [(5, 12), (31, 400), (32, 400), (33, 500), (64, 300), (65, 700), (130, 900),
+                                            (1024, 1500), (1025, 1500)])
+def test_dense_path_matches_general(hm, n_nodes, n_edges):
+    """Hypergraphs of at most 1,024 nodes with bit rows take the bit-tensor
+    path: the same classes, counts and estimates as the general path (taken
+    without bit rows), around the edges of a bit row's words and of the rule;
+    some hyperedges drawn twice."""
+    h = W.random_small(9900 + n_nodes, n_nodes, n_edges, MIX, allow_dups=True)
+    nh = core.normalise(h)
+    rng = np.random.default_rng(n_nodes)
+    samples = {j: rng.integers(0, nh.count(j), size=min(nh.count(j), 40) + 3) for j in (2, 3, 4, 5) if nh.count(j)}
+    got = {}
+    for bits in (8192, 0):
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+        try:
+            with hm.hm_graph_create(h.members, h.offsets, h.n_nodes) as g:
+                got[bits] = hm.count_sampled5_indices(g, samples)
+        finally:
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+    for dense, general in zip(got[8192], got[0]):
+        assert np.array_equal(dense, general)
+
+
 def test_order5_errors(hm):
     h = W.random_small(9800, 12, 40, MIX)
     nh = core.normalise(h)
