@@ -176,8 +176,6 @@ uint64_t radix_ws_words(uint64_t n);
 int radix_sort_ws(unsigned long long* keys, uint32_t* vals, unsigned long long* keys_tmp, uint32_t* vals_tmp,
                   uint64_t n, int bits, uint32_t* ws, hipStream_t stream);
 int fill_u64(unsigned long long* p, unsigned long long value, uint64_t n, hipStream_t stream);
-// *out = max(*out, v[0..n)) (out zeroed by the caller)
-int max_u32(const uint32_t* v, uint64_t n, uint32_t* out, hipStream_t stream);
 
 // ----------------------------------------------------------------- profiling
 // While hm_profile_enable(1) is in effect, a scope records HIP events around
@@ -217,6 +215,23 @@ void dfree_on(void* const* ps, size_t n, hipStream_t st);
 // cache.
 int dalloc_filled(void** p, size_t bytes, bool* filled);
 void mark_filled(void* p);
+
+// Temporaries of one call, released in stream order (see dfree_on), also
+// when the call returns early on an error.
+struct Scratch {
+  std::vector<void*> ptrs;
+  hipStream_t st;
+  explicit Scratch(hipStream_t s) : st(s) {}
+  ~Scratch() { dfree_on(ptrs.data(), ptrs.size(), st); }
+  template <typename T>
+  int get(T** p, uint64_t n) {
+    void* q = nullptr;
+    HM_TRY(dalloc(&q, size_t(n ? n : 1) * sizeof(T)));
+    ptrs.push_back(q);
+    *p = static_cast<T*>(q);
+    return HM_OK;
+  }
+};
 
 // Order-k counts of the pairs-only shapes and of case (b) without bit rows
 // into H->hist (case (a) is counted by the caller).

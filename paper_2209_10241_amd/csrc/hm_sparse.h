@@ -116,30 +116,6 @@ __device__ inline uint32_t pl_codeg(const PairLinks& pl, uint32_t x, uint32_t y)
 
 __device__ inline uint32_t deg2_of(const View& v, uint32_t x) { return v.g2_off[x + 1] - v.g2_off[x]; }
 
-// |N(s) n N(x)| and, with y given, |N(s) n N(x) n N(y)|, over s's row (wave)
-__device__ inline void row_probe(const View& v, uint32_t s, uint32_t x, uint32_t y, uint32_t& cx, uint32_t& cy,
-                                 uint32_t& cxy) {
-  const int lane = threadIdx.x & (kWave - 1);
-  uint32_t nx = 0, ny = 0, nxy = 0;
-  for (uint32_t p = v.g2_off[s] + lane; p < v.g2_off[s + 1]; p += kWave) {
-    const uint32_t z = v.g2_adj[p];
-    const uint32_t hx = has2(v.hs2, x, z), hy = has2(v.hs2, y, z);
-    nx += hx;
-    ny += hy;
-    nxy += hx & hy;
-  }
-  cx = wave_sum_u32(nx);
-  cy = wave_sum_u32(ny);
-  cxy = wave_sum_u32(nxy);
-}
-
-__device__ inline uint32_t row_count(const View& v, uint32_t s, uint32_t x) {
-  const int lane = threadIdx.x & (kWave - 1);
-  uint32_t n = 0;
-  for (uint32_t p = v.g2_off[s] + lane; p < v.g2_off[s + 1]; p += kWave) n += has2(v.hs2, x, v.g2_adj[p]);
-  return wave_sum_u32(n);
-}
-
 // The hyperedge e = {a<b<c} with its pairwise pattern and the ranges of its
 // exceptional nodes: slot 0..2 the pair index entries of {a,b}, {a,c},
 // {b,c}; slot 3 the fourth nodes of the 4-node hyperedges holding e (with

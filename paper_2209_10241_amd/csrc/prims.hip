@@ -79,35 +79,42 @@ __global__ void k_scan_total(const T* in, const T* out, uint64_t n, T* total) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *total = n ? out[n - 1] + in[n - 1] : T(0);
 }
 
+// Multi-level exclusive scan of n values: level l scans the block sums of
+// level l-1, in ws (scan_ws_count(n) values).  No allocation and no host
+// synchronisation.
+uint64_t scan_ws_count(uint64_t n) {
+  uint64_t count = 0;
+  while (n > uint64_t(kScanTile)) {
+    n = (n + kScanTile - 1) / kScanTile;
+    count += 2 * n;    // block sums and their scan
+  }
+  return count + 1;
+}
+
 template <typename T>
-int scan_impl(const T* in, T* out, uint64_t n, hipStream_t st) {
+int scan_ws(const T* in, T* out, uint64_t n, T* ws, hipStream_t st) {
   if (n == 0) return HM_OK;
   const uint64_t nb = (n + kScanTile - 1) / kScanTile;
   if (nb == 1) {
     k_scan_tile<T><<<1, kScanThreads, 0, st>>>(in, out, nullptr, n);
+  } else {
+    T *sums = ws, *sums_scan = ws + nb;
+    k_scan_tile<T><<<unsigned(nb), kScanThreads, 0, st>>>(in, out, sums, n);
     HM_HIP(hipGetLastError());
-    return HM_OK;
+    HM_TRY(scan_ws<T>(sums, sums_scan, nb, ws + 2 * nb, st));
+    k_scan_add<T><<<unsigned((n + 255) / 256), 256, 0, st>>>(out, sums_scan, n);
   }
-  void* sums = nullptr;
-  void* sums_scan = nullptr;
-  HM_TRY(dalloc(&sums, nb * sizeof(T)));
-  int rc = dalloc(&sums_scan, nb * sizeof(T));
-  if (rc != HM_OK) {
-    dfree(sums);
-    return rc;
-  }
-  k_scan_tile<T><<<unsigned(nb), kScanThreads, 0, st>>>(in, out, static_cast<T*>(sums), n);
-  rc = (hipGetLastError() == hipSuccess) ? HM_OK : HM_EDEVICE;
-  if (rc == HM_OK) rc = scan_impl<T>(static_cast<T*>(sums), static_cast<T*>(sums_scan), nb, st);
-  if (rc == HM_OK) {
-    k_scan_add<T><<<unsigned((n + 255) / 256), 256, 0, st>>>(out, static_cast<T*>(sums_scan), n);
-    rc = (hipGetLastError() == hipSuccess) ? HM_OK : HM_EDEVICE;
-  }
-  (void)hipStreamSynchronize(st);
-  dfree(sums);
-  dfree(sums_scan);
-  if (rc == HM_EDEVICE) set_error("scan kernel launch failed");
-  return rc;
+  HM_HIP(hipGetLastError());
+  return HM_OK;
+}
+
+// The same with a workspace of its own, released in stream order.
+template <typename T>
+int scan_impl(const T* in, T* out, uint64_t n, hipStream_t st) {
+  Scratch tmp(st);
+  T* ws = nullptr;
+  if (n > uint64_t(kScanTile)) HM_TRY(tmp.get(&ws, scan_ws_count(n)));
+  return scan_ws<T>(in, out, n, ws, st);
 }
 
 // ------------------------------------------------------------------ radix sort
@@ -244,34 +251,14 @@ __global__ void k_copy(const T* __restrict__ src, T* __restrict__ dst, uint64_t 
 }  // namespace
 
 // ------------------------------------------------------------------ planned (workspace) variants
-// Multi-level exclusive scan of up to n uint32 values: level l scans the
-// block sums of level l-1.  No allocation and no host synchronisation.
-uint64_t scan_ws_words(uint64_t n) {
-  uint64_t words = 0;
-  while (n > uint64_t(kScanTile)) {
-    n = (n + kScanTile - 1) / kScanTile;
-    words += 2 * n;    // block sums and their scan
-  }
-  return words + 1;
-}
+uint64_t scan_ws_words(uint64_t n) { return scan_ws_count(n); }
 
 int scan_u32_ws(const uint32_t* in, uint32_t* out, uint64_t n, uint32_t* total_dev, uint32_t* ws, hipStream_t st) {
   if (n == 0) {
     if (total_dev) HM_TRY(fill_u32(total_dev, 0, 1, st));
     return HM_OK;
   }
-  const uint64_t nb = (n + kScanTile - 1) / kScanTile;
-  if (nb == 1) {
-    k_scan_tile<uint32_t><<<1, kScanThreads, 0, st>>>(in, out, nullptr, n);
-  } else {
-    uint32_t* sums = ws;
-    uint32_t* sums_scan = ws + nb;
-    k_scan_tile<uint32_t><<<unsigned(nb), kScanThreads, 0, st>>>(in, out, sums, n);
-    HM_HIP(hipGetLastError());
-    HM_TRY(scan_u32_ws(sums, sums_scan, nb, nullptr, ws + 2 * nb, st));
-    k_scan_add<uint32_t><<<unsigned((n + 255) / 256), 256, 0, st>>>(out, sums_scan, n);
-  }
-  HM_HIP(hipGetLastError());
+  HM_TRY(scan_ws<uint32_t>(in, out, n, ws, st));
   if (total_dev) {
     k_scan_total<uint32_t><<<1, 1, 0, st>>>(in, out, n, total_dev);
     HM_HIP(hipGetLastError());
@@ -350,77 +337,16 @@ int scan_exclusive_u64(const unsigned long long* in, unsigned long long* out, ui
 int radix_sort_pairs(unsigned long long* keys, uint32_t* vals, unsigned long long* keys_tmp, uint32_t* vals_tmp,
                      uint64_t n, int bits, hipStream_t st) {
   if (n <= 1 || bits <= 0) return HM_OK;
-  if (bits > 64) bits = 64;
-  const uint64_t nb64 = (n + kSortTile - 1) / kSortTile;
-  if (nb64 > 0xFFFFFFull) {
-    set_error("radix sort of %llu items is too large", (unsigned long long)n);
-    return HM_EUNSUPPORTED;
-  }
-  const uint32_t nb = uint32_t(nb64);
-  void* hist = nullptr;
-  void* offs = nullptr;
-  HM_TRY(dalloc(&hist, size_t(256) * nb * sizeof(uint32_t)));
-  int rc = dalloc(&offs, size_t(256) * nb * sizeof(uint32_t));
-  if (rc != HM_OK) {
-    dfree(hist);
-    return rc;
-  }
-  unsigned long long* src_k = keys;
-  uint32_t* src_v = vals;
-  unsigned long long* dst_k = keys_tmp;
-  uint32_t* dst_v = vals_tmp;
-  for (int shift = 0; shift < bits && rc == HM_OK; shift += 8) {
-    const int db = (bits - shift) < 8 ? (bits - shift) : 8;
-    const uint32_t mask = (1u << db) - 1u;
-    k_sort_hist<<<nb, kSortThreads, 0, st>>>(src_k, n, shift, mask, static_cast<uint32_t*>(hist), nb);
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-    if (rc == HM_OK)
-      rc = scan_exclusive_u32(static_cast<uint32_t*>(hist), static_cast<uint32_t*>(offs), uint64_t(256) * nb,
-                              nullptr, st);
-    if (rc == HM_OK) {
-      k_sort_scatter<<<nb, kSortThreads, 0, st>>>(src_k, src_v, dst_k, dst_v, n, shift, db,
-                                                  static_cast<const uint32_t*>(hist), static_cast<uint32_t*>(offs), nb);
-      if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-    }
-    std::swap(src_k, dst_k);
-    std::swap(src_v, dst_v);
-  }
-  if (rc == HM_OK && src_k != keys) {
-    if (hipMemcpyAsync(keys, src_k, n * sizeof(unsigned long long), hipMemcpyDeviceToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(vals, src_v, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st) != hipSuccess)
-      rc = HM_EDEVICE;
-  }
-  (void)hipStreamSynchronize(st);
-  dfree(hist);
-  dfree(offs);
-  if (rc == HM_EDEVICE) set_error("radix sort kernel failed");
-  return rc;
+  Scratch tmp(st);
+  uint32_t* ws = nullptr;
+  HM_TRY(tmp.get(&ws, radix_ws_words(n)));
+  return radix_sort_ws(keys, vals, keys_tmp, vals_tmp, n, bits, ws, st);
 }
 
 int fill_u32(uint32_t* p, uint32_t value, uint64_t n, hipStream_t st) { return fill_impl<uint32_t>(p, value, n, st); }
 
 int fill_u64(unsigned long long* p, unsigned long long value, uint64_t n, hipStream_t st) {
   return fill_impl<unsigned long long>(p, value, n, st);
-}
-
-__global__ void k_max_u32(const uint32_t* __restrict__ v, uint64_t n, uint32_t* out) {
-  uint32_t m = 0;
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
-    m = v[i] > m ? v[i] : m;
-  for (int d = kWave / 2; d > 0; d >>= 1) {
-    const uint32_t o = __shfl_xor(m, d, kWave);
-    m = o > m ? o : m;
-  }
-  if ((threadIdx.x & (kWave - 1)) == 0 && m) atomicMax(out, m);
-}
-
-int max_u32(const uint32_t* v, uint64_t n, uint32_t* out, hipStream_t st) {
-  if (!n) return HM_OK;
-  uint64_t g = (n + 255) / 256;
-  if (g > 1024) g = 1024;
-  k_max_u32<<<unsigned(g), 256, 0, st>>>(v, n, out);
-  HM_HIP(hipGetLastError());
-  return HM_OK;
 }
 
 }  // namespace hm

@@ -1206,8 +1206,8 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   }
   if (k == 4 && !bits) {
     HM_TRY(ensure_pair_links(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_node_stats(const_cast<hm_graph*>(H), st));
     HM_TRY(ensure_edge_stats(const_cast<hm_graph*>(H), st));
+    HM_TRY(ensure_node_stats(const_cast<hm_graph*>(H), st));
     HM_TRY(ensure_hub_rows(const_cast<hm_graph*>(H), st));
   }
   SampledArgs a;

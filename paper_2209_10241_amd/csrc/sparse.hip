@@ -10,28 +10,22 @@
 //       connected k-node sets of the pairwise graph G2 per induced shape
 //       follows from non-induced subgraph counts: 3-stars sum C(d,3),
 //       3-paths sum over edges (d_u-1)(d_v-1) - 3T, paws sum t_v (d_v-2),
-//       diamonds sum over edges C(t_e,2), 4-cycles and 4-cliques by
-//       degree-ordered enumeration, inverted through the matrix of how often
-//       each shape contains another; then the sets that (a) or (b) own are
-//       subtracted by shape.
-// Degree order: x precedes y when (deg x, x) < (deg y, y); a node's
-// neighbours that follow it number at most sqrt(2 |E2|).
+//       diamonds sum over edges C(t_e,2), triangles, 4-cycles and 4-cliques
+//       by degree-ordered walks (wedge.hip), inverted through the matrix of
+//       how often each shape contains another; then the sets that (a) or (b)
+//       own are subtracted by shape.
 #include <algorithm>
 #include <map>
 #include <mutex>
 #include <vector>
 
 #include "hm_sparse.h"
+#include "hm_wedge.h"
 
 namespace hm {
 namespace {
 
-enum : int { kAccT3 = 0, kAccDiamond, kAccP4, kAccStar, kAccPaw, kAccC4, kAccK4, kAccWedge, kAccN };
-
-__device__ inline bool rank_less(const View& v, uint32_t x, uint32_t y) {
-  const uint32_t dx = deg2_of(v, x), dy = deg2_of(v, y);
-  return dx < dy || (dx == dy && x < y);
-}
+enum : int { kAccT3 = 0, kAccDiamond, kAccP4, kAccPaw2, kAccStar, kAccWedge, kAccC4, kAccK4, kAccN };
 
 // sum of x over the workgroup, added to *out by one thread
 __device__ inline void block_add(unsigned long long x, unsigned long long* out) {
@@ -48,345 +42,36 @@ __device__ inline void block_add(unsigned long long x, unsigned long long* out) 
   __syncthreads();
 }
 
-// Triangles on each pair {a, b} of G2: t_e = |N(a) n N(b)| over the smaller
-// row.  tv[x] collects sum of t_e over the pairs at x (= 2 t_x).
-__global__ void __launch_bounds__(kThreads) k_sp_edge_tri(View v, uint64_t n2, uint32_t* __restrict__ tri_e,
-                                                          unsigned long long* __restrict__ tv,
-                                                          unsigned long long* __restrict__ acc) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint64_t wave = uint64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-  const uint64_t n_waves = uint64_t(gridDim.x) * kWavesPerBlock;
-  unsigned long long st = 0, sd = 0, sp = 0;
-  for (uint64_t e = wave; e < n2; e += n_waves) {
-    const uint32_t a = v.e2[2 * e], b = v.e2[2 * e + 1];
-    const uint32_t da = deg2_of(v, a), db = deg2_of(v, b);
-    const uint32_t s = da <= db ? a : b, o = da <= db ? b : a;
-    const uint32_t t = row_count(v, s, o);
-    if (lane == 0) {
-      tri_e[e] = t;
-      if (t) {
-        atomicAdd(&tv[a], (unsigned long long)t);
-        atomicAdd(&tv[b], (unsigned long long)t);
-      }
-      st += t;
-      sd += (unsigned long long)t * (t - 1) / 2;
-      sp += (unsigned long long)(da - 1) * (db - 1);
-    }
+// Per pair {a, b} of G2, from its triangles t: t (3 x triangles), C(t, 2)
+// (diamonds through their diagonal), (d_a - 1)(d_b - 1) (3-paths, plus 3 x
+// triangles), t (d_a + d_b - 4) (twice the paws).
+__global__ void __launch_bounds__(kThreads) k_sp_pairs(View v, uint64_t n2, const uint32_t* __restrict__ tri_e,
+                                                       unsigned long long* __restrict__ acc) {
+  unsigned long long st = 0, sd = 0, sp = 0, sw = 0;
+  for (uint64_t e = uint64_t(blockIdx.x) * kThreads + threadIdx.x; e < n2; e += uint64_t(gridDim.x) * kThreads) {
+    const unsigned long long t = tri_e[e];
+    const unsigned long long da = deg2_of(v, v.e2[2 * e]), db = deg2_of(v, v.e2[2 * e + 1]);
+    st += t;
+    sd += t * (t - (t > 0)) / 2;
+    sp += (da - 1) * (db - 1);
+    if (t) sw += t * (da + db - 4);   // (then both degrees are at least 2)
   }
   block_add(st, acc + kAccT3);
   block_add(sd, acc + kAccDiamond);
   block_add(sp, acc + kAccP4);
+  block_add(sw, acc + kAccPaw2);
 }
 
-// Per node: C(d,3) (3-stars), C(d,2) (wedges), t_x (d - 2) (paws).
-__global__ void __launch_bounds__(kThreads) k_sp_nodes(View v, const unsigned long long* __restrict__ tv,
-                                                       unsigned long long* __restrict__ acc) {
-  unsigned long long s3 = 0, s2 = 0, sp = 0;
+// Per node: C(d,3) (3-stars), C(d,2) (wedges).
+__global__ void __launch_bounds__(kThreads) k_sp_nodes(View v, unsigned long long* __restrict__ acc) {
+  unsigned long long s3 = 0, s2 = 0;
   for (uint32_t x = blockIdx.x * kThreads + threadIdx.x; x < v.N; x += gridDim.x * kThreads) {
     const unsigned long long d = deg2_of(v, x);
-    if (d >= 2) {
-      s2 += d * (d - 1) / 2;
-      sp += (tv[x] / 2) * (d - 2);
-    }
+    if (d >= 2) s2 += d * (d - 1) / 2;
     if (d >= 3) s3 += d * (d - 1) / 2 * (d - 2) / 3;
   }
   block_add(s3, acc + kAccStar);
   block_add(s2, acc + kAccWedge);
-  block_add(sp, acc + kAccPaw);
-}
-
-
-// 4-cycles without atomics per wedge: every wedge (u, x, w) with x and w
-// before the top node u in degree order becomes the key (u << B) | w; sorted,
-// each run of equal keys holds the middle nodes of one (u, w) and adds
-// C(run, 2) cycles.  Each pair {x, u} of G2 (x the earlier) walks the row of x,
-// so the walked positions are laid out flat, pair after pair, and cut into
-// tiles of kC4Tile positions that span at most kC4Tile + 1 pairs (every row
-// walked is non-empty).  Positions that are not wedges get the key kC4None.
-constexpr unsigned long long kC4None = ~0ull;
-constexpr uint32_t kC4Tile = 2048;
-
-// Walked positions of each pair (the degree of its earlier node) and their sum.
-__global__ void k_c4_len(View v, uint64_t n2, uint32_t* __restrict__ len, unsigned long long* __restrict__ total) {
-  unsigned long long s = 0;
-  for (uint64_t e = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n2; e += uint64_t(gridDim.x) * blockDim.x) {
-    const uint32_t a = v.e2[2 * e], b = v.e2[2 * e + 1];
-    const uint32_t d = deg2_of(v, rank_less(v, a, b) ? a : b);
-    len[e] = d;
-    s += d;
-  }
-  block_add(s, total);
-}
-
-// The pair that holds the first position of each tile (pos = exclusive scan of len).
-__global__ void k_c4_tile_starts(const uint32_t* __restrict__ pos, const uint32_t* __restrict__ len, uint64_t n2,
-                                 uint32_t* __restrict__ start) {
-  for (uint64_t e = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n2; e += uint64_t(gridDim.x) * blockDim.x) {
-    const uint64_t lo = pos[e], hi = lo + len[e];
-    for (uint64_t t = (lo + kC4Tile - 1) / kC4Tile; t * kC4Tile < hi; ++t) start[t] = uint32_t(e);
-  }
-}
-
-// One workgroup per tile: the tile's pairs are staged in LDS (start offset,
-// top node, row of the earlier node) and each position finds its pair there.
-__global__ void __launch_bounds__(kThreads) k_c4_keys(View v, int B, const uint32_t* __restrict__ pos,
-                                                      const uint32_t* __restrict__ start, uint64_t n2,
-                                                      uint32_t n_pos, uint32_t n_tiles,
-                                                      unsigned long long* __restrict__ keys,
-                                                      uint32_t* __restrict__ vals) {
-  __shared__ uint32_t s_pos[kC4Tile + 2], s_top[kC4Tile + 2], s_row[kC4Tile + 2];
-  const uint32_t tid = threadIdx.x, t = blockIdx.x;
-  const uint32_t p0 = t * kC4Tile;
-  const uint32_t p1 = n_pos - p0 < kC4Tile ? n_pos : p0 + kC4Tile;
-  const uint32_t c0 = start[t];
-  const uint32_t c1 = t + 1 < n_tiles ? start[t + 1] : uint32_t(n2 - 1);
-  const uint32_t cnt = c1 - c0 + 1;   // at most kC4Tile + 1
-  for (uint32_t i = tid; i < cnt; i += kThreads) {
-    const uint32_t e = c0 + i, a = v.e2[2 * uint64_t(e)], b = v.e2[2 * uint64_t(e) + 1];
-    const bool ab = rank_less(v, a, b);
-    s_pos[i] = pos[e];
-    s_top[i] = ab ? b : a;
-    s_row[i] = v.g2_off[ab ? a : b];
-  }
-  __syncthreads();
-  for (uint32_t p = p0 + tid; p < p1; p += kThreads) {
-    uint32_t lo = 0, hi = cnt;   // s_pos[lo] <= p < s_pos[hi]
-    while (hi - lo > 1) {
-      const uint32_t m = (lo + hi) >> 1;
-      if (s_pos[m] <= p) lo = m; else hi = m;
-    }
-    const uint32_t u = s_top[lo], w = v.g2_adj[s_row[lo] + (p - s_pos[lo])];
-    keys[p] = (w == u || !rank_less(v, w, u)) ? kC4None : ((unsigned long long)u << B) | (unsigned long long)w;
-    vals[p] = p;
-  }
-}
-
-// Per-pair 4-cycle counts from the sorted wedge keys (vals: the walked
-// position of each key): a wedge (u, x, w) in a run of r >= 2 equal keys
-// closes r - 1 cycles, one with each other middle node of the run, and each
-// holds its pairs {u, x} (the pair whose walk the position belongs to) and
-// {x, w} (x's row entry).  One thread per key: it finds its run's ends by
-// galloping search (runs of hub pairs are long, most runs hold one key).
-__device__ inline uint64_t run_end(const unsigned long long* keys, uint64_t n, uint64_t i, unsigned long long key) {
-  uint64_t step = 1, lo = i;   // keys[lo] == key
-  while (lo + step < n && keys[lo + step] == key) {
-    lo += step;
-    step <<= 1;
-  }
-  uint64_t hi = min<uint64_t>(n, lo + step);   // keys[hi] != key or hi == n
-  while (hi - lo > 1) {
-    const uint64_t m = lo + ((hi - lo) >> 1);
-    if (keys[m] == key) lo = m; else hi = m;
-  }
-  return hi;
-}
-__device__ inline uint64_t run_begin(const unsigned long long* keys, uint64_t i, unsigned long long key) {
-  uint64_t step = 1, hi = i;   // keys[hi] == key
-  while (hi >= step && keys[hi - step] == key) {
-    hi -= step;
-    step <<= 1;
-  }
-  uint64_t lo = hi >= step ? hi - step : 0;   // keys[lo] != key, or lo == 0
-  if (keys[lo] == key) return lo;
-  while (hi - lo > 1) {
-    const uint64_t m = lo + ((hi - lo) >> 1);
-    if (keys[m] == key) hi = m; else lo = m;
-  }
-  return hi;
-}
-
-__global__ void k_c4_pair_counts(View v, const unsigned long long* __restrict__ keys, const uint32_t* __restrict__ vals,
-                                 uint64_t n, const uint32_t* __restrict__ pos, const uint32_t* __restrict__ start,
-                                 uint64_t n2, const uint32_t* __restrict__ eid, unsigned long long* __restrict__ c4e) {
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x) {
-    const unsigned long long key = keys[i];
-    if (key == kC4None) continue;
-    const bool prev = i > 0 && keys[i - 1] == key, next = i + 1 < n && keys[i + 1] == key;
-    if (!prev && !next) continue;   // a run of one closes no cycle
-    const unsigned long long c = run_end(keys, n, i, key) - run_begin(keys, i, key) - 1;
-    const uint32_t p = vals[i];
-    // the pair whose walk holds position p: from the first pair of p's tile
-    uint64_t a = start[p / kC4Tile], b = min<uint64_t>(n2, a + kC4Tile + 2);   // pos[a] <= p < pos[b]
-    while (b - a > 1) {
-      const uint64_t m = (a + b) >> 1;
-      if (pos[m] <= p) a = m; else b = m;
-    }
-    const uint32_t x0 = v.e2[2 * a], x1 = v.e2[2 * a + 1];
-    const uint32_t x = rank_less(v, x0, x1) ? x0 : x1;
-    atomicAdd(&c4e[a], c);
-    atomicAdd(&c4e[eid[v.g2_off[x] + (p - pos[a])]], c);
-  }
-}
-
-// Sum of C(run, 2) over the runs of equal keys (kC4None excluded) of the
-// sorted keys[0, n).
-__global__ void k_c4_runs(const unsigned long long* __restrict__ keys, uint64_t n, unsigned long long none,
-                          unsigned long long* __restrict__ acc) {
-  unsigned long long s = 0;
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x) {
-    const unsigned long long key = keys[i];
-    if (key == none || (i > 0 && keys[i - 1] == key)) continue;
-    uint64_t lo = i, hi = n;   // keys[lo] == key, keys[hi] != key (or hi = n)
-    while (hi - lo > 1) {
-      const uint64_t m = lo + ((hi - lo) >> 1);
-      if (keys[m] == key) lo = m; else hi = m;
-    }
-    const unsigned long long run = hi - i;
-    s += run * (run - 1) / 2;
-  }
-  block_add(s, acc);
-}
-
-int node_bits_of(uint32_t n) {
-  int b = 1;
-  while (b < 32 && (1ull << b) < n) ++b;
-  return b;
-}
-
-// The sorted wedge keys of the 4-cycle count (see k_c4_keys).
-struct C4Keys {
-  unsigned long long* keys = nullptr;   // ascending, n_keys
-  uint32_t* vals = nullptr;             // the walked position of each key
-  uint32_t* pos = nullptr;              // first position of each pair of G2
-  uint32_t* start = nullptr;            // first pair of each tile of positions
-  uint64_t n_keys = 0;
-};
-
-// Neighbours that follow each node in degree order (outdeg zeroed by the caller).
-__global__ void k_sp_outdeg(View v, uint64_t n2, uint32_t* __restrict__ outdeg) {
-  for (uint64_t e = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n2; e += uint64_t(gridDim.x) * blockDim.x) {
-    const uint32_t a = v.e2[2 * e], b = v.e2[2 * e + 1];
-    atomicAdd(&outdeg[rank_less(v, a, b) ? a : b], 1u);
-  }
-}
-
-// 4-cliques: for each pair {lo, hi} of G2 (lo before hi in degree order),
-// W = common neighbours after hi; every pair of W joined by a pair of G2
-// closes one 4-clique, found once at its first two nodes.  One wavefront per
-// pair; W goes to a per-wavefront list of cap entries.
-__device__ inline uint32_t row_pos(const View& v, uint32_t r, uint32_t x) {
-  uint32_t lo = v.g2_off[r], hi = v.g2_off[r + 1];
-  while (lo < hi) {
-    const uint32_t m = lo + ((hi - lo) >> 1);
-    if (v.g2_adj[m] < x) lo = m + 1; else hi = m;
-  }
-  return lo;
-}
-
-template <bool PER_EDGE>
-__global__ void __launch_bounds__(kThreads) k_sp_k4(View v, uint64_t n2, uint32_t cap, uint32_t* __restrict__ wlist,
-                                                    unsigned long long* __restrict__ acc,
-                                                    const uint32_t* __restrict__ eid,
-                                                    unsigned long long* __restrict__ k4e) {
-  const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint64_t wave = uint64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-  const uint64_t n_waves = uint64_t(gridDim.x) * kWavesPerBlock;
-  uint32_t* W = wlist + wave * cap * (PER_EDGE ? 2 : 1);
-  uint32_t* Wp = W + cap;   // position of each W entry in lo's row (PER_EDGE)
-  unsigned long long total = 0;
-  for (uint64_t e = wave; e < n2; e += n_waves) {
-    uint32_t lo = v.e2[2 * e], hi = v.e2[2 * e + 1];
-    if (rank_less(v, hi, lo)) {
-      const uint32_t t = lo;
-      lo = hi;
-      hi = t;
-    }
-    uint32_t nw = 0;
-    for (uint32_t p0 = v.g2_off[lo]; p0 < v.g2_off[lo + 1]; p0 += kWave) {
-      const uint32_t p = p0 + lane;
-      bool keep = false;
-      uint32_t w = 0;
-      if (p < v.g2_off[lo + 1]) {
-        w = v.g2_adj[p];
-        keep = rank_less(v, hi, w) && has2(v.hs2, hi, w);
-      }
-      const unsigned long long m = __ballot(keep);
-      if (keep) {
-        const uint32_t slot = nw + uint32_t(__popcll(m & ((1ull << lane) - 1ull)));
-        W[slot] = w;
-        if (PER_EDGE) Wp[slot] = p;
-      }
-      nw += uint32_t(__popcll(m));
-    }
-    wave_sync();
-    if (PER_EDGE) {
-      // Each lane owns slots s and counts, over every other slot t, the
-      // cliques {lo, hi, w_s, w_t}: the pairs {lo, w_s} and {hi, w_s} take
-      // that count once, the pair {w_s, w_t} one per clique (from s < t), and
-      // {lo, hi} the wavefront's total over the slots, halved.
-      unsigned long long twice = 0;
-      for (uint32_t s = lane; s < nw; s += kWave) {
-        const uint32_t ws = W[s];
-        uint32_t cs = 0;
-        for (uint32_t t = 0; t < nw; ++t) {
-          const uint32_t wt = W[t];
-          if (t == s || !has2(v.hs2, ws, wt)) continue;
-          ++cs;
-          if (s < t) {
-            const bool sw = deg2_of(v, ws) <= deg2_of(v, wt);
-            atomicAdd(&k4e[eid[sw ? row_pos(v, ws, wt) : row_pos(v, wt, ws)]], 1ull);
-          }
-        }
-        if (cs) {
-          atomicAdd(&k4e[eid[Wp[s]]], (unsigned long long)cs);
-          atomicAdd(&k4e[eid[row_pos(v, hi, ws)]], (unsigned long long)cs);
-          twice += cs;
-        }
-      }
-      twice = wave_sum(twice);
-      if (lane == 0 && twice) atomicAdd(&k4e[e], twice / 2);
-      total += twice / 2;
-    } else {
-      uint32_t c = 0;
-      for (uint32_t i = 0; i + 1 < nw; ++i) {
-        const uint32_t wi = W[i];
-        for (uint32_t j = i + 1 + lane; j < nw; j += kWave) {
-          if (has2(v.hs2, wi, W[j])) ++c;
-        }
-      }
-      total += wave_sum_u32(c);
-    }
-    wave_sync();
-  }
-  if (lane == 0) atomicAdd(acc + kAccK4, total);
-}
-
-// Per pair e = {u < w}: over the common neighbours x, the sums of t_{ux},
-// t_{wx} and deg x (the smaller row walked, the other row searched).
-__global__ void __launch_bounds__(kThreads) k_es_sums(View v, uint64_t n2, const uint32_t* __restrict__ eid,
-                                                      const uint32_t* __restrict__ tri_e,
-                                                      unsigned long long* __restrict__ su,
-                                                      unsigned long long* __restrict__ sw,
-                                                      unsigned long long* __restrict__ sd) {
-  const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint64_t wave = uint64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-  const uint64_t n_waves = uint64_t(gridDim.x) * kWavesPerBlock;
-  for (uint64_t e = wave; e < n2; e += n_waves) {
-    const uint32_t u = v.e2[2 * e], w = v.e2[2 * e + 1];
-    const bool walk_u = deg2_of(v, u) <= deg2_of(v, w);
-    const uint32_t r = walk_u ? u : w, o = walk_u ? w : u;
-    unsigned long long a = 0, b = 0, c = 0;   // sums over the walked and the searched side
-    for (uint32_t p = v.g2_off[r] + lane; p < v.g2_off[r + 1]; p += kWave) {
-      const uint32_t x = v.g2_adj[p];
-      if (!has2(v.hs2, o, x)) continue;
-      a += tri_e[eid[p]];
-      b += tri_e[eid[row_pos(v, o, x)]];
-      c += deg2_of(v, x);
-    }
-    a = wave_sum(a);
-    b = wave_sum(b);
-    c = wave_sum(c);
-    if (lane == 0) {
-      su[e] = walk_u ? a : b;
-      sw[e] = walk_u ? b : a;
-      sd[e] = c;
-    }
-  }
-}
-
-__global__ void k_es_widen(const uint32_t* __restrict__ t32, uint64_t n, unsigned long long* __restrict__ t64) {
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
-    t64[i] = t32[i];
 }
 
 // (b) at order 4 without bit rows: one wavefront per 3-node hyperedge, taken
@@ -475,7 +160,7 @@ __global__ void k_sp_shapes(const unsigned long long* __restrict__ acc, int k, S
   const unsigned long long k4 = acc[kAccK4];
   const unsigned long long dia = acc[kAccDiamond] - 6 * k4;
   const unsigned long long cyc = acc[kAccC4] - dia - 3 * k4;
-  const unsigned long long paw = acc[kAccPaw] - 4 * dia - 12 * k4;
+  const unsigned long long paw = acc[kAccPaw2] / 2 - 4 * dia - 12 * k4;
   const unsigned long long star = acc[kAccStar] - paw - 2 * dia - 4 * k4;
   const unsigned long long path = (acc[kAccP4] - 3 * T) - 4 * cyc - 2 * paw - 6 * dia - 12 * k4;
   hist[kG2 + cls.clique] = k4;
@@ -596,78 +281,11 @@ __global__ void k_pl_codeg(View v, const unsigned long long* __restrict__ keys, 
   }
 }
 
-// Temporaries of one call, released in stream order (see dfree_on), also
-// when the call returns early on an error.
-struct Scratch {
-  std::vector<void*> ptrs;
-  hipStream_t st;
-  explicit Scratch(hipStream_t s) : st(s) {}
-  ~Scratch() { dfree_on(ptrs.data(), ptrs.size(), st); }
-  template <typename T>
-  int get(T** p, uint64_t n) {
-    void* q = nullptr;
-    HM_TRY(dalloc(&q, size_t(n ? n : 1) * sizeof(T)));
-    ptrs.push_back(q);
-    *p = static_cast<T*>(q);
-    return HM_OK;
-  }
-};
-
 unsigned grid_cap(uint64_t items, uint64_t per_block, unsigned cap) {
   uint64_t g = (items + per_block - 1) / per_block;
   return unsigned(std::max<uint64_t>(1, std::min<uint64_t>(g, cap)));
 }
 
-
-// The wedge keys of the 4-cycle count, built and sorted into scratch (one
-// host read-back: the number of walked positions).
-int c4_sorted_keys(const hm_graph* H, hipStream_t st, Scratch& tmp, C4Keys* out) {
-  const View v = view_of(H);
-  const uint64_t n2 = H->n_by_size[2];
-  *out = C4Keys{};
-  if (!n2) return HM_OK;
-  unsigned long long* walk = nullptr;
-  uint32_t* len = nullptr;
-  HM_TRY(tmp.get(&walk, 1));
-  HM_TRY(tmp.get(&len, n2));
-  HM_TRY(tmp.get(&out->pos, n2));
-  HM_TRY(fill_u64(walk, 0, 1, st));
-  k_c4_len<<<grid_cap(n2, 256, 2048), 256, 0, st>>>(v, n2, len, walk);
-  HM_HIP(hipGetLastError());
-  unsigned long long n_keys = 0;
-  HM_HIP(hipMemcpyAsync(&n_keys, walk, sizeof(n_keys), hipMemcpyDeviceToHost, st));
-  HM_HIP(hipStreamSynchronize(st));
-  const int B = node_bits_of(H->n_nodes);
-  if (n_keys >= 0xFFFFFFFFull || 2 * B > 63 || n2 >= 0xFFFFFFFFull) {
-    set_error("4-cycle wedges of %llu positions exceed the sort's range", n_keys);
-    return HM_EUNSUPPORTED;
-  }
-  if (!n_keys) return HM_OK;
-  const uint32_t n_tiles = uint32_t((n_keys + kC4Tile - 1) / kC4Tile);
-  unsigned long long* keys_tmp = nullptr;
-  uint32_t* vals_tmp = nullptr;
-  HM_TRY(tmp.get(&out->start, n_tiles));
-  HM_TRY(tmp.get(&out->keys, n_keys));
-  HM_TRY(tmp.get(&keys_tmp, n_keys));
-  HM_TRY(tmp.get(&out->vals, n_keys));
-  HM_TRY(tmp.get(&vals_tmp, n_keys));
-  HM_TRY(scan_exclusive_u32(len, out->pos, n2, nullptr, st));
-  k_c4_tile_starts<<<grid_cap(n2, 256, 4096), 256, 0, st>>>(out->pos, len, n2, out->start);
-  HM_HIP(hipGetLastError());
-  {
-    ProfileScope ps("k_c4_keys", st);
-    k_c4_keys<<<n_tiles, kThreads, 0, st>>>(v, B, out->pos, out->start, n2, uint32_t(n_keys), n_tiles, out->keys,
-                                           out->vals);
-  }
-  HM_HIP(hipGetLastError());
-  // the positions that are not wedges carry all ones and sort last
-  {
-    ProfileScope ps("c4_sort", st);
-    HM_TRY(radix_sort_pairs(out->keys, out->vals, keys_tmp, vals_tmp, n_keys, 2 * B + 1, st));
-  }
-  out->n_keys = n_keys;
-  return HM_OK;
-}
 
 // Workgroups of kThreads threads (no dynamic LDS) of `kernel` resident on the
 // current device at once.
@@ -691,17 +309,43 @@ unsigned resident_blocks(const void* kernel) {
 
 namespace {
 
-__global__ void k_ns_half(const unsigned long long* __restrict__ tv, uint32_t n, unsigned long long* __restrict__ tri) {
-  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) tri[x] = tv[x] / 2;
+// Per node, over its adjacency row: the sum of the neighbours' degrees, and
+// of its pairs' triangles (twice the triangles at the node).  A wavefront
+// takes 64 consecutive entries, sums them by row with a segmented scan, and
+// each row's last lane adds once.
+__global__ void k_ns_rows(View v, uint64_t m, const uint32_t* __restrict__ eid, const unsigned long long* __restrict__ tri_e,
+                          unsigned long long* __restrict__ nbr, unsigned long long* __restrict__ tri2) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  for (uint64_t base = (uint64_t(blockIdx.x) * blockDim.x + threadIdx.x) & ~uint64_t(kWave - 1); base < m;
+       base += uint64_t(gridDim.x) * blockDim.x) {
+    const uint64_t i = base + lane;
+    uint32_t owner = 0xFFFFFFFFu;
+    unsigned long long d = 0, t = 0;
+    if (i < m) {
+      const uint32_t z = v.g2_adj[i];
+      const uint64_t e = eid[i];
+      owner = v.e2[2 * e] ^ v.e2[2 * e + 1] ^ z;
+      d = deg2_of(v, z);
+      t = tri_e[e];
+    }
+    for (int s = 1; s < kWave; s <<= 1) {
+      const uint32_t o = uint32_t(__shfl_up(int(owner), s, kWave));
+      const unsigned long long dd = __shfl_up(d, s, kWave), tt = __shfl_up(t, s, kWave);
+      if (int(lane) >= s && o == owner) {   // (a row's entries are consecutive)
+        d += dd;
+        t += tt;
+      }
+    }
+    const uint32_t after = uint32_t(__shfl_down(int(owner), 1, kWave));
+    if (i < m && (lane == kWave - 1 || after != owner)) {
+      atomicAdd(&nbr[owner], d);
+      if (t) atomicAdd(&tri2[owner], t);
+    }
+  }
 }
 
-// sum of the neighbours' degrees, per node
-__global__ void k_ns_nbr(View v, uint64_t n2, unsigned long long* __restrict__ nbr) {
-  for (uint64_t e = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n2; e += uint64_t(gridDim.x) * blockDim.x) {
-    const uint32_t a = v.e2[2 * e], b = v.e2[2 * e + 1];
-    atomicAdd(&nbr[a], (unsigned long long)deg2_of(v, b));
-    atomicAdd(&nbr[b], (unsigned long long)deg2_of(v, a));
-  }
+__global__ void k_ns_half(unsigned long long* __restrict__ tri, uint32_t n) {
+  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) tri[x] /= 2;
 }
 
 // per node o, its 3-node hyperedges {o, y, z} (y < z) by (o~y, o~z, y~z)
@@ -717,22 +361,31 @@ __global__ void k_ns_h3(View v, uint64_t n3, uint32_t* __restrict__ h3) {
 
 }  // namespace
 
+// Per-pair statistics of H for the pair sampler without bit rows (layout in
+// hm_graph::es), built on first use.
+int ensure_edge_stats(hm_graph* H, hipStream_t st) {
+  note_use(H, st);
+  if (H->es) return HM_OK;
+  void* es = nullptr;
+  HM_TRY(dalloc(&es, 6 * std::max<uint64_t>(H->n_by_size[2], 1) * sizeof(unsigned long long)));
+  const int rc = wedge_edge_stats(H, static_cast<unsigned long long*>(es), st);
+  if (rc != HM_OK) {
+    dfree_on(es, st);
+    return rc;
+  }
+  H->es = static_cast<unsigned long long*>(es);
+  return HM_OK;
+}
+
 // Per-node statistics of H for the pair samplers without bit rows, built on
-// first use: triangles at each node, the sum of its neighbours' degrees, and
-// its 3-node hyperedges by pairwise pattern.
+// first use (after the per-pair ones): triangles at each node, the sum of its
+// neighbours' degrees, and its 3-node hyperedges by pairwise pattern.
 int ensure_node_stats(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->ns_tri) return HM_OK;
+  HM_TRY(ensure_edge_stats(H, st));
   const View v = view_of(H);
   const uint64_t n2 = H->n_by_size[2], n3 = H->n_by_size[3], N = H->n_nodes;
-  Scratch tmp(st);
-  unsigned long long *acc = nullptr, *tv = nullptr;
-  uint32_t* tri_e = nullptr;
-  HM_TRY(tmp.get(&acc, kAccN));
-  HM_TRY(tmp.get(&tv, N));
-  HM_TRY(tmp.get(&tri_e, n2));
-  HM_TRY(fill_u64(acc, 0, kAccN, st));
-  HM_TRY(fill_u64(tv, 0, N, st));
   void *p_tri = nullptr, *p_nbr = nullptr, *p_h3 = nullptr;
   int rc = dalloc(&p_tri, N * sizeof(unsigned long long));
   if (rc == HM_OK) rc = dalloc(&p_nbr, N * sizeof(unsigned long long));
@@ -740,85 +393,26 @@ int ensure_node_stats(hm_graph* H, hipStream_t st) {
   auto* tri = static_cast<unsigned long long*>(p_tri);
   auto* nbr = static_cast<unsigned long long*>(p_nbr);
   auto* h3 = static_cast<uint32_t*>(p_h3);
+  if (rc == HM_OK) rc = fill_u64(tri, 0, N, st);
   if (rc == HM_OK) rc = fill_u64(nbr, 0, N, st);
   if (rc == HM_OK) rc = fill_u32(h3, 0, 8 * N, st);
   if (rc == HM_OK) {
-    if (n2) k_sp_edge_tri<<<grid_cap(n2, kWavesPerBlock, 2048), kThreads, 0, st>>>(v, n2, tri_e, tv, acc);
-    k_ns_half<<<grid_cap(N, 256, 1024), 256, 0, st>>>(tv, uint32_t(N), tri);
-    if (n2) k_ns_nbr<<<grid_cap(n2, 256, 2048), 256, 0, st>>>(v, n2, nbr);
+    if (n2) k_ns_rows<<<grid_cap(2 * n2, 256, 4096), 256, 0, st>>>(v, 2 * n2, H->g2_eid, H->es, nbr, tri);
+    k_ns_half<<<grid_cap(N, 256, 1024), 256, 0, st>>>(tri, uint32_t(N));
     if (n3) k_ns_h3<<<grid_cap(n3, 256, 2048), 256, 0, st>>>(v, n3, h3);
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
+    if (hipGetLastError() != hipSuccess) {
+      set_error("per-node statistics: kernel launch failed");
+      rc = HM_EDEVICE;
+    }
   }
-  if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
   if (rc != HM_OK) {
-    dfree(p_tri);
-    dfree(p_nbr);
-    dfree(p_h3);
+    void* ps[] = {p_tri, p_nbr, p_h3};
+    dfree_on(ps, 3, st);
     return rc;
   }
   H->ns_tri = tri;
   H->ns_nbr = nbr;
   H->ns_h3 = h3;
-  return HM_OK;
-}
-
-// Per-pair statistics of H for the pair sampler without bit rows (layout in
-// hm_graph::es), built on first use.
-int ensure_edge_stats(hm_graph* H, hipStream_t st) {
-  note_use(H, st);
-  if (H->es) return HM_OK;
-  const View v = view_of(H);
-  const uint64_t n2 = H->n_by_size[2], N = H->n_nodes;
-  void* p_es = nullptr;
-  HM_TRY(dalloc(&p_es, 6 * std::max<uint64_t>(n2, 1) * sizeof(unsigned long long)));
-  auto* es = static_cast<unsigned long long*>(p_es);
-  int rc = fill_u64(es, 0, 6 * n2, st);
-  {
-    Scratch tmp(st);
-    unsigned long long *acc = nullptr, *tv = nullptr;
-    uint32_t *tri_e = nullptr, *outdeg = nullptr, *dmax = nullptr, *wlist = nullptr;
-    if (rc == HM_OK) rc = tmp.get(&acc, kAccN);
-    if (rc == HM_OK) rc = tmp.get(&tv, N);
-    if (rc == HM_OK) rc = tmp.get(&tri_e, n2);
-    if (rc == HM_OK) rc = tmp.get(&outdeg, N);
-    if (rc == HM_OK) rc = tmp.get(&dmax, 1);
-    if (rc == HM_OK) rc = fill_u64(acc, 0, kAccN, st);
-    if (rc == HM_OK) rc = fill_u64(tv, 0, N, st);
-    if (rc == HM_OK) rc = fill_u32(dmax, 0, 1, st);
-    if (rc == HM_OK && n2) {
-      k_sp_edge_tri<<<grid_cap(n2, kWavesPerBlock, 2048), kThreads, 0, st>>>(v, n2, tri_e, tv, acc);
-      k_es_widen<<<grid_cap(n2, 256, 2048), 256, 0, st>>>(tri_e, n2, es);
-      k_es_sums<<<grid_cap(n2, kWavesPerBlock, 2048), kThreads, 0, st>>>(v, n2, H->g2_eid, tri_e, es + 3 * n2,
-                                                                         es + 4 * n2, es + 5 * n2);
-      // per-pair 4-cycles from the sorted wedge keys
-      C4Keys ck;
-      if (rc == HM_OK) rc = c4_sorted_keys(H, st, tmp, &ck);
-      if (rc == HM_OK && ck.n_keys)
-        k_c4_pair_counts<<<grid_cap(ck.n_keys, 256, 4096), 256, 0, st>>>(v, ck.keys, ck.vals, ck.n_keys, ck.pos,
-                                                                        ck.start, n2, H->g2_eid, es + 2 * n2);
-      if (fill_u32(outdeg, 0, N, st) != HM_OK) rc = HM_EDEVICE;
-      k_sp_outdeg<<<grid_cap(n2, 256, 2048), 256, 0, st>>>(v, n2, outdeg);
-      if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-      if (rc == HM_OK) rc = max_u32(outdeg, N, dmax, st);
-      uint32_t cap = 0;
-      if (rc == HM_OK && hipMemcpyAsync(&cap, dmax, sizeof(uint32_t), hipMemcpyDeviceToHost, st) != hipSuccess)
-        rc = HM_EDEVICE;
-      if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
-      cap = std::max<uint32_t>(cap, 1);
-      const unsigned gk = grid_cap(n2, kWavesPerBlock, 1024);
-      if (rc == HM_OK) rc = tmp.get(&wlist, uint64_t(gk) * kWavesPerBlock * cap * 2);
-      if (rc == HM_OK) {
-        k_sp_k4<true><<<gk, kThreads, 0, st>>>(v, n2, cap, wlist, acc, H->g2_eid, es + 1 * n2);
-        if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-      }
-    }
-    if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
-  }
-  if (rc != HM_OK) {
-    dfree(p_es);
-    return rc;
-  }
-  H->es = es;
   return HM_OK;
 }
 
@@ -869,15 +463,9 @@ int build_quad_index(hm_graph* H, hipStream_t st) {
                                          static_cast<unsigned long long*>(slots), cap - 1);
     if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
   }
-  if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
-  dfree(k);
-  dfree(kt);
-  dfree(ft);
-  if (rc != HM_OK) {
-    dfree(f);
-    dfree(slots);
-    return rc;
-  }
+  void* used[] = {k, kt, ft, f, slots};   // (the last two are kept)
+  dfree_on(used, rc == HM_OK ? 3 : 5, st);
+  if (rc != HM_OK) return rc;
   H->q_slot = static_cast<unsigned long long*>(slots);
   H->q_mask = cap - 1;
   H->q_fourth = static_cast<uint32_t*>(f);
@@ -944,19 +532,9 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
     if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
     if (rc == HM_OK) rc = scan_exclusive_u32(static_cast<const uint32_t*>(et), out, n, out + n, st);
   }
-  if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
-  dfree(kt);
-  dfree(et);
-  if (rc != HM_OK) {
-    dfree(k);
-    dfree(e);
-    dfree(slots);
-    dfree(codeg);
-    dfree(third);
-    dfree(adj);
-    dfree(pre);
-    return rc;
-  }
+  void* used[] = {kt, et, k, e, slots, codeg, third, adj, pre};   // (all but the first two are kept)
+  dfree_on(used, rc == HM_OK ? 2 : 9, st);
+  if (rc != HM_OK) return rc;
   H->pl_keys = static_cast<unsigned long long*>(k);
   H->pl_edge = static_cast<uint32_t*>(e);
   H->pl_slot = static_cast<unsigned long long*>(slots);
@@ -1083,14 +661,9 @@ int ensure_b4_order(hm_graph* H, hipStream_t st) {
   if (rc == HM_OK)
     rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(o),
                           static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(ot), n3, 32, st);
-  if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
-  dfree(k);
-  dfree(kt);
-  dfree(ot);
-  if (rc != HM_OK) {
-    dfree(o);
-    return rc;
-  }
+  void* used[] = {k, kt, ot, o};   // (the last is kept)
+  dfree_on(used, rc == HM_OK ? 3 : 4, st);
+  if (rc != HM_OK) return rc;
   H->b4_order = static_cast<uint32_t*>(o);
   return HM_OK;
 }
@@ -1104,20 +677,19 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   const View v = view_of(H);
   const uint64_t n2 = H->n_by_size[2], n3 = H->n_by_size[3];
   Scratch tmp(st);
-  unsigned long long *acc = nullptr, *tv = nullptr;
+  unsigned long long* acc = nullptr;
   uint32_t* tri_e = nullptr;
   HM_TRY(tmp.get(&acc, kAccN));
-  HM_TRY(tmp.get(&tv, H->n_nodes));
   HM_TRY(tmp.get(&tri_e, n2));
   HM_TRY(fill_u64(acc, 0, kAccN, st));
-  HM_TRY(fill_u64(tv, 0, H->n_nodes, st));
   if (n2) {
-    ProfileScope ps("k_sp_edge_tri", st);
-    k_sp_edge_tri<<<grid_cap(n2, kWavesPerBlock, 2048), kThreads, 0, st>>>(v, n2, tri_e, tv, acc);
+    HM_TRY(wedge_counts(H, k, tri_e, acc + kAccC4, acc + kAccK4, st));
+    ProfileScope ps("k_sp_pairs", st);
+    k_sp_pairs<<<grid_cap(n2, kThreads, 512), kThreads, 0, st>>>(v, n2, tri_e, acc);
   }
   {
     ProfileScope ps("k_sp_nodes", st);
-    k_sp_nodes<<<grid_cap(H->n_nodes, kThreads, 1024), kThreads, 0, st>>>(v, tv, acc);
+    k_sp_nodes<<<grid_cap(H->n_nodes, kThreads, 512), kThreads, 0, st>>>(v, acc);
   }
   HM_HIP(hipGetLastError());
   const ClassTables& t = class_tables();
@@ -1131,35 +703,6 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   cls.paw = t.lut4[(1u << 0) | (1u << 1) | (1u << 2) | (1u << 4)];
   cls.diamond = t.lut4[(1u << 0) | (1u << 1) | (1u << 2) | (1u << 4) | (1u << 5)];
   cls.clique = t.lut4[kPairBits4];
-  if (k == 4 && n2) {
-    // 4-cycles: wedge keys, sorted, counted by runs
-    C4Keys ck;
-    HM_TRY(c4_sorted_keys(H, st, tmp, &ck));
-    if (ck.n_keys) {
-      ProfileScope ps("k_c4_runs", st);
-      k_c4_runs<<<grid_cap(ck.n_keys, 256, 4096), 256, 0, st>>>(ck.keys, ck.n_keys, kC4None, acc + kAccC4);
-    }
-    HM_HIP(hipGetLastError());
-    // 4-cliques
-    uint32_t *outdeg = nullptr, *dmax = nullptr;
-    HM_TRY(tmp.get(&outdeg, H->n_nodes));
-    HM_TRY(tmp.get(&dmax, 1));
-    HM_TRY(fill_u32(dmax, 0, 1, st));
-    HM_TRY(fill_u32(outdeg, 0, H->n_nodes, st));
-    k_sp_outdeg<<<grid_cap(n2, 256, 2048), 256, 0, st>>>(v, n2, outdeg);
-    HM_TRY(max_u32(outdeg, H->n_nodes, dmax, st));
-    uint32_t cap = 0;
-    HM_HIP(hipMemcpyAsync(&cap, dmax, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HM_HIP(hipStreamSynchronize(st));
-    const unsigned gk = grid_cap(n2, kWavesPerBlock, 1024);
-    uint32_t* wlist = nullptr;
-    HM_TRY(tmp.get(&wlist, uint64_t(gk) * kWavesPerBlock * std::max<uint32_t>(cap, 1)));
-    {
-      ProfileScope ps("k_sp_k4", st);
-      k_sp_k4<false><<<gk, kThreads, 0, st>>>(v, n2, std::max<uint32_t>(cap, 1), wlist, acc, nullptr, nullptr);
-    }
-    HM_HIP(hipGetLastError());
-  }
   if (k == 4 && n3) {
     HM_TRY(ensure_pair_links(const_cast<hm_graph*>(H), st));
     HM_TRY(ensure_b4_order(const_cast<hm_graph*>(H), st));
@@ -1183,8 +726,6 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   }
   k_sp_shapes<<<1, 64, 0, st>>>(acc, k, cls, H->hist);
   HM_HIP(hipGetLastError());
-  // the scratch is released when the work is done
-  HM_HIP(hipStreamSynchronize(st));
   return HM_OK;
 }
 

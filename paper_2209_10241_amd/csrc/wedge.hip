@@ -1,0 +1,905 @@
+// Triangles, 4-cycles and 4-cliques of the pairwise graph without adjacency
+// bit rows: the counts behind the graph identities of the exact count
+// (sparse.hip) and the per-pair statistics of the pair sampler.
+//
+// The nodes are ranked by degree (x before y: fewer pairwise neighbours, or
+// as many in the same class of degrees) and the graph is kept once more in
+// rank space, without the neighbours of degree 1, which close nothing (the
+// core rows).  Every pair {x, u}, x before u, is walked from its later node
+// u: one workgroup takes u, marks N(u) in LDS, and for each neighbour x
+// before u walks the row of x.  A node w met there closes a triangle when it
+// is marked, and, when w is before u, one more path u - x - w, counted per w
+// in LDS: c such paths close C(c, 2) 4-cycles whose last node is u.  So the
+// membership tests and the path counters are LDS operations, where a hash
+// probe per position and a sort of one key per path went to memory before.
+// Triangles and 4-cycles together: co-authorship (N = 10^6, 2 x 10^7
+// positions) 3.8 -> 1.2 ms, communication (N = 5 x 10^4, 1.3 x 10^8
+// positions) 14.0 -> 2.1 ms; 4-cliques 1.0 -> 0.16 and 6.4 -> 0.74 ms.  The
+// longest walk, on one CU, bounds the launch.
+//
+// u is taken by the size of its walk: a wavefront with a hash table of 1,024
+// slots (degree below 24), a workgroup of 256 threads with 4,096 slots (at
+// most 3,072 nodes marked and met), or one of 1,024 threads with counters
+// addressed by rank, a range of ranks at a time.
+#include <algorithm>
+
+#include "hm_sparse.h"
+#include "hm_wedge.h"
+
+namespace hm {
+namespace {
+
+// ------------------------------------------------------------------ rank space
+constexpr uint32_t kSmallDeg = 24;        // degrees below: one wavefront a node
+constexpr uint32_t kSmallSlots = 1024;    // 23 x 23 paths and 23 neighbours: load at most 0.54
+constexpr uint32_t kMidSlots = 4096;
+constexpr uint32_t kMidMost = 3072;
+constexpr uint32_t kRankBits = 8;
+
+// Class of a degree: itself below 64, then eight classes per octave.
+__device__ inline uint32_t degree_class(uint32_t d) {
+  if (d < 64) return d;
+  const uint32_t e = 31 - __clz(int(d));
+  return min(255u, 64 + 8 * (e - 6) + ((d >> (e - 3)) & 7u));
+}
+
+// Graph in rank space: node ranks, core rows and, in them, the later
+// neighbours alone (out rows).
+struct Ranked {
+  uint32_t n;                // nodes
+  const uint32_t* rank_of;   // node -> rank
+  const uint32_t* node_of;   // rank -> node
+  const uint2* core;         // rank -> (first entry, entries) of the core row
+  const uint2* out;          // rank -> the same of the out row
+  const uint32_t* core_adj;  // ranks
+  const uint32_t* core_eid;  // position in e2 of the entry's pair
+  const uint32_t* out_adj;
+  const uint32_t* out_eid;
+  const uint32_t* weight;    // rank -> nodes marked and positions walked (degree >= kSmallDeg)
+  const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg, largest out row
+};
+
+__global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, unsigned long long* __restrict__ keys,
+                            uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
+  if (blockIdx.x == 0 && threadIdx.x < 3) bounds[threadIdx.x] = threadIdx.x < 2 ? n : 0u;
+  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
+    keys[x] = degree_class(g2_off[x + 1] - g2_off[x]);
+    vals[x] = x;
+  }
+}
+
+__global__ void k_rank_assign(const unsigned long long* __restrict__ keys, const uint32_t* __restrict__ node_of,
+                              uint32_t n, uint32_t* __restrict__ rank_of, uint32_t* __restrict__ bounds) {
+  for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+    rank_of[node_of[r]] = r;
+    const uint32_t k = uint32_t(keys[r]), before = r ? uint32_t(keys[r - 1]) : 0u;
+    if (k >= 2 && (r == 0 || before < 2)) bounds[0] = r;
+    if (k >= kSmallDeg && (r == 0 || before < kSmallDeg)) bounds[1] = r;
+  }
+}
+
+// Per adjacency entry: whether it is in the core rows (low half) and in the
+// out rows (high half), for one scan of both.
+__global__ void k_core_flags(const uint32_t* __restrict__ g2_adj, const uint32_t* __restrict__ g2_eid,
+                             const uint32_t* __restrict__ e2, uint64_t m, const uint32_t* __restrict__ rank_of,
+                             const uint32_t* __restrict__ bounds, unsigned long long* __restrict__ flag) {
+  const uint32_t r2 = bounds[0];
+  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < m; i += uint64_t(gridDim.x) * blockDim.x) {
+    const uint32_t z = g2_adj[i];
+    const uint64_t e = g2_eid[i];
+    const uint32_t owner = e2[2 * e] ^ e2[2 * e + 1] ^ z;
+    const uint32_t rz = rank_of[z];
+    flag[i] = rz >= r2 ? (1ull | ((unsigned long long)(rz > rank_of[owner]) << 32)) : 0ull;
+  }
+}
+
+__global__ void k_core_fill(const uint32_t* __restrict__ g2_adj, const uint32_t* __restrict__ g2_eid, uint64_t m,
+                            const uint32_t* __restrict__ rank_of, const unsigned long long* __restrict__ flag,
+                            const unsigned long long* __restrict__ pos, uint32_t* __restrict__ core_adj,
+                            uint32_t* __restrict__ core_eid, uint32_t* __restrict__ out_adj,
+                            uint32_t* __restrict__ out_eid) {
+  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < m; i += uint64_t(gridDim.x) * blockDim.x) {
+    const unsigned long long f = flag[i], p = pos[i];
+    if (!f) continue;
+    const uint32_t r = rank_of[g2_adj[i]], e = g2_eid[i];
+    core_adj[uint32_t(p)] = r;
+    core_eid[uint32_t(p)] = e;
+    if (f >> 32) {
+      out_adj[p >> 32] = r;
+      out_eid[p >> 32] = e;
+    }
+  }
+}
+
+__global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uint64_t m,
+                            const uint32_t* __restrict__ node_of, const unsigned long long* __restrict__ flag,
+                            const unsigned long long* __restrict__ pos, uint2* __restrict__ core,
+                            uint2* __restrict__ out, uint32_t* __restrict__ bounds) {
+  uint32_t most = 0;
+  auto at = [&](uint32_t i) { return i < m ? pos[i] : (m ? pos[m - 1] + flag[m - 1] : 0ull); };
+  for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+    const uint32_t x = node_of[r];
+    const unsigned long long b = at(g2_off[x]), e = at(g2_off[x + 1]);
+    core[r] = make_uint2(uint32_t(b), uint32_t(e) - uint32_t(b));
+    out[r] = make_uint2(uint32_t(b >> 32), uint32_t(e >> 32) - uint32_t(b >> 32));
+    most = max(most, uint32_t(e >> 32) - uint32_t(b >> 32));
+  }
+  for (int d = kWave / 2; d > 0; d >>= 1) most = max(most, uint32_t(__shfl_xor(int(most), d, kWave)));
+  if ((threadIdx.x & (kWave - 1)) == 0 && most > 2) atomicMax(&bounds[2], most);
+}
+
+// Nodes marked and positions walked for every u of degree >= kSmallDeg
+// (saturating): one wavefront per u.
+__global__ void k_core_weight(Ranked g, uint32_t* __restrict__ weight) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave, n_waves = gridDim.x * blockDim.x / kWave;
+  const uint32_t r1 = g.bounds[1];
+  for (uint32_t i = wave; i < g.n - r1; i += n_waves) {
+    const uint32_t u = r1 + i;
+    const uint2 row = g.core[u];
+    unsigned long long s = 0;
+    for (uint32_t q = lane; q < row.y; q += kWave) {
+      const uint32_t x = g.core_adj[row.x + q];
+      if (x < u) s += g.core[x].y;
+    }
+    s = wave_sum(s) + row.y;
+    if (lane == 0) weight[u] = s > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(s);
+  }
+}
+
+// ------------------------------------------------------------------ the walk
+// What a walk computes: the triangles of each pair (always); the number of
+// 4-cycles; the 4-cycles through each pair too; or, from the triangles of
+// each pair, the sums over the common neighbours.
+enum : int { kTri = 0, kCycles = 1, kPairCycles = 2, kSums = 3 };
+
+struct WalkArgs {
+  Ranked g;
+  uint32_t* tri_e;                  // triangles of each pair: written (zero before), or read by kSums
+  unsigned long long* cycles;       // 4-cycles: kAccCopies counters
+  unsigned long long* c4e;          // kPairCycles: 4-cycles of each pair (zero before)
+  // kSums: over the common neighbours w of the pair {a < b}: triangles of
+  // {a, w}, of {b, w}, pairwise degrees of w
+  unsigned long long *sum_a, *sum_b, *sum_d;
+  const uint32_t* g2_off;
+};
+
+// A set of ranks with a value each, open addressing in LDS.
+template <uint32_t SLOTS>
+struct HashTab {
+  uint32_t *key, *val;
+  uint32_t mask;
+  __device__ void begin(uint32_t most) {
+    uint32_t cap = 64;
+    while (cap < 2 * most && cap < SLOTS) cap <<= 1;
+    mask = cap - 1;
+    for (uint32_t i = threadIdx.x; i < cap; i += blockDim.x) {
+      key[i] = kEmpty32;
+      val[i] = 0u;
+    }
+  }
+  __device__ uint32_t home(uint32_t w) const { return (w * 0x9E3779B1u >> 16) & mask; }
+  __device__ uint32_t insert(uint32_t w) const {
+    uint32_t h = home(w);
+    while (true) {
+      const uint32_t cur = atomicCAS(&key[h], kEmpty32, w);
+      if (cur == kEmpty32 || cur == w) return h;
+      h = (h + 1) & mask;
+    }
+  }
+  // slot of w, or kEmpty32
+  __device__ uint32_t find(uint32_t w) const {
+    uint32_t h = home(w);
+    while (true) {
+      const uint32_t cur = key[h];
+      if (cur == w) return h;
+      if (cur == kEmpty32) return kEmpty32;
+      h = (h + 1) & mask;
+    }
+  }
+  __device__ bool covers(uint32_t) const { return true; }
+  __device__ void mark(uint32_t w) const { val[insert(w)] = 0x80000000u; }
+  __device__ void put(uint32_t w, uint32_t v) const { val[insert(w)] = v; }
+  __device__ bool marked(uint32_t w) const {
+    const uint32_t h = find(w);
+    return h != kEmpty32 && (val[h] >> 31);
+  }
+  // one more path to w; whether w is marked
+  __device__ bool add(uint32_t w) const { return atomicAdd(&val[insert(w)], 1u) >> 31; }
+  __device__ uint32_t paths(uint32_t w) const { return val[find(w)] & 0x7FFFFFFFu; }
+  __device__ uint32_t get(uint32_t w) const {
+    const uint32_t h = find(w);
+    return h == kEmpty32 ? 0u : val[h];
+  }
+  // this thread's share of the sum of C(paths, 2)
+  __device__ unsigned long long pairs() const {
+    unsigned long long s = 0;
+    for (uint32_t i = threadIdx.x; i <= mask; i += blockDim.x) {
+      const unsigned long long c = val[i] & 0x7FFFFFFFu;
+      s += c * (c - (c > 0)) / 2;
+    }
+    return s;
+  }
+  __device__ void end() const {}
+};
+
+// Values by rank for the ranks [lo, lo + n): path counts of 16 bits beside a
+// mark bit each (or, `wide`, of 32 bits for half as many ranks), values of 32
+// bits for kSums, or mark bits alone for kTri.  All zero between walks.
+constexpr uint32_t kDirectRanks = 51200;   // 16-bit counts: 100 KB, marks 6.25 KB
+constexpr uint32_t kDirectWords = kDirectRanks / 2;
+constexpr uint32_t kDirectMarks = kDirectRanks / 32;
+struct DirectTab {
+  uint32_t *cnt, *bits;
+  uint32_t lo, n;
+  bool wide;
+  __device__ bool covers(uint32_t w) const { return w - lo < n; }
+  __device__ void mark(uint32_t w) const { atomicOr(&bits[(w - lo) >> 5], 1u << ((w - lo) & 31)); }
+  __device__ bool marked(uint32_t w) const { return (bits[(w - lo) >> 5] >> ((w - lo) & 31)) & 1u; }
+  __device__ bool add(uint32_t w) const {
+    const uint32_t i = w - lo;
+    if (wide) atomicAdd(&cnt[i], 1u);
+    else atomicAdd(&cnt[i >> 1], 1u << (16 * (i & 1)));
+    return marked(w);
+  }
+  __device__ uint32_t paths(uint32_t w) const {
+    const uint32_t i = w - lo;
+    return wide ? cnt[i] : (cnt[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+  }
+  __device__ void put(uint32_t w, uint32_t v) const { cnt[w - lo] = v; }
+  __device__ uint32_t get(uint32_t w) const { return cnt[w - lo]; }
+  __device__ uint32_t words() const { return wide ? n : (n + 1) / 2; }
+  __device__ unsigned long long pairs() const {
+    unsigned long long s = 0;
+    for (uint32_t i = threadIdx.x; i < words(); i += blockDim.x) {
+      const uint32_t v = cnt[i];
+      if (wide) {
+        const unsigned long long c = v;
+        s += c * (c - (c > 0)) / 2;
+      } else {
+        const uint32_t a = v & 0xFFFFu, b = v >> 16;
+        s += (a * (a - (a > 0)) / 2) + (b * (b - (b > 0)) / 2);
+      }
+    }
+    return s;
+  }
+};
+
+// Neighbours of u before u, in chunks of XS: where each one's positions start
+// in the chunk, its row, its entry in u's row, and what it collects.
+template <uint32_t XS, int MODE>
+struct WalkLds {
+  uint32_t pos[XS], row[XS], ent[XS], tri[XS];
+  unsigned long long sum[MODE == kPairCycles ? XS : 1];
+  unsigned long long sums[MODE == kSums ? 3 * XS : 1];
+  uint32_t wave_tot[1024 / kWave][2];
+  uint32_t n, total;
+};
+
+// Every thread of the workgroup (T threads) calls this.  L consecutive
+// positions per thread and round: one search for the first's row, then L
+// loads in flight.
+template <uint32_t T, uint32_t XPT, uint32_t L, int MODE, typename Tab>
+__device__ void walk_top(const WalkArgs& a, WalkLds<T * XPT, MODE>& S, const Tab& tab, uint32_t u, bool shared_pairs,
+                         unsigned long long& cycles) {
+  constexpr uint32_t XS = T * XPT;
+  const Ranked& g = a.g;
+  const uint2 ru = g.core[u];
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  for (uint32_t i = tid; i < ru.y; i += T) {
+    const uint32_t w = g.core_adj[ru.x + i];
+    if (!tab.covers(w)) continue;
+    if constexpr (MODE == kSums) tab.put(w, a.tri_e[g.core_eid[ru.x + i]] + 1u);
+    else tab.mark(w);
+  }
+  // (pass 1 of kPairCycles, after every path is counted, walks again)
+  for (int pass = 0; pass < (MODE == kPairCycles ? 2 : 1); ++pass) {
+    for (uint32_t base = 0; base < ru.y; base += XS) {
+      if (pass == 0 || ru.y > XS) {
+        // the chunk's neighbours before u, compacted with the positions
+        // where their rows start
+        uint32_t x[XPT], len[XPT], row[XPT], mine = 0, kept = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < XPT; ++k) {
+          const uint32_t i = base + tid * XPT + k;
+          x[k] = i < ru.y ? g.core_adj[ru.x + i] : kEmpty32;
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < XPT; ++k) {
+          len[k] = 0;
+          if (x[k] < u) {
+            const uint2 r = g.core[x[k]];
+            row[k] = r.x;
+            len[k] = r.y;
+            mine += r.y;
+            ++kept;
+          }
+        }
+        uint32_t tot_len, tot_n;
+        uint32_t at = wave_exclusive_scan(mine, &tot_len), slot = wave_exclusive_scan(kept, &tot_n);
+        __syncthreads();   // the previous chunk's arrays are no longer read
+        if (T > kWave) {
+          if (lane == 0) {
+            S.wave_tot[wv][0] = tot_len;
+            S.wave_tot[wv][1] = tot_n;
+          }
+          __syncthreads();
+          tot_len = tot_n = 0;
+          for (uint32_t q = 0; q < T / kWave; ++q) {
+            if (q == wv) {
+              at += tot_len;
+              slot += tot_n;
+            }
+            tot_len += S.wave_tot[q][0];
+            tot_n += S.wave_tot[q][1];
+          }
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < XPT; ++k)
+          if (x[k] < u) {
+            S.pos[slot] = at;
+            S.row[slot] = row[k];
+            S.ent[slot] = ru.x + base + tid * XPT + k;
+            S.tri[slot] = 0;
+            if constexpr (MODE == kPairCycles) S.sum[slot] = 0;
+            if constexpr (MODE == kSums) S.sums[slot] = S.sums[XS + slot] = S.sums[2 * XS + slot] = 0;
+            at += len[k];
+            ++slot;
+          }
+        if (tid == 0) {
+          S.n = tot_n;
+          S.total = tot_len;
+        }
+      }
+      __syncthreads();
+      const uint32_t n = S.n, total = S.total;
+      for (uint32_t p0 = tid * L; p0 < total; p0 += T * L) {
+        uint32_t lo = 0, hi = n;   // pos[lo] <= p0 < pos[hi]
+        while (hi - lo > 1) {
+          const uint32_t m = (lo + hi) >> 1;
+          if (S.pos[m] <= p0) lo = m; else hi = m;
+        }
+        uint32_t next = lo + 1 < n ? S.pos[lo + 1] : total, shift = S.row[lo] - S.pos[lo];
+        uint32_t k[L], q[L], w[L];
+#pragma unroll
+        for (uint32_t r = 0; r < L; ++r) {
+          const uint32_t p = min(p0 + r, total - 1);
+          if (p >= next) {   // (every row holds u at least)
+            ++lo;
+            next = lo + 1 < n ? S.pos[lo + 1] : total;
+            shift = S.row[lo] - S.pos[lo];
+          }
+          k[r] = lo;
+          q[r] = shift + p;
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < L; ++r) w[r] = g.core_adj[q[r]];
+#pragma unroll
+        for (uint32_t r = 0; r < L; ++r) {
+          if (p0 + r >= total || w[r] == u || !tab.covers(w[r])) continue;
+          if constexpr (MODE == kSums) {
+            const uint32_t t = tab.get(w[r]);
+            if (t) {
+              const uint32_t node = g.node_of[w[r]];
+              atomicAdd(&S.sums[k[r]], (unsigned long long)a.tri_e[g.core_eid[q[r]]]);
+              atomicAdd(&S.sums[XS + k[r]], (unsigned long long)(t - 1));
+              atomicAdd(&S.sums[2 * XS + k[r]], (unsigned long long)(a.g2_off[node + 1] - a.g2_off[node]));
+            }
+          } else if (pass == 0) {
+            bool hit;
+            if (MODE != kTri && w[r] < u) hit = tab.add(w[r]);
+            else hit = tab.marked(w[r]);
+            if (hit) atomicAdd(&S.tri[k[r]], 1u);
+          } else if (w[r] < u) {
+            // a path of c to w closes c - 1 cycles, each holding its two pairs
+            const uint32_t c = tab.paths(w[r]);
+            if (c >= 2) {
+              atomicAdd(&S.sum[k[r]], (unsigned long long)(c - 1));
+              atomicAdd(&a.c4e[g.core_eid[q[r]]], (unsigned long long)(c - 1));
+            }
+          }
+        }
+      }
+      __syncthreads();
+      for (uint32_t i = tid; i < n; i += T) {
+        const uint32_t e = g.core_eid[S.ent[i]];
+        if constexpr (MODE == kSums) {
+          if (!S.sums[XS + i] && !S.sums[i] && !S.sums[2 * XS + i]) continue;
+          const bool x_first = g.node_of[g.core_adj[S.ent[i]]] < g.node_of[u];
+          atomicAdd(x_first ? &a.sum_a[e] : &a.sum_b[e], S.sums[i]);
+          atomicAdd(x_first ? &a.sum_b[e] : &a.sum_a[e], S.sums[XS + i]);
+          atomicAdd(&a.sum_d[e], S.sums[2 * XS + i]);
+        } else if (pass == 0) {
+          if (S.tri[i]) {
+            if (shared_pairs) atomicAdd(&a.tri_e[e], S.tri[i]);
+            else a.tri_e[e] = S.tri[i];
+          }
+        } else if (MODE == kPairCycles && S.sum[i]) {
+          atomicAdd(&a.c4e[e], S.sum[i]);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if constexpr (MODE == kCycles || MODE == kPairCycles) cycles += tab.pairs();
+}
+
+// Sum of x over the workgroup (T threads) to one of the copies of *out.
+template <uint32_t T>
+__device__ void add_copies(unsigned long long x, unsigned long long* out) {
+  __shared__ unsigned long long part[T / kWave];
+  x = wave_sum(x);
+  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long s = 0;
+    for (uint32_t q = 0; q < T / kWave; ++q) s += part[q];
+    if (s) atomicAdd(&out[blockIdx.x % kAccCopies], s);
+  }
+}
+
+// Degree below kSmallDeg: a wavefront per node.
+template <int MODE>
+__global__ void __launch_bounds__(kWave) k_walk_small(WalkArgs a) {
+  __shared__ WalkLds<kWave, MODE> S;
+  __shared__ uint32_t key[kSmallSlots], val[kSmallSlots];
+  HashTab<kSmallSlots> tab{key, val, 0};
+  unsigned long long cycles = 0;
+  const uint32_t r0 = a.g.bounds[0], r1 = a.g.bounds[1];
+  for (uint32_t u = r0 + blockIdx.x; u < r1; u += gridDim.x) {
+    const uint2 row = a.g.core[u];
+    if (row.y < 2) continue;   // one neighbour of degree 2 or more closes nothing
+    // what the walk may meet: every path, when the table holds paths
+    uint32_t most = row.y;
+    if (MODE == kCycles || MODE == kPairCycles) {
+      const uint32_t x = threadIdx.x < row.y ? a.g.core_adj[row.x + threadIdx.x] : kEmpty32;
+      most += wave_sum_u32(x < u ? a.g.core[x].y : 0u);
+    }
+    __syncthreads();   // the previous node's table is no longer read
+    tab.begin(most);
+    __syncthreads();
+    walk_top<kWave, 1, 2, MODE>(a, S, tab, u, false, cycles);
+  }
+  if (MODE == kCycles || MODE == kPairCycles) add_copies<kWave>(cycles, a.cycles);
+}
+
+// The ranks of the workgroups' shares are strided; each takes up to T
+// candidates at a time, drops those of the other classes, and walks the rest,
+// the latest (longest) first.
+template <uint32_t T, typename F, typename G>
+__device__ void for_candidates(uint64_t count, uint32_t* list, uint32_t* n_list, F keep, G body) {
+  for (uint64_t base = 0; base + blockIdx.x < count; base += uint64_t(T) * gridDim.x) {
+    const uint64_t c = base + uint64_t(threadIdx.x) * gridDim.x + blockIdx.x;
+    const bool on = c < count && keep(c);
+    __syncthreads();
+    if (threadIdx.x == 0) *n_list = 0;
+    __syncthreads();
+    // in order: a wavefront's kept candidates after those of the wavefronts
+    // before it
+    const unsigned long long m = __ballot(on);
+    for (uint32_t q = 0; q < T / kWave; ++q) {
+      if (threadIdx.x / kWave == q) {
+        const uint32_t lane = threadIdx.x & (kWave - 1);
+        const uint32_t at = *n_list;
+        if (on) list[at + uint32_t(__popcll(m & ((1ull << lane) - 1ull)))] = threadIdx.x;
+        wave_sync();
+        if (lane == 0) *n_list = at + uint32_t(__popcll(m));
+      }
+      __syncthreads();
+    }
+    const uint32_t n = *n_list;
+    for (uint32_t i = 0; i < n; ++i) body(base + uint64_t(list[i]) * gridDim.x + blockIdx.x);
+  }
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(256) k_walk_mid(WalkArgs a) {
+  __shared__ WalkLds<1024, MODE> S;
+  __shared__ uint32_t key[kMidSlots], val[kMidSlots];
+  __shared__ uint32_t list[256], n_list;
+  HashTab<kMidSlots> tab{key, val, 0};
+  unsigned long long cycles = 0;
+  const uint32_t n = a.g.n, r1 = a.g.bounds[1];
+  for_candidates<256>(
+      n - r1, list, &n_list, [&](uint64_t c) { return a.g.weight[n - 1 - uint32_t(c)] <= kMidMost; },
+      [&](uint64_t c) {
+        const uint32_t u = n - 1 - uint32_t(c);
+        __syncthreads();
+        tab.begin(a.g.weight[u]);
+        __syncthreads();
+        walk_top<256, 4, 4, MODE>(a, S, tab, u, false, cycles);
+      });
+  if (MODE == kCycles || MODE == kPairCycles) add_copies<256>(cycles, a.cycles);
+}
+
+// Ranks a direct table holds in this mode, and threads' neighbours per chunk
+// (the LDS beside it).
+template <int MODE>
+struct DirectMode {
+  static constexpr uint32_t kRanks = MODE == kTri ? kDirectWords * 32 : MODE == kSums ? kDirectWords : kDirectRanks;
+  static constexpr uint32_t kXpt = MODE == kSums ? 1 : 2;
+};
+
+template <int MODE>
+__global__ void __launch_bounds__(1024) k_walk_large(WalkArgs a, uint32_t parts) {
+  constexpr uint32_t R = DirectMode<MODE>::kRanks, XPT = DirectMode<MODE>::kXpt;
+  __shared__ WalkLds<1024 * XPT, MODE> S;
+  __shared__ uint32_t words[kDirectWords];
+  __shared__ uint32_t marks[MODE == kTri || MODE == kSums ? 1 : kDirectMarks];
+  __shared__ uint32_t list[1024], n_list;
+  for (uint32_t i = threadIdx.x; i < kDirectWords; i += 1024) words[i] = 0;
+  if (MODE != kTri && MODE != kSums)
+    for (uint32_t i = threadIdx.x; i < kDirectMarks; i += 1024) marks[i] = 0;
+  unsigned long long cycles = 0;
+  const uint32_t n = a.g.n, r0 = a.g.bounds[0], r1 = a.g.bounds[1];
+  for_candidates<1024>(
+      uint64_t(n - r1) * parts, list, &n_list,
+      [&](uint64_t c) {
+        const uint32_t part = uint32_t(c % parts);
+        return uint64_t(r0) + uint64_t(part) * R < n && a.g.weight[n - 1 - uint32_t(c / parts)] > kMidMost;
+      },
+      [&](uint64_t c) {
+        const uint32_t u = n - 1 - uint32_t(c / parts), part = uint32_t(c % parts);
+        const uint32_t first = r0 + part * R, size = min(R, n - first);
+        // a 16-bit count holds every path when u has at most 65,535
+        // neighbours that could be on one
+        const bool wide = (MODE == kCycles || MODE == kPairCycles) && a.g.core[u].y > 65535u;
+        for (uint32_t half = 0; half < (wide ? 2u : 1u); ++half) {
+          const uint32_t step = wide ? R / 2 : R;
+          if (half * step >= size) break;
+          DirectTab tab{words, MODE == kTri ? words : marks, first + half * step,
+                         size - half * step < step ? size - half * step : step, wide};
+          __syncthreads();
+          walk_top<1024, XPT, 8, MODE>(a, S, tab, u, parts > 1 || wide, cycles);
+          __syncthreads();
+          const uint32_t used = MODE == kTri ? (tab.n + 31) / 32 : MODE == kSums ? tab.n : tab.words();
+          for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = 0;
+          if (MODE != kTri && MODE != kSums)
+            for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) marks[i] = 0;
+        }
+      });
+  if (MODE == kCycles || MODE == kPairCycles) add_copies<1024>(cycles, a.cycles);
+}
+
+// ------------------------------------------------------------------ 4-cliques
+// A 4-clique is counted at its first node lo, as a triangle among the later
+// neighbours D of lo: the pairs of G2 inside D are found by walking the out
+// rows of D against a hash table of D, as bit rows over D; a second walk adds,
+// for each pair of D, the common neighbours (the members of D after both, or
+// with EDGE every member adjacent to both: the 4-cliques through lo and the
+// pair).  D of at most CAP nodes, one workgroup of T threads per lo.
+template <uint32_t T, uint32_t CAP, bool EDGE>
+struct CliqueLds {
+  static constexpr uint32_t kWords = CAP / 32;
+  uint32_t pos[CAP], row[CAP];
+  uint32_t bits[CAP * (kWords + 1)];   // rows an odd number of words apart (fewer bank conflicts)
+  uint32_t key[2 * CAP], val[2 * CAP];
+  uint32_t own[EDGE ? CAP : 1];
+  uint32_t wave_tot[T / kWave];
+};
+
+template <uint32_t T, uint32_t CAP, bool EDGE>
+__global__ void __launch_bounds__(T) k_clique(Ranked g, uint32_t least, unsigned long long* __restrict__ acc,
+                                              unsigned long long* __restrict__ k4e) {
+  using Lds = CliqueLds<T, CAP, EDGE>;
+  constexpr uint32_t DPT = CAP / T, STRIDE = Lds::kWords + 1, SLOTS = 2 * CAP, L = 4;
+  __shared__ Lds S;
+  __shared__ uint32_t list[T], n_list;
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  unsigned long long cliques = 0;
+  const uint32_t r0 = g.bounds[0];
+  auto keep = [&](uint64_t c) {
+    const uint32_t n = g.out[r0 + uint32_t(c)].y;
+    return n >= least && n <= CAP;
+  };
+  for_candidates<T>(g.n - r0, list, &n_list, keep, [&](uint64_t c) {
+    const uint32_t lo = r0 + uint32_t(c);
+    const uint2 d = g.out[lo];
+    const uint32_t words = (d.y + 31) / 32;
+    __syncthreads();   // the previous node's arrays are no longer read
+    for (uint32_t i = tid; i < SLOTS; i += T) S.key[i] = kEmpty32;
+    for (uint32_t i = tid; i < d.y * STRIDE; i += T) S.bits[i] = 0;
+    uint32_t x[DPT], len[DPT], row[DPT], mine = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < DPT; ++k) {
+      const uint32_t i = tid * DPT + k;
+      x[k] = i < d.y ? g.out_adj[d.x + i] : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < DPT; ++k) {
+      const uint32_t i = tid * DPT + k;
+      const uint2 r = i < d.y ? g.out[x[k]] : make_uint2(0u, 0u);
+      row[k] = r.x;
+      len[k] = r.y;
+      mine += r.y;
+      if (EDGE && i < d.y) S.own[i] = 0;
+    }
+    uint32_t total;
+    uint32_t at = wave_exclusive_scan(mine, &total);
+    if (lane == 0) S.wave_tot[wv] = total;
+    __syncthreads();
+    total = 0;
+    for (uint32_t q = 0; q < T / kWave; ++q) {
+      if (q == wv) at += total;
+      total += S.wave_tot[q];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < DPT; ++k) {
+      const uint32_t i = tid * DPT + k;
+      if (i < d.y) {
+        S.pos[i] = at;
+        S.row[i] = row[k];
+        at += len[k];
+        uint32_t h = (x[k] * 0x9E3779B1u >> 16) & (SLOTS - 1);
+        while (atomicCAS(&S.key[h], kEmpty32, x[k]) != kEmpty32) h = (h + 1) & (SLOTS - 1);
+        S.val[h] = i;
+      }
+    }
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+      for (uint32_t p0 = tid * L; p0 < total; p0 += T * L) {
+        uint32_t a = 0, b = d.y;   // the last row that starts at or before p0
+        while (b - a > 1) {
+          const uint32_t m = (a + b) >> 1;
+          if (S.pos[m] <= p0) a = m; else b = m;
+        }
+        uint32_t i[L], q[L], w[L];
+#pragma unroll
+        for (uint32_t r = 0; r < L; ++r) {
+          const uint32_t p = min(p0 + r, total - 1);
+          while (a + 1 < d.y && S.pos[a + 1] <= p) ++a;   // (rows may be empty)
+          i[r] = a;
+          q[r] = S.row[a] + (p - S.pos[a]);
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < L; ++r) w[r] = g.out_adj[q[r]];
+#pragma unroll
+        for (uint32_t r = 0; r < L; ++r) {
+          if (p0 + r >= total) continue;
+          uint32_t h = (w[r] * 0x9E3779B1u >> 16) & (SLOTS - 1);
+          uint32_t cur = S.key[h];
+          while (cur != w[r] && cur != kEmpty32) {
+            h = (h + 1) & (SLOTS - 1);
+            cur = S.key[h];
+          }
+          if (cur == kEmpty32) continue;
+          const uint32_t j = S.val[h];
+          if (pass == 0) {
+            atomicOr(&S.bits[i[r] * STRIDE + (j >> 5)], 1u << (j & 31));
+            if (EDGE) atomicOr(&S.bits[j * STRIDE + (i[r] >> 5)], 1u << (i[r] & 31));
+          } else {
+            uint32_t c = 0;
+            for (uint32_t k = 0; k < words; ++k) c += __popc(S.bits[i[r] * STRIDE + k] & S.bits[j * STRIDE + k]);
+            if (!c) continue;
+            cliques += c;
+            if (EDGE) {
+              atomicAdd(&S.own[i[r]], c);
+              atomicAdd(&S.own[j], c);
+              atomicAdd(&k4e[g.out_eid[q[r]]], (unsigned long long)c);
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (EDGE)
+      for (uint32_t i = tid; i < d.y; i += T)
+        if (S.own[i]) atomicAdd(&k4e[g.out_eid[d.x + i]], (unsigned long long)(S.own[i] / 2));
+  });
+  // (with EDGE each 4-clique was met at the three pairs of D it holds)
+  add_copies<T>(cliques, acc);
+}
+
+// D of more nodes than an LDS bit matrix holds: its rows in device memory
+// (`cap` rows of cap / 32 words per workgroup), filled by probing every pair.
+template <bool EDGE>
+__global__ void __launch_bounds__(1024) k_clique_wide(Ranked g, View v, uint32_t least, uint32_t cap,
+                                                      uint32_t* __restrict__ matrix,
+                                                      unsigned long long* __restrict__ acc,
+                                                      unsigned long long* __restrict__ k4e,
+                                                      const uint32_t* __restrict__ g2_eid) {
+  const uint32_t cap_words = (cap + 31) / 32;
+  uint32_t* M = matrix + uint64_t(blockIdx.x) * cap * cap_words;
+  unsigned long long cliques = 0;
+  for (uint32_t lo = g.bounds[0] + blockIdx.x; lo < g.n; lo += gridDim.x) {
+    const uint2 d = g.out[lo];
+    if (d.y < least) continue;
+    const uint32_t words = (d.y + 31) / 32;
+    // a thread owns a word: 32 members of D against one
+    for (uint64_t t = threadIdx.x; t < uint64_t(d.y) * words; t += 1024) {
+      const uint32_t i = uint32_t(t / words), w = uint32_t(t % words);
+      const uint32_t x = g.node_of[g.out_adj[d.x + i]];
+      uint32_t word = 0;
+      for (uint32_t b = 0; b < 32; ++b) {
+        const uint32_t j = 32 * w + b;
+        if (j < d.y && j != i && has2(v.hs2, x, g.node_of[g.out_adj[d.x + j]])) word |= 1u << b;
+      }
+      __hip_atomic_store(&M[uint64_t(i) * cap_words + w], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();   // (the words are read back past the L1 cache)
+    auto word_of = [&](uint32_t i, uint32_t w) {
+      return __hip_atomic_load(&M[uint64_t(i) * cap_words + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // a thread owns a member: its pairs in D, their common members
+    for (uint32_t i = threadIdx.x; i < d.y; i += 1024) {
+      unsigned long long own = 0;
+      for (uint32_t w = 0; w < words; ++w)
+        for (uint32_t rest = word_of(i, w); rest; rest &= rest - 1) {
+          const uint32_t j = 32 * w + uint32_t(__ffs(rest) - 1);
+          if (!EDGE && j < i) continue;
+          // (without EDGE the members after both, so that each 4-clique is
+          // met once)
+          uint32_t c = 0;
+          for (uint32_t k = EDGE ? 0 : w; k < words; ++k)
+            c += __popc(word_of(i, k) & word_of(j, k) & (EDGE ? ~0u : mask_gt(j, k)));
+          own += c;
+          if (j < i || !c) continue;
+          cliques += c;
+          if (EDGE) {
+            const uint32_t x = g.node_of[g.out_adj[d.x + i]], y = g.node_of[g.out_adj[d.x + j]];
+            uint32_t p = v.g2_off[x], e = v.g2_off[x + 1];
+            while (p < e) {
+              const uint32_t m = p + ((e - p) >> 1);
+              if (v.g2_adj[m] < y) p = m + 1; else e = m;
+            }
+            atomicAdd(&k4e[g2_eid[p]], (unsigned long long)c);
+          }
+        }
+      if (EDGE && own) atomicAdd(&k4e[g.out_eid[d.x + i]], own / 2);
+    }
+    __syncthreads();
+  }
+  add_copies<1024>(cliques, acc);
+}
+
+__global__ void k_sum_copies(const unsigned long long* __restrict__ copies, unsigned long long* __restrict__ out) {
+  unsigned long long s = threadIdx.x < kAccCopies ? copies[threadIdx.x] : 0ull;
+  s = wave_sum(s);
+  if (threadIdx.x == 0) *out = s;
+}
+
+unsigned grid_of(uint64_t items, uint64_t per_block, unsigned cap) {
+  return unsigned(std::max<uint64_t>(1, std::min<uint64_t>((items + per_block - 1) / per_block, cap)));
+}
+
+// H's pairwise graph in rank space, in buffers of tmp; *most receives the
+// largest out row (one host read-back) when asked for.
+int ranked_graph(const hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_t* most) {
+  const uint32_t n = H->n_nodes;
+  const uint64_t n2 = H->n_by_size[2], m = 2 * n2;
+  unsigned long long *keys = nullptr, *keys_tmp = nullptr, *flag = nullptr, *pos = nullptr;
+  uint32_t *node_of = nullptr, *vals_tmp = nullptr, *rank_of = nullptr, *core_adj = nullptr, *core_eid = nullptr,
+           *out_adj = nullptr, *out_eid = nullptr, *weight = nullptr, *bounds = nullptr;
+  uint2 *core = nullptr, *rows = nullptr;
+  HM_TRY(tmp.get(&keys, n));
+  HM_TRY(tmp.get(&keys_tmp, n));
+  HM_TRY(tmp.get(&node_of, n));
+  HM_TRY(tmp.get(&vals_tmp, n));
+  HM_TRY(tmp.get(&rank_of, n));
+  HM_TRY(tmp.get(&weight, n));
+  HM_TRY(tmp.get(&core, n));
+  HM_TRY(tmp.get(&rows, n));
+  HM_TRY(tmp.get(&bounds, 4));
+  HM_TRY(tmp.get(&flag, m));
+  HM_TRY(tmp.get(&pos, m));
+  HM_TRY(tmp.get(&core_adj, m));
+  HM_TRY(tmp.get(&core_eid, m));
+  HM_TRY(tmp.get(&out_adj, n2));
+  HM_TRY(tmp.get(&out_eid, n2));
+  k_rank_keys<<<grid_of(n, 256, 2048), 256, 0, st>>>(H->g2_off, n, keys, node_of, bounds);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(keys, node_of, keys_tmp, vals_tmp, n, kRankBits, st));
+  k_rank_assign<<<grid_of(n, 256, 2048), 256, 0, st>>>(keys, node_of, n, rank_of, bounds);
+  k_core_flags<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, H->e2, m, rank_of, bounds, flag);
+  HM_HIP(hipGetLastError());
+  HM_TRY(scan_exclusive_u64(flag, pos, m, st));
+  k_core_fill<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, m, rank_of, flag, pos, core_adj, core_eid,
+                                                     out_adj, out_eid);
+  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, node_of, flag, pos, core, rows, bounds);
+  HM_HIP(hipGetLastError());
+  *out = Ranked{n, rank_of, node_of, core, rows, core_adj, core_eid, out_adj, out_eid, weight, bounds};
+  k_core_weight<<<512, 256, 0, st>>>(*out, weight);
+  HM_HIP(hipGetLastError());
+  if (most) {
+    HM_HIP(hipMemcpyAsync(most, bounds + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HM_HIP(hipStreamSynchronize(st));
+  }
+  return HM_OK;
+}
+
+// The three walk launches of one mode, the longest walks first.
+template <int MODE>
+int launch_walks(const WalkArgs& a, const char* name, hipStream_t st) {
+  ProfileScope ps(name, st);
+  const uint64_t r = DirectMode<MODE>::kRanks;
+  const uint32_t parts = uint32_t(std::max<uint64_t>(1, (a.g.n + r - 1) / r));
+  k_walk_large<MODE><<<256, 1024, 0, st>>>(a, parts);
+  k_walk_mid<MODE><<<768, 256, 0, st>>>(a);
+  k_walk_small<MODE><<<grid_of(a.g.n, 1, 3072), kWave, 0, st>>>(a);
+  HM_HIP(hipGetLastError());
+  return HM_OK;
+}
+
+template <bool EDGE>
+int launch_cliques(const hm_graph* H, const Ranked& g, uint32_t most, unsigned long long* copies,
+                   unsigned long long* k4e, hipStream_t st, Scratch& tmp) {
+  ProfileScope ps("k_clique", st);
+  if (most > 512) {
+    // at most 2 GiB of matrices
+    const uint64_t each = uint64_t(most) * ((most + 31) / 32);
+    const unsigned blocks = unsigned(std::max<uint64_t>(1, std::min<uint64_t>(256, (1ull << 29) / each)));
+    uint32_t* matrix = nullptr;
+    HM_TRY(tmp.get(&matrix, each * blocks));
+    k_clique_wide<EDGE><<<blocks, 1024, 0, st>>>(g, view_of(H), 513, most, matrix, copies, k4e, H->g2_eid);
+  }
+  if (most > 64) k_clique<256, 512, EDGE><<<768, 256, 0, st>>>(g, 65, copies, k4e);
+  if (most > 2) k_clique<64, 64, EDGE><<<grid_of(g.n, 1, 4096), 64, 0, st>>>(g, 3, copies, k4e);
+  HM_HIP(hipGetLastError());
+  return HM_OK;
+}
+
+}  // namespace
+
+// Triangles of every pair of G2 (tri_e, n2 values) and, at order 4, the number
+// of 4-cycles and of 4-cliques of G2 (non-induced; device words).
+int wedge_counts(const hm_graph* H, int k, uint32_t* tri_e, unsigned long long* n_cycles, unsigned long long* n_cliques,
+                 hipStream_t st) {
+  const uint64_t n2 = H->n_by_size[2];
+  Scratch tmp(st);
+  unsigned long long* copies = nullptr;
+  HM_TRY(tmp.get(&copies, 2 * kAccCopies));
+  HM_TRY(fill_u64(copies, 0, 2 * kAccCopies, st));
+  HM_TRY(fill_u32(tri_e, 0, n2, st));
+  Ranked g;
+  uint32_t most = 0;
+  HM_TRY(ranked_graph(H, st, tmp, &g, k == 4 ? &most : nullptr));
+  WalkArgs a{};
+  a.g = g;
+  a.tri_e = tri_e;
+  a.cycles = copies;
+  if (k == 3) return launch_walks<kTri>(a, "k_walk", st);
+  HM_TRY(launch_walks<kCycles>(a, "k_walk", st));
+  HM_TRY(launch_cliques<false>(H, g, most, copies + kAccCopies, nullptr, st, tmp));
+  k_sum_copies<<<1, kWave, 0, st>>>(copies, n_cycles);
+  k_sum_copies<<<1, kWave, 0, st>>>(copies + kAccCopies, n_cliques);
+  HM_HIP(hipGetLastError());
+  return HM_OK;
+}
+
+__global__ void k_es_widen(const uint32_t* __restrict__ t32, uint64_t n, unsigned long long* __restrict__ t64) {
+  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
+    t64[i] = t32[i];
+}
+
+// The per-pair statistics of hm_graph::es (6 x n2).
+int wedge_edge_stats(const hm_graph* H, unsigned long long* es, hipStream_t st) {
+  const uint64_t n2 = H->n_by_size[2];
+  HM_TRY(fill_u64(es, 0, 6 * n2, st));
+  if (!n2) return HM_OK;
+  Scratch tmp(st);
+  unsigned long long* copies = nullptr;
+  uint32_t* tri_e = nullptr;
+  HM_TRY(tmp.get(&copies, 2 * kAccCopies));
+  HM_TRY(tmp.get(&tri_e, n2));
+  HM_TRY(fill_u64(copies, 0, 2 * kAccCopies, st));
+  HM_TRY(fill_u32(tri_e, 0, n2, st));
+  Ranked g;
+  uint32_t most = 0;
+  HM_TRY(ranked_graph(H, st, tmp, &g, &most));
+  WalkArgs a{};
+  a.g = g;
+  a.tri_e = tri_e;
+  a.cycles = copies;
+  a.c4e = es + 2 * n2;
+  a.sum_a = es + 3 * n2;
+  a.sum_b = es + 4 * n2;
+  a.sum_d = es + 5 * n2;
+  a.g2_off = H->g2_off;
+  HM_TRY(launch_walks<kPairCycles>(a, "k_walk", st));
+  k_es_widen<<<grid_of(n2, 256, 2048), 256, 0, st>>>(tri_e, n2, es);
+  HM_TRY(launch_walks<kSums>(a, "k_walk_sums", st));
+  HM_TRY(launch_cliques<true>(H, g, most, copies + kAccCopies, es + n2, st, tmp));
+  return HM_OK;
+}
+
+}  // namespace hm

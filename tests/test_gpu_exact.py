@@ -598,3 +598,92 @@ def test_count_exact_many_repeats_the_duplicate_search(hm):
         hm.hm_set_option(hm.HM_OPT_DEDUP_TAG_BITS, 32)
     for g, h in enumerate(hs):
         assert np.array_equal(got[g], core.count_exact(h, 4)), g
+
+
+def _hub_graph(n, hubs, hub_degree, ring, clique, seed):
+    """Pairs only: a ring-like sparse part, `hubs` nodes of high degree, and a complete graph on `clique` nodes."""
+    rng = np.random.default_rng(seed)
+    parts = []
+    if ring:
+        v = np.arange(n)
+        parts += [np.stack([v, (v + 1) % n], 1), np.stack([v, (v + 7) % n], 1)]
+    for h in range(hubs):
+        parts.append(np.stack([np.full(hub_degree, h), rng.choice(np.arange(hubs, n), hub_degree, replace=False)], 1))
+    if hubs > 1:
+        a, b = np.triu_indices(hubs, 1)
+        parts.append(np.stack([a, b], 1))
+    if clique:
+        nodes = rng.choice(n, clique, replace=False)
+        a, b = np.triu_indices(clique, 1)
+        parts.append(np.stack([nodes[a], nodes[b]], 1))
+    e = np.sort(np.concatenate(parts), axis=1)
+    e = np.unique(e[e[:, 0] != e[:, 1]], axis=0)
+    return e
+
+
+def _pair_shape_counts(hm, e, n):
+    """Non-induced copies of the pair shapes of order 3 and 4 (but 4-cliques), from sparse matrix products."""
+    import scipy.sparse as sp
+    A = sp.csr_matrix((np.ones(2 * len(e), np.int64), (np.r_[e[:, 0], e[:, 1]], np.r_[e[:, 1], e[:, 0]])), shape=(n, n))
+    d = np.asarray(A.sum(1)).ravel()
+    C = (A @ A).tocoo()
+    off = C.row < C.col
+    cyc2 = int((C.data[off] * (C.data[off] - 1) // 2).sum())
+    T = (A @ A).multiply(A).tocoo()
+    up = T.row < T.col
+    t, a, b = T.data[up], T.row[up], T.col[up]
+    tri = int(t.sum()) // 3
+    du, dv = d[e[:, 0]], d[e[:, 1]]
+    return {"tri": tri, "cyc": cyc2 // 2, "dia": int((t * (t - 1) // 2).sum()), "paw": int((t * (d[a] + d[b] - 4)).sum()) // 2,
+            "p4": int(((du - 1) * (dv - 1)).sum()) - 3 * tri, "star": int((d * (d - 1) * (d - 2) // 6).sum())}
+
+
+def test_walks_over_several_rank_ranges(hm):
+    """More than 51,200 nodes of degree two and above, and hubs whose walks
+    exceed the hash tables: the six pairs-only shapes against matrix products
+    in int64 (order 3 too)."""
+    n = 130_000
+    e = _hub_graph(n, 4, 3000, True, 0, 5)
+    want = _pair_shape_counts(hm, e, n)
+    offsets = np.arange(0, 2 * len(e) + 1, 2, dtype=np.uint64)
+    with hm.hm_graph_create(e.astype(np.uint32).ravel(), offsets, n) as g:
+        got = hm.count_exact(g, 4).cpu().numpy()
+        got3 = hm.count_exact(g, 3).cpu().numpy()
+    cls = lambda *bits: hm.hm_pattern_class(4, sum(1 << b for b in bits))
+    path, star, cycle = got[cls(0, 2, 7)], got[cls(0, 1, 4)], got[cls(0, 2, 7, 4)]
+    paw, dia, k4 = got[cls(0, 1, 2, 4)], got[cls(0, 1, 2, 4, 5)], got[cls(0, 1, 2, 4, 5, 7)]
+    assert dia + 6 * k4 == want["dia"]
+    assert cycle + dia + 3 * k4 == want["cyc"]
+    assert paw + 4 * dia + 12 * k4 == want["paw"]
+    assert star + paw + 2 * dia + 4 * k4 == want["star"]
+    assert path + 4 * cycle + 2 * paw + 6 * dia + 12 * k4 == want["p4"]
+    assert got3[hm.hm_pattern_class(3, 7)] == want["tri"]
+    assert k4 >= 1 and got.sum() == path + star + cycle + paw + dia + k4
+
+
+@pytest.mark.parametrize("n,hubs,hub_degree,ring,clique", [
+    (200, 0, 0, True, 0), (3000, 3, 2900, True, 0), (3000, 40, 700, True, 66), (1500, 0, 0, False, 24),
+    (2000, 2, 500, True, 120), (2500, 0, 0, True, 700)])
+def test_walks_match_bit_rows(hm, n, hubs, hub_degree, ring, clique):
+    """Triangles, 4-cycles and 4-cliques without bit rows (hash tables of
+    every size, counters by rank, cliques of one word, of many and beyond the
+    LDS matrix) against the bit-row path; and the per-pair statistics through
+    samples of every kind of pair."""
+    e = _hub_graph(n, hubs, hub_degree, ring, clique, n + clique)
+    rng = np.random.default_rng(1)
+    tri = np.sort(rng.choice(n, (300, 3)), axis=1)
+    tri = tri[(tri[:, 0] < tri[:, 1]) & (tri[:, 1] < tri[:, 2])]
+    members = np.r_[e.ravel(), tri.ravel()].astype(np.uint32)
+    offsets = np.r_[np.arange(0, 2 * len(e), 2), 2 * len(e) + np.arange(0, 3 * len(tri) + 1, 3)].astype(np.uint64)
+    got = {}
+    for bits in (8192, 0):
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+        try:
+            with hm.hm_graph_create(members, offsets, n) as g:
+                idx = rng.integers(0, g.stats()["n2"], 200) if not got else idx
+                raw = hm.count_sampled_indices(g, 4, {2: idx})[1].cpu().numpy()
+                got[bits] = (hm.count_exact(g, 4).cpu().numpy(), hm.count_exact(g, 3).cpu().numpy(), raw)
+        finally:
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+    for b, h in zip(got[8192], got[0]):
+        assert np.array_equal(b, h)
