@@ -488,8 +488,8 @@ int count_sampled_weighted_indices(const hm_graph* H, int k, const uint32_t* idx
  *                            probes everywhere.
  *   HM_OPT_SAMPLE_CHUNK_SCALE the sampled counts of graphs without bit rows
  *                            hand the long walks of heavy samples to a work
- *                            queue in chunks (2 nodes of T, 4 correction
- *                            items, 128 exception positions, 256 hyperedges;
+ *                            queue in chunks (2 nodes of T, 64 correction
+ *                            items, 512 exception positions, 256 hyperedges;
  *                            pair samples with a bound above 4096 visited
  *                            positions); every chunk size and that bound
  *                            are divided by this value

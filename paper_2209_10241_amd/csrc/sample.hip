@@ -88,10 +88,16 @@ __device__ void sample_j4(const View& v, const Draws& d, uint32_t part, uint32_t
 // Work chunks of heavy samples (without bit rows), drained by every
 // workgroup of a second launch so that one sample's work spreads over many.
 enum : uint32_t { kJobNone = 0, kJobPairT = 1, kJobPairR = 2, kJobTriple = 3, kJobPairS = 4, kJobPairQ = 5 };
-// default chunk sizes (divided by the HM_OPT_SAMPLE_CHUNK_SCALE option)
-constexpr uint32_t kChunkT = 2;    // nodes of T per chunk
-constexpr uint32_t kChunkR = 4;    // correction items per chunk
-constexpr uint32_t kChunkX = 128;  // exception positions per chunk
+// default chunk sizes (divided by the HM_OPT_SAMPLE_CHUNK_SCALE option).  A
+// chunk costs its claim and four or five dependent rounds of loads before its
+// first position, about 10 us, so it has to hold more work than that: with 4
+// correction items per chunk 656,000 of them held 108 positions each on the
+// communication graph (2% of every stratum, 10.1 ms; 64 items 4.1 ms, 256 no
+// better, and at 0.1%, where a few heavy samples are the tail, 0.80, 0.60 and
+// 1.00 ms).
+constexpr uint32_t kChunkT = 2;    // nodes of T per chunk (about 5,000 positions)
+constexpr uint32_t kChunkR = 64;   // correction items per chunk
+constexpr uint32_t kChunkX = 512;  // exception positions per chunk
 constexpr uint32_t kChunkH = 256;  // hyperedges at s (3-node) or holding e (4-node) per chunk
 // queue entries per sample of strata 2 and 3 (times the chunk option), at
 // most kQueueMax in all; work that finds the queue full is done in place
@@ -228,6 +234,7 @@ struct J2SparseLds {
   uint32_t seg_base[kThreads][3];
   uint32_t seg_len[kThreads][3];
   uint32_t cnt[kThreads][11];
+  int row[kThreads];   // dense adjacency row of the item's node, or -1 (walk over T)
   // the sorted lists the correction walk searches, when they fit (at most
   // kHeldList entries): T and the pairwise row of s
   uint32_t t_list[1024], s_list[1024];
@@ -364,28 +371,6 @@ __device__ inline uint32_t j2_agg_pat_t(const J2Ctx& c, uint32_t t, uint32_t cls
   const uint32_t st = cls & 1u, ot = cls >> 1;
   return c.s < t ? (1u | (1u << 2) | (ot << 5) | (st << 7)) : (1u | (ot << 2) | (1u << 5) | (st << 7));
 }
-// a pair {x, y} outside X whose set holds a larger hyperedge, taken off
-__device__ inline void j2_remove(const View& v, const J2Ctx& c, const uint8_t* lut, unsigned long long* h, uint32_t x,
-                                 uint32_t y) {
-  if (x == c.s || x == c.o || y == c.s || y == c.o || j2_in_t(v, c, x) || j2_in_t(v, c, y)) return;
-  hsub(lut, h,
-       1u | (has2(v.hs2, c.s, x) << 1) | (has2(v.hs2, c.o, x) << 2) | (has2(v.hs2, c.s, y) << 4) |
-           (has2(v.hs2, c.o, y) << 5) | (has2(v.hs2, x, y) << 7),
-       1);
-}
-// a 3-node hyperedge {o, y, z} as the histogram at o counts it
-__device__ inline uint32_t j2_agg_pat(const View& v, const J2Ctx& c, uint32_t y, uint32_t z) {
-  if (z < y) {
-    const uint32_t t = y;
-    y = z;
-    z = t;
-  }
-  return 1u | (has2(v.hs2, c.o, y) << 2) | (has2(v.hs2, c.o, z) << 5) | (has2(v.hs2, y, z) << 7);
-}
-__device__ inline bool j2_near_s(const View& v, const J2Ctx& c, uint32_t y) {
-  return has2(v.hs2, c.s, y) || j2_in_t(v, c, y);
-}
-
 // Pairs touching T, for the nodes t of T at positions [first, last) of its
 // index range.  The neighbours y of t outside e by class follow from
 // |N(t) n N(s)| and |N(t) n N(s) n N(o)| (the shorter of the two rows walked)
@@ -417,6 +402,7 @@ __device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, ui
       [&](uint32_t j, uint32_t* base, uint32_t* len) {
         const uint32_t t = j2_t_node(v, pl, c, c.tlo + j);
         const uint32_t dt = deg2_of(v, t);
+        L.row[threadIdx.x] = hub_of(pl, t);
         base[0] = dt <= c.ds ? v.g2_off[t] : v.g2_off[c.s];
         len[0] = dt <= c.ds ? dt : c.ds;
         base[1] = dt <= c.dO ? v.g2_off[t] : v.g2_off[c.o];
@@ -427,16 +413,20 @@ __device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, ui
       [&](uint32_t slot, uint32_t sg, uint32_t pos) {
         const uint32_t t = j2_t_node(v, pl, c, c.tlo + L.item[slot]);
         const uint32_t dt = deg2_of(v, t);
+        auto t_adj = [&](uint32_t z) {
+          const int r = L.row[slot];
+          return r >= 0 ? hub_adj(pl, r, z) : uint32_t(has2(v.hs2, t, z));
+        };
         if (sg == 0) {
           const uint32_t z = v.g2_adj[pos];
-          const uint32_t hit = dt <= c.ds ? s_adj(z) : uint32_t(has2(v.hs2, t, z));
+          const uint32_t hit = dt <= c.ds ? s_adj(z) : t_adj(z);
           if (hit) {
             atomicAdd(&L.cnt[slot][0], 1u);
             if (j2_o_adj(v, pl, c, z)) atomicAdd(&L.cnt[slot][1], 1u);
           }
         } else if (sg == 1) {
           const uint32_t z = v.g2_adj[pos];
-          if (dt <= c.dO ? j2_o_adj(v, pl, c, z) : uint32_t(has2(v.hs2, t, z))) atomicAdd(&L.cnt[slot][2], 1u);
+          if (dt <= c.dO ? j2_o_adj(v, pl, c, z) : t_adj(z)) atomicAdd(&L.cnt[slot][2], 1u);
         } else {
           uint32_t y, cy;
           if (dt <= n_t) {
@@ -445,7 +435,7 @@ __device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, ui
             cy = s_adj(y) | (j2_o_adj(v, pl, c, y) << 1);
           } else {
             y = j2_t_node(v, pl, c, pos);
-            if (y == t || !has2(v.hs2, t, y)) return;
+            if (y == t || !t_adj(y)) return;
             cy = j2_t_cls(pl, c, pos);
           }
           atomicAdd(&L.cnt[slot][3 + cy], 1u);
@@ -563,16 +553,61 @@ __device__ void j2_walk_r(const View& v, const PairLinks& pl, const J2Ctx& c, ui
       [](uint32_t, uint32_t) {});
 }
 
+// The lookups of an item of the two passes below, for its two nodes y < z
+// outside e: their pairs with s and o and with each other, and whether
+// {s, o, y}, {s, o, z} are 3-node hyperedges.  The first slot of every probe
+// is loaded by start, so that they take one round of latency together.
+struct J2Item {
+  Probe64 psy, psz, poy, poz, pyz;
+  Probe128 pty, ptz;
+  uint32_t sy, sz, oy, oz, yz, ty, tz;
+  __device__ void start(const View& v, const J2Ctx& c, uint32_t y, uint32_t z) {
+    if (c.rs < 0) {
+      psy = probe2_start(v.hs2, c.s, y);
+      psz = probe2_start(v.hs2, c.s, z);
+    }
+    if (c.ro < 0) {
+      poy = probe2_start(v.hs2, c.o, y);
+      poz = probe2_start(v.hs2, c.o, z);
+    }
+    pyz = probe2_start(v.hs2, y, z);
+    if (c.any_t) {
+      pty = probe3_start(v.hs3, c.s, c.o, y);
+      ptz = probe3_start(v.hs3, c.s, c.o, z);
+    }
+  }
+  __device__ void end(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t y, uint32_t z) {
+    sy = c.rs >= 0 ? hub_adj(pl, c.rs, y) : uint32_t(probe64_end(v.hs2, psy));
+    sz = c.rs >= 0 ? hub_adj(pl, c.rs, z) : uint32_t(probe64_end(v.hs2, psz));
+    oy = c.ro >= 0 ? hub_adj(pl, c.ro, y) : uint32_t(probe64_end(v.hs2, poy));
+    oz = c.ro >= 0 ? hub_adj(pl, c.ro, z) : uint32_t(probe64_end(v.hs2, poz));
+    yz = probe64_end(v.hs2, pyz);
+    ty = c.any_t && probe128_end(v.hs3, pty);
+    tz = c.any_t && probe128_end(v.hs3, ptz);
+  }
+  // the pair {y, z} outside X whose set holds a larger hyperedge, taken off
+  __device__ void remove(const uint8_t* lut, unsigned long long* h) const {
+    if (!(ty | tz)) hsub(lut, h, 1u | (sy << 1) | (oy << 2) | (sz << 4) | (oz << 5) | (yz << 7), 1);
+  }
+};
+
 // The 3-node hyperedges at s, entries [first, last) of its incidence row, one
 // by one (with the hyperedges at o that match one at s on the far side).
-__device__ void j2_pass_s(const View& v, const J2Ctx& c, uint32_t first, uint32_t last, uint32_t lane,
-                          uint32_t stride, const uint8_t* lut, unsigned long long* h) {
+__device__ void j2_pass_s(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t first, uint32_t last,
+                          uint32_t lane, uint32_t stride, const uint8_t* lut, unsigned long long* h) {
   for (uint32_t p = v.i3_off[c.s] + first + lane; p < v.i3_off[c.s] + last; p += stride) {
     const uint32_t* f = v.e3 + 3ull * v.i3_idx[p];
-    if (f[0] == c.o || f[1] == c.o || f[2] == c.o) continue;
-    const uint32_t y = f[0] == c.s ? f[1] : f[0], z = f[2] == c.s ? f[1] : f[2];
-    j2_remove(v, c, lut, h, y, z);
-    if (!j2_near_s(v, c, y) && !j2_near_s(v, c, z) && has3(v.hs3, c.o, y, z)) hadd(lut, h, j2_agg_pat(v, c, y, z), 1);
+    const uint32_t f0 = f[0], f1 = f[1], f2 = f[2];
+    if (f0 == c.o || f1 == c.o || f2 == c.o) continue;
+    const uint32_t y = f0 == c.s ? f1 : f0, z = f2 == c.s ? f1 : f2;
+    J2Item it;
+    it.start(v, c, y, z);
+    const Probe128 po = probe3_start(v.hs3, c.o, y, z);
+    it.end(v, pl, c, y, z);
+    it.remove(lut, h);
+    // a 3-node hyperedge {o, y, z} away from s, as the histogram at o counts it
+    if (!(it.sy | it.ty | it.sz | it.tz) && probe128_end(v.hs3, po))
+      hadd(lut, h, 1u | (it.oy << 2) | (it.oz << 5) | (it.yz << 7), 1);
   }
 }
 
@@ -582,8 +617,8 @@ __device__ inline uint32_t j2_q_node(const View& v, const J2Ctx& c) {
   const uint32_t fs = v.i4_off[c.s + 1] - v.i4_off[c.s], fo = v.i4_off[c.o + 1] - v.i4_off[c.o];
   return fs <= fo ? c.s : c.o;
 }
-__device__ void j2_pass_q(const View& v, const J2Ctx& c, uint32_t first, uint32_t last, uint32_t lane,
-                          uint32_t stride, const uint8_t* lut, unsigned long long* h) {
+__device__ void j2_pass_q(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t first, uint32_t last,
+                          uint32_t lane, uint32_t stride, const uint8_t* lut, unsigned long long* h) {
   const uint32_t a = j2_q_node(v, c), other = a == c.s ? c.o : c.s;
   for (uint32_t p = v.i4_off[a] + first + lane; p < v.i4_off[a] + last; p += stride) {
     const uint32_t* f = v.e4 + 4ull * v.i4_idx[p];
@@ -594,8 +629,12 @@ __device__ void j2_pass_q(const View& v, const J2Ctx& c, uint32_t first, uint32_
       if (m == c.s || m == c.o) continue;
       if (x == 0xFFFFFFFFu) x = m; else y = m;
     }
-    if (has3(v.hs3, c.s, x, y) || has3(v.hs3, c.o, x, y)) continue;   // removed with a 3-node hyperedge
-    j2_remove(v, c, lut, h, x, y);
+    J2Item it;
+    it.start(v, c, x, y);
+    const Probe128 ps = probe3_start(v.hs3, c.s, x, y), po = probe3_start(v.hs3, c.o, x, y);
+    it.end(v, pl, c, x, y);
+    if (probe128_end(v.hs3, ps) || probe128_end(v.hs3, po)) continue;   // removed with a 3-node hyperedge
+    it.remove(lut, h);
   }
 }
 
@@ -747,8 +786,8 @@ __device__ void sample_j2_k4_sparse(const View& v, const PairLinks& pl, const No
       }
     }
     if (here) {
-      j2_pass_s(v, c, 0, n_s, tid, kThreads, lut, h);
-      j2_pass_q(v, c, 0, n_q, tid, kThreads, lut, h);
+      j2_pass_s(v, pl, c, 0, n_s, tid, kThreads, lut, h);
+      j2_pass_q(v, pl, c, 0, n_q, tid, kThreads, lut, h);
       j2_walk_t(v, pl, c, tc1, tc2, tc3, 0, n_t, L, lut, h);
       j2_walk_r(v, pl, c, 0, n_r, L, lut, h);
     }
@@ -1124,8 +1163,10 @@ __global__ void __launch_bounds__(kThreads) k_sampled(SampledArgs a) {
   flush(h_lds, hist_copy(a.hist, kSampleHistStride), 256);
 }
 
-// Drain the work queue that k_sampled filled (without bit rows).
-__global__ void __launch_bounds__(kThreads) k_sampled_drain(SampledArgs a) {
+// Drain the work queue that k_sampled filled (without bit rows).  Its jobs are
+// chains of dependent lookups: held to the registers of four wavefronts per
+// SIMD (4.07 -> 3.48 ms per estimate on the communication graph at 2%).
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) k_sampled_drain(SampledArgs a) {
   __shared__ uint8_t lut[2048];
   __shared__ unsigned long long h_lds[256];
   __shared__ J2SparseLds L;
@@ -1150,8 +1191,8 @@ __global__ void __launch_bounds__(kThreads) k_sampled_drain(SampledArgs a) {
     if (jb.x == kJobPairS || jb.x == kJobPairQ) {
       const J2Ctx c = j2_ctx(a.v, a.pl, a.es, a.d.n[2], a.d.at(2, jb.y));
       if (a.rows[2]) row = a.rows[2] + uint64_t(jb.y) * 256;
-      if (jb.x == kJobPairS) j2_pass_s(a.v, c, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
-      else j2_pass_q(a.v, c, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
+      if (jb.x == kJobPairS) j2_pass_s(a.v, a.pl, c, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
+      else j2_pass_q(a.v, a.pl, c, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
     } else if (jb.x == kJobPairT || jb.x == kJobPairR) {
       const uint64_t i = a.d.at(2, jb.y);
       const J2Ctx c = j2_ctx(a.v, a.pl, a.es, a.d.n[2], i);
