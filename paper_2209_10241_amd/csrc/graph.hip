@@ -1356,7 +1356,8 @@ void release(hm_graph* H, hipStream_t st = nullptr, bool ordered = false) {
   // and those built later, on first use
   void* later[] = {H->g2_eid,  H->pl_keys,  H->pl_edge,  H->pl_slot,   H->pl_codeg, H->pl_third, H->pl_adj,
                    H->pl_pre,  H->q_slot,   H->q_fourth, H->b4_order,  H->hub_rank, H->hub_bits, H->proj_bits,
-                   H->ns_tri,  H->ns_nbr,   H->ns_h3,    H->es,        H->e5,       H->hs5,   H->dense5};
+                   H->ns_tri,  H->ns_nbr,   H->ns_h3,    H->es,        H->e5,       H->hs5,   H->dense5,
+                   H->rank_of, H->node_of, H->rank_bounds};
   std::vector<void*> ps(std::begin(later), std::end(later));
   if (H->arena)
     ps.push_back(H->arena);

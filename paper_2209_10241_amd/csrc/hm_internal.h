@@ -238,6 +238,7 @@ struct Scratch {
 int count_sparse(const hm_graph* H, int k, hipStream_t st);
 int ensure_pair_links(hm_graph* H, hipStream_t st);
 int ensure_hub_rows(hm_graph* H, hipStream_t st);
+int ensure_ranks(hm_graph* H, hipStream_t st);
 int ensure_node_stats(hm_graph* H, hipStream_t st);
 int ensure_edge_stats(hm_graph* H, hipStream_t st);
 
@@ -323,6 +324,12 @@ struct hm_graph {
   // the 3-node hyperedges by decreasing estimated cost of their exact
   // neighbourhood count (built on first use without bit rows)
   uint32_t* b4_order = nullptr;
+  // the nodes by ascending class of degrees (built on first use without bit
+  // rows; see wedge.hip): rank of each node, node of each rank, and the first
+  // ranks of degree >= 2 and of wedge.hip's larger classes
+  uint32_t* rank_of = nullptr;
+  uint32_t* node_of = nullptr;
+  uint32_t* rank_bounds = nullptr;
   // dense adjacency bit rows of the highest-degree nodes (built on first use
   // without bit rows): hub_rank[v] is v's row or -1; rows of hub_words words
   int32_t* hub_rank = nullptr;

@@ -124,10 +124,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   flush(h_sub, hc + kSub, 256);
 }
 
-// Sort keys of the 3-node hyperedges for k_sp_b4: the complement of an
-// estimate of the memory transactions of each (two per entry of its shortest
-// pairwise row, six per entry of the 4-node incidence list it reads when
-// there is no 4-node index), with the hyperedge as value.
+// Sort keys of the 3-node hyperedges for k_sp_b4: the complement of the
+// logarithmic class (eight per octave, so that one radix pass orders them) of
+// an estimate of the memory transactions of each (two per entry of its
+// shortest pairwise row, six per entry of the 4-node incidence list it reads
+// when there is no 4-node index), with the hyperedge as value.
 __global__ void k_b4_cost_keys(View v, PairLinks pl, uint64_t n3, unsigned long long* __restrict__ keys,
                                uint32_t* __restrict__ vals) {
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n3; i += uint64_t(gridDim.x) * blockDim.x) {
@@ -137,7 +138,8 @@ __global__ void k_b4_cost_keys(View v, PairLinks pl, uint64_t n3, unsigned long 
                    fc = v.i4_off[c + 1] - v.i4_off[c];
     // (with the 4-node index, the 4-node hyperedges holding e are one lookup)
     const uint64_t cost = 2 * dmin + (pl.q_bits ? 0 : 6 * uint64_t(min(fa, min(fb, fc))));
-    keys[i] = 0xFFFFFFFFull - min<uint64_t>(cost, 0xFFFFFFFFull);
+    const uint32_t x = uint32_t(min<uint64_t>(cost, 0x7FFFFFFFull)) + 8, e = 31 - uint32_t(__clz(int(x)));
+    keys[i] = 255u - min(255u, 8 * (e - 3) + ((x >> (e - 3)) & 7u));
     vals[i] = uint32_t(i);
   }
 }
@@ -189,14 +191,23 @@ __global__ void k_pl_third_keys(const uint32_t* __restrict__ e3, uint64_t n, uns
   }
 }
 
-__global__ void k_pl_pair_keys(const uint32_t* __restrict__ e3, const uint32_t* __restrict__ codes, uint64_t n,
+// (packed to `bits` per node for the sort, which then needs 2 * bits of key;
+// k_pl_wide_keys widens them to (x << 32) | y)
+__global__ void k_pl_pair_keys(const uint32_t* __restrict__ e3, const uint32_t* __restrict__ codes, uint64_t n, int bits,
                                unsigned long long* __restrict__ keys) {
   for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x) {
     const uint32_t code = codes[p];
     const uint64_t i = code / 3;
     const uint32_t s = code % 3;
     const unsigned long long a = e3[3 * i], b = e3[3 * i + 1], c = e3[3 * i + 2];
-    keys[p] = s == 0 ? ((a << 32) | b) : (s == 1 ? ((a << 32) | c) : ((b << 32) | c));
+    keys[p] = s == 0 ? ((a << bits) | b) : (s == 1 ? ((a << bits) | c) : ((b << bits) | c));
+  }
+}
+
+__global__ void k_pl_wide_keys(unsigned long long* __restrict__ keys, uint64_t n, int bits) {
+  for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x) {
+    const unsigned long long k = keys[p];
+    keys[p] = ((k >> bits) << 32) | (k & ((1ull << bits) - 1));
   }
 }
 
@@ -249,34 +260,83 @@ __global__ void k_pl_third(const uint32_t* __restrict__ e3, const unsigned long 
 }
 
 // Common pairwise neighbours of every distinct pair of the index, into the
-// pair's slot: each wavefront takes 64 positions of the sorted keys at a
-// time and, for each run that starts among them, walks the shorter of the two
-// rows and probes the other.
-__global__ void k_pl_codeg(View v, const unsigned long long* __restrict__ keys, uint64_t n,
-                           const unsigned long long* __restrict__ slot, unsigned long long mask,
-                           uint32_t* __restrict__ codeg) {
-  const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint64_t wave = (uint64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
-  const uint64_t n_waves = uint64_t(gridDim.x) * blockDim.x / kWave;
-  for (uint64_t p0 = wave * kWave; p0 < n; p0 += n_waves * kWave) {
-    const uint64_t p = p0 + lane;
-    const bool start = p < n && (p == 0 || keys[p - 1] != keys[p]);
-    unsigned long long m = __ballot(start);
-    while (m) {
-      const uint32_t l = uint32_t(__ffsll(m) - 1);
-      m &= m - 1;
-      const unsigned long long key = keys[p0 + l];
-      const uint32_t x = uint32_t(key >> 32), y = uint32_t(key);
-      const uint32_t dx = deg2_of(v, x), dy = deg2_of(v, y);
-      const uint32_t sn = dx <= dy ? x : y, on = dx <= dy ? y : x;
-      uint32_t c = 0;
-      for (uint32_t q = v.g2_off[sn] + lane; q < v.g2_off[sn + 1]; q += kWave) c += has2(v.hs2, on, v.g2_adj[q]);
-      c = wave_sum_u32(c);
-      if (lane == 0) {
-        unsigned long long h = mix64(key) & mask;
-        while (slot[2 * h] != key) h = (h + 1) & mask;
-        codeg[h] = c;
+// pair's slot: a workgroup takes 256 positions of the sorted keys; for each
+// run that starts among them the shorter of the pair's two rows is walked,
+// all rows laid out flat (four positions per thread and round), and tested
+// against the other node's dense row, or probed.  (A wavefront per run left
+// most lanes idle and probed every position: 2.8 ms on the communication
+// graph, 1.3 on the co-authorship one.)
+__global__ void __launch_bounds__(kThreads) k_pl_codeg(View v, const unsigned long long* __restrict__ keys, uint64_t n,
+                                                       const unsigned long long* __restrict__ slot,
+                                                       unsigned long long mask, const int32_t* __restrict__ hub_rank,
+                                                       const uint32_t* __restrict__ hub_bits, uint32_t hub_w,
+                                                       uint32_t* __restrict__ codeg) {
+  constexpr uint32_t L = 4;
+  __shared__ uint32_t pos[kThreads + 1], row[kThreads], other[kThreads], cnt[kThreads];
+  __shared__ int hub[kThreads];
+  __shared__ uint32_t wave_tot[kWavesPerBlock];
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  for (uint64_t p0 = uint64_t(blockIdx.x) * kThreads; p0 < n; p0 += uint64_t(gridDim.x) * kThreads) {
+    const uint64_t p = p0 + tid;
+    unsigned long long key = 0;
+    uint32_t len = 0;
+    bool start = false;
+    __syncthreads();   // the previous positions' arrays are no longer read
+    if (p < n) {
+      key = keys[p];
+      start = p == 0 || keys[p - 1] != key;
+      if (start) {
+        const uint32_t x = uint32_t(key >> 32), y = uint32_t(key);
+        const uint32_t xb = v.g2_off[x], xe = v.g2_off[x + 1], yb = v.g2_off[y], ye = v.g2_off[y + 1];
+        const bool at_x = xe - xb <= ye - yb;
+        len = at_x ? xe - xb : ye - yb;
+        row[tid] = at_x ? xb : yb;
+        other[tid] = at_x ? y : x;
+        hub[tid] = hub_rank ? hub_rank[at_x ? y : x] : -1;
       }
+    }
+    cnt[tid] = 0;
+    uint32_t tot;
+    uint32_t at = wave_exclusive_scan(len, &tot);
+    if (lane == 0) wave_tot[wv] = tot;
+    __syncthreads();
+    for (uint32_t q = 0; q < wv; ++q) at += wave_tot[q];
+    pos[tid] = at;
+    if (tid == kThreads - 1) pos[kThreads] = at + len;
+    __syncthreads();
+    const uint32_t total = pos[kThreads];
+    for (uint32_t t0 = tid * L; t0 < total; t0 += kThreads * L) {
+      uint32_t lo = 0, hi = kThreads;   // pos[lo] <= t0 < pos[hi]
+      while (hi - lo > 1) {
+        const uint32_t m = (lo + hi) >> 1;
+        if (pos[m] <= t0) lo = m; else hi = m;
+      }
+      uint32_t k[L], z[L];
+      Probe64 pr[L];
+#pragma unroll
+      for (uint32_t r = 0; r < L; ++r) {
+        const uint32_t t = min(t0 + r, total - 1);
+        while (pos[lo + 1] <= t) ++lo;   // (positions without a start have no row)
+        k[r] = lo;
+        z[r] = v.g2_adj[row[lo] + (t - pos[lo])];
+      }
+#pragma unroll
+      for (uint32_t r = 0; r < L; ++r)
+        if (hub[k[r]] < 0) pr[r] = probe2_start(v.hs2, other[k[r]], z[r]);
+#pragma unroll
+      for (uint32_t r = 0; r < L; ++r) {
+        if (t0 + r >= total) continue;
+        const int h = hub[k[r]];
+        const bool hit = h >= 0 ? (hub_bits[uint64_t(h) * hub_w + (z[r] >> 5)] >> (z[r] & 31)) & 1u
+                                : probe64_end(v.hs2, pr[r]);
+        if (hit) atomicAdd(&cnt[k[r]], 1u);
+      }
+    }
+    __syncthreads();
+    if (start) {
+      unsigned long long h = mix64(key) & mask;
+      while (slot[2 * h] != key) h = (h + 1) & mask;
+      codeg[h] = cnt[tid];
     }
   }
 }
@@ -478,6 +538,7 @@ int build_quad_index(hm_graph* H, hipStream_t st) {
 int ensure_pair_links(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->pl_keys || H->n_by_size[3] == 0) return HM_OK;
+  HM_TRY(ensure_hub_rows(H, st));
   const uint64_t n = 3 * H->n_by_size[3];
   void *k = nullptr, *e = nullptr, *kt = nullptr, *et = nullptr;
   HM_TRY(dalloc(&k, n * sizeof(unsigned long long)));
@@ -495,13 +556,17 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
     rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(e),
                           static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(et), n, bits, st);
   if (rc == HM_OK) {
-    k_pl_pair_keys<<<grid_cap(n, 256, 4096), 256, 0, st>>>(H->e3, static_cast<const uint32_t*>(e), n,
+    k_pl_pair_keys<<<grid_cap(n, 256, 4096), 256, 0, st>>>(H->e3, static_cast<const uint32_t*>(e), n, bits,
                                                            static_cast<unsigned long long*>(k));
     if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
   }
   if (rc == HM_OK)
     rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(e),
-                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(et), n, 32 + bits, st);
+                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(et), n, 2 * bits, st);
+  if (rc == HM_OK) {
+    k_pl_wide_keys<<<grid_cap(n, 256, 4096), 256, 0, st>>>(static_cast<unsigned long long*>(k), n, bits);
+    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
+  }
   // the index: at most n distinct keys, load at most 1/2
   const unsigned long long cap = pow2_capacity(n);
   void *slots = nullptr, *codeg = nullptr, *third = nullptr, *adj = nullptr, *pre = nullptr;
@@ -519,9 +584,9 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
                                          static_cast<unsigned long long*>(slots), cap - 1);
     k_pl_third<<<g, 256, 0, st>>>(H->e3, static_cast<const unsigned long long*>(k), static_cast<uint32_t*>(e), n,
                                   H->hs2, static_cast<uint32_t*>(third), static_cast<uint8_t*>(adj));
-    k_pl_codeg<<<grid_cap((n + kWave - 1) / kWave, kWavesPerBlock, 4096), kThreads, 0, st>>>(
+    k_pl_codeg<<<grid_cap(n, kThreads, 8192), kThreads, 0, st>>>(
         view_of(H), static_cast<const unsigned long long*>(k), n, static_cast<const unsigned long long*>(slots),
-        cap - 1, static_cast<uint32_t*>(codeg));
+        cap - 1, H->hub_rank, H->hub_bits, H->hub_words, static_cast<uint32_t*>(codeg));
     if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
   }
   // prefix counts of the entries by adjacency class (the flags reuse et)
@@ -567,76 +632,79 @@ PairLinks pair_links_of(const hm_graph* H) {
   return pl;
 }
 
-// One workgroup per dense row: the bits of the node's pairwise neighbours.
-__global__ void k_hub_rows(const uint32_t* __restrict__ g2_off, const uint32_t* __restrict__ g2_adj,
-                           const uint32_t* __restrict__ hubs, uint32_t n_hub, uint32_t words,
-                           uint32_t* __restrict__ bits) {
-  for (uint32_t r = blockIdx.x; r < n_hub; r += gridDim.x) {
-    const uint32_t x = hubs[r];
-    uint32_t* row = bits + uint64_t(r) * words;
-    for (uint32_t p = g2_off[x] + threadIdx.x; p < g2_off[x + 1]; p += blockDim.x) {
+// Dense rows: row i is that of the node of rank n - 1 - i, when it has at
+// least min_deg pairwise neighbours.
+__global__ void k_hub_ranks(const uint32_t* __restrict__ g2_off, const uint32_t* __restrict__ rank_of, uint32_t n,
+                            uint32_t n_rows, uint32_t min_deg, int32_t* __restrict__ hub_rank) {
+  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
+    const uint32_t i = n - 1 - rank_of[x];
+    hub_rank[x] = i < n_rows && g2_off[x + 1] - g2_off[x] >= min_deg ? int32_t(i) : -1;
+  }
+}
+
+// One workgroup per dense row and range of kHubChunk words: the bits gather
+// in LDS and go out once (an atomic per neighbour on device memory took 0.39
+// ms for 363 rows of 2.3 MB, most of it the longest row).
+constexpr uint32_t kHubChunk = 8192;
+__global__ void __launch_bounds__(1024) k_hub_rows(const uint32_t* __restrict__ g2_off,
+                                                   const uint32_t* __restrict__ g2_adj,
+                                                   const uint32_t* __restrict__ node_of, uint32_t n, uint32_t n_rows,
+                                                   uint32_t min_deg, uint32_t words, uint32_t chunks,
+                                                   uint32_t* __restrict__ bits) {
+  __shared__ uint32_t part[kHubChunk];
+  for (uint64_t t = blockIdx.x; t < uint64_t(n_rows) * chunks; t += gridDim.x) {
+    const uint32_t r = uint32_t(t / chunks), w0 = uint32_t(t % chunks) * kHubChunk;
+    const uint32_t x = node_of[n - 1 - r], cnt = min(kHubChunk, words - w0);
+    uint32_t b = g2_off[x], e = g2_off[x + 1];
+    if (e - b < min_deg) continue;
+    // the row's entries (ascending) in this range of words
+    if (w0) b = upper_bound(g2_adj, b, e, w0 * 32 - 1);
+    if (w0 + cnt < words) e = upper_bound(g2_adj, b, e, (w0 + cnt) * 32 - 1);
+    __syncthreads();   // the previous part is written out
+    for (uint32_t i = threadIdx.x; i < cnt; i += 1024) part[i] = 0;
+    __syncthreads();
+    for (uint32_t p = b + threadIdx.x; p < e; p += 1024) {
       const uint32_t z = g2_adj[p];
-      atomicOr(&row[z >> 5], 1u << (z & 31));
+      atomicOr(&part[(z >> 5) - w0], 1u << (z & 31));
     }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < cnt; i += 1024) bits[uint64_t(r) * words + w0 + i] = part[i];
   }
 }
 
 // H->hub_rank and H->hub_bits: the nodes with at least hub_min_degree()
-// pairwise neighbours, highest degree first (ties by id), as many as fit in
-// kHubRowBytes.  Built once per graph.
+// pairwise neighbours, the highest ranks first (wedge.hip's order by degree),
+// as many as fit in kHubRowBytes.  Built once per graph, without a host
+// round trip.
 int ensure_hub_rows(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->hub_built) return HM_OK;
   const uint32_t n = H->n_nodes, min_deg = hub_min_degree();
   const uint32_t words = (n + 31) / 32;
-  if (n == 0 || min_deg == 0 || !H->g2_off) {
+  uint64_t rows = 0;
+  if (n && min_deg && H->g2_off) {
+    // at most 2 |E2| / min_deg nodes have that many neighbours
+    rows = std::min<uint64_t>(kHubRowBytes / (uint64_t(words) * sizeof(uint32_t)), 2 * H->n_by_size[2] / min_deg);
+    rows = std::min<uint64_t>(rows, n);
+  }
+  if (!rows) {
     H->hub_built = true;
     return HM_OK;
   }
-  std::vector<uint32_t> off(size_t(n) + 1);
-  HM_HIP(hipMemcpyAsync(off.data(), H->g2_off, off.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HM_HIP(hipStreamSynchronize(st));
-  std::vector<uint32_t> hubs;
-  for (uint32_t x = 0; x < n; ++x)
-    if (off[x + 1] - off[x] >= min_deg) hubs.push_back(x);
-  std::sort(hubs.begin(), hubs.end(), [&](uint32_t p, uint32_t q) {
-    const uint32_t dp = off[p + 1] - off[p], dq = off[q + 1] - off[q];
-    return dp != dq ? dp > dq : p < q;
-  });
-  const uint64_t max_rows = kHubRowBytes / (uint64_t(words) * sizeof(uint32_t));
-  if (hubs.size() > max_rows) hubs.resize(size_t(max_rows));
-  if (hubs.empty()) {
-    H->hub_built = true;
-    return HM_OK;
-  }
-  std::vector<int32_t> rank(n, -1);
-  for (size_t r = 0; r < hubs.size(); ++r) rank[hubs[r]] = int32_t(r);
-  const uint32_t n_hub = uint32_t(hubs.size());
-  void *rank_d = nullptr, *hubs_d = nullptr, *bits_d = nullptr;
-  int rc = dalloc(&rank_d, size_t(n) * sizeof(int32_t));
-  if (rc == HM_OK) rc = dalloc(&hubs_d, size_t(n_hub) * sizeof(uint32_t));
-  if (rc == HM_OK) rc = dalloc(&bits_d, size_t(n_hub) * words * sizeof(uint32_t));
-  if (rc == HM_OK && (hipMemcpyAsync(rank_d, rank.data(), rank.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) !=
-                          hipSuccess ||
-                      hipMemcpyAsync(hubs_d, hubs.data(), hubs.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st) !=
-                          hipSuccess))
-    rc = HM_EDEVICE;
-  if (rc == HM_OK) rc = fill_u32(static_cast<uint32_t*>(bits_d), 0, uint64_t(n_hub) * words, st);
-  if (rc == HM_OK) {
-    k_hub_rows<<<std::min<uint32_t>(n_hub, 4096), 256, 0, st>>>(H->g2_off, H->g2_adj, static_cast<const uint32_t*>(hubs_d),
-                                                               n_hub, words, static_cast<uint32_t*>(bits_d));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  // the host vectors stay alive until the copies have run
-  if (hipStreamSynchronize(st) != hipSuccess && rc == HM_OK) rc = HM_EDEVICE;
-  dfree(hubs_d);
-  if (rc != HM_OK) {
-    dfree(rank_d);
-    dfree(bits_d);
-    return rc;
-  }
-  H->hub_rank = static_cast<int32_t*>(rank_d);
-  H->hub_bits = static_cast<uint32_t*>(bits_d);
+  HM_TRY(ensure_ranks(H, st));
+  Scratch kept(st);
+  int32_t* rank = nullptr;
+  uint32_t* bits = nullptr;
+  HM_TRY(kept.get(&rank, n));
+  HM_TRY(kept.get(&bits, rows * words));
+  const uint32_t chunks = (words + kHubChunk - 1) / kHubChunk;
+  k_hub_ranks<<<grid_cap(n, 256, 2048), 256, 0, st>>>(H->g2_off, H->rank_of, n, uint32_t(rows), min_deg, rank);
+  k_hub_rows<<<grid_cap(rows * chunks, 1, 2048), 1024, 0, st>>>(H->g2_off, H->g2_adj, H->node_of, n, uint32_t(rows),
+                                                                 min_deg, words, chunks, bits);
+  HM_HIP(hipGetLastError());
+  kept.ptrs.clear();
+  H->hub_rank = rank;
+  H->hub_bits = bits;
   H->hub_words = words;
   H->hub_built = true;
   return HM_OK;
@@ -660,7 +728,7 @@ int ensure_b4_order(hm_graph* H, hipStream_t st) {
   }
   if (rc == HM_OK)
     rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(o),
-                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(ot), n3, 32, st);
+                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(ot), n3, 8, st);
   void* used[] = {k, kt, ot, o};   // (the last is kept)
   dfree_on(used, rc == HM_OK ? 3 : 4, st);
   if (rc != HM_OK) return rc;
@@ -683,7 +751,7 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   HM_TRY(tmp.get(&tri_e, n2));
   HM_TRY(fill_u64(acc, 0, kAccN, st));
   if (n2) {
-    HM_TRY(wedge_counts(H, k, tri_e, acc + kAccC4, acc + kAccK4, st));
+    HM_TRY(wedge_counts(const_cast<hm_graph*>(H), k, tri_e, acc + kAccC4, acc + kAccK4, st));
     ProfileScope ps("k_sp_pairs", st);
     k_sp_pairs<<<grid_cap(n2, kThreads, 512), kThreads, 0, st>>>(v, n2, tri_e, acc);
   }

@@ -55,13 +55,13 @@ struct Ranked {
   const uint32_t* core_eid;  // position in e2 of the entry's pair
   const uint32_t* out_adj;
   const uint32_t* out_eid;
-  const uint32_t* weight;    // rank -> nodes marked and positions walked (degree >= kSmallDeg)
-  const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg, largest out row
+  const uint32_t* weight;    // rank -> bound on the nodes marked and positions walked (degree >= kSmallDeg)
+  const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg
 };
 
 __global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, unsigned long long* __restrict__ keys,
                             uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
-  if (blockIdx.x == 0 && threadIdx.x < 3) bounds[threadIdx.x] = threadIdx.x < 2 ? n : 0u;
+  if (blockIdx.x == 0 && threadIdx.x < 2) bounds[threadIdx.x] = n;
   for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
     keys[x] = degree_class(g2_off[x + 1] - g2_off[x]);
     vals[x] = x;
@@ -79,17 +79,36 @@ __global__ void k_rank_assign(const unsigned long long* __restrict__ keys, const
 }
 
 // Per adjacency entry: whether it is in the core rows (low half) and in the
-// out rows (high half), for one scan of both.
-__global__ void k_core_flags(const uint32_t* __restrict__ g2_adj, const uint32_t* __restrict__ g2_eid,
-                             const uint32_t* __restrict__ e2, uint64_t m, const uint32_t* __restrict__ rank_of,
-                             const uint32_t* __restrict__ bounds, unsigned long long* __restrict__ flag) {
-  const uint32_t r2 = bounds[0];
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < m; i += uint64_t(gridDim.x) * blockDim.x) {
-    const uint32_t z = g2_adj[i];
-    const uint64_t e = g2_eid[i];
-    const uint32_t owner = e2[2 * e] ^ e2[2 * e + 1] ^ z;
-    const uint32_t rz = rank_of[z];
-    flag[i] = rz >= r2 ? (1ull | ((unsigned long long)(rz > rank_of[owner]) << 32)) : 0ull;
+// out rows (high half), for one scan of both.  And per rank u (weight, zero
+// before) a bound on what its walk marks and walks: its degree and the
+// degrees of its neighbours before it.  A wavefront takes 64 consecutive
+// entries, sums them by row with a segmented scan and adds once per row (a
+// wavefront per row left the longest row, 1.1e5 entries, as a tail of 0.2 ms).
+__global__ void k_core_flags(const uint32_t* __restrict__ g2_off, const uint32_t* __restrict__ g2_adj,
+                             const uint32_t* __restrict__ g2_eid, const uint32_t* __restrict__ e2, uint64_t m,
+                             const uint32_t* __restrict__ rank_of, const uint32_t* __restrict__ bounds,
+                             unsigned long long* __restrict__ flag, uint32_t* __restrict__ weight) {
+  const uint32_t r0 = bounds[0], r1 = bounds[1];
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  for (uint64_t base = (uint64_t(blockIdx.x) * blockDim.x + threadIdx.x) & ~uint64_t(kWave - 1); base < m;
+       base += uint64_t(gridDim.x) * blockDim.x) {
+    const uint64_t i = base + lane;
+    uint32_t ro = kEmpty32, d = 0;
+    if (i < m) {
+      const uint32_t z = g2_adj[i];
+      const uint64_t e = g2_eid[i];
+      ro = rank_of[e2[2 * e] ^ e2[2 * e + 1] ^ z];
+      const uint32_t rz = rank_of[z];
+      flag[i] = rz >= r0 ? (1ull | ((unsigned long long)(rz > ro) << 32)) : 0ull;
+      d = 1 + (rz < ro && ro >= r1 ? g2_off[z + 1] - g2_off[z] : 0u);
+    }
+    for (int s = 1; s < kWave; s <<= 1) {
+      const uint32_t o = uint32_t(__shfl_up(int(ro), s, kWave)), dd = uint32_t(__shfl_up(int(d), s, kWave));
+      if (int(lane) >= s && o == ro) d += dd;   // (a row's entries are consecutive)
+    }
+    const uint32_t after = uint32_t(__shfl_down(int(ro), 1, kWave));
+    // (degrees add up to at most 2 |E2|, below 2^32)
+    if (i < m && ro >= r1 && (lane == kWave - 1 || after != ro)) atomicAdd(&weight[ro], d);
   }
 }
 
@@ -114,7 +133,7 @@ __global__ void k_core_fill(const uint32_t* __restrict__ g2_adj, const uint32_t*
 __global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uint64_t m,
                             const uint32_t* __restrict__ node_of, const unsigned long long* __restrict__ flag,
                             const unsigned long long* __restrict__ pos, uint2* __restrict__ core,
-                            uint2* __restrict__ out, uint32_t* __restrict__ bounds) {
+                            uint2* __restrict__ out, uint32_t* __restrict__ longest) {
   uint32_t most = 0;
   auto at = [&](uint32_t i) { return i < m ? pos[i] : (m ? pos[m - 1] + flag[m - 1] : 0ull); };
   for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
@@ -125,26 +144,7 @@ __global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uin
     most = max(most, uint32_t(e >> 32) - uint32_t(b >> 32));
   }
   for (int d = kWave / 2; d > 0; d >>= 1) most = max(most, uint32_t(__shfl_xor(int(most), d, kWave)));
-  if ((threadIdx.x & (kWave - 1)) == 0 && most > 2) atomicMax(&bounds[2], most);
-}
-
-// Nodes marked and positions walked for every u of degree >= kSmallDeg
-// (saturating): one wavefront per u.
-__global__ void k_core_weight(Ranked g, uint32_t* __restrict__ weight) {
-  const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave, n_waves = gridDim.x * blockDim.x / kWave;
-  const uint32_t r1 = g.bounds[1];
-  for (uint32_t i = wave; i < g.n - r1; i += n_waves) {
-    const uint32_t u = r1 + i;
-    const uint2 row = g.core[u];
-    unsigned long long s = 0;
-    for (uint32_t q = lane; q < row.y; q += kWave) {
-      const uint32_t x = g.core_adj[row.x + q];
-      if (x < u) s += g.core[x].y;
-    }
-    s = wave_sum(s) + row.y;
-    if (lane == 0) weight[u] = s > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(s);
-  }
+  if ((threadIdx.x & (kWave - 1)) == 0 && most > 2) atomicMax(longest, most);
 }
 
 // ------------------------------------------------------------------ the walk
@@ -764,44 +764,37 @@ unsigned grid_of(uint64_t items, uint64_t per_block, unsigned cap) {
 
 // H's pairwise graph in rank space, in buffers of tmp; *most receives the
 // largest out row (one host read-back) when asked for.
-int ranked_graph(const hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_t* most) {
+int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_t* most) {
+  HM_TRY(ensure_ranks(H, st));
   const uint32_t n = H->n_nodes;
   const uint64_t n2 = H->n_by_size[2], m = 2 * n2;
-  unsigned long long *keys = nullptr, *keys_tmp = nullptr, *flag = nullptr, *pos = nullptr;
-  uint32_t *node_of = nullptr, *vals_tmp = nullptr, *rank_of = nullptr, *core_adj = nullptr, *core_eid = nullptr,
-           *out_adj = nullptr, *out_eid = nullptr, *weight = nullptr, *bounds = nullptr;
+  unsigned long long *flag = nullptr, *pos = nullptr;
+  uint32_t *core_adj = nullptr, *core_eid = nullptr, *out_adj = nullptr, *out_eid = nullptr, *weight = nullptr,
+           *longest = nullptr;
   uint2 *core = nullptr, *rows = nullptr;
-  HM_TRY(tmp.get(&keys, n));
-  HM_TRY(tmp.get(&keys_tmp, n));
-  HM_TRY(tmp.get(&node_of, n));
-  HM_TRY(tmp.get(&vals_tmp, n));
-  HM_TRY(tmp.get(&rank_of, n));
   HM_TRY(tmp.get(&weight, n));
   HM_TRY(tmp.get(&core, n));
   HM_TRY(tmp.get(&rows, n));
-  HM_TRY(tmp.get(&bounds, 4));
+  HM_TRY(tmp.get(&longest, 1));
   HM_TRY(tmp.get(&flag, m));
   HM_TRY(tmp.get(&pos, m));
   HM_TRY(tmp.get(&core_adj, m));
   HM_TRY(tmp.get(&core_eid, m));
   HM_TRY(tmp.get(&out_adj, n2));
   HM_TRY(tmp.get(&out_eid, n2));
-  k_rank_keys<<<grid_of(n, 256, 2048), 256, 0, st>>>(H->g2_off, n, keys, node_of, bounds);
-  HM_HIP(hipGetLastError());
-  HM_TRY(radix_sort_pairs(keys, node_of, keys_tmp, vals_tmp, n, kRankBits, st));
-  k_rank_assign<<<grid_of(n, 256, 2048), 256, 0, st>>>(keys, node_of, n, rank_of, bounds);
-  k_core_flags<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, H->e2, m, rank_of, bounds, flag);
+  HM_TRY(fill_u32(longest, 0, 1, st));
+  HM_TRY(fill_u32(weight, 0, n, st));
+  k_core_flags<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_off, H->g2_adj, H->g2_eid, H->e2, m, H->rank_of,
+                                                      H->rank_bounds, flag, weight);
   HM_HIP(hipGetLastError());
   HM_TRY(scan_exclusive_u64(flag, pos, m, st));
-  k_core_fill<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, m, rank_of, flag, pos, core_adj, core_eid,
-                                                     out_adj, out_eid);
-  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, node_of, flag, pos, core, rows, bounds);
+  k_core_fill<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, m, H->rank_of, flag, pos, core_adj,
+                                                     core_eid, out_adj, out_eid);
+  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, H->node_of, flag, pos, core, rows, longest);
   HM_HIP(hipGetLastError());
-  *out = Ranked{n, rank_of, node_of, core, rows, core_adj, core_eid, out_adj, out_eid, weight, bounds};
-  k_core_weight<<<512, 256, 0, st>>>(*out, weight);
-  HM_HIP(hipGetLastError());
+  *out = Ranked{n, H->rank_of, H->node_of, core, rows, core_adj, core_eid, out_adj, out_eid, weight, H->rank_bounds};
   if (most) {
-    HM_HIP(hipMemcpyAsync(most, bounds + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HM_HIP(hipMemcpyAsync(most, longest, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HM_HIP(hipStreamSynchronize(st));
   }
   return HM_OK;
@@ -840,9 +833,38 @@ int launch_cliques(const hm_graph* H, const Ranked& g, uint32_t most, unsigned l
 
 }  // namespace
 
+// H->rank_of, node_of and rank_bounds, on first use.
+int ensure_ranks(hm_graph* H, hipStream_t st) {
+  if (H->rank_of) return HM_OK;
+  note_use(H, st);
+  const uint32_t n = H->n_nodes;
+  Scratch tmp(st);
+  unsigned long long *keys = nullptr, *keys_tmp = nullptr;
+  uint32_t* vals_tmp = nullptr;
+  HM_TRY(tmp.get(&keys, n));
+  HM_TRY(tmp.get(&keys_tmp, n));
+  HM_TRY(tmp.get(&vals_tmp, n));
+  // (handed over to the graph once the launches are in)
+  Scratch kept(st);
+  uint32_t *rank_of = nullptr, *node_of = nullptr, *bounds = nullptr;
+  HM_TRY(kept.get(&rank_of, n));
+  HM_TRY(kept.get(&node_of, n));
+  HM_TRY(kept.get(&bounds, 2));
+  k_rank_keys<<<grid_of(n, 256, 2048), 256, 0, st>>>(H->g2_off, n, keys, node_of, bounds);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(keys, node_of, keys_tmp, vals_tmp, n, kRankBits, st));
+  k_rank_assign<<<grid_of(n, 256, 2048), 256, 0, st>>>(keys, node_of, n, rank_of, bounds);
+  HM_HIP(hipGetLastError());
+  kept.ptrs.clear();
+  H->rank_of = rank_of;
+  H->node_of = node_of;
+  H->rank_bounds = bounds;
+  return HM_OK;
+}
+
 // Triangles of every pair of G2 (tri_e, n2 values) and, at order 4, the number
 // of 4-cycles and of 4-cliques of G2 (non-induced; device words).
-int wedge_counts(const hm_graph* H, int k, uint32_t* tri_e, unsigned long long* n_cycles, unsigned long long* n_cliques,
+int wedge_counts(hm_graph* H, int k, uint32_t* tri_e, unsigned long long* n_cycles, unsigned long long* n_cliques,
                  hipStream_t st) {
   const uint64_t n2 = H->n_by_size[2];
   Scratch tmp(st);
@@ -872,7 +894,7 @@ __global__ void k_es_widen(const uint32_t* __restrict__ t32, uint64_t n, unsigne
 }
 
 // The per-pair statistics of hm_graph::es (6 x n2).
-int wedge_edge_stats(const hm_graph* H, unsigned long long* es, hipStream_t st) {
+int wedge_edge_stats(hm_graph* H, unsigned long long* es, hipStream_t st) {
   const uint64_t n2 = H->n_by_size[2];
   HM_TRY(fill_u64(es, 0, 6 * n2, st));
   if (!n2) return HM_OK;
