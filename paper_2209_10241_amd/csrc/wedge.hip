@@ -13,9 +13,11 @@
 // membership tests and the path counters are LDS operations, where a hash
 // probe per position and a sort of one key per path went to memory before.
 // Triangles and 4-cycles together: co-authorship (N = 10^6, 2 x 10^7
-// positions) 3.8 -> 1.2 ms, communication (N = 5 x 10^4, 1.3 x 10^8
-// positions) 14.0 -> 2.1 ms; 4-cliques 1.0 -> 0.16 and 6.4 -> 0.74 ms.  The
-// longest walk, on one CU, bounds the launch.
+// positions) 3.8 -> 1.1 ms, communication (N = 5 x 10^4, 1.3 x 10^8
+// positions) 14.0 -> 1.0 ms; 4-cliques 1.0 -> 0.16 and 6.4 -> 0.74 ms.
+//
+// The longest walks are split by the neighbours x into shares on several CUs,
+// whose counters are summed by another launch.
 //
 // u is taken by the size of its walk: a wavefront with a hash table of 1,024
 // slots (degree below 24), a workgroup of 256 threads with 4,096 slots (at
@@ -57,7 +59,12 @@ struct Ranked {
   const uint32_t* out_eid;
   const uint32_t* weight;    // rank -> bound on the nodes marked and positions walked (degree >= kSmallDeg)
   const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg
+  const uint32_t* facts;     // kLongestOut ..
 };
+
+// Words of Ranked::facts: the longest out row, the nodes with more than
+// 65,535 core neighbours, and the split walks' nodes and shares.
+enum : int { kLongestOut = 0, kManyCore = 1, kSplitNodes = 2, kSplitShares = 3, kFacts = 4 };
 
 __global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, unsigned long long* __restrict__ keys,
                             uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
@@ -133,7 +140,7 @@ __global__ void k_core_fill(const uint32_t* __restrict__ g2_adj, const uint32_t*
 __global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uint64_t m,
                             const uint32_t* __restrict__ node_of, const unsigned long long* __restrict__ flag,
                             const unsigned long long* __restrict__ pos, uint2* __restrict__ core,
-                            uint2* __restrict__ out, uint32_t* __restrict__ longest) {
+                            uint2* __restrict__ out, uint32_t* __restrict__ facts) {
   uint32_t most = 0;
   auto at = [&](uint32_t i) { return i < m ? pos[i] : (m ? pos[m - 1] + flag[m - 1] : 0ull); };
   for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
@@ -142,9 +149,10 @@ __global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uin
     core[r] = make_uint2(uint32_t(b), uint32_t(e) - uint32_t(b));
     out[r] = make_uint2(uint32_t(b >> 32), uint32_t(e >> 32) - uint32_t(b >> 32));
     most = max(most, uint32_t(e >> 32) - uint32_t(b >> 32));
+    if (uint32_t(e) - uint32_t(b) > 65535u) atomicAdd(&facts[kManyCore], 1u);
   }
   for (int d = kWave / 2; d > 0; d >>= 1) most = max(most, uint32_t(__shfl_xor(int(most), d, kWave)));
-  if ((threadIdx.x & (kWave - 1)) == 0 && most > 2) atomicMax(longest, most);
+  if ((threadIdx.x & (kWave - 1)) == 0 && most > 2) atomicMax(&facts[kLongestOut], most);
 }
 
 // ------------------------------------------------------------------ the walk
@@ -279,30 +287,35 @@ struct WalkLds {
 // Every thread of the workgroup (T threads) calls this.  L consecutive
 // positions per thread and round: one search for the first's row, then L
 // loads in flight.
+// The neighbours at entries [e0, e1) of u's core row are walked; passes
+// [pass0, pass1): 0 counts, 1 (kPairCycles, after every path is counted) adds
+// the cycles to the pairs.
 template <uint32_t T, uint32_t XPT, uint32_t L, int MODE, typename Tab>
-__device__ void walk_top(const WalkArgs& a, WalkLds<T * XPT, MODE>& S, const Tab& tab, uint32_t u, bool shared_pairs,
-                         unsigned long long& cycles) {
+__device__ void walk_top(const WalkArgs& a, WalkLds<T * XPT, MODE>& S, const Tab& tab, uint32_t u, uint32_t e0,
+                         uint32_t e1, int pass0, int pass1, bool shared_pairs) {
   constexpr uint32_t XS = T * XPT;
   const Ranked& g = a.g;
   const uint2 ru = g.core[u];
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-  for (uint32_t i = tid; i < ru.y; i += T) {
-    const uint32_t w = g.core_adj[ru.x + i];
-    if (!tab.covers(w)) continue;
-    if constexpr (MODE == kSums) tab.put(w, a.tri_e[g.core_eid[ru.x + i]] + 1u);
-    else tab.mark(w);
+  if (pass0 == 0) {
+#pragma unroll 4
+    for (uint32_t i = tid; i < ru.y; i += T) {
+      const uint32_t w = g.core_adj[ru.x + i];
+      if (!tab.covers(w)) continue;
+      if constexpr (MODE == kSums) tab.put(w, a.tri_e[g.core_eid[ru.x + i]] + 1u);
+      else tab.mark(w);
+    }
   }
-  // (pass 1 of kPairCycles, after every path is counted, walks again)
-  for (int pass = 0; pass < (MODE == kPairCycles ? 2 : 1); ++pass) {
-    for (uint32_t base = 0; base < ru.y; base += XS) {
-      if (pass == 0 || ru.y > XS) {
+  for (int pass = pass0; pass < pass1; ++pass) {
+    for (uint32_t base = e0; base < e1; base += XS) {
+      if (pass == pass0 || e1 - e0 > XS) {
         // the chunk's neighbours before u, compacted with the positions
         // where their rows start
         uint32_t x[XPT], len[XPT], row[XPT], mine = 0, kept = 0;
 #pragma unroll
         for (uint32_t k = 0; k < XPT; ++k) {
           const uint32_t i = base + tid * XPT + k;
-          x[k] = i < ru.y ? g.core_adj[ru.x + i] : kEmpty32;
+          x[k] = i < e1 ? g.core_adj[ru.x + i] : kEmpty32;
         }
 #pragma unroll
         for (uint32_t k = 0; k < XPT; ++k) {
@@ -421,8 +434,10 @@ __device__ void walk_top(const WalkArgs& a, WalkLds<T * XPT, MODE>& S, const Tab
     }
     __syncthreads();
   }
-  if constexpr (MODE == kCycles || MODE == kPairCycles) cycles += tab.pairs();
 }
+
+constexpr bool counts_paths(int mode) { return mode == kCycles || mode == kPairCycles; }
+constexpr int passes_of(int mode) { return mode == kPairCycles ? 2 : 1; }
 
 // Sum of x over the workgroup (T threads) to one of the copies of *out.
 template <uint32_t T>
@@ -451,16 +466,17 @@ __global__ void __launch_bounds__(kWave) k_walk_small(WalkArgs a) {
     if (row.y < 2) continue;   // one neighbour of degree 2 or more closes nothing
     // what the walk may meet: every path, when the table holds paths
     uint32_t most = row.y;
-    if (MODE == kCycles || MODE == kPairCycles) {
+    if (counts_paths(MODE)) {
       const uint32_t x = threadIdx.x < row.y ? a.g.core_adj[row.x + threadIdx.x] : kEmpty32;
       most += wave_sum_u32(x < u ? a.g.core[x].y : 0u);
     }
     __syncthreads();   // the previous node's table is no longer read
     tab.begin(most);
     __syncthreads();
-    walk_top<kWave, 1, 2, MODE>(a, S, tab, u, false, cycles);
+    walk_top<kWave, 1, 2, MODE>(a, S, tab, u, 0, row.y, 0, passes_of(MODE), false);
+    if (counts_paths(MODE)) cycles += tab.pairs();
   }
-  if (MODE == kCycles || MODE == kPairCycles) add_copies<kWave>(cycles, a.cycles);
+  if (counts_paths(MODE)) add_copies<kWave>(cycles, a.cycles);
 }
 
 // The ranks of the workgroups' shares are strided; each takes up to T
@@ -507,9 +523,72 @@ __global__ void __launch_bounds__(256) k_walk_mid(WalkArgs a) {
         __syncthreads();
         tab.begin(a.g.weight[u]);
         __syncthreads();
-        walk_top<256, 4, 4, MODE>(a, S, tab, u, false, cycles);
+        walk_top<256, 4, 4, MODE>(a, S, tab, u, 0, a.g.core[u].y, 0, passes_of(MODE), false);
+        if (counts_paths(MODE)) cycles += tab.pairs();
       });
-  if (MODE == kCycles || MODE == kPairCycles) add_copies<256>(cycles, a.cycles);
+  if (counts_paths(MODE)) add_copies<256>(cycles, a.cycles);
+}
+
+// A 16-bit count holds every path u - x - w when u or w has at most 65,535
+// core neighbours: always, unless u and another node have more.
+__device__ inline bool wide_counts(const Ranked& g, uint32_t u) {
+  return g.core[u].y > 65535u && g.facts[kManyCore] >= 2u;
+}
+
+// The walks of more than kSplitWork positions are split into shares of about
+// as many (communication: the longest, on one CU, took 1.6 ms beside 0.3 ms
+// of evenly spread work).  Split nodes are marked in weight.
+constexpr uint32_t kSplitWork = 1u << 17;
+constexpr uint32_t kSplitWalk = 0xFFFFFFFFu;
+constexpr uint32_t kSplitRanks = 4096;     // only the latest ranks are looked at
+constexpr uint32_t kSplitMostShares = 64;  // per node
+struct SplitNode {
+  uint32_t u, first, shares;   // rank; its shares are [first, first + shares)
+};
+
+__global__ void __launch_bounds__(1024) k_split_plan(Ranked g, uint32_t* __restrict__ weight, uint32_t capacity,
+                                                     SplitNode* __restrict__ nodes, uint32_t* __restrict__ facts) {
+  __shared__ uint32_t wave_tot[2][1024 / kWave];
+  constexpr uint32_t P = kSplitRanks / 1024;
+  const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  uint32_t shares[P], mine = 0, n_mine = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < P; ++k) {
+    const uint32_t i = threadIdx.x * P + k;
+    shares[k] = 0;
+    if (i < g.n && g.n - 1 - i >= g.bounds[1]) {
+      const uint32_t u = g.n - 1 - i, w = weight[u];
+      if (w > kSplitWork && !wide_counts(g, u)) shares[k] = min(kSplitMostShares, (w + kSplitWork - 1) / kSplitWork);
+    }
+    mine += shares[k];
+    n_mine += shares[k] != 0;
+  }
+  uint32_t tot, n_tot;
+  uint32_t at = wave_exclusive_scan(mine, &tot), slot = wave_exclusive_scan(n_mine, &n_tot);
+  if (lane == 0) {
+    wave_tot[0][wv] = tot;
+    wave_tot[1][wv] = n_tot;
+  }
+  __syncthreads();
+  for (uint32_t q = 0; q < wv; ++q) {
+    at += wave_tot[0][q];
+    slot += wave_tot[1][q];
+  }
+  // in rank order, as many as the shares' counters hold: those taken are a
+  // prefix, so the last one taken ends the totals
+#pragma unroll
+  for (uint32_t k = 0; k < P; ++k) {
+    if (!shares[k]) continue;
+    if (at + shares[k] <= capacity) {
+      const uint32_t u = g.n - 1 - (threadIdx.x * P + k);
+      nodes[slot] = SplitNode{u, at, shares[k]};
+      weight[u] = kSplitWalk;
+      atomicMax(&facts[kSplitNodes], slot + 1);
+      atomicMax(&facts[kSplitShares], at + shares[k]);
+    }
+    at += shares[k];
+    ++slot;
+  }
 }
 
 // Ranks a direct table holds in this mode, and threads' neighbours per chunk
@@ -536,21 +615,21 @@ __global__ void __launch_bounds__(1024) k_walk_large(WalkArgs a, uint32_t parts)
       uint64_t(n - r1) * parts, list, &n_list,
       [&](uint64_t c) {
         const uint32_t part = uint32_t(c % parts);
-        return uint64_t(r0) + uint64_t(part) * R < n && a.g.weight[n - 1 - uint32_t(c / parts)] > kMidMost;
+        const uint32_t w = a.g.weight[n - 1 - uint32_t(c / parts)];
+        return uint64_t(r0) + uint64_t(part) * R < n && w > kMidMost && w != kSplitWalk;
       },
       [&](uint64_t c) {
         const uint32_t u = n - 1 - uint32_t(c / parts), part = uint32_t(c % parts);
         const uint32_t first = r0 + part * R, size = min(R, n - first);
-        // a 16-bit count holds every path when u has at most 65,535
-        // neighbours that could be on one
-        const bool wide = (MODE == kCycles || MODE == kPairCycles) && a.g.core[u].y > 65535u;
+        const bool wide = counts_paths(MODE) && wide_counts(a.g, u);
         for (uint32_t half = 0; half < (wide ? 2u : 1u); ++half) {
           const uint32_t step = wide ? R / 2 : R;
           if (half * step >= size) break;
           DirectTab tab{words, MODE == kTri ? words : marks, first + half * step,
                          size - half * step < step ? size - half * step : step, wide};
           __syncthreads();
-          walk_top<1024, XPT, 8, MODE>(a, S, tab, u, parts > 1 || wide, cycles);
+          walk_top<1024, XPT, 8, MODE>(a, S, tab, u, 0, a.g.core[u].y, 0, passes_of(MODE), parts > 1 || wide);
+          if (counts_paths(MODE)) cycles += tab.pairs();
           __syncthreads();
           const uint32_t used = MODE == kTri ? (tab.n + 31) / 32 : MODE == kSums ? tab.n : tab.words();
           for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = 0;
@@ -558,7 +637,75 @@ __global__ void __launch_bounds__(1024) k_walk_large(WalkArgs a, uint32_t parts)
             for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) marks[i] = 0;
         }
       });
-  if (MODE == kCycles || MODE == kPairCycles) add_copies<1024>(cycles, a.cycles);
+  if (counts_paths(MODE)) add_copies<1024>(cycles, a.cycles);
+}
+
+// The shares of the split walks, a (share, range of ranks) per workgroup.
+// Counting modes leave a share's counts in `dump` (kDirectWords per task) for
+// k_split_sum; with SECOND, the pass of kPairCycles over the summed counts.
+template <int MODE, bool SECOND>
+__global__ void __launch_bounds__(1024) k_walk_split(WalkArgs a, const SplitNode* __restrict__ nodes, uint32_t parts,
+                                                     uint32_t* __restrict__ dump) {
+  constexpr uint32_t R = DirectMode<MODE>::kRanks, XPT = DirectMode<MODE>::kXpt;
+  __shared__ WalkLds<1024 * XPT, MODE> S;
+  __shared__ uint32_t words[kDirectWords];
+  __shared__ uint32_t marks[MODE == kSums ? 1 : kDirectMarks];
+  const uint32_t n = a.g.n, r0 = a.g.bounds[0];
+  const uint32_t n_nodes = a.g.facts[kSplitNodes], n_shares = a.g.facts[kSplitShares];
+  for (uint64_t t = blockIdx.x; t < uint64_t(n_shares) * parts; t += gridDim.x) {
+    const uint32_t share = uint32_t(t / parts), part = uint32_t(t % parts);
+    if (uint64_t(r0) + uint64_t(part) * R >= n) continue;
+    uint32_t lo = 0, hi = n_nodes;   // nodes[lo].first <= share < nodes[hi].first
+    while (hi - lo > 1) {
+      const uint32_t m = (lo + hi) >> 1;
+      if (nodes[m].first <= share) lo = m; else hi = m;
+    }
+    const SplitNode node = nodes[lo];
+    const uint32_t s = share - node.first, len = a.g.core[node.u].y;
+    const uint32_t e0 = uint32_t(uint64_t(len) * s / node.shares), e1 = uint32_t(uint64_t(len) * (s + 1) / node.shares);
+    const uint32_t first = r0 + part * R;
+    DirectTab tab{words, marks, first, min(R, n - first), false};
+    __syncthreads();   // the previous task's tables are no longer read
+    const uint32_t used = MODE == kSums ? tab.n : tab.words();
+    if (SECOND) {
+      const uint32_t* summed = dump + (uint64_t(node.first) * parts + part) * kDirectWords;
+      for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = summed[i];
+    } else {
+      for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = 0;
+      if (MODE != kSums)
+        for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) marks[i] = 0;
+    }
+    __syncthreads();
+    walk_top<1024, XPT, 8, MODE>(a, S, tab, node.u, e0, e1, SECOND ? 1 : 0, SECOND ? 2 : 1, true);
+    if (counts_paths(MODE) && !SECOND) {
+      uint32_t* out = dump + t * kDirectWords;
+      for (uint32_t i = threadIdx.x; i < used; i += 1024) out[i] = words[i];
+    }
+  }
+}
+
+// The counts of each split node's shares summed into its first share's, and
+// the 4-cycles they close.  (Two 16-bit counts per word: neither half's sum
+// passes 65,535, see wide_counts.)
+__global__ void __launch_bounds__(1024) k_split_sum(Ranked g, const SplitNode* __restrict__ nodes, uint32_t parts,
+                                                    uint32_t* __restrict__ dump, unsigned long long* __restrict__ out) {
+  const uint32_t n = g.n, r0 = g.bounds[0], n_nodes = g.facts[kSplitNodes];
+  unsigned long long cycles = 0;
+  for (uint64_t t = blockIdx.x; t < uint64_t(n_nodes) * parts; t += gridDim.x) {
+    const SplitNode node = nodes[t / parts];
+    const uint32_t part = uint32_t(t % parts);
+    if (uint64_t(r0) + uint64_t(part) * kDirectRanks >= n) continue;
+    const uint32_t words = (min(kDirectRanks, n - (r0 + part * kDirectRanks)) + 1) / 2;
+    uint32_t* base = dump + (uint64_t(node.first) * parts + part) * kDirectWords;
+    for (uint32_t i = threadIdx.x; i < words; i += 1024) {
+      uint32_t v = 0;
+      for (uint32_t s = 0; s < node.shares; ++s) v += base[uint64_t(s) * parts * kDirectWords + i];
+      base[i] = v;
+      const unsigned long long a = v & 0xFFFFu, b = v >> 16;
+      cycles += a * (a - (a > 0)) / 2 + b * (b - (b > 0)) / 2;
+    }
+  }
+  add_copies<1024>(cycles, out);
 }
 
 // ------------------------------------------------------------------ 4-cliques
@@ -770,19 +917,19 @@ int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_
   const uint64_t n2 = H->n_by_size[2], m = 2 * n2;
   unsigned long long *flag = nullptr, *pos = nullptr;
   uint32_t *core_adj = nullptr, *core_eid = nullptr, *out_adj = nullptr, *out_eid = nullptr, *weight = nullptr,
-           *longest = nullptr;
+           *facts = nullptr;
   uint2 *core = nullptr, *rows = nullptr;
   HM_TRY(tmp.get(&weight, n));
   HM_TRY(tmp.get(&core, n));
   HM_TRY(tmp.get(&rows, n));
-  HM_TRY(tmp.get(&longest, 1));
+  HM_TRY(tmp.get(&facts, kFacts));
   HM_TRY(tmp.get(&flag, m));
   HM_TRY(tmp.get(&pos, m));
   HM_TRY(tmp.get(&core_adj, m));
   HM_TRY(tmp.get(&core_eid, m));
   HM_TRY(tmp.get(&out_adj, n2));
   HM_TRY(tmp.get(&out_eid, n2));
-  HM_TRY(fill_u32(longest, 0, 1, st));
+  HM_TRY(fill_u32(facts, 0, kFacts, st));
   HM_TRY(fill_u32(weight, 0, n, st));
   k_core_flags<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_off, H->g2_adj, H->g2_eid, H->e2, m, H->rank_of,
                                                       H->rank_bounds, flag, weight);
@@ -790,22 +937,53 @@ int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_
   HM_TRY(scan_exclusive_u64(flag, pos, m, st));
   k_core_fill<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, m, H->rank_of, flag, pos, core_adj,
                                                      core_eid, out_adj, out_eid);
-  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, H->node_of, flag, pos, core, rows, longest);
+  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, H->node_of, flag, pos, core, rows, facts);
   HM_HIP(hipGetLastError());
-  *out = Ranked{n, H->rank_of, H->node_of, core, rows, core_adj, core_eid, out_adj, out_eid, weight, H->rank_bounds};
+  *out = Ranked{n, H->rank_of, H->node_of, core, rows, core_adj, core_eid, out_adj, out_eid, weight, H->rank_bounds,
+                facts};
   if (most) {
-    HM_HIP(hipMemcpyAsync(most, longest, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HM_HIP(hipMemcpyAsync(most, facts + kLongestOut, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HM_HIP(hipStreamSynchronize(st));
   }
   return HM_OK;
 }
 
-// The three walk launches of one mode, the longest walks first.
+// Split walks of one graph: their nodes, and room for the shares' counts.
+struct Split {
+  SplitNode* nodes = nullptr;
+  uint32_t* dump = nullptr;
+  uint32_t parts = 0;   // ranges of ranks of the counting modes
+};
+
 template <int MODE>
-int launch_walks(const WalkArgs& a, const char* name, hipStream_t st) {
+uint32_t parts_of(uint32_t n) {
+  constexpr uint64_t r = DirectMode<MODE>::kRanks;
+  return uint32_t(std::max<uint64_t>(1, (n + r - 1) / r));
+}
+
+// Plans the split walks (marking their nodes in g.weight), with counters for
+// 1,024 (share, range) tasks (100 MB).
+int plan_split(const Ranked& g, Scratch& tmp, Split* sp, hipStream_t st) {
+  sp->parts = parts_of<kCycles>(g.n);
+  const uint32_t capacity = 1024 / sp->parts;
+  HM_TRY(tmp.get(&sp->nodes, kSplitRanks));
+  HM_TRY(tmp.get(&sp->dump, uint64_t(std::max<uint32_t>(capacity, 1)) * sp->parts * kDirectWords));
+  k_split_plan<<<1, 1024, 0, st>>>(g, const_cast<uint32_t*>(g.weight), capacity, sp->nodes,
+                                   const_cast<uint32_t*>(g.facts));
+  HM_HIP(hipGetLastError());
+  return HM_OK;
+}
+
+// The walk launches of one mode, the longest walks first.
+template <int MODE>
+int launch_walks(const WalkArgs& a, const Split& sp, const char* name, hipStream_t st) {
   ProfileScope ps(name, st);
-  const uint64_t r = DirectMode<MODE>::kRanks;
-  const uint32_t parts = uint32_t(std::max<uint64_t>(1, (a.g.n + r - 1) / r));
+  const uint32_t parts = parts_of<MODE>(a.g.n);
+  if constexpr (MODE != kTri) {
+    k_walk_split<MODE, false><<<256, 1024, 0, st>>>(a, sp.nodes, parts, sp.dump);
+    if constexpr (counts_paths(MODE)) k_split_sum<<<256, 1024, 0, st>>>(a.g, sp.nodes, parts, sp.dump, a.cycles);
+    if constexpr (MODE == kPairCycles) k_walk_split<MODE, true><<<256, 1024, 0, st>>>(a, sp.nodes, parts, sp.dump);
+  }
   k_walk_large<MODE><<<256, 1024, 0, st>>>(a, parts);
   k_walk_mid<MODE><<<768, 256, 0, st>>>(a);
   k_walk_small<MODE><<<grid_of(a.g.n, 1, 3072), kWave, 0, st>>>(a);
@@ -879,8 +1057,10 @@ int wedge_counts(hm_graph* H, int k, uint32_t* tri_e, unsigned long long* n_cycl
   a.g = g;
   a.tri_e = tri_e;
   a.cycles = copies;
-  if (k == 3) return launch_walks<kTri>(a, "k_walk", st);
-  HM_TRY(launch_walks<kCycles>(a, "k_walk", st));
+  Split sp;
+  if (k == 3) return launch_walks<kTri>(a, sp, "k_walk", st);
+  HM_TRY(plan_split(g, tmp, &sp, st));
+  HM_TRY(launch_walks<kCycles>(a, sp, "k_walk", st));
   HM_TRY(launch_cliques<false>(H, g, most, copies + kAccCopies, nullptr, st, tmp));
   k_sum_copies<<<1, kWave, 0, st>>>(copies, n_cycles);
   k_sum_copies<<<1, kWave, 0, st>>>(copies + kAccCopies, n_cliques);
@@ -917,9 +1097,11 @@ int wedge_edge_stats(hm_graph* H, unsigned long long* es, hipStream_t st) {
   a.sum_b = es + 4 * n2;
   a.sum_d = es + 5 * n2;
   a.g2_off = H->g2_off;
-  HM_TRY(launch_walks<kPairCycles>(a, "k_walk", st));
+  Split sp;
+  HM_TRY(plan_split(g, tmp, &sp, st));
+  HM_TRY(launch_walks<kPairCycles>(a, sp, "k_walk", st));
   k_es_widen<<<grid_of(n2, 256, 2048), 256, 0, st>>>(tri_e, n2, es);
-  HM_TRY(launch_walks<kSums>(a, "k_walk_sums", st));
+  HM_TRY(launch_walks<kSums>(a, sp, "k_walk_sums", st));
   HM_TRY(launch_cliques<true>(H, g, most, copies + kAccCopies, es + n2, st, tmp));
   return HM_OK;
 }

@@ -662,11 +662,11 @@ def test_walks_over_several_rank_ranges(hm):
 
 
 @pytest.mark.parametrize("n,hubs,hub_degree,ring,clique", [
-    (200, 0, 0, True, 0), (3000, 3, 2900, True, 0), (3000, 40, 700, True, 66), (1500, 0, 0, False, 24),
+    (200, 0, 0, True, 0), (4000, 40, 3700, True, 0), (3000, 3, 2900, True, 0), (3000, 40, 700, True, 66), (1500, 0, 0, False, 24),
     (2000, 2, 500, True, 120), (2500, 0, 0, True, 700)])
 def test_walks_match_bit_rows(hm, n, hubs, hub_degree, ring, clique):
     """Triangles, 4-cycles and 4-cliques without bit rows (hash tables of
-    every size, counters by rank, cliques of one word, of many and beyond the
+    every size, counters by rank, walks split into shares, cliques of one word, of many and beyond the
     LDS matrix) against the bit-row path; and the per-pair statistics through
     samples of every kind of pair."""
     e = _hub_graph(n, hubs, hub_degree, ring, clique, n + clique)
