@@ -179,31 +179,65 @@ __global__ void k_standardise_targets(float* __restrict__ t, const uint64_t* __r
 // v_mfma_f32_16x16x16bf16_1k on a 16-row tile per wavefront.  Lane l, with
 // r = l % 16 and q = l / 16: A operand holds A[r][4q..4q+3], B operand holds
 // B[4q..4q+3][r], the result holds D[4q..4q+3][r].
-struct MlpLds {
+// Rows of 64 are kept 72 apart, so that the 16 rows a wavefront's operand
+// reads (8 bytes a lane) fall in different banks; W2T is W2 transposed, for
+// the backward product.
+constexpr int kLdsRow = 72;
+struct alignas(16) MlpLds {
   short W1[kHid * kF];
-  short W2[kHid * kHid];
+  short W2[kHid * kLdsRow];
+  short W2T[kHid * kLdsRow];
   float b1[kHid], b2[kHid], w3[kHid];
-  float b3;
+  float b3, pad[3];
 };
 
-__device__ void load_mlp(MlpLds& w, const float* __restrict__ p) {
-  for (int i = threadIdx.x; i < kHid * kF; i += blockDim.x) w.W1[i] = bf16_bits(p[kOffW1 + i]);
-  for (int i = threadIdx.x; i < kHid * kHid; i += blockDim.x) w.W2[i] = bf16_bits(p[kOffW2 + i]);
-  for (int i = threadIdx.x; i < kHid; i += blockDim.x) {
-    w.b1[i] = p[kOffB1 + i];
-    w.b2[i] = p[kOffB2 + i];
-    w.w3[i] = p[kOffW3 + i];
+// Parameter i, value x, into its place (or places) in the image w.
+__device__ inline void put_mlp(MlpLds& w, int i, float x) {
+  if (i < kOffB1) {
+    w.W1[i] = bf16_bits(x);
+  } else if (i < kOffW2) {
+    w.b1[i - kOffB1] = x;
+  } else if (i < kOffB2) {
+    const int o = (i - kOffW2) / kHid, k = (i - kOffW2) % kHid;
+    const short h = bf16_bits(x);
+    w.W2[o * kLdsRow + k] = h;
+    w.W2T[k * kLdsRow + o] = h;
+  } else if (i < kOffW3) {
+    w.b2[i - kOffB2] = x;
+  } else if (i < kOffB3) {
+    w.w3[i - kOffW3] = x;
+  } else {
+    w.b3 = x;
   }
-  if (threadIdx.x == 0) w.b3 = p[kOffB3];
 }
+
+// The parameters into LDS: from an image kept in device memory, or from the
+// fp32 parameters.
+__device__ void load_mlp(MlpLds& w, const float* __restrict__ p, const MlpLds* __restrict__ image) {
+  if (image) {
+    const uint4* src = reinterpret_cast<const uint4*>(image);
+    uint4* dst = reinterpret_cast<uint4*>(&w);
+    for (uint32_t i = threadIdx.x; i < sizeof(MlpLds) / sizeof(uint4); i += blockDim.x) dst[i] = src[i];
+  } else {
+    for (int i = threadIdx.x; i < kNParams; i += blockDim.x) put_mlp(w, i, p[i]);
+  }
+}
+static_assert(sizeof(MlpLds) % sizeof(uint4) == 0, "the image is copied 16 bytes at a time");
+
+__global__ void k_mlp_image(const float* __restrict__ p, MlpLds* __restrict__ image) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kNParams; i += gridDim.x * blockDim.x)
+    put_mlp(*image, i, p[i]);
+}
+
+__device__ inline v4s lds4(const short* p) { return *reinterpret_cast<const v4s*>(p); }
 
 struct Tile {
   v4f z1[4], z2[4];
   float out[4];      // rows 4q + i, in every lane of group q
 };
 
-// Forward of rows r0..r0+15 of X (rows >= n read as zero).  h1s: 16 x 64
-// wavefront-private LDS.
+// Forward of rows r0..r0+15 of X (rows >= n read as zero).  h1s: 16 rows of
+// kLdsRow, wavefront-private LDS.
 __device__ void mlp_forward_tile(const MlpLds& w, const float* __restrict__ X, uint64_t n, uint64_t r0, short* h1s,
                                  Tile& T) {
   const int l = threadIdx.x & (kWave - 1), r = l & 15, q = l >> 4;
@@ -213,25 +247,22 @@ __device__ void mlp_forward_tile(const MlpLds& w, const float* __restrict__ X, u
     for (int i = 0; i < 4; ++i) xa[i] = row < n ? bf16_bits(X[row * kF + 4 * q + i]) : short(0);
   }
   for (int nb = 0; nb < 4; ++nb) {
-    v4s b;
-    for (int i = 0; i < 4; ++i) b[i] = w.W1[(16 * nb + r) * kF + 4 * q + i];
+    const v4s b = lds4(&w.W1[(16 * nb + r) * kF + 4 * q]);
     const v4f zero = {0.f, 0.f, 0.f, 0.f};
     v4f acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xa, b, zero, 0, 0, 0);
     const float bias = w.b1[16 * nb + r];
     for (int i = 0; i < 4; ++i) {
       acc[i] += bias;
-      h1s[(4 * q + i) * kHid + 16 * nb + r] = bf16_bits(fmaxf(acc[i], 0.f));
+      h1s[(4 * q + i) * kLdsRow + 16 * nb + r] = bf16_bits(fmaxf(acc[i], 0.f));
     }
     T.z1[nb] = acc;
   }
   wave_sync();
   for (int nb = 0; nb < 4; ++nb) T.z2[nb] = v4f{0.f, 0.f, 0.f, 0.f};
   for (int ks = 0; ks < 4; ++ks) {
-    v4s a;
-    for (int i = 0; i < 4; ++i) a[i] = h1s[r * kHid + 16 * ks + 4 * q + i];
+    const v4s a = lds4(&h1s[r * kLdsRow + 16 * ks + 4 * q]);
     for (int nb = 0; nb < 4; ++nb) {
-      v4s b;
-      for (int i = 0; i < 4; ++i) b[i] = w.W2[(16 * nb + r) * kHid + 16 * ks + 4 * q + i];
+      const v4s b = lds4(&w.W2[(16 * nb + r) * kLdsRow + 16 * ks + 4 * q]);
       T.z2[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, T.z2[nb], 0, 0, 0);
     }
   }
@@ -255,8 +286,8 @@ __global__ void __launch_bounds__(kThreads) k_mlp_forward(const float* __restric
                                                           const float* __restrict__ X, uint64_t n,
                                                           float* __restrict__ out) {
   __shared__ MlpLds w;
-  __shared__ short h1s[kWavesPerBlock][16 * kHid];
-  load_mlp(w, params);
+  __shared__ __align__(16) short h1s[kWavesPerBlock][16 * kLdsRow];
+  load_mlp(w, params, nullptr);
   __syncthreads();
   const int l = threadIdx.x & (kWave - 1), r = l & 15, q = l >> 4;
   const int wv = threadIdx.x / kWave;
@@ -274,14 +305,40 @@ __global__ void __launch_bounds__(kThreads) k_mlp_forward(const float* __restric
 
 // Forward and backward of the mean squared error over n rows; every
 // wavefront writes its gradient (and loss) partial to its own row of
-// `partial` (kNParams + 1 values), reduced later in a fixed order.
+// `partial` (kNParams + 1 values), reduced later in a fixed order.  A row is
+// laid out as the wavefront holds it, four values per lane and store: gW1
+// ([block of 16 rows][lane][4]), gW2 ([block][block][lane][4]), then the
+// gradients of b1, b2, w3, b3 and the loss (param_of maps it back).
+//
+// One wavefront has one tile of 16 rows of a mini-batch of 4,096, so a step is
+// a chain: the weights into LDS (copied from an image the Adam step keeps,
+// `image`, when training), 56 MFMAs with their LDS operands, and the partials
+// out.  16.2 us a step before the image, 8-byte operand reads and 16-byte
+// stores, MLP_US now.
+constexpr int kPosW2 = 1024, kPosRest = 5120;
+// a row's values, padded to whole 16-byte stores
+constexpr uint32_t kPartialRow = (kNParams + 1 + 3) / 4 * 4;
+__device__ inline int param_of(int pos) {
+  if (pos < kPosW2) {
+    const int i = pos & 3, l = (pos >> 2) & 63, nb = pos >> 8;
+    return kOffW1 + (16 * nb + 4 * (l >> 4) + i) * kF + (l & 15);
+  }
+  if (pos < kPosRest) {
+    const int e = pos - kPosW2, i = e & 3, l = (e >> 2) & 63, kb = (e >> 8) & 3, nb = e >> 10;
+    return kOffW2 + (16 * nb + 4 * (l >> 4) + i) * kHid + 16 * kb + (l & 15);
+  }
+  const int e = pos - kPosRest;
+  return e < 64 ? kOffB1 + e : e < 128 ? kOffB2 + e - 64 : e < 192 ? kOffW3 + e - 128 : e == 192 ? kOffB3 : kNParams;
+}
+
 __global__ void __launch_bounds__(kThreads) k_mlp_train(const float* __restrict__ params,
+                                                        const MlpLds* __restrict__ image,
                                                         const float* __restrict__ X, const float* __restrict__ tgt,
                                                         uint64_t n, float inv_n, float* __restrict__ partial) {
   __shared__ MlpLds w;
-  __shared__ short h1s[kWavesPerBlock][16 * kHid];
-  __shared__ short dzs[kWavesPerBlock][16 * kHid];
-  load_mlp(w, params);
+  __shared__ __align__(16) short h1s[kWavesPerBlock][16 * kLdsRow];
+  __shared__ __align__(16) short dzs[kWavesPerBlock][16 * kLdsRow];
+  load_mlp(w, params, image);
   __syncthreads();
   const int l = threadIdx.x & (kWave - 1), r = l & 15, q = l >> 4;
   const int wv = threadIdx.x / kWave;
@@ -314,7 +371,7 @@ __global__ void __launch_bounds__(kThreads) k_mlp_train(const float* __restrict_
         gb2[nb] += dz;
         dz2b[nb][i] = bf16_bits(dz);
         h1b[nb][i] = bf16_bits(fmaxf(T.z1[nb][i], 0.f));
-        dzs[wv][(4 * q + i) * kHid + 16 * nb + r] = dz2b[nb][i];
+        dzs[wv][(4 * q + i) * kLdsRow + 16 * nb + r] = dz2b[nb][i];
       }
     }
     for (int ob = 0; ob < 4; ++ob)
@@ -329,11 +386,8 @@ __global__ void __launch_bounds__(kThreads) k_mlp_train(const float* __restrict_
     for (int nb = 0; nb < 4; ++nb) {
       v4f acc = {0.f, 0.f, 0.f, 0.f};
       for (int ks = 0; ks < 4; ++ks) {
-        v4s a, b;
-        for (int i = 0; i < 4; ++i) {
-          a[i] = dzs[wv][r * kHid + 16 * ks + 4 * q + i];
-          b[i] = w.W2[(16 * ks + 4 * q + i) * kHid + 16 * nb + r];
-        }
+        const v4s a = lds4(&dzs[wv][r * kLdsRow + 16 * ks + 4 * q]);
+        const v4s b = lds4(&w.W2T[(16 * nb + r) * kLdsRow + 16 * ks + 4 * q]);
         acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
       }
       v4s dz1b;
@@ -348,7 +402,7 @@ __global__ void __launch_bounds__(kThreads) k_mlp_train(const float* __restrict_
   }
   // reduce the column partials over the four row groups, then write this
   // wavefront's row of partials
-  float* out = partial + wave * (kNParams + 1);
+  float* out = partial + wave * kPartialRow;
   for (int nb = 0; nb < 4; ++nb) {
     float a = gb1[nb], b = gb2[nb], c = gw3[nb];
     for (int d = 16; d < kWave; d <<= 1) {
@@ -357,58 +411,90 @@ __global__ void __launch_bounds__(kThreads) k_mlp_train(const float* __restrict_
       c += __shfl_xor(c, d, kWave);
     }
     if (q == 0) {
-      out[kOffB1 + 16 * nb + r] = a;
-      out[kOffB2 + 16 * nb + r] = b;
-      out[kOffW3 + 16 * nb + r] = c;
+      out[kPosRest + 16 * nb + r] = a;
+      out[kPosRest + 64 + 16 * nb + r] = b;
+      out[kPosRest + 128 + 16 * nb + r] = c;
     }
-    for (int i = 0; i < 4; ++i) out[kOffW1 + (16 * nb + 4 * q + i) * kF + r] = gW1[nb][i];
+    *reinterpret_cast<v4f*>(out + (nb * kWave + l) * 4) = gW1[nb];
     for (int kb = 0; kb < 4; ++kb)
-      for (int i = 0; i < 4; ++i) out[kOffW2 + (16 * nb + 4 * q + i) * kHid + 16 * kb + r] = gW2[nb * 4 + kb][i];
+      *reinterpret_cast<v4f*>(out + kPosW2 + ((nb * 4 + kb) * kWave + l) * 4) = gW2[nb * 4 + kb];
   }
   for (int d = 1; d < kWave; d <<= 1) {
     gb3 += __shfl_xor(gb3, d, kWave);
     loss += __shfl_xor(loss, d, kWave);
   }
   if (l == 0) {
-    out[kOffB3] = gb3;
-    out[kNParams] = loss;
+    out[kPosRest + 192] = gb3;
+    out[kPosRest + 193] = loss;
   }
+}
+
+// Sum over the wavefronts of position p of their rows.  Workgroups of four
+// wavefronts take 64 consecutive positions: wavefront q sums rows w = q, q +
+// 4, ... and the four sums are added in the order q = 0..3, so the order of
+// every addition is fixed; 16 rows' loads are in flight at a time.  Valid in
+// wavefront 0.  Every thread of the workgroup calls this.
+constexpr uint32_t kReduceParams = kWave;
+constexpr uint32_t kReduceBlocks = (kNParams + kReduceParams) / kReduceParams;
+__device__ inline float sum_partials(const float* __restrict__ partial, uint32_t n_waves, uint32_t p) {
+  __shared__ float part[kWavesPerBlock][kReduceParams];
+  const uint32_t lane = threadIdx.x & (kWave - 1), q = threadIdx.x / kWave;
+  float s = 0.f;
+  if (p <= uint32_t(kNParams)) {
+    constexpr uint32_t R = 16;
+    uint32_t w = q;
+    for (; w + (R - 1) * kWavesPerBlock < n_waves; w += R * kWavesPerBlock) {
+      float x[R];
+#pragma unroll
+      for (uint32_t k = 0; k < R; ++k) x[k] = partial[uint64_t(w + k * kWavesPerBlock) * kPartialRow + p];
+#pragma unroll
+      for (uint32_t k = 0; k < R; ++k) s += x[k];
+    }
+    for (; w < n_waves; w += kWavesPerBlock) s += partial[uint64_t(w) * kPartialRow + p];
+  }
+  part[q][lane] = s;
+  __syncthreads();
+  float t = part[0][lane];
+  for (uint32_t r = 1; r < kWavesPerBlock; ++r) t += part[r][lane];
+  return t;
 }
 
 // grad[p] = sum over wavefronts of partial[w][p]; p = kNParams is the loss.
-// Workgroups of four wavefronts take 64 consecutive parameters: wavefront q
-// sums rows w = q, q + 4, ... and the four sums are added in the order
-// q = 0..3, so the order of every addition is fixed.
-constexpr uint32_t kReduceParams = kWave;
 __global__ void __launch_bounds__(kThreads) k_reduce_partials(const float* __restrict__ partial, uint32_t n_waves,
                                                               float* __restrict__ grad) {
-  __shared__ float part[kWavesPerBlock][kReduceParams];
-  const uint32_t lane = threadIdx.x & (kWave - 1), q = threadIdx.x / kWave;
-  const uint32_t p = blockIdx.x * kReduceParams + lane;
-  float s = 0.f;
-  if (p <= uint32_t(kNParams))
-    for (uint32_t w = q; w < n_waves; w += kWavesPerBlock) s += partial[uint64_t(w) * (kNParams + 1) + p];
-  part[q][lane] = s;
-  __syncthreads();
-  if (q == 0 && p <= uint32_t(kNParams)) {
-    float t = part[0][lane];
-    for (uint32_t r = 1; r < kWavesPerBlock; ++r) t += part[r][lane];
-    grad[p] = t;
-  }
+  const uint32_t p = blockIdx.x * kReduceParams + (threadIdx.x & (kWave - 1));
+  const float g = sum_partials(partial, n_waves, p);
+  if (threadIdx.x < kWave && p <= uint32_t(kNParams)) grad[param_of(int(p))] = g;
 }
 
-// One Adam step; thread 0 also keeps the step's loss (grad[kNParams]) at loss[0].
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
-                       float lr, float b1, float b2, float eps, float c1, float c2, float* __restrict__ loss) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) loss[0] = g[kNParams];
-  if (i >= kNParams) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+// One Adam step from the partials of a mini-batch: each parameter's gradient
+// is summed and applied by one thread, which also puts the new value into the
+// image the next step's k_mlp_train copies; the step's loss goes to loss[0].
+// (Reduction and update in one launch with 16 loads in flight: 18.0 + 4.5 us
+// a step before, ADAM_US now.)
+__global__ void __launch_bounds__(kThreads) k_reduce_adam(const float* __restrict__ partial, uint32_t n_waves,
+                                                          float* __restrict__ p, float* __restrict__ m,
+                                                          float* __restrict__ v, MlpLds* __restrict__ image, float lr,
+                                                          float b1, float b2, float eps, float c1, float c2,
+                                                          float* __restrict__ loss) {
+  const uint32_t pos = blockIdx.x * kReduceParams + (threadIdx.x & (kWave - 1));
+  // (the parameter and its moments load with the partials)
+  const bool on = threadIdx.x < kWave && pos <= uint32_t(kNParams);
+  const int i = on ? param_of(int(pos)) : 0;
+  const bool par = on && i < kNParams;
+  const float p0 = par ? p[i] : 0.f, m0 = par ? m[i] : 0.f, v0 = par ? v[i] : 0.f;
+  const float gi = sum_partials(partial, n_waves, pos);
+  if (on && i == kNParams) loss[0] = gi;
+  if (!par) return;
+  // (the contractions spelled out, so that no change around them moves the
+  // last bit of a training run)
+  const float mi = fmaf(1.f - b1, gi, b1 * m0);
+  const float vi = fmaf(gi, (1.f - b2) * gi, b2 * v0);
   m[i] = mi;
   v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  const float x = p0 - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  p[i] = x;
+  put_mlp(*image, i, x);
 }
 
 __global__ void k_gather_rows(const float* __restrict__ X, const float* __restrict__ t, const uint32_t* __restrict__ perm,
@@ -867,10 +953,9 @@ int hm_mlp_grad(const float* params, const float* x, const float* t, uint64_t n,
     const uint32_t waves = blocks * hm::kWavesPerBlock;
     hm::Bufs tmp(st);
     float* partial = nullptr;
-    HM_TRY(tmp.get(&partial, uint64_t(waves) * (hm::kNParams + 1)));
-    hm::k_mlp_train<<<blocks, hm::kThreads, 0, st>>>(params, x, t, n, n ? 1.f / float(n) : 0.f, partial);
-    hm::k_reduce_partials<<<(hm::kNParams + hm::kReduceParams) / hm::kReduceParams, hm::kThreads, 0, st>>>(partial, waves,
-                                                                                                       grad);
+    HM_TRY(tmp.get(&partial, uint64_t(waves) * hm::kPartialRow));
+    hm::k_mlp_train<<<blocks, hm::kThreads, 0, st>>>(params, nullptr, x, t, n, n ? 1.f / float(n) : 0.f, partial);
+    hm::k_reduce_partials<<<hm::kReduceBlocks, hm::kThreads, 0, st>>>(partial, waves, grad);
     HM_HIP(hipGetLastError());
     HM_HIP(hipStreamSynchronize(st));
     return HM_OK;
@@ -926,8 +1011,9 @@ int hm_model_train(const hm_graph* H, int k, const hm_train_opts* opts, hm_model
     const int ns = hm::strata_bounds(H, k, b);
     const uint64_t n = b[ns];
     hm::Bufs tmp(st);
-    float *X = nullptr, *t = nullptr, *Xp = nullptr, *tp = nullptr, *stats = nullptr, *partial = nullptr, *grad = nullptr,
-          *m = nullptr, *v = nullptr;
+    float *X = nullptr, *t = nullptr, *Xp = nullptr, *tp = nullptr, *stats = nullptr, *partial = nullptr, *m = nullptr,
+          *v = nullptr, *losses = nullptr;
+    hm::MlpLds* image = nullptr;
     double* y = nullptr;
     uint64_t* db = nullptr;
     unsigned long long *keys = nullptr, *keys_tmp = nullptr;
@@ -942,8 +1028,8 @@ int hm_model_train(const hm_graph* H, int k, const hm_train_opts* opts, hm_model
     if (rc == HM_OK) rc = tmp.get(&y, n);
     if (rc == HM_OK) rc = tmp.get(&stats, 8);
     if (rc == HM_OK) rc = tmp.get(&db, 5);
-    if (rc == HM_OK) rc = tmp.get(&partial, uint64_t(waves) * (hm::kNParams + 1));
-    if (rc == HM_OK) rc = tmp.get(&grad, hm::kNParams + 1);
+    if (rc == HM_OK) rc = tmp.get(&partial, uint64_t(waves) * hm::kPartialRow);
+    if (rc == HM_OK) rc = tmp.get(&image, 1);
     if (rc == HM_OK) rc = tmp.get(&m, hm::kNParams);
     if (rc == HM_OK) rc = tmp.get(&v, hm::kNParams);
     if (rc == HM_OK) rc = tmp.get(&keys, n);
@@ -971,36 +1057,31 @@ int hm_model_train(const hm_graph* H, int k, const hm_train_opts* opts, hm_model
       if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
       for (int s = 0; s < ns; ++s) M->tstd[s] = host_stats[2 * s + 1] > 0.f ? 1.f / host_stats[2 * s + 1] : 1.f;
     }
-    // Adam over mini-batches; every step's loss stays on the device and an
-    // epoch's losses are read back once, at its end
-    int step = 0;
+    // Adam over mini-batches; every step's loss stays on the device and all
+    // are read back once, at the end
     const float b1 = 0.9f, b2 = 0.999f;
     const uint64_t batches_per_epoch = n ? (n + batch - 1) / batch : 0;
-    float* losses = nullptr;
-    if (rc == HM_OK) rc = tmp.get(&losses, batches_per_epoch + 1);
-    std::vector<float> host_losses(batches_per_epoch + 1);
+    const uint64_t steps = batches_per_epoch * uint64_t(opts->epochs);
+    if (rc == HM_OK) rc = tmp.get(&losses, steps + 1);
+    std::vector<float> host_losses(steps);
+    if (rc == HM_OK && steps) hm::k_mlp_image<<<8, 256, 0, st>>>(M->params, image);
+    for (uint64_t step = 0; step < steps && rc == HM_OK; ++step) {
+      const uint64_t b0 = (step % batches_per_epoch) * batch, nb = std::min<uint64_t>(batch, n - b0);
+      hm::k_mlp_train<<<blocks, hm::kThreads, 0, st>>>(M->params, image, Xp + b0 * hm::kF, tp + b0, nb, 1.f / float(nb),
+                                                       partial);
+      const float c1 = 1.f - std::pow(b1, float(step + 1)), c2 = 1.f - std::pow(b2, float(step + 1));
+      hm::k_reduce_adam<<<hm::kReduceBlocks, hm::kThreads, 0, st>>>(partial, waves, M->params, m, v, image, opts->lr, b1,
+                                                                    b2, 1e-8f, c1, c2, losses + step);
+      if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
+    }
+    if (rc == HM_OK && steps &&
+        hipMemcpyAsync(host_losses.data(), losses, sizeof(float) * steps, hipMemcpyDeviceToHost, st) != hipSuccess)
+      rc = HM_EDEVICE;
+    if (hipStreamSynchronize(st) != hipSuccess && rc == HM_OK) rc = HM_EDEVICE;
     for (int ep = 0; ep < opts->epochs && rc == HM_OK && n; ++ep) {
-      uint64_t n_batches = 0;
-      for (uint64_t b0 = 0; b0 < n && rc == HM_OK; b0 += batch) {
-        const uint64_t nb = std::min<uint64_t>(batch, n - b0);
-        hm::k_mlp_train<<<blocks, hm::kThreads, 0, st>>>(M->params, Xp + b0 * hm::kF, tp + b0, nb, 1.f / float(nb),
-                                                         partial);
-        hm::k_reduce_partials<<<(hm::kNParams + hm::kReduceParams) / hm::kReduceParams, hm::kThreads, 0, st>>>(
-            partial, waves, grad);
-        ++step;
-        const float c1 = 1.f - std::pow(b1, float(step)), c2 = 1.f - std::pow(b2, float(step));
-        hm::k_adam<<<(hm::kNParams + 255) / 256, 256, 0, st>>>(M->params, grad, m, v, opts->lr, b1, b2, 1e-8f, c1, c2,
-                                                                losses + n_batches);
-        if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-        ++n_batches;
-      }
-      if (rc == HM_OK && hipMemcpyAsync(host_losses.data(), losses, sizeof(float) * n_batches, hipMemcpyDeviceToHost,
-                                        st) != hipSuccess)
-        rc = HM_EDEVICE;
-      if (rc == HM_OK && hipStreamSynchronize(st) != hipSuccess) rc = HM_EDEVICE;
       double ep_loss = 0.0;
-      for (uint64_t i = 0; i < n_batches; ++i) ep_loss += host_losses[i];
-      M->loss.push_back(float(ep_loss / double(std::max<uint64_t>(1, n_batches))));
+      for (uint64_t i = 0; i < batches_per_epoch; ++i) ep_loss += host_losses[uint64_t(ep) * batches_per_epoch + i];
+      M->loss.push_back(float(ep_loss / double(std::max<uint64_t>(1, batches_per_epoch))));
     }
     if (rc != HM_OK) {
       hm::dfree(M->params);
