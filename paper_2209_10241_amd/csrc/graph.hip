@@ -950,14 +950,6 @@ struct Temps {
   int commit() { return staged.take(&ptrs); }
 };
 
-template <typename T>
-int owned(T** p, uint64_t count) {
-  void* q = nullptr;
-  HM_TRY(dalloc(&q, size_t(count ? count : 1) * sizeof(T)));
-  *p = static_cast<T*>(q);
-  return HM_OK;
-}
-
 int node_bits(uint32_t n_nodes) {
   int b = 1;
   while (b < 32 && (1ull << b) < n_nodes) ++b;
@@ -1325,16 +1317,19 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
     const int B = node_bits(H->n_nodes);
     const uint64_t m = 2 * n2;
     unsigned long long *keys, *keys_tmp;
-    uint32_t* vals_tmp;
+    uint32_t *eid, *eid_tmp;
     HM_TRY(tmp.get(&keys, m));
     HM_TRY(tmp.get(&keys_tmp, m));
-    HM_TRY(tmp.get(&vals_tmp, m));
-    HM_TRY(owned(&H->g2_eid, m));
-    k_pair_keys<<<grid_for(n2), 256, 0, st>>>(H->e2, n2, B, keys, H->g2_eid);
+    HM_TRY(tmp.get(&eid, m));
+    HM_TRY(tmp.get(&eid_tmp, m));
+    k_pair_keys<<<grid_for(n2), 256, 0, st>>>(H->e2, n2, B, keys, eid);
     HM_HIP(hipGetLastError());
-    HM_TRY(radix_sort_pairs(keys, H->g2_eid, keys_tmp, vals_tmp, m, 2 * B, st));
+    HM_TRY(radix_sort_pairs(keys, eid, keys_tmp, eid_tmp, m, 2 * B, st));
     k_pair_adj<<<grid_for(m), 256, 0, st>>>(keys, m, (1ull << B) - 1, H->g2_adj);
     HM_HIP(hipGetLastError());
+    // (the sort leaves the positions in either buffer; the graph keeps that one)
+    tmp.ptrs.erase(std::find(tmp.ptrs.begin(), tmp.ptrs.end(), static_cast<void*>(eid)));
+    H->g2_eid = eid;
   }
   if (one_pass) HM_TRY(read_report());
   // the gather leaves the duplicate search's table all-ones again (it ran:

@@ -160,10 +160,14 @@ int scan_exclusive_u32(const uint32_t* in, uint32_t* out, uint64_t n, uint32_t* 
                        hipStream_t stream);
 int scan_exclusive_u64(const unsigned long long* in, unsigned long long* out, uint64_t n,
                        hipStream_t stream);
-// Stable LSD radix sort of (key, value) pairs on bits [0, bits) of the key.
-// Buffers are ping-ponged; the sorted result ends in keys/vals (the first pair).
-int radix_sort_pairs(unsigned long long* keys, uint32_t* vals, unsigned long long* keys_tmp,
-                     uint32_t* vals_tmp, uint64_t n, int bits, hipStream_t stream);
+// Stable LSD radix sort of (key, value) pairs on bits [0, bits) of the key (32
+// or 64 bits), eight a pass.  Each pass moves the pairs from one pair of
+// buffers to the other; after an odd number of passes the pointers are
+// swapped, so that the sorted pairs are in keys, vals.
+inline int radix_passes(int bits) { return bits > 0 ? (bits + 7) / 8 : 0; }
+template <typename K>
+int radix_sort_pairs(K*& keys, uint32_t*& vals, K*& keys_tmp, uint32_t*& vals_tmp, uint64_t n, int bits,
+                     hipStream_t stream);
 int fill_u32(uint32_t* p, uint32_t value, uint64_t n, hipStream_t stream);
 int copy_u32(const uint32_t* src, uint32_t* dst, uint64_t n, hipStream_t stream);
 int copy_u64(const unsigned long long* src, unsigned long long* dst, uint64_t n, hipStream_t stream);
@@ -173,8 +177,9 @@ uint64_t scan_ws_words(uint64_t n);
 int scan_u32_ws(const uint32_t* in, uint32_t* out, uint64_t n, uint32_t* total_dev, uint32_t* ws,
                 hipStream_t stream);
 uint64_t radix_ws_words(uint64_t n);
-int radix_sort_ws(unsigned long long* keys, uint32_t* vals, unsigned long long* keys_tmp, uint32_t* vals_tmp,
-                  uint64_t n, int bits, uint32_t* ws, hipStream_t stream);
+// The sorted pairs end in k0, v0 after an even number of passes, else in k1, v1.
+int radix_sort_ws(unsigned long long* k0, uint32_t* v0, unsigned long long* k1, uint32_t* v1, uint64_t n, int bits,
+                  uint32_t* ws, hipStream_t stream);
 int fill_u64(unsigned long long* p, unsigned long long value, uint64_t n, hipStream_t stream);
 
 // ----------------------------------------------------------------- profiling

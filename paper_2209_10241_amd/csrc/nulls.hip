@@ -1235,6 +1235,7 @@ struct NullPlan {
   uint32_t* members = nullptr;
   unsigned long long *skeys = nullptr, *skeys_tmp = nullptr;
   uint32_t *svals = nullptr, *svals_tmp = nullptr;
+  uint32_t* order = nullptr;   // the last sorted order: svals or svals_tmp
   uint32_t* sort_ws = nullptr;
   RepairScratch rs{};
   uint32_t* failed = nullptr;
@@ -1422,14 +1423,16 @@ int make_plan(const hm_graph* H, int k, uint32_t R, int model, int sweeps, NullP
   return HM_OK;
 }
 
-// P.svals := for each copy in turn, its `per` items in the order of their
+// P.order := for each copy in turn, its `per` items in the order of their
 // words (see k_order_keys); no allocation, no sync.
 int enqueue_order(NullPlan& P, uint64_t n, uint64_t per, uint64_t round, unsigned long long domain, uint32_t c0,
                   hipStream_t st) {
   k_order_keys<<<grid_for(n), 256, 0, st>>>(c0, P.R, per, round, domain, P.seed, P.skeys, P.svals);
   HM_HIP(hipGetLastError());
   HM_TRY(radix_sort_ws(P.skeys, P.svals, P.skeys_tmp, P.svals_tmp, n, 32 + bits_for(P.R), P.sort_ws, st));
-  k_fix_ties<<<grid_for(n), 256, 0, st>>>(P.skeys, P.svals, n, per, round, c0, domain, P.seed);
+  const bool odd = radix_passes(32 + bits_for(P.R)) & 1;
+  P.order = odd ? P.svals_tmp : P.svals;
+  k_fix_ties<<<grid_for(n), 256, 0, st>>>(odd ? P.skeys_tmp : P.skeys, P.order, n, per, round, c0, domain, P.seed);
   HM_HIP(hipGetLastError());
   return HM_OK;
 }
@@ -1443,10 +1446,10 @@ int enqueue_stubs(const hm_graph* H, NullPlan& P, uint32_t c0, hipStream_t st) {
   const bool pre = P.R <= P.repair_blocks;
   if (pre) {
     HM_TRY(fill_u32(P.rs.counts, 0, uint64_t(P.R) * kBadLists * kBadStride, st));
-    k_null_deal<<<grid_for(uint64_t(P.R) * P.E), 256, 0, st>>>(P.R, P.E, P.T, H->all_off, P.svals, H->all_members,
+    k_null_deal<<<grid_for(uint64_t(P.R) * P.E), 256, 0, st>>>(P.R, P.E, P.T, H->all_off, P.order, H->all_members,
                                                                 P.members, P.rs);
   } else {
-    k_null_gather<<<grid_for(n), 256, 0, st>>>(P.svals, n, P.T, H->all_members, P.members);
+    k_null_gather<<<grid_for(n), 256, 0, st>>>(P.order, n, P.T, H->all_members, P.members);
   }
   HM_HIP(hipGetLastError());
   k_null_repair<<<P.repair_blocks, kThreads, 0, st>>>(c0, P.R, P.E, P.T, H->all_off, P.members, P.seed, P.rs, pre,
@@ -1467,7 +1470,7 @@ int enqueue_config(const hm_graph* H, NullPlan& P, uint32_t c0, hipStream_t st) 
   if (P.E < 2) return HM_OK;
   for (int r = 0; r < P.sweeps; ++r) {
     HM_TRY(enqueue_order(P, ne, P.E, uint64_t(r), kDomainConfig, c0, st));
-    k_cfg_pairs<<<grid_for(uint64_t(P.R) * (P.E / 2)), 256, 0, st>>>(c0, P.R, P.E, P.T, uint32_t(r), P.seed, P.svals,
+    k_cfg_pairs<<<grid_for(uint64_t(P.R) * (P.E / 2)), 256, 0, st>>>(c0, P.R, P.E, P.T, uint32_t(r), P.seed, P.order,
                                                                     H->all_off, P.members, P.cfg_tmp);
     HM_HIP(hipGetLastError());
   }
@@ -1505,7 +1508,8 @@ int enqueue_ingest(const hm_graph* H, NullPlan& P, hipStream_t st) {
     k_b_pair_keys<<<grid_for(m2), 256, 0, st>>>(m2, P.tot + 0, P.e2, P.copy2, N, P.B, P.pkeys, P.pvals, P.deg);
     HM_HIP(hipGetLastError());
     HM_TRY(radix_sort_ws(P.pkeys, P.pvals, P.pkeys_tmp, P.pvals_tmp, 2 * m2, 2 * P.B + bits_for(R), P.sort_ws, st));
-    k_b_pair_adj<<<grid_for(2 * m2), 256, 0, st>>>(P.pkeys, 2 * m2, (1ull << P.B) - 1, P.g2_adj);
+    const bool odd = radix_passes(2 * P.B + bits_for(R)) & 1;
+    k_b_pair_adj<<<grid_for(2 * m2), 256, 0, st>>>(odd ? P.pkeys_tmp : P.pkeys, 2 * m2, (1ull << P.B) - 1, P.g2_adj);
     HM_HIP(hipGetLastError());
   }
   HM_TRY(scan_u32_ws(P.deg, P.g2_off, RN, P.g2_off + RN, P.scan_ws, st));

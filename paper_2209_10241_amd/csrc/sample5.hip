@@ -1290,10 +1290,10 @@ int sampled5(hm_graph* H, const uint32_t* const idx[6], const uint64_t S[6], uin
     void *skt = nullptr, *svt = nullptr;
     HM_TRY(get(&skt, size_t(nc) * 8));
     HM_TRY(get(&svt, size_t(nc) * 4));
-    HM_TRY(radix_sort_pairs(canon64, static_cast<uint32_t*>(sv), static_cast<unsigned long long*>(skt),
-                            static_cast<uint32_t*>(svt), nc, 26, st));
-    k_finish5<<<grid5(nc), 256, 0, st>>>(canon64, static_cast<uint32_t*>(sv), static_cast<unsigned long long*>(cnt), nc,
-                                         sc, canon, raw, est);
+    auto *order = static_cast<uint32_t*>(sv), *order_tmp = static_cast<uint32_t*>(svt);
+    auto* canon_tmp = static_cast<unsigned long long*>(skt);
+    HM_TRY(radix_sort_pairs(canon64, order, canon_tmp, order_tmp, nc, 26, st));
+    k_finish5<<<grid5(nc), 256, 0, st>>>(canon64, order, static_cast<unsigned long long*>(cnt), nc, sc, canon, raw, est);
   }
   HM_HIP(hipGetLastError());
   HM_HIP(hipStreamSynchronize(st));

@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 // an estimate of the memory transactions of each (two per entry of its
 // shortest pairwise row, six per entry of the 4-node incidence list it reads
 // when there is no 4-node index), with the hyperedge as value.
-__global__ void k_b4_cost_keys(View v, PairLinks pl, uint64_t n3, unsigned long long* __restrict__ keys,
+__global__ void k_b4_cost_keys(View v, PairLinks pl, uint64_t n3, uint32_t* __restrict__ keys,
                                uint32_t* __restrict__ vals) {
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n3; i += uint64_t(gridDim.x) * blockDim.x) {
     const uint32_t a = v.e3[3 * i], b = v.e3[3 * i + 1], c = v.e3[3 * i + 2];
@@ -183,7 +183,7 @@ __device__ inline uint32_t pl_third_of(const uint32_t* e3, uint32_t code) {
   return e3[3 * i + 2 - s];
 }
 
-__global__ void k_pl_third_keys(const uint32_t* __restrict__ e3, uint64_t n, unsigned long long* __restrict__ keys,
+__global__ void k_pl_third_keys(const uint32_t* __restrict__ e3, uint64_t n, uint32_t* __restrict__ keys,
                                 uint32_t* __restrict__ codes) {
   for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x) {
     keys[p] = pl_third_of(e3, uint32_t(p));
@@ -191,30 +191,86 @@ __global__ void k_pl_third_keys(const uint32_t* __restrict__ e3, uint64_t n, uns
   }
 }
 
-// (packed to `bits` per node for the sort, which then needs 2 * bits of key;
-// k_pl_wide_keys widens them to (x << 32) | y)
+// (packed to `bits` per node for the sort, which then needs 2 * bits of key,
+// in 32 bits when they fit; k_pl_wide_keys widens them to (x << 32) | y)
+template <typename K>
 __global__ void k_pl_pair_keys(const uint32_t* __restrict__ e3, const uint32_t* __restrict__ codes, uint64_t n, int bits,
-                               unsigned long long* __restrict__ keys) {
+                               K* __restrict__ keys) {
   for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x) {
     const uint32_t code = codes[p];
     const uint64_t i = code / 3;
     const uint32_t s = code % 3;
-    const unsigned long long a = e3[3 * i], b = e3[3 * i + 1], c = e3[3 * i + 2];
+    const K a = e3[3 * i], b = e3[3 * i + 1], c = e3[3 * i + 2];
     keys[p] = s == 0 ? ((a << bits) | b) : (s == 1 ? ((a << bits) | c) : ((b << bits) | c));
   }
 }
 
-__global__ void k_pl_wide_keys(unsigned long long* __restrict__ keys, uint64_t n, int bits) {
+template <typename K>
+__global__ void k_pl_wide_keys(const K* __restrict__ packed, uint64_t n, int bits, unsigned long long* __restrict__ keys) {
   for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x) {
-    const unsigned long long k = keys[p];
+    const unsigned long long k = packed[p];
     keys[p] = ((k >> bits) << 32) | (k & ((1ull << bits) - 1));
   }
 }
 
-// One-hot of adjacency class cl over the entries (for the prefix counts).
-__global__ void k_pl_class_flags(const uint8_t* __restrict__ adj, uint64_t n, uint32_t cl, uint32_t* __restrict__ out) {
-  for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x)
-    out[p] = adj[p] == cl ? 1u : 0u;
+// Prefix counts of the entries by adjacency class: the four classes' counts of
+// each tile of kClassTile entries (class-major, so that one scan serves all
+// four), then within each tile.
+constexpr uint32_t kClassTile = 2048;
+__global__ void __launch_bounds__(kThreads) k_pl_class_count(const uint8_t* __restrict__ adj, uint64_t n,
+                                                             uint32_t* __restrict__ counts) {
+  __shared__ uint32_t c[4];
+  if (threadIdx.x < 4) c[threadIdx.x] = 0;
+  __syncthreads();
+  const uint64_t base = uint64_t(blockIdx.x) * kClassTile;
+#pragma unroll
+  for (uint32_t r = 0; r < kClassTile / kThreads; ++r) {
+    const uint64_t p = base + r * kThreads + threadIdx.x;
+    const uint32_t a = p < n ? adj[p] : 4u;
+#pragma unroll
+    for (uint32_t cl = 0; cl < 4; ++cl) {
+      const uint32_t k = uint32_t(__popcll(__ballot(a == cl)));
+      if ((threadIdx.x & (kWave - 1)) == 0 && k) atomicAdd(&c[cl], k);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) counts[uint64_t(threadIdx.x) * gridDim.x + blockIdx.x] = c[threadIdx.x];
+}
+
+__global__ void __launch_bounds__(kThreads) k_pl_class_prefix(const uint8_t* __restrict__ adj, uint64_t n,
+                                                              const uint32_t* __restrict__ before,
+                                                              uint32_t* __restrict__ pre) {
+  __shared__ uint32_t part[2][4][kWavesPerBlock];
+  const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const uint64_t base = uint64_t(blockIdx.x) * kClassTile;
+  uint32_t at[4];
+#pragma unroll
+  for (uint32_t cl = 0; cl < 4; ++cl)
+    at[cl] = before[uint64_t(cl) * gridDim.x + blockIdx.x] - before[uint64_t(cl) * gridDim.x];
+  for (uint32_t r = 0; r < kClassTile / kThreads; ++r) {
+    const uint64_t p = base + r * kThreads + threadIdx.x;
+    const uint32_t a = p < n ? adj[p] : 4u;
+    uint32_t mine[4];
+#pragma unroll
+    for (uint32_t cl = 0; cl < 4; ++cl) {
+      const unsigned long long m = __ballot(a == cl);
+      mine[cl] = uint32_t(__popcll(m & below));
+      if (lane == 0) part[r & 1][cl][wv] = uint32_t(__popcll(m));
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t cl = 0; cl < 4; ++cl) {
+      uint32_t x = at[cl] + mine[cl];
+      for (uint32_t q = 0; q < uint32_t(kWavesPerBlock); ++q) {
+        const uint32_t k = part[r & 1][cl][q];
+        if (q < wv) x += k;
+        at[cl] += k;
+      }
+      if (p < n) pre[cl * (n + 1) + p] = x;
+      if (p + 1 == n) pre[cl * (n + 1) + n] = x + (a == cl);
+    }
+  }
 }
 
 // Hash index over the runs of the sorted pair keys.  First pass: every run's
@@ -491,6 +547,13 @@ __global__ void k_quad_keys(const uint32_t* __restrict__ e4, uint64_t n4, int q,
   }
 }
 
+// Takes p (allocated in tmp) out of tmp: it stays with its new owner.
+template <typename T>
+T* keep(Scratch& tmp, T* p) {
+  tmp.ptrs.erase(std::find(tmp.ptrs.begin(), tmp.ptrs.end(), static_cast<void*>(p)));
+  return p;
+}
+
 // The 3-node subset -> 4-node hyperedge index (H->q_*), when the packed key
 // fits 63 bits; otherwise none (q_bits = 0) and the incidence lists serve.
 int build_quad_index(hm_graph* H, hipStream_t st) {
@@ -499,37 +562,43 @@ int build_quad_index(hm_graph* H, hipStream_t st) {
   while (bits < 32 && (1ull << bits) < H->n_nodes) ++bits;
   if (n4 == 0 || 3 * bits > 63) return HM_OK;
   const uint64_t n = 4 * n4;
-  void *k = nullptr, *f = nullptr, *kt = nullptr, *ft = nullptr, *slots = nullptr;
-  int rc = dalloc(&k, n * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = dalloc(&f, n * sizeof(uint32_t));
-  if (rc == HM_OK) rc = dalloc(&kt, n * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = dalloc(&ft, n * sizeof(uint32_t));
-  if (rc == HM_OK) {
-    k_quad_keys<<<grid_cap(n4, 256, 4096), 256, 0, st>>>(H->e4, n4, bits, static_cast<unsigned long long*>(k),
-                                                         static_cast<uint32_t*>(f));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  if (rc == HM_OK)
-    rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(f),
-                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(ft), n, 3 * bits, st);
+  Scratch tmp(st);
+  unsigned long long *k = nullptr, *kt = nullptr, *slots = nullptr;
+  uint32_t *f = nullptr, *ft = nullptr;
   const unsigned long long cap = pow2_capacity(n);
-  if (rc == HM_OK) rc = dalloc(&slots, 2 * cap * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = fill_u64(static_cast<unsigned long long*>(slots), kEmpty64, 2 * cap, st);
-  if (rc == HM_OK) {
-    const unsigned g = grid_cap(n, 256, 4096);
-    k_pl_index_starts<<<g, 256, 0, st>>>(static_cast<const unsigned long long*>(k), n,
-                                         static_cast<unsigned long long*>(slots), cap - 1);
-    k_pl_index_counts<<<g, 256, 0, st>>>(static_cast<const unsigned long long*>(k), n,
-                                         static_cast<unsigned long long*>(slots), cap - 1);
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  void* used[] = {k, kt, ft, f, slots};   // (the last two are kept)
-  dfree_on(used, rc == HM_OK ? 3 : 5, st);
-  if (rc != HM_OK) return rc;
-  H->q_slot = static_cast<unsigned long long*>(slots);
+  HM_TRY(tmp.get(&k, n));
+  HM_TRY(tmp.get(&kt, n));
+  HM_TRY(tmp.get(&f, n));
+  HM_TRY(tmp.get(&ft, n));
+  HM_TRY(tmp.get(&slots, 2 * cap));
+  HM_TRY(fill_u64(slots, kEmpty64, 2 * cap, st));
+  k_quad_keys<<<grid_cap(n4, 256, 4096), 256, 0, st>>>(H->e4, n4, bits, k, f);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(k, f, kt, ft, n, 3 * bits, st));
+  const unsigned g = grid_cap(n, 256, 4096);
+  k_pl_index_starts<<<g, 256, 0, st>>>(k, n, slots, cap - 1);
+  k_pl_index_counts<<<g, 256, 0, st>>>(k, n, slots, cap - 1);
+  HM_HIP(hipGetLastError());
+  H->q_slot = keep(tmp, slots);
   H->q_mask = cap - 1;
-  H->q_fourth = static_cast<uint32_t*>(f);
+  H->q_fourth = keep(tmp, f);
   H->q_bits = bits;
+  return HM_OK;
+}
+
+// The entries' codes in *e (buffers *e and *et) into the order of their pairs,
+// whose keys go to `keys`; packed keys of type K.
+template <typename K>
+int sort_by_pair(const hm_graph* H, uint64_t n, int bits, uint32_t*& e, uint32_t*& et, unsigned long long* keys,
+                 hipStream_t st, Scratch& tmp) {
+  K *k = nullptr, *kt = nullptr;
+  HM_TRY(tmp.get(&k, n));
+  HM_TRY(tmp.get(&kt, n));
+  k_pl_pair_keys<K><<<grid_cap(n, 256, 4096), 256, 0, st>>>(H->e3, e, n, bits, k);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(k, e, kt, et, n, 2 * bits, st));
+  k_pl_wide_keys<K><<<grid_cap(n, 256, 4096), 256, 0, st>>>(k, n, bits, keys);
+  HM_HIP(hipGetLastError());
   return HM_OK;
 }
 
@@ -540,74 +609,53 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
   if (H->pl_keys || H->n_by_size[3] == 0) return HM_OK;
   HM_TRY(ensure_hub_rows(H, st));
   const uint64_t n = 3 * H->n_by_size[3];
-  void *k = nullptr, *e = nullptr, *kt = nullptr, *et = nullptr;
-  HM_TRY(dalloc(&k, n * sizeof(unsigned long long)));
-  int rc = dalloc(&e, n * sizeof(uint32_t));
-  if (rc == HM_OK) rc = dalloc(&kt, n * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = dalloc(&et, n * sizeof(uint32_t));
   int bits = 1;
   while (bits < 32 && (1ull << bits) < H->n_nodes) ++bits;
-  if (rc == HM_OK) {
-    k_pl_third_keys<<<grid_cap(n, 256, 4096), 256, 0, st>>>(H->e3, n, static_cast<unsigned long long*>(k),
-                                                            static_cast<uint32_t*>(e));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  if (rc == HM_OK)
-    rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(e),
-                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(et), n, bits, st);
-  if (rc == HM_OK) {
-    k_pl_pair_keys<<<grid_cap(n, 256, 4096), 256, 0, st>>>(H->e3, static_cast<const uint32_t*>(e), n, bits,
-                                                           static_cast<unsigned long long*>(k));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  if (rc == HM_OK)
-    rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(e),
-                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(et), n, 2 * bits, st);
-  if (rc == HM_OK) {
-    k_pl_wide_keys<<<grid_cap(n, 256, 4096), 256, 0, st>>>(static_cast<unsigned long long*>(k), n, bits);
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
   // the index: at most n distinct keys, load at most 1/2
   const unsigned long long cap = pow2_capacity(n);
-  void *slots = nullptr, *codeg = nullptr, *third = nullptr, *adj = nullptr, *pre = nullptr;
-  if (rc == HM_OK) rc = dalloc(&slots, 2 * cap * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = dalloc(&codeg, cap * sizeof(uint32_t));
-  if (rc == HM_OK) rc = dalloc(&third, n * sizeof(uint32_t));
-  if (rc == HM_OK) rc = dalloc(&adj, n * sizeof(uint8_t));
-  if (rc == HM_OK) rc = dalloc(&pre, 4 * (n + 1) * sizeof(uint32_t));
-  if (rc == HM_OK) rc = fill_u64(static_cast<unsigned long long*>(slots), kEmpty64, 2 * cap, st);
-  if (rc == HM_OK) {
-    const unsigned g = grid_cap(n, 256, 4096);
-    k_pl_index_starts<<<g, 256, 0, st>>>(static_cast<const unsigned long long*>(k), n,
-                                         static_cast<unsigned long long*>(slots), cap - 1);
-    k_pl_index_counts<<<g, 256, 0, st>>>(static_cast<const unsigned long long*>(k), n,
-                                         static_cast<unsigned long long*>(slots), cap - 1);
-    k_pl_third<<<g, 256, 0, st>>>(H->e3, static_cast<const unsigned long long*>(k), static_cast<uint32_t*>(e), n,
-                                  H->hs2, static_cast<uint32_t*>(third), static_cast<uint8_t*>(adj));
-    k_pl_codeg<<<grid_cap(n, kThreads, 8192), kThreads, 0, st>>>(
-        view_of(H), static_cast<const unsigned long long*>(k), n, static_cast<const unsigned long long*>(slots),
-        cap - 1, H->hub_rank, H->hub_bits, H->hub_words, static_cast<uint32_t*>(codeg));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  // prefix counts of the entries by adjacency class (the flags reuse et)
-  for (uint32_t cl = 0; cl < 4 && rc == HM_OK; ++cl) {
-    uint32_t* out = static_cast<uint32_t*>(pre) + cl * (n + 1);
-    k_pl_class_flags<<<grid_cap(n, 256, 4096), 256, 0, st>>>(static_cast<const uint8_t*>(adj), n, cl,
-                                                             static_cast<uint32_t*>(et));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-    if (rc == HM_OK) rc = scan_exclusive_u32(static_cast<const uint32_t*>(et), out, n, out + n, st);
-  }
-  void* used[] = {kt, et, k, e, slots, codeg, third, adj, pre};   // (all but the first two are kept)
-  dfree_on(used, rc == HM_OK ? 2 : 9, st);
-  if (rc != HM_OK) return rc;
-  H->pl_keys = static_cast<unsigned long long*>(k);
-  H->pl_edge = static_cast<uint32_t*>(e);
-  H->pl_slot = static_cast<unsigned long long*>(slots);
+  Scratch tmp(st);
+  unsigned long long *keys = nullptr, *slots = nullptr;
+  uint32_t *t = nullptr, *tt = nullptr, *e = nullptr, *et = nullptr, *codeg = nullptr, *third = nullptr, *pre = nullptr,
+           *counts = nullptr, *before = nullptr;
+  uint8_t* adj = nullptr;
+  const uint64_t tiles = (n + kClassTile - 1) / kClassTile;
+  HM_TRY(tmp.get(&keys, n));
+  HM_TRY(tmp.get(&t, n));
+  HM_TRY(tmp.get(&tt, n));
+  HM_TRY(tmp.get(&e, n));
+  HM_TRY(tmp.get(&et, n));
+  HM_TRY(tmp.get(&slots, 2 * cap));
+  HM_TRY(tmp.get(&codeg, cap));
+  HM_TRY(tmp.get(&third, n));
+  HM_TRY(tmp.get(&adj, n));
+  HM_TRY(tmp.get(&pre, 4 * (n + 1)));
+  HM_TRY(tmp.get(&counts, 4 * tiles));
+  HM_TRY(tmp.get(&before, 4 * tiles));
+  const unsigned g = grid_cap(n, 256, 4096);
+  k_pl_third_keys<<<g, 256, 0, st>>>(H->e3, n, t, e);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(t, e, tt, et, n, bits, st));
+  if (2 * bits <= 32) HM_TRY(sort_by_pair<uint32_t>(H, n, bits, e, et, keys, st, tmp));
+  else HM_TRY(sort_by_pair<unsigned long long>(H, n, bits, e, et, keys, st, tmp));
+  HM_TRY(fill_u64(slots, kEmpty64, 2 * cap, st));
+  k_pl_index_starts<<<g, 256, 0, st>>>(keys, n, slots, cap - 1);
+  k_pl_index_counts<<<g, 256, 0, st>>>(keys, n, slots, cap - 1);
+  k_pl_third<<<g, 256, 0, st>>>(H->e3, keys, e, n, H->hs2, third, adj);
+  k_pl_codeg<<<grid_cap(n, kThreads, 8192), kThreads, 0, st>>>(view_of(H), keys, n, slots, cap - 1, H->hub_rank,
+                                                               H->hub_bits, H->hub_words, codeg);
+  k_pl_class_count<<<unsigned(tiles), kThreads, 0, st>>>(adj, n, counts);
+  HM_HIP(hipGetLastError());
+  HM_TRY(scan_exclusive_u32(counts, before, 4 * tiles, nullptr, st));
+  k_pl_class_prefix<<<unsigned(tiles), kThreads, 0, st>>>(adj, n, before, pre);
+  HM_HIP(hipGetLastError());
+  H->pl_edge = keep(tmp, e);
+  H->pl_slot = keep(tmp, slots);
   H->pl_mask = cap - 1;
-  H->pl_codeg = static_cast<uint32_t*>(codeg);
-  H->pl_third = static_cast<uint32_t*>(third);
-  H->pl_adj = static_cast<uint8_t*>(adj);
-  H->pl_pre = static_cast<uint32_t*>(pre);
+  H->pl_codeg = keep(tmp, codeg);
+  H->pl_third = keep(tmp, third);
+  H->pl_adj = keep(tmp, adj);
+  H->pl_pre = keep(tmp, pre);
+  H->pl_keys = keep(tmp, keys);
   return build_quad_index(H, st);
 }
 
@@ -716,23 +764,16 @@ int ensure_b4_order(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   const uint64_t n3 = H->n_by_size[3];
   if (H->b4_order || n3 == 0) return HM_OK;
-  void *k = nullptr, *o = nullptr, *kt = nullptr, *ot = nullptr;
-  int rc = dalloc(&k, n3 * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = dalloc(&o, n3 * sizeof(uint32_t));
-  if (rc == HM_OK) rc = dalloc(&kt, n3 * sizeof(unsigned long long));
-  if (rc == HM_OK) rc = dalloc(&ot, n3 * sizeof(uint32_t));
-  if (rc == HM_OK) {
-    k_b4_cost_keys<<<grid_cap(n3, 256, 4096), 256, 0, st>>>(view_of(H), pair_links_of(H), n3,
-                                                            static_cast<unsigned long long*>(k), static_cast<uint32_t*>(o));
-    if (hipGetLastError() != hipSuccess) rc = HM_EDEVICE;
-  }
-  if (rc == HM_OK)
-    rc = radix_sort_pairs(static_cast<unsigned long long*>(k), static_cast<uint32_t*>(o),
-                          static_cast<unsigned long long*>(kt), static_cast<uint32_t*>(ot), n3, 8, st);
-  void* used[] = {k, kt, ot, o};   // (the last is kept)
-  dfree_on(used, rc == HM_OK ? 3 : 4, st);
-  if (rc != HM_OK) return rc;
-  H->b4_order = static_cast<uint32_t*>(o);
+  Scratch tmp(st);
+  uint32_t *k = nullptr, *o = nullptr, *kt = nullptr, *ot = nullptr;
+  HM_TRY(tmp.get(&k, n3));
+  HM_TRY(tmp.get(&o, n3));
+  HM_TRY(tmp.get(&kt, n3));
+  HM_TRY(tmp.get(&ot, n3));
+  k_b4_cost_keys<<<grid_cap(n3, 256, 4096), 256, 0, st>>>(view_of(H), pair_links_of(H), n3, k, o);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(k, o, kt, ot, n3, 8, st));
+  H->b4_order = keep(tmp, o);
   return HM_OK;
 }
 

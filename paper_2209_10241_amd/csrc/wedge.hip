@@ -66,7 +66,7 @@ struct Ranked {
 // 65,535 core neighbours, and the split walks' nodes and shares.
 enum : int { kLongestOut = 0, kManyCore = 1, kSplitNodes = 2, kSplitShares = 3, kFacts = 4 };
 
-__global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, unsigned long long* __restrict__ keys,
+__global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, uint32_t* __restrict__ keys,
                             uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
   if (blockIdx.x == 0 && threadIdx.x < 2) bounds[threadIdx.x] = n;
   for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
@@ -75,11 +75,11 @@ __global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, uns
   }
 }
 
-__global__ void k_rank_assign(const unsigned long long* __restrict__ keys, const uint32_t* __restrict__ node_of,
+__global__ void k_rank_assign(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ node_of,
                               uint32_t n, uint32_t* __restrict__ rank_of, uint32_t* __restrict__ bounds) {
   for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
     rank_of[node_of[r]] = r;
-    const uint32_t k = uint32_t(keys[r]), before = r ? uint32_t(keys[r - 1]) : 0u;
+    const uint32_t k = keys[r], before = r ? keys[r - 1] : 0u;
     if (k >= 2 && (r == 0 || before < 2)) bounds[0] = r;
     if (k >= kSmallDeg && (r == 0 || before < kSmallDeg)) bounds[1] = r;
   }
@@ -1017,23 +1017,23 @@ int ensure_ranks(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   const uint32_t n = H->n_nodes;
   Scratch tmp(st);
-  unsigned long long *keys = nullptr, *keys_tmp = nullptr;
-  uint32_t* vals_tmp = nullptr;
+  uint32_t *keys = nullptr, *keys_tmp = nullptr;
   HM_TRY(tmp.get(&keys, n));
   HM_TRY(tmp.get(&keys_tmp, n));
-  HM_TRY(tmp.get(&vals_tmp, n));
-  // (handed over to the graph once the launches are in)
+  // (handed over to the graph once the launches are in; the sort's one pass
+  // leaves the order in the second buffer, which becomes node_of)
   Scratch kept(st);
-  uint32_t *rank_of = nullptr, *node_of = nullptr, *bounds = nullptr;
+  uint32_t *rank_of = nullptr, *node_of = nullptr, *vals_tmp = nullptr, *bounds = nullptr;
   HM_TRY(kept.get(&rank_of, n));
   HM_TRY(kept.get(&node_of, n));
+  HM_TRY(kept.get(&vals_tmp, n));
   HM_TRY(kept.get(&bounds, 2));
   k_rank_keys<<<grid_of(n, 256, 2048), 256, 0, st>>>(H->g2_off, n, keys, node_of, bounds);
   HM_HIP(hipGetLastError());
   HM_TRY(radix_sort_pairs(keys, node_of, keys_tmp, vals_tmp, n, kRankBits, st));
   k_rank_assign<<<grid_of(n, 256, 2048), 256, 0, st>>>(keys, node_of, n, rank_of, bounds);
   HM_HIP(hipGetLastError());
-  kept.ptrs.clear();
+  kept.ptrs.assign(1, vals_tmp);   // (the other order buffer goes)
   H->rank_of = rank_of;
   H->node_of = node_of;
   H->rank_bounds = bounds;
