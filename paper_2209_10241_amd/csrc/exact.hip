@@ -21,7 +21,9 @@
 namespace hm {
 namespace {
 
-// (a) at order 4: one thread per 4-node hyperedge.
+// (a) at order 4: one thread per 4-node hyperedge.  The set of one that holds
+// 3-node hyperedges was also counted by count_sparse's (b), as if it were no
+// hyperedge itself: that is taken back here, where the set's pattern is known.
 __global__ void __launch_bounds__(kThreads) k_case_a4(View v, uint64_t n4, const uint8_t* __restrict__ lut_g,
                                                       unsigned long long* __restrict__ hist) {
   __shared__ uint8_t lut[2048];
@@ -33,6 +35,11 @@ __global__ void __launch_bounds__(kThreads) k_case_a4(View v, uint64_t n4, const
   for (uint64_t i = uint64_t(blockIdx.x) * kThreads + threadIdx.x; i < n4; i += uint64_t(gridDim.x) * kThreads) {
     const uint32_t p = a4_pattern(v, v.e4[4 * i], v.e4[4 * i + 1], v.e4[4 * i + 2], v.e4[4 * i + 3]);
     count_class(lut, h_main, h_sub, p, kPairBits4);
+    if (p & kTripleBits4) {
+      const uint8_t m = lut[p & (kPairBits4 | kTripleBits4)], g = lut[p & kPairBits4];
+      if (m != 0xFF) atomicAdd(&h_main[m], ~0ull);
+      if (g != 0xFF) atomicAdd(&h_sub[g], ~0ull);
+    }
   }
   __syncthreads();
   unsigned long long* hc = hist_copy(hist, kExactHistStride);

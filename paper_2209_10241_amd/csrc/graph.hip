@@ -1350,7 +1350,7 @@ void release(hm_graph* H, hipStream_t st = nullptr, bool ordered = false) {
                    H->i3_idx, H->i4_off, H->i4_idx, H->hist,        H->sample_hist};
   // and those built later, on first use
   void* later[] = {H->g2_eid,  H->pl_keys,  H->pl_edge,  H->pl_slot,   H->pl_codeg, H->pl_third, H->pl_adj,
-                   H->pl_pre,  H->q_slot,   H->q_fourth, H->b4_order,  H->hub_rank, H->hub_bits, H->proj_bits,
+                   H->q_slot,  H->q_fourth, H->hub_rank, H->hub_bits, H->proj_bits,
                    H->ns_tri,  H->ns_nbr,   H->ns_h3,    H->es,        H->e5,       H->hs5,   H->dense5,
                    H->rank_of, H->node_of, H->rank_bounds};
   std::vector<void*> ps(std::begin(later), std::end(later));

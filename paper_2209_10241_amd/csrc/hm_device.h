@@ -11,6 +11,7 @@ constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = kThreads / kWave;
 // pattern bits of the pairs among 4 local nodes: masks 3,5,6,9,10,12 -> bits 0,1,2,4,5,7
 constexpr uint32_t kPairBits4 = (1u << 0) | (1u << 1) | (1u << 2) | (1u << 4) | (1u << 5) | (1u << 7);
+constexpr uint32_t kTripleBits4 = (1u << 3) | (1u << 6) | (1u << 8) | (1u << 9);
 constexpr uint32_t kPairBits3 = 0x7u;
 
 __device__ inline bool has2(const Set64& s, uint32_t u, uint32_t v) {

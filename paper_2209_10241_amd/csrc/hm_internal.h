@@ -242,6 +242,7 @@ struct Scratch {
 // into H->hist (case (a) is counted by the caller).
 int count_sparse(const hm_graph* H, int k, hipStream_t st);
 int ensure_pair_links(hm_graph* H, hipStream_t st);
+int ensure_quad_index(hm_graph* H, hipStream_t st);
 int ensure_hub_rows(hm_graph* H, hipStream_t st);
 int ensure_ranks(hm_graph* H, hipStream_t st);
 int ensure_node_stats(hm_graph* H, hipStream_t st);
@@ -320,15 +321,13 @@ struct hm_graph {
   // adjacency to the pair's two nodes (bits 0 and 1)
   uint32_t* pl_third = nullptr;
   uint8_t* pl_adj = nullptr;
-  uint32_t* pl_pre = nullptr;
-  // 3-node subset -> 4-node hyperedges (see quad_find; q_bits = 0: not built)
+  // 3-node subset -> 4-node hyperedges (see quad_find; q_bits = 0: not built,
+  // q_done: nothing more to build)
   unsigned long long* q_slot = nullptr;
   unsigned long long q_mask = 0;
   uint32_t* q_fourth = nullptr;
-  int q_bits = 0;   // 4 x (entries + 1) prefix counts by adjacency class
-  // the 3-node hyperedges by decreasing estimated cost of their exact
-  // neighbourhood count (built on first use without bit rows)
-  uint32_t* b4_order = nullptr;
+  int q_bits = 0;
+  bool q_done = false;
   // the nodes by ascending class of degrees (built on first use without bit
   // rows; see wedge.hip): rank of each node, node of each rank, and the first
   // ranks of degree >= 2 and of wedge.hip's larger classes

@@ -135,7 +135,7 @@ __device__ __forceinline__ void j3_exceptions(const View& v, const PairLinks& pl
                                      unsigned long long* h) {
   for (uint64_t t = first + lane; t < last; t += stride) {
     uint32_t pat;
-    const uint32_t r = b4_exception<false>(v, pl, x, t, &pat, b4_short_none());
+    const uint32_t r = b4_exception(v, pl, x, t, &pat);
     if (!r) continue;
     if (r & 7u) {
       const uint8_t cc = lut[b4_combo_pattern(x, r & 7u)];
@@ -1247,6 +1247,7 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   }
   if (k == 4 && !bits) {
     HM_TRY(ensure_pair_links(const_cast<hm_graph*>(H), st));
+    HM_TRY(ensure_quad_index(const_cast<hm_graph*>(H), st));
     HM_TRY(ensure_edge_stats(const_cast<hm_graph*>(H), st));
     HM_TRY(ensure_node_stats(const_cast<hm_graph*>(H), st));
     HM_TRY(ensure_hub_rows(const_cast<hm_graph*>(H), st));
@@ -1261,7 +1262,6 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   a.pl.codeg = H->pl_codeg;
   a.pl.third = H->pl_third;
   a.pl.adj = H->pl_adj;
-  a.pl.pre = H->pl_pre;
   a.pl.q_slot = reinterpret_cast<const ulonglong2*>(H->q_slot);
   a.pl.q_mask = H->q_mask;
   a.pl.q_fourth = H->q_fourth;

@@ -4,8 +4,8 @@
 //
 // The generators and ownership rules are those of the bit-row path:
 //   (a) every k-node hyperedge, classified by fill-in;
-//   (b) order 4: every 3-node hyperedge with each fourth node, counted per
-//       pairwise combination by inclusion-exclusion (hm_sparse.h);
+//   (b) order 4: the sets around 3-node hyperedges, counted by
+//       inclusion-exclusion (triples.hip);
 //   (c) sets connected through pairs only: never enumerated.  The number of
 //       connected k-node sets of the pairwise graph G2 per induced shape
 //       follows from non-induced subgraph counts: 3-stars sum C(d,3),
@@ -15,8 +15,6 @@
 //       how often each shape contains another; then the sets that (a) or (b)
 //       own are subtracted by shape.
 #include <algorithm>
-#include <map>
-#include <mutex>
 #include <vector>
 
 #include "hm_sparse.h"
@@ -72,76 +70,6 @@ __global__ void __launch_bounds__(kThreads) k_sp_nodes(View v, unsigned long lon
   }
   block_add(s3, acc + kAccStar);
   block_add(s2, acc + kAccWedge);
-}
-
-// (b) at order 4 without bit rows: one wavefront per 3-node hyperedge, taken
-// in the order `order` (decreasing estimated cost), so that the grid's
-// wavefronts, each taking every n_waves-th, get like shares of a
-// heavy-tailed workload.
-__global__ void __launch_bounds__(kThreads) k_sp_b4(View v, PairLinks pl, uint64_t n3, const uint32_t* __restrict__ order,
-                                                    const uint8_t* __restrict__ lut_g,
-                                                    unsigned long long* __restrict__ hist) {
-  __shared__ uint8_t lut[2048];
-  __shared__ unsigned long long h_main[256], h_sub[256];
-  __shared__ __align__(16) uint32_t short_lists[kWavesPerBlock][kB4ShortWords];
-  load_lut(lut, lut_g, 2048);
-  h_main[threadIdx.x] = 0;
-  h_sub[threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t wave = uint64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-  const uint64_t n_waves = uint64_t(gridDim.x) * kWavesPerBlock;
-  uint32_t* short_mem = short_lists[threadIdx.x / kWave];
-  for (uint64_t j = wave; j < n3; j += n_waves) {
-    const uint64_t i = order[j];
-    b4_sparse<true, true>(v, pl, v.e3[3 * i], v.e3[3 * i + 1], v.e3[3 * i + 2], lut, h_main, h_sub, short_mem, false);
-  }
-  __syncthreads();
-  unsigned long long* hc = hist_copy(hist, kExactHistStride);
-  flush(h_main, hc + kMain, 256);
-  flush(h_sub, hc + kSub, 256);
-}
-
-// (b) at order 4 without bit rows, the pair-run terms: one wavefront per
-// entry of the pair index, in index order, so that the entries of one run
-// (and their shared lists) are taken by neighbouring wavefronts.
-// (four wavefronts per SIMD: its items are chains of dependent lookups)
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) k_sp_b4_runs(View v, PairLinks pl, const uint8_t* __restrict__ lut_g,
-                                                         unsigned long long* __restrict__ hist) {
-  __shared__ uint8_t lut[2048];
-  __shared__ unsigned long long h_main[256], h_sub[256];
-  __shared__ __align__(16) uint32_t short_lists[kWavesPerBlock][kB4ShortWords];
-  load_lut(lut, lut_g, 2048);
-  h_main[threadIdx.x] = 0;
-  h_sub[threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t wave = uint64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-  const uint64_t n_waves = uint64_t(gridDim.x) * kWavesPerBlock;
-  uint32_t* short_mem = short_lists[threadIdx.x / kWave];
-  for (uint64_t p = wave; p < pl.n; p += n_waves) b4_run_entry(v, pl, p, lut, h_main, h_sub, short_mem);
-  __syncthreads();
-  unsigned long long* hc = hist_copy(hist, kExactHistStride);
-  flush(h_main, hc + kMain, 256);
-  flush(h_sub, hc + kSub, 256);
-}
-
-// Sort keys of the 3-node hyperedges for k_sp_b4: the complement of the
-// logarithmic class (eight per octave, so that one radix pass orders them) of
-// an estimate of the memory transactions of each (two per entry of its
-// shortest pairwise row, six per entry of the 4-node incidence list it reads
-// when there is no 4-node index), with the hyperedge as value.
-__global__ void k_b4_cost_keys(View v, PairLinks pl, uint64_t n3, uint32_t* __restrict__ keys,
-                               uint32_t* __restrict__ vals) {
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n3; i += uint64_t(gridDim.x) * blockDim.x) {
-    const uint32_t a = v.e3[3 * i], b = v.e3[3 * i + 1], c = v.e3[3 * i + 2];
-    const uint64_t dmin = min(deg2_of(v, a), min(deg2_of(v, b), deg2_of(v, c)));
-    const uint32_t fa = v.i4_off[a + 1] - v.i4_off[a], fb = v.i4_off[b + 1] - v.i4_off[b],
-                   fc = v.i4_off[c + 1] - v.i4_off[c];
-    // (with the 4-node index, the 4-node hyperedges holding e are one lookup)
-    const uint64_t cost = 2 * dmin + (pl.q_bits ? 0 : 6 * uint64_t(min(fa, min(fb, fc))));
-    const uint32_t x = uint32_t(min<uint64_t>(cost, 0x7FFFFFFFull)) + 8, e = 31 - uint32_t(__clz(int(x)));
-    keys[i] = 255u - min(255u, 8 * (e - 3) + ((x >> (e - 3)) & 7u));
-    vals[i] = uint32_t(i);
-  }
 }
 
 // Induced shape counts from the non-induced ones, into the G2 region.
@@ -210,66 +138,6 @@ __global__ void k_pl_wide_keys(const K* __restrict__ packed, uint64_t n, int bit
   for (uint64_t p = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += uint64_t(gridDim.x) * blockDim.x) {
     const unsigned long long k = packed[p];
     keys[p] = ((k >> bits) << 32) | (k & ((1ull << bits) - 1));
-  }
-}
-
-// Prefix counts of the entries by adjacency class: the four classes' counts of
-// each tile of kClassTile entries (class-major, so that one scan serves all
-// four), then within each tile.
-constexpr uint32_t kClassTile = 2048;
-__global__ void __launch_bounds__(kThreads) k_pl_class_count(const uint8_t* __restrict__ adj, uint64_t n,
-                                                             uint32_t* __restrict__ counts) {
-  __shared__ uint32_t c[4];
-  if (threadIdx.x < 4) c[threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t base = uint64_t(blockIdx.x) * kClassTile;
-#pragma unroll
-  for (uint32_t r = 0; r < kClassTile / kThreads; ++r) {
-    const uint64_t p = base + r * kThreads + threadIdx.x;
-    const uint32_t a = p < n ? adj[p] : 4u;
-#pragma unroll
-    for (uint32_t cl = 0; cl < 4; ++cl) {
-      const uint32_t k = uint32_t(__popcll(__ballot(a == cl)));
-      if ((threadIdx.x & (kWave - 1)) == 0 && k) atomicAdd(&c[cl], k);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) counts[uint64_t(threadIdx.x) * gridDim.x + blockIdx.x] = c[threadIdx.x];
-}
-
-__global__ void __launch_bounds__(kThreads) k_pl_class_prefix(const uint8_t* __restrict__ adj, uint64_t n,
-                                                              const uint32_t* __restrict__ before,
-                                                              uint32_t* __restrict__ pre) {
-  __shared__ uint32_t part[2][4][kWavesPerBlock];
-  const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  const uint64_t base = uint64_t(blockIdx.x) * kClassTile;
-  uint32_t at[4];
-#pragma unroll
-  for (uint32_t cl = 0; cl < 4; ++cl)
-    at[cl] = before[uint64_t(cl) * gridDim.x + blockIdx.x] - before[uint64_t(cl) * gridDim.x];
-  for (uint32_t r = 0; r < kClassTile / kThreads; ++r) {
-    const uint64_t p = base + r * kThreads + threadIdx.x;
-    const uint32_t a = p < n ? adj[p] : 4u;
-    uint32_t mine[4];
-#pragma unroll
-    for (uint32_t cl = 0; cl < 4; ++cl) {
-      const unsigned long long m = __ballot(a == cl);
-      mine[cl] = uint32_t(__popcll(m & below));
-      if (lane == 0) part[r & 1][cl][wv] = uint32_t(__popcll(m));
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t cl = 0; cl < 4; ++cl) {
-      uint32_t x = at[cl] + mine[cl];
-      for (uint32_t q = 0; q < uint32_t(kWavesPerBlock); ++q) {
-        const uint32_t k = part[r & 1][cl][q];
-        if (q < wv) x += k;
-        at[cl] += k;
-      }
-      if (p < n) pre[cl * (n + 1) + p] = x;
-      if (p + 1 == n) pre[cl * (n + 1) + n] = x + (a == cl);
-    }
   }
 }
 
@@ -403,27 +271,6 @@ unsigned grid_cap(uint64_t items, uint64_t per_block, unsigned cap) {
 }
 
 
-// Workgroups of kThreads threads (no dynamic LDS) of `kernel` resident on the
-// current device at once.
-unsigned resident_blocks(const void* kernel) {
-  static std::mutex mu;
-  static std::map<std::pair<const void*, int>, unsigned> cache;
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = cache.find({kernel, dev});
-  if (it != cache.end()) return it->second;
-  int cus = 256, per_cu = 1;
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess || per_cu < 1) per_cu = 1;
-  const unsigned r = unsigned(std::max(cus, 1)) * unsigned(per_cu);
-  cache[{kernel, dev}] = r;
-  return r;
-}
-
-}  // namespace
-
-namespace {
 
 // Per node, over its adjacency row: the sum of the neighbours' degrees, and
 // of its pairs' triangles (twice the triangles at the node).  A wavefront
@@ -556,11 +403,17 @@ T* keep(Scratch& tmp, T* p) {
 
 // The 3-node subset -> 4-node hyperedge index (H->q_*), when the packed key
 // fits 63 bits; otherwise none (q_bits = 0) and the incidence lists serve.
-int build_quad_index(hm_graph* H, hipStream_t st) {
+// Built on first use.
+int ensure_quad_index(hm_graph* H, hipStream_t st) {
+  note_use(H, st);
+  if (H->q_done) return HM_OK;
   const uint64_t n4 = H->n_by_size[4];
   int bits = 1;
   while (bits < 32 && (1ull << bits) < H->n_nodes) ++bits;
-  if (n4 == 0 || 3 * bits > 63) return HM_OK;
+  if (n4 == 0 || 3 * bits > 63) {
+    H->q_done = true;
+    return HM_OK;
+  }
   const uint64_t n = 4 * n4;
   Scratch tmp(st);
   unsigned long long *k = nullptr, *kt = nullptr, *slots = nullptr;
@@ -583,6 +436,7 @@ int build_quad_index(hm_graph* H, hipStream_t st) {
   H->q_mask = cap - 1;
   H->q_fourth = keep(tmp, f);
   H->q_bits = bits;
+  H->q_done = true;
   return HM_OK;
 }
 
@@ -602,8 +456,7 @@ int sort_by_pair(const hm_graph* H, uint64_t n, int bits, uint32_t*& e, uint32_t
   return HM_OK;
 }
 
-// The pair -> 3-node hyperedge index of H, built on first use (with the
-// 4-node index beside it).
+// The pair -> 3-node hyperedge index of H, built on first use.
 int ensure_pair_links(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->pl_keys || H->n_by_size[3] == 0) return HM_OK;
@@ -615,10 +468,8 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
   const unsigned long long cap = pow2_capacity(n);
   Scratch tmp(st);
   unsigned long long *keys = nullptr, *slots = nullptr;
-  uint32_t *t = nullptr, *tt = nullptr, *e = nullptr, *et = nullptr, *codeg = nullptr, *third = nullptr, *pre = nullptr,
-           *counts = nullptr, *before = nullptr;
+  uint32_t *t = nullptr, *tt = nullptr, *e = nullptr, *et = nullptr, *codeg = nullptr, *third = nullptr;
   uint8_t* adj = nullptr;
-  const uint64_t tiles = (n + kClassTile - 1) / kClassTile;
   HM_TRY(tmp.get(&keys, n));
   HM_TRY(tmp.get(&t, n));
   HM_TRY(tmp.get(&tt, n));
@@ -628,9 +479,6 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
   HM_TRY(tmp.get(&codeg, cap));
   HM_TRY(tmp.get(&third, n));
   HM_TRY(tmp.get(&adj, n));
-  HM_TRY(tmp.get(&pre, 4 * (n + 1)));
-  HM_TRY(tmp.get(&counts, 4 * tiles));
-  HM_TRY(tmp.get(&before, 4 * tiles));
   const unsigned g = grid_cap(n, 256, 4096);
   k_pl_third_keys<<<g, 256, 0, st>>>(H->e3, n, t, e);
   HM_HIP(hipGetLastError());
@@ -643,10 +491,6 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
   k_pl_third<<<g, 256, 0, st>>>(H->e3, keys, e, n, H->hs2, third, adj);
   k_pl_codeg<<<grid_cap(n, kThreads, 8192), kThreads, 0, st>>>(view_of(H), keys, n, slots, cap - 1, H->hub_rank,
                                                                H->hub_bits, H->hub_words, codeg);
-  k_pl_class_count<<<unsigned(tiles), kThreads, 0, st>>>(adj, n, counts);
-  HM_HIP(hipGetLastError());
-  HM_TRY(scan_exclusive_u32(counts, before, 4 * tiles, nullptr, st));
-  k_pl_class_prefix<<<unsigned(tiles), kThreads, 0, st>>>(adj, n, before, pre);
   HM_HIP(hipGetLastError());
   H->pl_edge = keep(tmp, e);
   H->pl_slot = keep(tmp, slots);
@@ -654,9 +498,8 @@ int ensure_pair_links(hm_graph* H, hipStream_t st) {
   H->pl_codeg = keep(tmp, codeg);
   H->pl_third = keep(tmp, third);
   H->pl_adj = keep(tmp, adj);
-  H->pl_pre = keep(tmp, pre);
   H->pl_keys = keep(tmp, keys);
-  return build_quad_index(H, st);
+  return HM_OK;
 }
 
 PairLinks pair_links_of(const hm_graph* H) {
@@ -669,7 +512,6 @@ PairLinks pair_links_of(const hm_graph* H) {
   pl.codeg = H->pl_codeg;
   pl.third = H->pl_third;
   pl.adj = H->pl_adj;
-  pl.pre = H->pl_pre;
   pl.q_slot = reinterpret_cast<const ulonglong2*>(H->q_slot);
   pl.q_mask = H->q_mask;
   pl.q_fourth = H->q_fourth;
@@ -758,25 +600,6 @@ int ensure_hub_rows(hm_graph* H, hipStream_t st) {
   return HM_OK;
 }
 
-// H->b4_order, after the pair index: the 3-node hyperedges sorted by
-// decreasing cost estimate.
-int ensure_b4_order(hm_graph* H, hipStream_t st) {
-  note_use(H, st);
-  const uint64_t n3 = H->n_by_size[3];
-  if (H->b4_order || n3 == 0) return HM_OK;
-  Scratch tmp(st);
-  uint32_t *k = nullptr, *o = nullptr, *kt = nullptr, *ot = nullptr;
-  HM_TRY(tmp.get(&k, n3));
-  HM_TRY(tmp.get(&o, n3));
-  HM_TRY(tmp.get(&kt, n3));
-  HM_TRY(tmp.get(&ot, n3));
-  k_b4_cost_keys<<<grid_cap(n3, 256, 4096), 256, 0, st>>>(view_of(H), pair_links_of(H), n3, k, o);
-  HM_HIP(hipGetLastError());
-  HM_TRY(radix_sort_pairs(k, o, kt, ot, n3, 8, st));
-  H->b4_order = keep(tmp, o);
-  return HM_OK;
-}
-
 // Fills the main, sub and G2 regions of H->hist (zeroed by the caller) except
 // case (a), which the caller counts.
 int count_sparse(const hm_graph* H, int k, hipStream_t st) {
@@ -784,7 +607,7 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   const uint8_t *lut4 = nullptr, *lut3 = nullptr;
   HM_TRY(device_luts(H->device, &lut4, &lut3));
   const View v = view_of(H);
-  const uint64_t n2 = H->n_by_size[2], n3 = H->n_by_size[3];
+  const uint64_t n2 = H->n_by_size[2];
   Scratch tmp(st);
   unsigned long long* acc = nullptr;
   uint32_t* tri_e = nullptr;
@@ -812,27 +635,7 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   cls.paw = t.lut4[(1u << 0) | (1u << 1) | (1u << 2) | (1u << 4)];
   cls.diamond = t.lut4[(1u << 0) | (1u << 1) | (1u << 2) | (1u << 4) | (1u << 5)];
   cls.clique = t.lut4[kPairBits4];
-  if (k == 4 && n3) {
-    HM_TRY(ensure_pair_links(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_b4_order(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_hub_rows(const_cast<hm_graph*>(H), st));
-    // no more workgroups than are resident at once: each wavefront's share is
-    // fixed, and a workgroup that starts late would finish late
-    const unsigned grid = grid_cap(n3, kWavesPerBlock, resident_blocks(reinterpret_cast<const void*>(k_sp_b4)));
-    {
-      ProfileScope ps("k_sp_b4", st);
-      k_sp_b4<<<grid, kThreads, 0, st>>>(v, pair_links_of(H), n3, H->b4_order, lut4, H->hist);
-    }
-    HM_HIP(hipGetLastError());
-    const uint64_t n_entries = 3 * n3;
-    const unsigned grid_r =
-        grid_cap(n_entries, kWavesPerBlock, resident_blocks(reinterpret_cast<const void*>(k_sp_b4_runs)));
-    {
-      ProfileScope ps("k_sp_b4_runs", st);
-      k_sp_b4_runs<<<grid_r, kThreads, 0, st>>>(v, pair_links_of(H), lut4, H->hist);
-    }
-    HM_HIP(hipGetLastError());
-  }
+  if (k == 4) HM_TRY(count_triples(H, st));
   k_sp_shapes<<<1, 64, 0, st>>>(acc, k, cls, H->hist);
   HM_HIP(hipGetLastError());
   return HM_OK;

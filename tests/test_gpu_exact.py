@@ -687,3 +687,41 @@ def test_walks_match_bit_rows(hm, n, hubs, hub_degree, ring, clique):
             hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
     for b, h in zip(got[8192], got[0]):
         assert np.array_equal(b, h)
+
+
+@pytest.mark.parametrize("hub_min_degree", [0, 16, 2048])
+@pytest.mark.parametrize("n,run,pairs", [(40, 12, 300), (1200, 700, 15000), (1200, 700, 300), (2500, 2, 4000)])
+def test_triples_match_bit_rows(hm, n, run, pairs, hub_min_degree):
+    """Sets around 3-node hyperedges without bit rows (pair runs of two entries
+    up to more than a list that is searched, walked or looked up from the third
+    node's lists, alone among many runs of one entry, with and without dense
+    rows) against the bit-row path."""
+    rng = np.random.default_rng(n + run + pairs)
+    def distinct(k, m):
+        s = np.sort(rng.choice(n, (m, k)), axis=1)
+        return s[(s[:, 1:] > s[:, :-1]).all(axis=1)]
+    third = np.sort(rng.choice(np.arange(3, n), run, replace=False))
+    with_pair = lambda a, b, t: np.sort(np.c_[np.full(len(t), a), np.full(len(t), b), t], axis=1)
+    e3 = np.r_[with_pair(0, 1, third), with_pair(0, 2, third[::2]), with_pair(1, int(third[0]), third[1::2]),
+               with_pair(n - 1, int(third[-1]), np.setdiff1d(third[:-1:3], [n - 1])), distinct(3, 200)]
+    e3 = e3[(e3[:, 0] < e3[:, 1]) & (e3[:, 1] < e3[:, 2])]
+    e4 = np.r_[np.sort(np.c_[np.zeros(len(third) // 2, int), np.ones(len(third) // 2, int), third[:-1:2], third[1::2]], axis=1),
+               distinct(4, 100)]
+    # the whole of a few nodes, so that rows of every kind meet the runs
+    hub = np.sort(np.array([(h, t) for h in (0, 1, 2, int(third[0])) for t in range(n) if t != h and rng.random() < 0.8]), axis=1)
+    e2 = np.r_[distinct(2, pairs), hub]
+    members = np.r_[e2.ravel(), e3.ravel(), e4.ravel()].astype(np.uint32)
+    sizes = np.r_[np.full(len(e2), 2), np.full(len(e3), 3), np.full(len(e4), 4)]
+    offsets = np.r_[0, np.cumsum(sizes)].astype(np.uint64)
+    keep = hm.hm_get_option(hm.HM_OPT_HUB_MIN_DEGREE)
+    got = {}
+    try:
+        hm.hm_set_option(hm.HM_OPT_HUB_MIN_DEGREE, hub_min_degree)
+        for bits in (8192, 0):
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+            with hm.hm_graph_create(members, offsets, n) as g:
+                got[bits] = hm.count_exact(g, 4).cpu().numpy()
+    finally:
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+        hm.hm_set_option(hm.HM_OPT_HUB_MIN_DEGREE, keep)
+    assert np.array_equal(got[8192], got[0])
