@@ -93,6 +93,23 @@ struct FastDedup {
   unsigned long long* slot_of;
 };
 
+// Enter hyperedge i with hash h in the one-launch search.
+__device__ inline void fast_insert(const FastDedup& dd, unsigned long long h, uint64_t i) {
+  const unsigned long long tag = (h >> 32) & dd.tag_mask;
+  const unsigned long long mine = (tag << 32) | i;
+  unsigned long long pos = h & dd.mask;
+  while (true) {
+    const unsigned long long cur = atomicCAS(&dd.slots[pos], kEmpty64, mine);
+    if (cur == kEmpty64) break;
+    if ((cur >> 32) == tag) {
+      atomicMin(&dd.slots[pos], mine);
+      break;
+    }
+    pos = (pos + 1) & dd.mask;
+  }
+  dd.slot_of[i] = pos;
+}
+
 // One thread per input hyperedge: copy its members, sort them, check ids and
 // repeats, record its size and hash, and (dd.slots set) enter it in the
 // duplicate search.  Offsets start at 0, never decrease and stay within the
@@ -173,25 +190,202 @@ __global__ void k_prepare(const uint32_t* __restrict__ members, const uint64_t* 
       }
       size[i] = s;
       hash[i] = h;
-      if (dd.slots && s >= 2) {
-        const unsigned long long tag = (h >> 32) & dd.tag_mask;
-        const unsigned long long mine = (tag << 32) | i;
-        unsigned long long pos = h & dd.mask;
-        while (true) {
-          const unsigned long long cur = atomicCAS(&dd.slots[pos], kEmpty64, mine);
-          if (cur == kEmpty64) break;
-          if ((cur >> 32) == tag) {
-            atomicMin(&dd.slots[pos], mine);
-            break;
-          }
-          pos = (pos + 1) & dd.mask;
-        }
-        dd.slot_of[i] = pos;
-      }
+      if (dd.slots && s >= 2) fast_insert(dd, h, i);
     }
     ecode[i] = uint8_t(err);
   }
   multi_fill(fills);
+}
+
+// The builds of large inputs (every build but the one-pass one) prepare tiles
+// of 256 hyperedges per workgroup: the tile's members are loaded into LDS in
+// one coalesced sweep, sorted there (up to 8 nodes by one thread's network; 9
+// to 16 by ranks among 16 lanes; up to 64 by ranks among a wavefront) and
+// written back in one sweep.  A tile of more than kPrepWords members, or with
+// an invalid offset, is read in place.  A thread per hyperedge, which sorted
+// more than 8 nodes by insertion in private or device memory, took 2.58 ms for
+// 5 million hyperedges of 2 to 50 nodes (28 million members), this one 0.53
+// (of 2 million with 7.2 million members: 0.43 and 0.20), of which the
+// duplicate search's atomics are a quarter to a half.  (Finding duplicates by
+// a radix partition of the hashes and LDS tables instead was no faster at 5
+// million and slower below 1.5 million.)
+//
+// The hash of more than 8 nodes is a sum over (node, position), so that lanes
+// form it together.
+constexpr uint32_t kPrepTile = 256;
+constexpr uint32_t kPrepWords = 6144;
+
+__device__ inline unsigned long long tuple_term(uint32_t x, uint32_t i) {
+  return mix64(x + 0x9e3779b97f4a7c15ull * (i + 1));
+}
+
+__global__ void __launch_bounds__(kPrepTile) k_prepare_tiles(
+    const uint32_t* __restrict__ members, const uint64_t* __restrict__ offsets, uint64_t n_edges, uint64_t n_members,
+    uint32_t n_nodes, uint32_t* __restrict__ sm, uint32_t* __restrict__ size, unsigned long long* __restrict__ hash,
+    uint8_t* __restrict__ ecode, FastDedup dd) {
+  __shared__ uint32_t mem[kPrepWords];
+  __shared__ unsigned long long s_hash[kPrepTile];
+  __shared__ uint32_t s_err[kPrepTile], s_size[kPrepTile];
+  __shared__ uint64_t s_at[kPrepTile];
+  __shared__ uint16_t mid[kPrepTile], wide[kPrepTile];   // hyperedges of 9 to 16 and of more nodes
+  __shared__ uint32_t n_mid, n_wide, n_long, odd;
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+  const uint64_t first = uint64_t(blockIdx.x) * kPrepTile, i = first + tid;
+  const bool have = i < n_edges;
+  const uint64_t b = have ? offsets[i] : 0, e = have ? offsets[i + 1] : 0;
+  const bool bad = have && (e < b || e > n_members || (i == 0 && b != 0));
+  if (tid == 0) n_mid = n_wide = n_long = odd = 0;
+  __syncthreads();
+  if (bad) atomicOr(&odd, 1u);
+  __syncthreads();
+  // (valid offsets: the tile's members are contiguous)
+  const uint64_t t0 = offsets[first], t1 = offsets[min<uint64_t>(n_edges, first + kPrepTile)];
+  const bool in_lds = !odd && t1 - t0 <= kPrepWords;
+  const uint32_t words = in_lds ? uint32_t(t1 - t0) : 0u;
+  for (uint32_t w = tid; w < words; w += kPrepTile) mem[w] = members[t0 + w];
+  const uint32_t s = bad || !have ? 0u : uint32_t(min<uint64_t>(e - b, 0xFFFFFFFFull));
+  uint32_t err = bad ? uint32_t(kErrOffsets) : (have && s == 0 ? uint32_t(kErrEmpty) : 0u);
+  unsigned long long h = 0;
+  s_size[tid] = s;
+  s_at[tid] = b;
+  if (s > kRegSort) {
+    wide[atomicAdd(&n_wide, 1u)] = uint16_t(tid);
+    if (s > uint32_t(kWave)) atomicAdd(&n_long, 1u);
+  } else if (s > kNetSort) {
+    mid[atomicAdd(&n_mid, 1u)] = uint16_t(tid);
+  }
+  __syncthreads();
+  if (s && s <= kNetSort) {
+    // (the padding, above any node id, sorts last)
+    uint32_t r[kNetSort];
+    const uint32_t at = uint32_t(b - t0);
+#pragma unroll
+    for (uint32_t j = 0; j < kNetSort; ++j) r[j] = j < s ? (in_lds ? mem[at + j] : members[b + j]) : 0xFFFFFFFFu;
+#pragma unroll
+    for (uint32_t j = 0; j < kNetSort; ++j)
+      if (j < s && r[j] >= n_nodes) err |= kErrBadId;
+    sort8(r);
+#pragma unroll
+    for (uint32_t j = 0; j < kNetSort; ++j)
+      if (j < s) {
+        if (in_lds) mem[at + j] = r[j];
+        else sm[b + j] = r[j];
+      }
+#pragma unroll
+    for (uint32_t j = 1; j < kNetSort; ++j)
+      if (j < s && r[j] == r[j - 1]) err |= kErrRepeat;
+    h = tuple_hash_start(s);
+#pragma unroll
+    for (uint32_t j = 0; j < kNetSort; ++j)
+      if (j < s) h = tuple_hash_step(h, r[j], j);
+  }
+  // 9 to 16 nodes: 16 lanes each; an element's place is the number of
+  // smaller ones
+  constexpr uint32_t kGroups = kPrepTile / kRegSort;
+  for (uint32_t q = tid / kRegSort; q < n_mid; q += kGroups) {
+    const uint32_t l = tid & (kRegSort - 1), o = mid[q], so = s_size[o];
+    const uint64_t bo = s_at[o];
+    const uint32_t at = uint32_t(bo - t0);
+    const uint32_t x = l < so ? (in_lds ? mem[at + l] : members[bo + l]) : 0xFFFFFFFFu;
+    uint32_t rank = 0, eo = l < so && x >= n_nodes ? uint32_t(kErrBadId) : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < uint32_t(kRegSort); ++j) {
+      const uint32_t y = uint32_t(__shfl(int(x), int(j), kRegSort));
+      rank += uint32_t(y < x || (y == x && j < l));
+      if (y == x && j != l && l < so && j < so) eo |= kErrRepeat;
+    }
+    unsigned long long t = l < so ? tuple_term(x, rank) : 0ull;
+    if (l < so) {
+      if (in_lds) mem[at + rank] = x;
+      else sm[bo + rank] = x;
+    }
+#pragma unroll
+    for (int d = kRegSort / 2; d > 0; d >>= 1) {
+      t += __shfl_xor(t, d, kRegSort);
+      eo |= uint32_t(__shfl_xor(int(eo), d, kRegSort));
+    }
+    if (l == 0) {
+      s_hash[o] = mix64(tuple_hash_start(so) ^ t);
+      s_err[o] = eo;
+    }
+  }
+  // up to 64 nodes: a wavefront each
+  for (uint32_t q = tid / kWave; q < n_wide; q += kPrepTile / kWave) {
+    const uint32_t o = wide[q], so = s_size[o];
+    if (so > uint32_t(kWave)) continue;
+    const uint64_t bo = s_at[o];
+    const uint32_t at = uint32_t(bo - t0);
+    const uint32_t x = lane < so ? (in_lds ? mem[at + lane] : members[bo + lane]) : 0xFFFFFFFFu;
+    uint32_t rank = 0;
+    bool again = false;
+    for (uint32_t j = 0; j < so; ++j) {
+      const uint32_t y = uint32_t(__builtin_amdgcn_readlane(int(x), int(j)));
+      rank += uint32_t(y < x || (y == x && j < lane));
+      again |= y == x && j != lane;
+    }
+    const unsigned long long t = wave_sum(lane < so ? tuple_term(x, rank) : 0ull);
+    const uint32_t eo = (__ballot(lane < so && x >= n_nodes) ? uint32_t(kErrBadId) : 0u) |
+                        (__ballot(lane < so && again) ? uint32_t(kErrRepeat) : 0u);
+    if (lane < so) {
+      if (in_lds) mem[at + rank] = x;
+      else sm[bo + rank] = x;
+    }
+    if (lane == 0) {
+      s_hash[o] = mix64(tuple_hash_start(so) ^ t);
+      s_err[o] = eo;
+    }
+  }
+  __syncthreads();
+  for (uint32_t w = tid; w < words; w += kPrepTile) sm[t0 + w] = mem[w];
+  if (n_long) {
+    // more than 64 nodes: a wavefront each, whose lanes rank the nodes among
+    // all (one check finds members that are ascending already), from the
+    // unsorted members in LDS or in the input
+    __syncthreads();   // (the sweep has written their places)
+    for (uint32_t q = tid / kWave; q < n_wide; q += kPrepTile / kWave) {
+      const uint32_t o = wide[q], so = s_size[o];
+      if (so <= uint32_t(kWave)) continue;
+      const uint64_t bo = s_at[o];
+      const uint32_t* src = in_lds ? mem + uint32_t(bo - t0) : members + bo;
+      bool up = true;
+      for (uint64_t k = uint64_t(lane) + 1; k < so; k += kWave) up &= src[k - 1] < src[k];
+      const bool sorted = __ballot(!up) == 0;
+      unsigned long long t = 0;
+      uint32_t eo = 0;
+      for (uint64_t k = lane; k < so; k += kWave) {
+        const uint32_t x = src[k];
+        if (x >= n_nodes) eo |= kErrBadId;
+        uint64_t rank = k;
+        if (!sorted) {
+          rank = 0;
+          for (uint64_t j = 0; j < so; ++j) {
+            const uint32_t y = src[j];
+            rank += uint64_t(y < x || (y == x && j < k));
+            if (y == x && j != k) eo |= kErrRepeat;
+          }
+        }
+        sm[bo + rank] = x;
+        t += tuple_term(x, uint32_t(rank));
+      }
+      t = wave_sum(t);
+#pragma unroll
+      for (int d = kWave / 2; d > 0; d >>= 1) eo |= uint32_t(__shfl_xor(int(eo), d, kWave));
+      if (lane == 0) {
+        s_hash[o] = mix64(tuple_hash_start(so) ^ t);
+        s_err[o] = eo;
+      }
+    }
+    __syncthreads();
+  }
+  if (!have) return;
+  if (s > kNetSort) {
+    h = s_hash[tid];
+    err |= s_err[tid];
+  }
+  size[i] = s;
+  hash[i] = h;
+  ecode[i] = uint8_t(err);
+  if (dd.slots && s >= 2) fast_insert(dd, h, i);
 }
 
 __device__ inline bool same_tuple(const uint32_t* sm, const uint64_t* off, const uint32_t* size,
@@ -274,7 +468,7 @@ struct Degrees {
 };
 
 // Each first occurrence of size 2, 3 or 4 also counts its members' degrees
-// (deg).  (verify: the table came from the one-launch search, so a hyperedge
+// (deg, unless its arrays are null).  (verify: the table came from the one-launch search, so a hyperedge
 // that met an earlier one compares their members, and a meeting of two
 // different hyperedges sets kErrCollide)
 __global__ void __launch_bounds__(kTile) k_first_tiles(const uint32_t* __restrict__ size, uint64_t n_edges,
@@ -308,7 +502,7 @@ __global__ void __launch_bounds__(kTile) k_first_tiles(const uint32_t* __restric
       dups = !first;
       const bool collide = verify && !first && !same_tuple(sm, off, size, hash, holder, i);
       // (only a hyperedge that passed validation: its ids are below n)
-      if (first && s <= 4 && !err) {
+      if (deg.deg2 && first && s <= 4 && !err) {
         uint32_t* d = s == 2 ? deg.deg2 : s == 3 ? deg.deg3 : deg.deg4;
         const uint32_t cp = degree_copy(mm, s, deg.R);
 #pragma unroll
@@ -532,6 +726,9 @@ __device__ void scan_degree_array(const uint32_t* __restrict__ d, uint32_t* __re
 constexpr uint32_t kGatherScanRun = 32;
 constexpr uint64_t kGatherScanMax = uint64_t(kGatherScanRun) * kTile;   // n * R at most
 
+// COPY_TOGETHER (large inputs): the workgroup copies its tile's members in one
+// coalesced sweep; else each thread copies its hyperedge's.
+template <bool COPY_TOGETHER>
 __global__ void __launch_bounds__(kTile) k_gather_tiles(const uint32_t* __restrict__ sm,
                                                          const uint64_t* __restrict__ off,
                                                          const uint32_t* __restrict__ size, uint64_t n_edges,
@@ -667,6 +864,27 @@ __global__ void __launch_bounds__(kTile) k_gather_tiles(const uint32_t* __restri
     if (lane == 0) part[k][wv] = tot;
   }
   __syncthreads();
+  if constexpr (COPY_TOGETHER) {
+    // per hyperedge of the tile, where its members begin in sm (from the
+    // tile's first) and in all_members (from the tile's base; ~0: a repeat)
+    __shared__ uint32_t s_src[kTile + 1], s_dst[kTile];
+    const uint64_t tile0 = uint64_t(blockIdx.x) * kTile, tile1 = min<uint64_t>(n_edges, tile0 + kTile);
+    const uint64_t src0 = off[tile0];
+    uint32_t dst = pre[4];
+    for (int q = 0; q < wv; ++q) dst += part[4][q];
+    const uint32_t words = uint32_t(off[tile1] - src0);
+    s_src[threadIdx.x] = i < n_edges ? uint32_t(at - src0) : words;
+    s_dst[threadIdx.x] = first ? dst : 0xFFFFFFFFu;
+    __syncthreads();
+    for (uint32_t w = threadIdx.x; w < words; w += kTile) {
+      uint32_t j = 0;
+#pragma unroll
+      for (uint32_t d = kTile / 2; d; d >>= 1)
+        if (s_src[j + d] <= w) j += d;
+      const uint32_t to = s_dst[j];
+      if (to != 0xFFFFFFFFu) g.all_members[uint64_t(base[4]) + to + (w - s_src[j])] = sm[src0 + w];
+    }
+  }
   if (!first) return;
   if (g.dedup_clear) g.dedup_clear[so] = kEmpty64;
   unsigned long long pos[kTileN];
@@ -675,11 +893,13 @@ __global__ void __launch_bounds__(kTile) k_gather_tiles(const uint32_t* __restri
     for (int q = 0; q < wv; ++q) p += part[k][q];
     pos[k] = p;
   }
-  const uint32_t* m = sm + at;
+  if constexpr (!COPY_TOGETHER) {
+    const uint32_t* m = sm + at;
 #pragma unroll
-  for (uint32_t j = 0; j < 4; ++j)
-    if (j < s) g.all_members[pos[4] + j] = mm[j];
-  for (uint32_t j = 4; j < s; ++j) g.all_members[pos[4] + j] = m[j];
+    for (uint32_t j = 0; j < 4; ++j)
+      if (j < s) g.all_members[pos[4] + j] = mm[j];
+    for (uint32_t j = 4; j < s; ++j) g.all_members[pos[4] + j] = m[j];
+  }
   g.all_off[pos[0]] = pos[4];
   if (pos[0] + 1 == total[0]) g.all_off[total[0]] = total[4];
   if (s == 2) {
@@ -805,8 +1025,7 @@ __device__ void rows_from_bits(const uint32_t* __restrict__ bits, uint32_t n, ui
 // Incidence lists of the 3- and 4-node hyperedges (positions in any order):
 // a hyperedge fills through the cursor of copy degree_copy() of each member,
 // the copy its degree was counted in (workgroup `block` of `n_blocks`).
-// With bit rows (oth3, oth4 not null) each entry also gets the hyperedge's
-// other members.
+// Each entry also gets the hyperedge's other members (oth3, oth4).
 __device__ void inc_fill(const uint32_t* __restrict__ e3, uint64_t n3, uint32_t* cur3, uint32_t* idx3,
                          const uint32_t* __restrict__ e4, uint64_t n4, uint32_t* cur4, uint32_t* idx4, uint32_t R,
                          uint32_t* __restrict__ oth3, unsigned long long* __restrict__ oth4, uint32_t block,
@@ -823,7 +1042,7 @@ __device__ void inc_fill(const uint32_t* __restrict__ e3, uint64_t n3, uint32_t*
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         idx3[at[j]] = uint32_t(i);
-        if (oth3) oth3[at[j]] = others3(m, j);
+        oth3[at[j]] = others3(m, j);
       }
     } else {
       const uint64_t q = i - n3;
@@ -835,7 +1054,7 @@ __device__ void inc_fill(const uint32_t* __restrict__ e3, uint64_t n3, uint32_t*
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         idx4[at[j]] = uint32_t(q);
-        if (oth4) oth4[at[j]] = others4(m, j);
+        oth4[at[j]] = others4(m, j);
       }
     }
   }
@@ -843,13 +1062,6 @@ __device__ void inc_fill(const uint32_t* __restrict__ e3, uint64_t n3, uint32_t*
 
 // (the counts of 3- and 4-node hyperedges are totals[2] and totals[3];
 // nothing is written when the input is invalid, totals[kTileN] != 0)
-__global__ void k_inc_fill(const uint32_t* __restrict__ e3, uint32_t* cur3, uint32_t* idx3,
-                           const uint32_t* __restrict__ e4, uint32_t* cur4, uint32_t* idx4, uint32_t R,
-                           const unsigned long long* __restrict__ totals) {
-  if (totals[kTileN]) return;
-  inc_fill(e3, totals[2], cur3, idx3, e4, totals[3], cur4, idx4, R, nullptr, nullptr, blockIdx.x, gridDim.x);
-}
-
 // Pairwise rows from the bit rows (workgroups [0, row_blocks)) and the
 // incidence lists (the rest) in one launch.
 __global__ void k_rows_and_incidence(const uint32_t* __restrict__ bits, uint32_t n, uint32_t W,
@@ -866,21 +1078,52 @@ __global__ void k_rows_and_incidence(const uint32_t* __restrict__ bits, uint32_t
              gridDim.x - row_blocks);
 }
 
-__global__ void k_pair_keys(const uint32_t* __restrict__ e2, uint64_t n, int bits_per_node,
-                            unsigned long long* keys, uint32_t* vals) {
+// Rows without bit rows, by stable radix sorts: every pair in both directions
+// under (node, other node) with its position in e2, every 3- or 4-node
+// hyperedge's position under each of its members.  (Counting each node's
+// entries and taking places by atomics, in up to 16 copies of each counter,
+// took 1.11 ms for the lists and 1.1 ms for the counts with 808,000 and 496,000
+// of them on 50,000 nodes; the sorts take 0.15.)
+template <typename K>
+__global__ void k_pair_keys(const uint32_t* __restrict__ e2, uint64_t n, int bits_per_node, K* keys, uint32_t* vals) {
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x) {
     const uint32_t a = e2[2 * i], b = e2[2 * i + 1];
-    keys[2 * i] = ((unsigned long long)a << bits_per_node) | b;
-    keys[2 * i + 1] = ((unsigned long long)b << bits_per_node) | a;
+    keys[2 * i] = (K(a) << bits_per_node) | b;
+    keys[2 * i + 1] = (K(b) << bits_per_node) | a;
     vals[2 * i] = uint32_t(i);
     vals[2 * i + 1] = uint32_t(i);
   }
 }
 
-__global__ void k_pair_adj(const unsigned long long* __restrict__ keys, uint64_t n, unsigned long long low_mask,
-                           uint32_t* adj) {
+template <typename K>
+__global__ void k_pair_adj(const K* __restrict__ keys, uint64_t n, K low_mask, uint32_t* adj) {
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
     adj[i] = uint32_t(keys[i] & low_mask);
+}
+
+template <uint32_t S>
+__global__ void k_member_keys(const uint32_t* __restrict__ e, uint64_t n, uint32_t* __restrict__ keys,
+                              uint32_t* __restrict__ vals) {
+  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < S * n; i += uint64_t(gridDim.x) * blockDim.x) {
+    keys[i] = e[i];
+    vals[i] = uint32_t(i / S);
+  }
+}
+
+// off[v] = the first of the n sorted keys of node v (its bits from `shift`) or
+// above, v = 0..n_nodes
+template <typename K>
+__global__ void k_row_starts(const K* __restrict__ keys, uint32_t n, int shift, uint32_t n_nodes,
+                             uint32_t* __restrict__ off) {
+  for (uint64_t v = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; v <= n_nodes; v += uint64_t(gridDim.x) * blockDim.x) {
+    uint32_t l = 0, h = n;
+    while (l < h) {
+      const uint32_t m = l + ((h - l) >> 1);
+      if (uint64_t(keys[m] >> shift) < v) l = m + 1;
+      else h = m;
+    }
+    off[v] = l;
+  }
 }
 
 unsigned grid_for(uint64_t n, unsigned block = 256) {
@@ -954,6 +1197,55 @@ int node_bits(uint32_t n_nodes) {
   int b = 1;
   while (b < 32 && (1ull << b) < n_nodes) ++b;
   return b;
+}
+
+// Pairwise rows of a graph without bit rows (see k_pair_keys).
+template <typename K>
+int sorted_pair_rows(hm_graph* H, Temps& tmp, hipStream_t st) {
+  const uint64_t n2 = H->n_by_size[2], m = 2 * n2;
+  const int B = node_bits(H->n_nodes);
+  K *keys, *keys_tmp;
+  uint32_t *eid, *eid_tmp;
+  HM_TRY(tmp.get(&keys, m));
+  HM_TRY(tmp.get(&keys_tmp, m));
+  HM_TRY(tmp.get(&eid, m));
+  HM_TRY(tmp.get(&eid_tmp, m));
+  if (m) {
+    k_pair_keys<K><<<grid_for(n2), 256, 0, st>>>(H->e2, n2, B, keys, eid);
+    HM_HIP(hipGetLastError());
+    HM_TRY(radix_sort_pairs(keys, eid, keys_tmp, eid_tmp, m, 2 * B, st));
+    k_pair_adj<K><<<grid_for(m), 256, 0, st>>>(keys, m, K((1ull << B) - 1), H->g2_adj);
+  }
+  k_row_starts<K><<<grid_for(uint64_t(H->n_nodes) + 1), 256, 0, st>>>(keys, uint32_t(m), B, H->n_nodes, H->g2_off);
+  HM_HIP(hipGetLastError());
+  // (the sort leaves the positions in either buffer; the graph keeps that one)
+  if (m) {
+    tmp.ptrs.erase(std::find(tmp.ptrs.begin(), tmp.ptrs.end(), static_cast<void*>(eid)));
+    H->g2_eid = eid;
+  }
+  return HM_OK;
+}
+
+// Incidence lists idx, by node from off, of the n hyperedges e of S nodes.
+template <uint32_t S>
+int sorted_incidence(const hm_graph* H, const uint32_t* e, uint64_t n, uint32_t* off, uint32_t* idx, Temps& tmp,
+                     hipStream_t st) {
+  const uint64_t m = S * n;
+  const int B = node_bits(H->n_nodes);
+  uint32_t *keys, *keys_tmp, *spare, *vals = idx;
+  HM_TRY(tmp.get(&keys, m));
+  HM_TRY(tmp.get(&keys_tmp, m));
+  HM_TRY(tmp.get(&spare, m));
+  // (an odd number of passes ends in the second buffer)
+  if (radix_passes(B) & 1) std::swap(vals, spare);
+  if (m) {
+    k_member_keys<S><<<grid_for(m), 256, 0, st>>>(e, n, keys, vals);
+    HM_HIP(hipGetLastError());
+    HM_TRY(radix_sort_pairs(keys, vals, keys_tmp, spare, m, B, st));
+  }
+  k_row_starts<uint32_t><<<grid_for(uint64_t(H->n_nodes) + 1), 256, 0, st>>>(keys, uint32_t(m), 0, H->n_nodes, off);
+  HM_HIP(hipGetLastError());
+  return HM_OK;
 }
 
 // Copies of each node's degree counters (see GatherOut): a power of two up to
@@ -1076,11 +1368,12 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
   const bool keep_bits = H->n_nodes <= bitset_max_nodes();
   const bool one_pass = keep_bits && E <= one_pass_max_edges();
   const bool self_offsets = one_pass && n_tiles <= kSelfOffsetTiles;
+  // (degrees are counted for the fills beside bit rows only)
   const uint32_t R = degree_copies(N);
-  const uint64_t NR = N * R;
+  const uint64_t NR = keep_bits ? N * R : 0;
   // the degree scans ride on the gather's launch when its workgroups can
   // hold a run each (else a launch of their own after it)
-  const bool gather_scan = E > 0 && NR <= kGatherScanMax;
+  const bool gather_scan = keep_bits && E > 0 && NR <= kGatherScanMax;
 
   unsigned long long* dev_totals = nullptr;
   uint32_t *sm = nullptr, *size = nullptr, *tile_cnt = nullptr;
@@ -1111,9 +1404,11 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
   // degree counters (counted by k_first_tiles, so staged and filled with the
   // first temporaries in either kind of build)
   uint32_t *deg2 = nullptr, *deg3 = nullptr, *deg4 = nullptr, *cur3 = nullptr, *cur4 = nullptr;
-  tmp.stage(&deg2, NR);
-  tmp.stage(&deg3, NR);
-  tmp.stage(&deg4, NR);
+  if (keep_bits) {
+    tmp.stage(&deg2, NR);
+    tmp.stage(&deg3, NR);
+    tmp.stage(&deg4, NR);
+  }
   tmp.stage(&dev_totals, kTileN + 1);
   tmp.stage(&sm, n_members);
   tmp.stage(&size, E);
@@ -1157,8 +1452,10 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
       own.add(&H->i3_oth, 3 * n3);
       own.add(&H->i4_oth, 4 * n4);
     }
-    tmp.stage(&cur3, NR + 1);
-    tmp.stage(&cur4, NR + 1);
+    if (keep_bits) {
+      tmp.stage(&cur3, NR + 1);
+      tmp.stage(&cur4, NR + 1);
+    }
     own.add(&H->g2_off, N + 1);
     own.add(&H->g2_adj, 2 * n2);
     own.add(&H->i3_off, N + 1);
@@ -1187,10 +1484,12 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
   FillList fl;
   if (one_pass) HM_TRY(allocate(E, E, E, E, n_members, fl));
   if (!fast_dedup) fl.add(slots, cap, kEmpty64, 1);
-  fl.add(deg2, NR, 0, 0);
-  fl.add(deg3, NR, 0, 0);
-  fl.add(deg4, NR, 0, 0);
-  if (!E) fl.launch(st);
+  if (keep_bits) {
+    fl.add(deg2, NR, 0, 0);
+    fl.add(deg3, NR, 0, 0);
+    fl.add(deg4, NR, 0, 0);
+  }
+  if ((!E || !one_pass) && fl.r.n) fl.launch(st);
   if (E) {
     // validate and sort; collapse repeated hyperedges onto first occurrences
     unsigned long long most = E;
@@ -1202,8 +1501,13 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
       dd.tag_mask = tag_bits >= 32 ? 0xFFFFFFFFull : (1ull << tag_bits) - 1;
       dd.slot_of = slot_of;
     }
-    k_prepare<<<grid_for(most), 256, 0, st>>>(members, offsets, E, n_members, H->n_nodes, sm, size, hash, ecode,
-                                              fl.r, dd);
+    if (one_pass) {
+      k_prepare<<<grid_for(most), 256, 0, st>>>(members, offsets, E, n_members, H->n_nodes, sm, size, hash, ecode,
+                                                fl.r, dd);
+    } else {
+      k_prepare_tiles<<<unsigned(n_tiles), kPrepTile, 0, st>>>(members, offsets, E, n_members, H->n_nodes, sm, size,
+                                                               hash, ecode, dd);
+    }
     if (!fast_dedup)
       k_dedup_insert<<<grid_for(E), 256, 0, st>>>(sm, offsets, size, hash, E, slots, cap - 1, slot_of);
     k_first_tiles<<<unsigned(n_tiles), kTile, 0, st>>>(size, E, slots, slot_of, ecode, first, tile_cnt, fast_dedup,
@@ -1276,15 +1580,23 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
     g.dev_totals = dev_totals;
     g.dedup_clear = fast_dedup ? slots : nullptr;
     g.slot_of = slot_of;
-    k_gather_tiles<<<unsigned(n_tiles) + (gather_scan ? 3u : 0u), kTile, 0, st>>>(sm, offsets, size, E, first,
-                                                                                  tile_cnt, g);
+    const unsigned blocks = unsigned(n_tiles) + (gather_scan ? 3u : 0u);
+    if (one_pass)
+      k_gather_tiles<false><<<blocks, kTile, 0, st>>>(sm, offsets, size, E, first, tile_cnt, g);
+    else
+      k_gather_tiles<true><<<blocks, kTile, 0, st>>>(sm, offsets, size, E, first, tile_cnt, g);
   }
   HM_HIP(hipGetLastError());
 
   // row offsets: pairwise rows, incidence lists of 3- and 4-node hyperedges;
   // fill cursors per (node, copy) (with gather_scan, done by the gather's
   // last three workgroups)
-  if (!gather_scan && NR <= 64 * 1024) {
+  if (!keep_bits) {
+    if (2 * node_bits(H->n_nodes) <= 32) HM_TRY(sorted_pair_rows<uint32_t>(H, tmp, st));
+    else HM_TRY(sorted_pair_rows<unsigned long long>(H, tmp, st));
+    HM_TRY(sorted_incidence<3>(H, H->e3, H->n_by_size[3], H->i3_off, H->i3_idx, tmp, st));
+    HM_TRY(sorted_incidence<4>(H, H->e4, H->n_by_size[4], H->i4_off, H->i4_idx, tmp, st));
+  } else if (!gather_scan && NR <= 64 * 1024) {
     k_scan_degrees<<<3, 1024, 0, st>>>(deg2, H->g2_off, deg3, H->i3_off, cur3, deg4, H->i4_off, cur4, uint32_t(N), R);
     HM_HIP(hipGetLastError());
   } else if (!gather_scan) {
@@ -1306,30 +1618,6 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
                                                                   H->e4, cur4, H->i4_idx, R, H->i3_oth, H->i4_oth,
                                                                   dev_totals);
     HM_HIP(hipGetLastError());
-  } else if (b34) {
-    k_inc_fill<<<grid_for(b34), 256, 0, st>>>(H->e3, cur3, H->i3_idx, H->e4, cur4, H->i4_idx, R, dev_totals);
-    HM_HIP(hipGetLastError());
-  }
-  if (!keep_bits && b2) {
-    // ascending rows from a radix sort of directed pairs, with the position
-    // in e2 of each entry's pair
-    const uint64_t n2 = b2;
-    const int B = node_bits(H->n_nodes);
-    const uint64_t m = 2 * n2;
-    unsigned long long *keys, *keys_tmp;
-    uint32_t *eid, *eid_tmp;
-    HM_TRY(tmp.get(&keys, m));
-    HM_TRY(tmp.get(&keys_tmp, m));
-    HM_TRY(tmp.get(&eid, m));
-    HM_TRY(tmp.get(&eid_tmp, m));
-    k_pair_keys<<<grid_for(n2), 256, 0, st>>>(H->e2, n2, B, keys, eid);
-    HM_HIP(hipGetLastError());
-    HM_TRY(radix_sort_pairs(keys, eid, keys_tmp, eid_tmp, m, 2 * B, st));
-    k_pair_adj<<<grid_for(m), 256, 0, st>>>(keys, m, (1ull << B) - 1, H->g2_adj);
-    HM_HIP(hipGetLastError());
-    // (the sort leaves the positions in either buffer; the graph keeps that one)
-    tmp.ptrs.erase(std::find(tmp.ptrs.begin(), tmp.ptrs.end(), static_cast<void*>(eid)));
-    H->g2_eid = eid;
   }
   if (one_pass) HM_TRY(read_report());
   // the gather leaves the duplicate search's table all-ones again (it ran:

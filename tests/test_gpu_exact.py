@@ -2,6 +2,8 @@
 import json
 import os
 
+import functools
+
 import numpy as np
 import pytest
 
@@ -725,3 +727,70 @@ def test_triples_match_bit_rows(hm, n, run, pairs, hub_min_degree):
         hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
         hm.hm_set_option(hm.HM_OPT_HUB_MIN_DEGREE, keep)
     assert np.array_equal(got[8192], got[0])
+
+
+@functools.lru_cache(maxsize=1)
+def _large_input():
+    """560,000 hyperedges of 1 to 100 nodes and two of 9,000 (one
+    ascending, one not), some of them repeated in other orders; and what a set
+    of sorted members keeps of them."""
+    n, m = 20_000, 560_000
+    rng = np.random.default_rng(5)
+    size = np.minimum(1 + rng.geometric(0.5, m), 8)
+    some = rng.choice(m, 4000, replace=False)
+    size[some] = rng.integers(1, 101, some.size)
+    size[[1234, 400_000]] = 9000
+    # small hyperedges among 250 nodes (many alike), larger ones among as many
+    # of 80 groups
+    rows = {s: np.argsort(rng.random((k, 250)), axis=1)[:, :s] if s > 8 else rng.integers(0, 250 // s, (k, s)) * s + rng.permutation(s)
+            for s, k in zip(*np.unique(size[size <= 100], return_counts=True))}
+    edges = [None] * m
+    for s, r in rows.items():
+        r = r + (250 * rng.integers(0, 80, len(r))[:, None] if s > 3 else 0)
+        for i, e in zip(np.nonzero(size == s)[0], r):
+            edges[i] = e
+    for i in (1234, 400_000):
+        e = rng.permutation(n)[:9000]
+        edges[i] = np.sort(e) if i == 1234 else e
+    edges[300_000] = edges[1234][::-1]
+    edges[500_000] = np.roll(edges[400_000], 77)
+    for i in some[:500]:
+        edges[(i * 7919) % m] = edges[i][::-1]
+    offsets = np.r_[0, np.cumsum([len(e) for e in edges])].astype(np.uint64)
+    members = np.concatenate(edges).astype(np.uint32)
+    first, strata, singles, dups = set(), {2: [], 3: [], 4: []}, 0, 0
+    for e in edges:
+        if len(e) == 1:
+            singles += 1
+            continue
+        t = tuple(sorted(e.tolist()))
+        if t in first:
+            dups += 1
+            continue
+        first.add(t)
+        if len(t) <= 4:
+            strata[len(t)].append(t)
+    want = (singles, dups, len(first), sum(map(len, first)))
+    return n, members, offsets, want, {j: np.array(x, dtype=np.uint32) for j, x in strata.items()}
+
+
+@pytest.mark.parametrize("tag_bits", [32, 0, -1])
+def test_large_build(hm, tag_bits):
+    """The build of a large input without bit rows (tiles of hyperedges of every
+    size class, and beyond the LDS staging); also with hashes cut so that
+    different hyperedges meet, and by the exact search.  An invalid hyperedge
+    far in is still named."""
+    n, members, offsets, want, strata = _large_input()
+    hm.hm_set_option(hm.HM_OPT_DEDUP_TAG_BITS, tag_bits)
+    try:
+        with hm.hm_graph_create(members, offsets, n) as g:
+            st = g.stats()
+            assert (st["singletons"], st["duplicates"], st["n_unique"], st["n_unique_members"]) == want
+            for j in (2, 3, 4):
+                assert np.array_equal(g.export(j), strata[j]), j
+        members = members.copy()
+        members[int(offsets[450_000])] = n
+        with pytest.raises(hm.HMError, match="node id.*450000"):
+            hm.hm_graph_create(members, offsets, n)
+    finally:
+        hm.hm_set_option(hm.HM_OPT_DEDUP_TAG_BITS, 32)
