@@ -34,13 +34,15 @@
 // concatenated list, finding an item's owner in a window of the scan held in
 // LDS.
 //
-// What bounds the item kernels is the latency of their dependent loads (a
-// record, a node, two or three memberships), so a thread takes several items
-// at once.  808,000 3-node hyperedges on 50,000 nodes (heavy-tailed; 2.4
-// million entries, runs of up to 7,490): 1.17 ms (1) and 1.26 ms (2), 0.14 ms
-// each for the plans.  A wavefront per hyperedge and then per entry, which
-// looked at every set from each of its 3-node hyperedges, took 2.06 and 6.33
-// ms, and needed an index of the 4-node hyperedges (0.55 ms).
+// What bounds the item kernels is the latency of their dependent loads (a node,
+// two or three memberships): (1) runs two items of a thread at once with eight
+// wavefronts per SIMD, (2) one item with six (it then needs no scratch; two
+// items with five took 0.96 ms).  808,000 3-node hyperedges on 50,000 nodes
+// (heavy-tailed; 2.4 million entries, runs of up to 7,490): 163 million items
+// in 0.50 ms (1) and 45 million in 0.88 (2), 0.14 ms each for the plans.  A
+// wavefront per hyperedge and then per entry, which looked at every set from
+// each of its 3-node hyperedges, took 2.06 and 6.33 ms, and needed an index of
+// the 4-node hyperedges (0.55 ms).
 #include <algorithm>
 
 #include "hm_sparse.h"
@@ -51,84 +53,120 @@ namespace {
 // Owners whose records are planned at once (bounds the planning memory, 64
 // bytes each).
 constexpr uint64_t kPlanChunk = 1ull << 25;
-constexpr uint32_t kUnit = 1024;      // items a workgroup takes at a time
+constexpr uint32_t kTriUnit = 16384, kRunUnit = 2048;   // items a workgroup takes at a time
 constexpr uint32_t kWindow = kThreads;   // owners of a unit looked at together
 // units after which a workgroup's 32-bit counters are emptied
-constexpr uint32_t kUnitsPerFlush = 1u << 20;
+constexpr uint32_t kUnitsPerFlush = 1u << 16;
 
 unsigned grid_cap(uint64_t items, uint64_t per_block, unsigned cap) {
   const uint64_t g = (items + per_block - 1) / per_block;
   return unsigned(std::max<uint64_t>(1, std::min<uint64_t>(g, cap)));
 }
 
+// The last p in [l, h) with pre[p] <= cur, given pre[l] <= cur < pre[h]; the
+// wavefront's lanes take 64 probes a step and all return it.
+__device__ __forceinline__ uint64_t owner_of(const unsigned long long* __restrict__ pre, uint64_t l, uint64_t h,
+                                             unsigned long long cur) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  while (h - l > 1) {
+    const uint64_t step = (h - l + kWave - 1) / kWave;
+    const uint64_t q = l + step * lane;
+    const bool le = q < h && pre[q] <= cur;
+    l += step * (uint32_t(__popcll(__ballot(le))) - 1u);
+    h = min(h, l + step);
+  }
+  return l;
+}
+
 // Hands out item k of every owner of [0, m), pre being the exclusive scan of
 // the owners' item counts (pre[m] the total), over the whole grid; every
-// thread of the workgroup calls this.  items(p, k, live) takes B of them at
-// once (p[b], k[b] meaningful when live[b]), so that the loads of a thread's
-// items go out together.  flush() is called by every thread after
-// kUnitsPerFlush units and at the end.  s_pre: LDS of kWindow + 1 words.
+// thread of the workgroup calls this.  stage(slot, p) puts what owner p needs
+// into slot of LDS, and items(slot, k, live) takes B items at once (slot[b],
+// k[b] meaningful when live[b]), so that the loads of a thread's items go out
+// together.  flush() is called by every thread after kUnitsPerFlush units and
+// at the end.  s_pre: LDS of kWindow + 1 words.
 //
-// A unit is kUnit items, fewer when there are not enough for the grid (owners
-// without items make a window of kWindow owners hold few: on 210,000 items of
-// 1.1 million owners k_run_items took 372 us with units of 1,024, 131 with
-// these).
-template <uint32_t B, typename Items, typename Flush>
-__device__ __forceinline__ void flat_items(const unsigned long long* __restrict__ pre, uint64_t m, uint32_t* s_pre,
-                                           Items items, Flush flush) {
+// A workgroup claims units of kUnit items, the first one by its number, fewer
+// items when there are not enough for the grid.  (In shares fixed beforehand
+// k_tri_items took 0.75 ms and k_run_items 1.15 where claims took 0.57 and
+// 0.87.)  Units whose owners fit in a few windows of kWindow find an item's
+// owner in LDS; where most owners have no items, every thread searches the
+// scan itself and stages its own owner (220,000 items of 1.1 million owners in
+// k_run_items: 372 us by windows in units of 1,024, 131 in small ones, 43 so).
+template <uint32_t B, uint32_t kUnit, typename Stage, typename Items, typename Flush>
+__device__ __forceinline__ void flat_items(const unsigned long long* __restrict__ pre, uint64_t m,
+                                           unsigned long long* __restrict__ next, uint32_t* s_pre,
+                                           Stage stage, Items items, Flush flush) {
   static_assert(kUnit % (kThreads * B) == 0, "whole batches");
-  __shared__ uint64_t s_owner;
-  const uint32_t lane = threadIdx.x & (kWave - 1);
+  static_assert(kWindow == uint32_t(kThreads), "an owner per thread");
+  __shared__ uint64_t s_first, s_last;
+  __shared__ unsigned long long s_unit;
+  const uint32_t tid = threadIdx.x;
   const unsigned long long total = pre[m];
   const uint32_t unit = uint32_t(min<unsigned long long>(kUnit, max<unsigned long long>(kWave, total / gridDim.x + 1)));
+  const unsigned long long n_units = (total + unit - 1) / unit;
   uint32_t done = 0;
-  for (unsigned long long u = blockIdx.x; u * unit < total; u += gridDim.x) {
+  for (unsigned long long u = blockIdx.x; u < n_units;) {
     unsigned long long cur = u * unit;
     const unsigned long long end = min(total, cur + unit);
     while (cur < end) {
-      if (threadIdx.x < uint32_t(kWave)) {
-        // the owner of item cur: the last p with pre[p] <= cur (64 probes a
-        // step; pre[l] <= cur < pre[h])
-        uint64_t l = 0, h = m;
-        while (h - l > 1) {
-          const uint64_t step = (h - l + kWave - 1) / kWave;
-          const uint64_t q = l + step * lane;
-          const bool le = q < h && pre[q] <= cur;
-          const uint32_t k = uint32_t(__popcll(__ballot(le))) - 1u;
-          l += step * k;
-          h = min(h, l + step);
-        }
-        if (lane == 0) s_owner = l;
+      if (tid < uint32_t(kWave)) {
+        const uint64_t p = owner_of(pre, 0, m, cur);
+        if (tid == 0) s_first = p;
+      } else if (tid < 2 * uint32_t(kWave)) {
+        const uint64_t p = owner_of(pre, 0, m, end - 1);
+        if (tid == uint32_t(kWave)) s_last = p;
       }
       __syncthreads();
-      const uint64_t p0 = s_owner;
-      const unsigned long long at0 = pre[p0];
-      for (uint32_t i = threadIdx.x; i <= kWindow; i += kThreads) {
-        const unsigned long long a = pre[min(p0 + i, m)];
-        s_pre[i] = a <= cur ? 0u : uint32_t(min<unsigned long long>(a - cur, kUnit));
+      const uint64_t p0 = s_first, p1 = s_last;
+      const bool sparse = p1 - p0 >= 4 * kWindow;
+      uint32_t n = uint32_t(end - cur), skipped = 0;
+      if (!sparse) {
+        const uint64_t p = p0 + tid;
+        const unsigned long long a = pre[min(p, m)], b = pre[min(p + 1, m)];
+        skipped = uint32_t(cur - pre[p0]);   // items of the first owner before cur
+        s_pre[tid] = a <= cur ? 0u : uint32_t(min<unsigned long long>(a - cur, kUnit));
+        if (tid == kThreads - 1) s_pre[kWindow] = uint32_t(min<unsigned long long>(b - cur, kUnit));
+        if (a < b && a < end) stage(tid, p);
+        __syncthreads();
+        n = min(n, s_pre[kWindow]);
       }
-      __syncthreads();
-      const uint32_t n = uint32_t(min<unsigned long long>(end - cur, s_pre[kWindow]));
-      const uint32_t skipped = uint32_t(cur - at0);   // items of the first owner before cur
-      for (uint32_t i0 = 0; i0 < n; i0 += kThreads * B) {
+      for (uint32_t i0 = 0; i0 < n; i0 += sparse ? uint32_t(kThreads) : kThreads * B) {
         uint32_t j[B], k[B];
-        uint64_t p[B];
         bool live[B];
 #pragma unroll
-        for (uint32_t b = 0; b < B; ++b) j[b] = 0;
-#pragma unroll
-        for (uint32_t s = kWindow / 2; s; s >>= 1) {
-#pragma unroll
-          for (uint32_t b = 0; b < B; ++b)
-            if (s_pre[j[b] + s] <= i0 + b * kThreads + threadIdx.x) j[b] += s;
-        }
-#pragma unroll
         for (uint32_t b = 0; b < B; ++b) {
-          const uint32_t i = i0 + b * kThreads + threadIdx.x;
-          live[b] = i < n;
-          p[b] = p0 + j[b];
-          k[b] = i - s_pre[j[b]] + (j[b] == 0 ? skipped : 0u);
+          j[b] = k[b] = 0;
+          live[b] = false;
         }
-        items(p, k, live);
+        if (sparse) {
+          live[0] = i0 + tid < n;
+          if (live[0]) {
+            uint64_t l = p0, h = p1 + 1;
+            while (h - l > 1) {
+              const uint64_t mid = (l + h) >> 1;
+              if (pre[mid] <= cur + i0 + tid) l = mid;
+              else h = mid;
+            }
+            j[0] = tid;
+            k[0] = uint32_t(cur + i0 + tid - pre[l]);
+            stage(tid, l);
+          }
+        } else {
+#pragma unroll
+          for (uint32_t s = kWindow / 2; s; s >>= 1) {
+#pragma unroll
+            for (uint32_t b = 0; b < B; ++b)
+              if (s_pre[j[b] + s] <= i0 + b * kThreads + tid) j[b] += s;
+          }
+#pragma unroll
+          for (uint32_t b = 0; b < B; ++b) {
+            const uint32_t i = i0 + b * kThreads + tid;
+            live[b] = i < n;
+            k[b] = i - s_pre[j[b]] + (j[b] == 0 ? skipped : 0u);
+          }
+        }
+        items(j, k, live);
       }
       __syncthreads();
       cur += n;
@@ -137,6 +175,10 @@ __device__ __forceinline__ void flat_items(const unsigned long long* __restrict_
       done = 0;
       flush();
     }
+    if (n_units <= gridDim.x) break;
+    if (tid == 0) s_unit = gridDim.x + atomicAdd(next, 1ull);
+    __syncthreads();
+    u = s_unit;
   }
   flush();
 }
@@ -178,13 +220,13 @@ struct TriRec {
   uint32_t x, y;
   int32_t hx, hy;    // dense rows of x and y, or -1
   uint32_t flags;    // bits 0..2: e's pairwise pattern; bit 3: dense rows combined
-  uint32_t pad[2];
 };
 
 constexpr uint32_t kTriCopies = 16;   // copies of the 64 counters (lanes of a wavefront add to like ones)
 
 __global__ void __launch_bounds__(kThreads) k_tri_plan(View v, PairLinks pl, uint64_t first, uint64_t m,
                                                        TriRec* __restrict__ rec, unsigned long long* __restrict__ cnt,
+                                                       unsigned long long* __restrict__ next,
                                                        const uint8_t* __restrict__ lut_g,
                                                        unsigned long long* __restrict__ hist) {
   __shared__ uint8_t lut[2048];
@@ -196,6 +238,7 @@ __global__ void __launch_bounds__(kThreads) k_tri_plan(View v, PairLinks pl, uin
   for (uint32_t i = threadIdx.x; i < 64 * kTriCopies; i += kThreads) (&bins[0][0])[i] = 0;
   __syncthreads();
   const uint32_t copy = threadIdx.x & (kTriCopies - 1);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next = 0;
   for (uint64_t i = uint64_t(blockIdx.x) * kThreads + threadIdx.x; i <= m; i += uint64_t(gridDim.x) * kThreads) {
     unsigned long long items = 0;
     if (i < m) {
@@ -233,7 +276,6 @@ __global__ void __launch_bounds__(kThreads) k_tri_plan(View v, PairLinks pl, uin
         t.hx = hx;
         t.hy = hy;
         t.flags = base | (uint32_t(dense) << 3);
-        t.pad[0] = t.pad[1] = 0;
         rec[i] = t;
       }
     }
@@ -251,9 +293,10 @@ __global__ void __launch_bounds__(kThreads) k_tri_plan(View v, PairLinks pl, uin
   flush(h_sub, hc + kSub, 256);
 }
 
-__global__ void __launch_bounds__(kThreads) k_tri_items(View v, PairLinks pl, uint64_t m,
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8,8))) k_tri_items(View v, PairLinks pl, uint64_t m,
                                                         const TriRec* __restrict__ rec,
                                                         const unsigned long long* __restrict__ pre,
+                                                        unsigned long long* __restrict__ next,
                                                         const uint8_t* __restrict__ lut_g,
                                                         unsigned long long* __restrict__ hist) {
   constexpr uint32_t kCopies = 32;
@@ -261,23 +304,25 @@ __global__ void __launch_bounds__(kThreads) k_tri_items(View v, PairLinks pl, ui
   __shared__ unsigned long long h_main[256], h_sub[256];
   __shared__ uint32_t bins[8][kCopies];
   __shared__ uint32_t s_pre[kWindow + 1];
+  __shared__ TriRec s_rec[kWindow];
   load_lut(lut, lut_g, 2048);
   h_main[threadIdx.x] = 0;
   h_sub[threadIdx.x] = 0;
   bins[threadIdx.x / kCopies][threadIdx.x % kCopies] = 0;
   __syncthreads();
   const uint32_t copy = threadIdx.x % kCopies;
-  flat_items<4>(
-      pre, m, s_pre,
-      [&](const uint64_t* p, const uint32_t* k, const bool* live) {
-        TriRec t[4];
-        uint32_t z[4], hits[4];
-        Probe64 q[4];
+  flat_items<2, kTriUnit>(
+      pre, m, next, s_pre,
+      [&](uint32_t slot, uint64_t p) { s_rec[slot] = rec[p]; },
+      [&](const uint32_t (&slot)[2], const uint32_t (&k)[2], const bool (&live)[2]) {
+        TriRec t[2];
+        uint32_t z[2], hits[2];
+        Probe64 q[2];
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-          if (live[b]) t[b] = rec[p[b]];
+        for (int b = 0; b < 2; ++b)
+          if (live[b]) t[b] = s_rec[slot[b]];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < 2; ++b) {
           z[b] = 0;
           if (!live[b]) continue;
           if (t[b].flags & 8u)
@@ -288,7 +333,7 @@ __global__ void __launch_bounds__(kThreads) k_tri_items(View v, PairLinks pl, ui
         }
         // (the first slot of a hash table and the word of a dense row alike)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < 2; ++b) {
           hits[b] = 0;
           if (!live[b]) continue;
           if (t[b].flags & 8u) hits[b] = uint32_t(__popc(z[b]));
@@ -296,16 +341,16 @@ __global__ void __launch_bounds__(kThreads) k_tri_items(View v, PairLinks pl, ui
           else q[b] = probe2_start(v.hs2, t[b].x, z[b]);
         }
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < 2; ++b)
           if (live[b] && !(t[b].flags & 8u) && t[b].hx < 0) hits[b] = uint32_t(probe64_end(v.hs2, q[b]));
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < 2; ++b) {
           if (!hits[b] || (t[b].flags & 8u)) continue;
           if (t[b].hy >= 0) hits[b] = hub_adj(pl, t[b].hy, z[b]);
           else q[b] = probe2_start(v.hs2, t[b].y, z[b]);
         }
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < 2; ++b) {
           if (!hits[b]) continue;
           if (!(t[b].flags & 8u) && t[b].hy < 0) hits[b] = uint32_t(probe64_end(v.hs2, q[b]));
           if (hits[b]) atomicAdd(&bins[t[b].flags & 7u][copy], hits[b]);
@@ -411,14 +456,14 @@ __global__ void __launch_bounds__(kThreads) k_pl_class_prefix(const uint8_t* __r
   }
 }
 
-// What entry t of the run of {x, y} looks at.  Bit 0 of flags set: the later
+// What entry t (position p of the index) of the run of {x, y} looks at.  Bit 0 of flags set: the later
 // entries of the run, each tested against t's pairwise row (n0 entries from
 // a0) and the runs of {x, t} (n1 from a1) and {y, t} (n2 from a2).  Otherwise
 // the entries above t of those three lists (n0, n1 and n2 of them), searched
 // for in the run of {x, y}, which ends at end.  flags: bits 1, 2 how t is
 // paired with x and y; bit 3: x ~ y; from bit 4: t's dense row plus one, or 0.
 struct RunRec {
-  uint32_t t, flags, a0, n0, a1, n1, a2, n2, end, pad[3];
+  uint32_t x, y, t, flags, a0, n0, a1, n1, a2, n2, p, end;
 };
 // t's related nodes in short lists are searched for there (the lists are
 // shared by an entry's items and stay in the L1), in longer ones by a probe of
@@ -428,6 +473,7 @@ constexpr uint32_t kSearchMax = 256;
 __global__ void __launch_bounds__(kThreads) k_run_plan(View v, PairLinks pl, const uint32_t* __restrict__ pre,
                                                        uint64_t first, uint64_t m, RunRec* __restrict__ rec,
                                                        unsigned long long* __restrict__ cnt,
+                                                       unsigned long long* __restrict__ next,
                                                        const uint8_t* __restrict__ lut_g,
                                                        unsigned long long* __restrict__ hist) {
   __shared__ uint8_t lut[2048];
@@ -438,6 +484,7 @@ __global__ void __launch_bounds__(kThreads) k_run_plan(View v, PairLinks pl, con
   h_sub[threadIdx.x] = 0;
   if (threadIdx.x < 32) closed[threadIdx.x] = 0;
   __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next = 0;
   for (uint64_t i = uint64_t(blockIdx.x) * kThreads + threadIdx.x; i <= m; i += uint64_t(gridDim.x) * kThreads) {
     unsigned long long items = 0;
     const uint64_t p = first + i;
@@ -468,6 +515,8 @@ __global__ void __launch_bounds__(kThreads) k_run_plan(View v, PairLinks pl, con
       const uint32_t end = uint32_t(lo) + L, later = end - uint32_t(p) - 1;
       if (dt || len_xt > 1 || len_yt > 1) {   // (else nothing is related to t)
         RunRec r;
+        r.x = x;
+        r.y = y;
         r.t = t;
         r.flags = 1u | (uint32_t(pl.adj[p]) << 1) | (xy << 3) | (uint32_t(hub_of(pl, t) + 1) << 4);
         r.a0 = row;
@@ -477,7 +526,7 @@ __global__ void __launch_bounds__(kThreads) k_run_plan(View v, PairLinks pl, con
         r.a2 = uint32_t(lo_yt);
         r.n2 = len_yt;
         r.end = end;
-        r.pad[0] = r.pad[1] = r.pad[2] = 0;
+        r.p = uint32_t(p);
         items = later;
         if (later > uint64_t(dt) + len_xt + len_yt) {
           r.flags &= ~1u;
@@ -509,82 +558,80 @@ __global__ void __launch_bounds__(kThreads) k_run_plan(View v, PairLinks pl, con
 // of z, t ~ z, {x, t, z}, {y, t, z}, whether {x, y, t} and {x, y, z} are the
 // two smallest 3-node hyperedges of the set), one set of counters per
 // wavefront, which become class counts at the end.
-__global__ void __launch_bounds__(kThreads) k_run_items(View v, PairLinks pl, uint64_t first, uint64_t m,
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6,6))) k_run_items(View v, PairLinks pl, uint64_t m,
                                                         const RunRec* __restrict__ rec,
                                                         const unsigned long long* __restrict__ pre,
+                                                        unsigned long long* __restrict__ next,
                                                         const uint8_t* __restrict__ lut_g,
                                                         unsigned long long* __restrict__ hist) {
   __shared__ uint8_t lut[2048];
   __shared__ unsigned long long h_main[256], h_sub[256];
-  __shared__ uint32_t bins[kWavesPerBlock][512];
+  __shared__ uint32_t bins[2][512];
   __shared__ uint32_t s_pre[kWindow + 1];
+  __shared__ RunRec s_rec[kWindow];
   load_lut(lut, lut_g, 2048);
   h_main[threadIdx.x] = 0;
   h_sub[threadIdx.x] = 0;
-  for (uint32_t i = threadIdx.x; i < kWavesPerBlock * 512; i += kThreads) (&bins[0][0])[i] = 0;
+  for (uint32_t i = threadIdx.x; i < 2 * 512; i += kThreads) (&bins[0][0])[i] = 0;
   __syncthreads();
-  uint32_t* mine = bins[threadIdx.x / kWave];
-  flat_items<2>(
-      pre, m, s_pre,
-      [&](const uint64_t* owner, const uint32_t* item, const bool* live) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          if (!live[b]) continue;
-          const RunRec r = rec[owner[b]];
-          const uint32_t k = item[b], p = uint32_t(first + owner[b]);
-          const unsigned long long key = pl.keys[p];
-          const uint32_t x = uint32_t(key >> 32), y = uint32_t(key), t = r.t;
-          const int rt = int(r.flags >> 4) - 1;
-          uint32_t z, cz, tz, xtz, ytz;
-          if (r.flags & 1u) {
-            z = pl.third[p + 1 + k];
-            cz = pl.adj[p + 1 + k];
-            Probe64 q2;
-            Probe128 qx, qy;
-            if (rt < 0 && r.n0 > kSearchMax) q2 = probe2_start(v.hs2, t, z);
-            if (r.n1 > kSearchMax) qx = probe3_start(v.hs3, x, t, z);
-            if (r.n2 > kSearchMax) qy = probe3_start(v.hs3, y, t, z);
+  uint32_t* mine = bins[(threadIdx.x / kWave) & 1];
+  flat_items<1, kRunUnit>(
+      pre, m, next, s_pre,
+      [&](uint32_t slot, uint64_t p) { s_rec[slot] = rec[p]; },
+      [&](const uint32_t (&slot)[1], const uint32_t (&item)[1], const bool (&live)[1]) {
+        if (!live[0]) return;
+        const RunRec& r = s_rec[slot[0]];
+        const uint32_t k = item[0], p = r.p, x = r.x, y = r.y, t = r.t;
+        const int rt = int(r.flags >> 4) - 1;
+        uint32_t z, cz, tz, xtz, ytz;
+        if (r.flags & 1u) {
+          z = pl.third[p + 1 + k];
+          cz = pl.adj[p + 1 + k];
+          Probe64 q2;
+          Probe128 qx, qy;
+          if (rt < 0 && r.n0 > kSearchMax) q2 = probe2_start(v.hs2, t, z);
+          if (r.n1 > kSearchMax) qx = probe3_start(v.hs3, x, t, z);
+          if (r.n2 > kSearchMax) qy = probe3_start(v.hs3, y, t, z);
+          tz = rt >= 0 ? hub_adj(pl, rt, z)
+                       : (r.n0 > kSearchMax ? uint32_t(probe64_end(v.hs2, q2)) : holds(v.g2_adj + r.a0, r.n0, z));
+          xtz = r.n1 > kSearchMax ? uint32_t(probe128_end(v.hs3, qx))
+                                  : (r.n1 > 1 ? holds(pl.third + r.a1, r.n1, z) : 0u);
+          ytz = r.n2 > kSearchMax ? uint32_t(probe128_end(v.hs3, qy))
+                                  : (r.n2 > 1 ? holds(pl.third + r.a2, r.n2, z) : 0u);
+          if (!(tz | xtz | ytz)) return;
+        } else {
+          // each related z once, from the first list that holds it
+          const int from = k < r.n0 ? 0 : (k < r.n0 + r.n1 ? 1 : 2);
+          z = from == 0 ? v.g2_adj[r.a0 + k] : pl.third[from == 1 ? r.a1 + (k - r.n0) : r.a2 + (k - r.n0 - r.n1)];
+          const uint64_t at = run_find(pl, p + 1, r.end - p - 1, z);
+          if (at == ~0ull) return;   // {x, y, z} is not a 3-node hyperedge
+          tz = 1;
+          if (from)
             tz = rt >= 0 ? hub_adj(pl, rt, z)
-                         : (r.n0 > kSearchMax ? uint32_t(probe64_end(v.hs2, q2)) : holds(v.g2_adj + r.a0, r.n0, z));
-            xtz = r.n1 > kSearchMax ? uint32_t(probe128_end(v.hs3, qx))
-                                    : (r.n1 > 1 ? holds(pl.third + r.a1, r.n1, z) : 0u);
-            ytz = r.n2 > kSearchMax ? uint32_t(probe128_end(v.hs3, qy))
-                                    : (r.n2 > 1 ? holds(pl.third + r.a2, r.n2, z) : 0u);
-            if (!(tz | xtz | ytz)) continue;
-          } else {
-            // each related z once, from the first list that holds it
-            const int from = k < r.n0 ? 0 : (k < r.n0 + r.n1 ? 1 : 2);
-            z = from == 0 ? v.g2_adj[r.a0 + k] : pl.third[from == 1 ? r.a1 + (k - r.n0) : r.a2 + (k - r.n0 - r.n1)];
-            const uint64_t at = run_find(pl, p + 1, r.end - p - 1, z);
-            if (at == ~0ull) continue;   // {x, y, z} is not a 3-node hyperedge
-            tz = 1;
-            if (from)
-              tz = rt >= 0 ? hub_adj(pl, rt, z)
-                           : (r.n0 > kSearchMax ? uint32_t(has2(v.hs2, t, z)) : holds(v.g2_adj + r.a0, r.n0, z));
-            if (from && tz) continue;
-            xtz = from == 1 ? 1u : 0u;
-            if (from != 1)
-              xtz = r.n1 > kSearchMax ? uint32_t(probe128_end(v.hs3, probe3_start(v.hs3, x, t, z)))
-                                      : holds(pl.third + r.a1, r.n1, z);
-            if (from == 2 && xtz) continue;
-            ytz = from == 2 ? 1u : 0u;
-            if (from != 2)
-              ytz = r.n2 > kSearchMax ? uint32_t(probe128_end(v.hs3, probe3_start(v.hs3, y, t, z)))
-                                      : holds(pl.third + r.a2, r.n2, z);
-            cz = pl.adj[at];
-          }
-          // the smaller of two 3-node hyperedges of a set leaves out the larger node
-          const uint32_t own = uint32_t((!xtz || y < t) && (!ytz || x < t));
-          const uint32_t xy = (r.flags >> 3) & 1u, ct = (r.flags >> 1) & 3u;
-          atomicAdd(&mine[xy | (ct << 1) | (cz << 3) | (tz << 5) | (xtz << 6) | (ytz << 7) | (own << 8)], 1u);
+                         : (r.n0 > kSearchMax ? uint32_t(has2(v.hs2, t, z)) : holds(v.g2_adj + r.a0, r.n0, z));
+          if (from && tz) return;
+          xtz = from == 1 ? 1u : 0u;
+          if (from != 1)
+            xtz = r.n1 > kSearchMax ? uint32_t(probe128_end(v.hs3, probe3_start(v.hs3, x, t, z)))
+                                    : holds(pl.third + r.a1, r.n1, z);
+          if (from == 2 && xtz) return;
+          ytz = from == 2 ? 1u : 0u;
+          if (from != 2)
+            ytz = r.n2 > kSearchMax ? uint32_t(probe128_end(v.hs3, probe3_start(v.hs3, y, t, z)))
+                                    : holds(pl.third + r.a2, r.n2, z);
+          cz = pl.adj[at];
         }
+        // the smaller of two 3-node hyperedges of a set leaves out the larger node
+        const uint32_t own = uint32_t((!xtz || y < t) && (!ytz || x < t));
+        const uint32_t xy = (r.flags >> 3) & 1u, ct = (r.flags >> 1) & 3u;
+        atomicAdd(&mine[xy | (ct << 1) | (cz << 3) | (tz << 5) | (xtz << 6) | (ytz << 7) | (own << 8)], 1u);
       },
       [&]() {
         __syncthreads();
         for (uint32_t b = threadIdx.x; b < 512; b += kThreads) {
           unsigned long long n = 0;
 #pragma unroll
-          for (uint32_t w = 0; w < uint32_t(kWavesPerBlock); ++w) {
+          for (uint32_t w = 0; w < 2u; ++w) {
             n += bins[w][b];
             bins[w][b] = 0;
           }
@@ -622,7 +669,8 @@ int count_triples(const hm_graph* H, hipStream_t st) {
   RunRec* rec = nullptr;
   uint32_t *pre = nullptr, *counts = nullptr, *before = nullptr;
   HM_TRY(tmp.get(&cnt, chunk + 1));
-  HM_TRY(tmp.get(&at, chunk + 1));
+  HM_TRY(tmp.get(&at, chunk + 2));
+  unsigned long long* next = at + chunk + 1;   // units claimed
   HM_TRY(tmp.get(&rec, chunk));
   HM_TRY(tmp.get(&pre, 4 * (n + 1)));
   HM_TRY(tmp.get(&counts, 4 * tiles));
@@ -630,11 +678,11 @@ int count_triples(const hm_graph* H, hipStream_t st) {
   TriRec* tri = reinterpret_cast<TriRec*>(rec);
   for (uint64_t i = 0; i < n3; i += chunk) {
     const uint64_t m = std::min(chunk, n3 - i);
-    k_tri_plan<<<grid_cap(m + 1, kThreads, 2048), kThreads, 0, st>>>(v, pl, i, m, tri, cnt, lut4, H->hist);
+    k_tri_plan<<<grid_cap(m + 1, kThreads, 2048), kThreads, 0, st>>>(v, pl, i, m, tri, cnt, next, lut4, H->hist);
     HM_HIP(hipGetLastError());
     HM_TRY(scan_exclusive_u64(cnt, at, m + 1, st));
     ProfileScope ps("k_tri_items", st);
-    k_tri_items<<<kItemGrid, kThreads, 0, st>>>(v, pl, m, tri, at, lut4, H->hist);
+    k_tri_items<<<kItemGrid, kThreads, 0, st>>>(v, pl, m, tri, at, next, lut4, H->hist);
     HM_HIP(hipGetLastError());
   }
   k_pl_class_count<<<unsigned(tiles), kThreads, 0, st>>>(pl.adj, n, counts);
@@ -644,11 +692,11 @@ int count_triples(const hm_graph* H, hipStream_t st) {
   HM_HIP(hipGetLastError());
   for (uint64_t p = 0; p < n; p += chunk) {
     const uint64_t m = std::min(chunk, n - p);
-    k_run_plan<<<grid_cap(m + 1, kThreads, 2048), kThreads, 0, st>>>(v, pl, pre, p, m, rec, cnt, lut4, H->hist);
+    k_run_plan<<<grid_cap(m + 1, kThreads, 2048), kThreads, 0, st>>>(v, pl, pre, p, m, rec, cnt, next, lut4, H->hist);
     HM_HIP(hipGetLastError());
     HM_TRY(scan_exclusive_u64(cnt, at, m + 1, st));
     ProfileScope ps("k_run_items", st);
-    k_run_items<<<kItemGrid, kThreads, 0, st>>>(v, pl, p, m, rec, at, lut4, H->hist);
+    k_run_items<<<kItemGrid, kThreads, 0, st>>>(v, pl, m, rec, at, next, lut4, H->hist);
     HM_HIP(hipGetLastError());
   }
   return HM_OK;
