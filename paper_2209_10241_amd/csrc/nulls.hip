@@ -96,6 +96,209 @@ __global__ void k_fix_ties(const unsigned long long* __restrict__ keys, uint32_t
   }
 }
 
+// Orders of fewer items per copy are sorted in LDS: the words are uniform, so
+// that kOrderCap items put by their next 12 bits into as many places leave
+// about one item a place, and each item's rank follows from a count, a scan
+// and a look at its place's other items.  A copy of at most kOrderCap items is
+// one workgroup's (k_order_copy); a larger one is first dealt to buckets of
+// about kOrderMean items by its words' top bits, at most kOrderBuckets of
+// them (k_order_words, k_order_deal), each of which is a workgroup's
+// (k_order_buckets).  Larger orders take the radix sort of k_order_keys: five
+// passes of 40 us over 3.8 million items (64 copies of 59,000), besides 33 for
+// the words and 10 for ties, where these take 115 us in all.
+constexpr uint32_t kOrderCap = 4096;
+constexpr uint32_t kOrderMean = 2900;   // (4096 lies more than 20 standard deviations above)
+constexpr uint32_t kOrderBuckets = 256;
+constexpr uint32_t kOrderTile = 4096;
+
+struct OrderLds {
+  uint32_t hi[kOrderCap], x[kOrderCap], start[kOrderCap + 1], wsum[1024 / kWave];
+};
+
+// Sorts n <= kOrderCap items by (hi, low(x), x), hi's top `drop` bits being the
+// same in all: get(i, &hi, &x) gives item i, put(rank, x) takes the result.
+// Every thread of the NT calls this.
+template <uint32_t NT, typename Get, typename Low, typename Put>
+__device__ void order_sort(OrderLds& l, uint32_t n, uint32_t drop, Get get, Low low, Put put) {
+  constexpr uint32_t K = kOrderCap / NT;
+  const uint32_t tid = threadIdx.x;
+  uint32_t hi[K], x[K], o[K];
+#pragma unroll
+  for (uint32_t r = 0; r < K; ++r) {
+    l.start[r * NT + tid] = 0;
+    if (r * NT + tid < n) get(r * NT + tid, &hi[r], &x[r]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < K; ++r)
+    if (r * NT + tid < n) o[r] = atomicAdd(&l.start[(hi[r] << drop) >> 20], 1u);
+  __syncthreads();
+  {
+    uint32_t c[K], sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < K; ++j) {
+      c[j] = l.start[tid * K + j];
+      sum += c[j];
+    }
+    const uint32_t inc = wave_inclusive_scan(sum);
+    if ((tid & (kWave - 1)) == kWave - 1) l.wsum[tid / kWave] = inc;
+    __syncthreads();
+    uint32_t at = inc - sum;
+    for (uint32_t w = 0; w < tid / kWave; ++w) at += l.wsum[w];
+#pragma unroll
+    for (uint32_t j = 0; j < K; ++j) {
+      l.start[tid * K + j] = at;
+      at += c[j];
+    }
+    if (tid == 0) l.start[kOrderCap] = n;
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < K; ++r)
+    if (r * NT + tid < n) {
+      const uint32_t p = l.start[(hi[r] << drop) >> 20] + o[r];
+      l.hi[p] = hi[r];
+      l.x[p] = x[r];
+    }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < K; ++r) {
+    const uint32_t p = r * NT + tid;
+    if (p >= n) continue;
+    const uint32_t h = l.hi[p], v = l.x[p], place = (h << drop) >> 20;
+    const uint32_t b = l.start[place], e = l.start[place + 1];
+    uint32_t rank = b;
+    for (uint32_t q = b; q < e; ++q) {
+      if (q == p) continue;
+      const uint32_t hq = l.hi[q], vq = l.x[q];
+      bool less = hq < h;
+      if (hq == h) {
+        const uint32_t lq = low(vq), lv = low(v);
+        less = lq < lv || (lq == lv && vq < v);
+      }
+      rank += uint32_t(less);
+    }
+    put(rank, v);
+  }
+}
+
+__device__ inline unsigned long long copy_word(uint64_t x, uint64_t round, unsigned long long seed,
+                                               unsigned long long key1) {
+  return philox4x64_10(x, round, 0, 0, seed, key1).v[0];
+}
+
+__global__ void __launch_bounds__(1024) k_order_copy(uint32_t c0, uint32_t per, uint64_t round,
+                                                     unsigned long long domain,
+                                                     const unsigned long long* __restrict__ seed_p,
+                                                     uint32_t* __restrict__ order) {
+  __shared__ OrderLds l;
+  const unsigned long long seed = *seed_p, key1 = (domain << 32) | (c0 + uint64_t(blockIdx.x));
+  const uint32_t base = blockIdx.x * per;
+  order_sort<1024>(
+      l, per, 0,
+      [&](uint32_t i, uint32_t* hi, uint32_t* x) {
+        *hi = uint32_t(copy_word(i, round, seed, key1) >> 32);
+        *x = i;
+      },
+      [&](uint32_t x) { return uint32_t(copy_word(x, round, seed, key1)); },
+      [&](uint32_t rank, uint32_t x) { order[base + rank] = base + x; });
+}
+
+// hi[c * per + x] := the word's high half, counts[(c * buckets + b) * tiles +
+// t] := the items of tile t of copy c in bucket b (one workgroup per tile)
+__global__ void __launch_bounds__(kThreads) k_order_words(uint32_t c0, uint32_t per, uint32_t tiles, uint32_t buckets,
+                                                          uint32_t shift, uint64_t round, unsigned long long domain,
+                                                          const unsigned long long* __restrict__ seed_p,
+                                                          uint32_t* __restrict__ hi, uint32_t* __restrict__ counts) {
+  __shared__ uint32_t cnt[kOrderBuckets];
+  const uint32_t c = blockIdx.x / tiles, t = blockIdx.x % tiles;
+  const unsigned long long seed = *seed_p, key1 = (domain << 32) | (c0 + uint64_t(c));
+  const uint32_t end = min(per, (t + 1) * kOrderTile);
+  for (uint32_t b = threadIdx.x; b < buckets; b += kThreads) cnt[b] = 0;
+  __syncthreads();
+  for (uint32_t x = t * kOrderTile + threadIdx.x; x < end; x += kThreads) {
+    const uint32_t h = uint32_t(copy_word(x, round, seed, key1) >> 32);
+    hi[uint64_t(c) * per + x] = h;
+    atomicAdd(&cnt[h >> shift], 1u);
+  }
+  __syncthreads();
+  for (uint32_t b = threadIdx.x; b < buckets; b += kThreads)
+    counts[(uint64_t(c) * buckets + b) * tiles + t] = cnt[b];
+}
+
+// (at: the scan of counts; items of one bucket and tile in any order)
+__global__ void __launch_bounds__(kThreads) k_order_deal(uint32_t per, uint32_t tiles, uint32_t buckets, uint32_t shift,
+                                                         const uint32_t* __restrict__ hi,
+                                                         const uint32_t* __restrict__ at,
+                                                         uint32_t* __restrict__ out_hi, uint32_t* __restrict__ out_x) {
+  __shared__ uint32_t cur[kOrderBuckets];
+  const uint32_t c = blockIdx.x / tiles, t = blockIdx.x % tiles;
+  const uint32_t end = min(per, (t + 1) * kOrderTile);
+  for (uint32_t b = threadIdx.x; b < buckets; b += kThreads) cur[b] = at[(uint64_t(c) * buckets + b) * tiles + t];
+  __syncthreads();
+  for (uint32_t x = t * kOrderTile + threadIdx.x; x < end; x += kThreads) {
+    const uint32_t h = hi[uint64_t(c) * per + x];
+    const uint32_t p = atomicAdd(&cur[h >> shift], 1u);
+    out_hi[p] = h;
+    out_x[p] = x;
+  }
+}
+
+__global__ void __launch_bounds__(kThreads) k_order_buckets(uint32_t c0, uint32_t per, uint32_t tiles, uint32_t buckets,
+                                                            uint32_t drop, uint64_t round, unsigned long long domain,
+                                                            const unsigned long long* __restrict__ seed_p, uint64_t n,
+                                                            const uint32_t* __restrict__ at,
+                                                            const uint32_t* __restrict__ hi,
+                                                            const uint32_t* __restrict__ x,
+                                                            uint32_t* __restrict__ order) {
+  __shared__ OrderLds l;
+  const uint32_t c = blockIdx.x / buckets, base = c * per;
+  const unsigned long long seed = *seed_p, key1 = (domain << 32) | (c0 + uint64_t(c));
+  const uint32_t b = at[uint64_t(blockIdx.x) * tiles];
+  const uint32_t e = blockIdx.x + 1 < gridDim.x ? at[uint64_t(blockIdx.x + 1) * tiles] : uint32_t(n);
+  auto low = [&](uint32_t v) { return uint32_t(copy_word(v, round, seed, key1)); };
+  if (e - b <= kOrderCap) {
+    order_sort<kThreads>(
+        l, e - b, drop,
+        [&](uint32_t i, uint32_t* h, uint32_t* v) {
+          *h = hi[b + i];
+          *v = x[b + i];
+        },
+        low, [&](uint32_t rank, uint32_t v) { order[b + rank] = base + v; });
+    return;
+  }
+  // (words this uneven are not drawn in practice)
+  for (uint32_t i = b + threadIdx.x; i < e; i += kThreads) {
+    const uint32_t h = hi[i], v = x[i];
+    uint32_t rank = 0;
+    for (uint32_t q = b; q < e; ++q) {
+      const uint32_t hq = hi[q], vq = x[q];
+      bool less = hq < h;
+      if (hq == h && vq != v) {
+        const uint32_t lq = low(vq), lv = low(v);
+        less = lq < lv || (lq == lv && vq < v);
+      }
+      rank += uint32_t(less);
+    }
+    order[b + rank] = base + v;
+  }
+}
+
+// Buckets per copy of an order of `per` items: 1 when a workgroup sorts the
+// copy, 0 when the radix sort does.
+uint32_t order_buckets(uint64_t per) {
+  if (per <= kOrderCap) return 1;
+  uint32_t b = 2;
+  while (b <= kOrderBuckets && uint64_t(b) * kOrderMean < per) b *= 2;
+  return b <= kOrderBuckets ? b : 0;
+}
+
+// Words of sort_ws that an order of R copies takes.
+uint64_t order_ws_words(uint64_t R, uint64_t per) {
+  const uint64_t b = order_buckets(per), tiles = (per + kOrderTile - 1) / kOrderTile, counts = R * b * tiles;
+  return b == 0 ? radix_ws_words(R * per) : (b == 1 ? 0 : 2 * counts + scan_ws_words(counts) + 16);
+}
+
 __global__ void k_null_gather(const uint32_t* __restrict__ vals, uint64_t n, uint64_t T,
                               const uint32_t* __restrict__ stubs, uint32_t* __restrict__ members) {
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x) {
@@ -114,11 +317,76 @@ __global__ void k_cfg_init(uint32_t R, uint64_t T, const uint32_t* __restrict__ 
     members[i] = src[i % T];
 }
 
-// One thread per (copy, pair): the pairwise reshuffle of the two hyperedges
-// the sorted order pairs.  members holds copy c's hyperedges at c * T +
-// off[e]; tmp (R x T) gives each pair the slots of its two hyperedges as
-// working space: virtual slot q < |e| is tmp[c*T + off[e] + q], the rest
-// tmp[c*T + off[f] + q - |e|].  D takes slots [0, |D|), I the last |I|.
+// The pairwise reshuffle of pair t of round r: hyperedges me (se nodes) and mf
+// (sf), ascending, with as many slots of working space at te and tf: virtual
+// slot q < se is te[q], the rest tf[q - se].  D takes slots [0, |D|), I the
+// last |I|.
+__device__ __forceinline__ void cfg_pair(uint32_t t, uint32_t r, unsigned long long seed, unsigned long long key1,
+                                         uint32_t* me, uint32_t se, uint32_t* mf, uint32_t sf, uint32_t* te,
+                                         uint32_t* tf) {
+  auto slot = [&](uint32_t q) -> uint32_t& { return q < se ? te[q] : tf[q - se]; };
+  // two merges of the ascending lists: e - f into D and e & f into I, then
+  // f - e after e - f
+  uint32_t nd = 0, ni = 0;
+  const uint32_t total = se + sf;
+  for (uint32_t x = 0, y = 0; x < se;) {
+    if (y == sf || me[x] < mf[y]) {
+      slot(nd++) = me[x++];
+    } else if (mf[y] < me[x]) {
+      ++y;
+    } else {
+      slot(total - 1 - ni++) = me[x];
+      ++x;
+      ++y;
+    }
+  }
+  const uint32_t a = nd;   // |e - f|
+  for (uint32_t x = 0, y = 0; y < sf;) {
+    if (x == se || mf[y] < me[x]) {
+      slot(nd++) = mf[y++];
+    } else if (me[x] < mf[y]) {
+      ++x;
+    } else {
+      ++x;
+      ++y;
+    }
+  }
+  Philox4 w{{0, 0, 0, 0}};
+  for (uint32_t q = 0; q < a; ++q) {
+    if ((q & 3) == 0) w = philox4x64_10(t, r, 1 + q / 4, 0, seed, key1);
+    const uint32_t j = q + uint32_t(bounded64(w.v[q & 3], nd - q));
+    const uint32_t tq = slot(q);
+    slot(q) = slot(j);
+    slot(j) = tq;
+  }
+  // e = sort(I + D[:a]), f = sort(I + D[a:]) (insertion sorts into place)
+  auto place = [&](uint32_t* out, uint32_t lo, uint32_t hi) {
+    uint32_t m = 0;
+    for (uint32_t u = 0; u < ni; ++u) {
+      const uint32_t v = slot(total - 1 - u);
+      uint32_t k = m++;
+      while (k > 0 && out[k - 1] > v) {
+        out[k] = out[k - 1];
+        --k;
+      }
+      out[k] = v;
+    }
+    for (uint32_t q = lo; q < hi; ++q) {
+      const uint32_t v = slot(q);
+      uint32_t k = m++;
+      while (k > 0 && out[k - 1] > v) {
+        out[k] = out[k - 1];
+        --k;
+      }
+      out[k] = v;
+    }
+  };
+  place(me, 0, a);
+  place(mf, a, nd);
+}
+
+// One thread per (copy, pair) of the sorted order.  members holds copy c's
+// hyperedges at c * T + off[e]; tmp (R x T) is the working space.
 __global__ void k_cfg_pairs(uint32_t c0, uint32_t R, uint32_t E, uint64_t T, uint32_t r,
                             const unsigned long long* __restrict__ seed_p, const uint32_t* __restrict__ order,
                             const unsigned long long* __restrict__ off, uint32_t* __restrict__ members,
@@ -131,71 +399,46 @@ __global__ void k_cfg_pairs(uint32_t c0, uint32_t R, uint32_t E, uint64_t T, uin
     const uint64_t base = uint64_t(c) * T;
     const uint32_t ie = order[uint64_t(c) * E + 2 * t] - c * E, jf = order[uint64_t(c) * E + 2 * t + 1] - c * E;
     const uint64_t oe = off[ie], of = off[jf];
-    const uint32_t se = uint32_t(off[ie + 1] - oe), sf = uint32_t(off[jf + 1] - of);
-    uint32_t* me = members + base + oe;
-    uint32_t* mf = members + base + of;
-    uint32_t* te = tmp + base + oe;
-    uint32_t* tf = tmp + base + of;
-    auto slot = [&](uint32_t q) -> uint32_t& { return q < se ? te[q] : tf[q - se]; };
-    // two merges of the ascending lists: e - f into D and e & f into I, then
-    // f - e after e - f
-    uint32_t nd = 0, ni = 0;
-    const uint32_t total = se + sf;
-    for (uint32_t x = 0, y = 0; x < se;) {
-      if (y == sf || me[x] < mf[y]) {
-        slot(nd++) = me[x++];
-      } else if (mf[y] < me[x]) {
-        ++y;
-      } else {
-        slot(total - 1 - ni++) = me[x];
-        ++x;
-        ++y;
-      }
-    }
-    const uint32_t a = nd;   // |e - f|
-    for (uint32_t x = 0, y = 0; y < sf;) {
-      if (x == se || mf[y] < me[x]) {
-        slot(nd++) = mf[y++];
-      } else if (me[x] < mf[y]) {
-        ++x;
-      } else {
-        ++x;
-        ++y;
-      }
-    }
-    Philox4 w{{0, 0, 0, 0}};
-    for (uint32_t q = 0; q < a; ++q) {
-      if ((q & 3) == 0) w = philox4x64_10(t, r, 1 + q / 4, 0, seed, (kDomainConfig << 32) | (c0 + c));
-      const uint32_t j = q + uint32_t(bounded64(w.v[q & 3], nd - q));
-      const uint32_t tq = slot(q);
-      slot(q) = slot(j);
-      slot(j) = tq;
-    }
-    // e = sort(I + D[:a]), f = sort(I + D[a:]) (insertion sorts into place)
-    auto place = [&](uint32_t* out, uint32_t lo, uint32_t hi) {
-      uint32_t m = 0;
-      for (uint32_t u = 0; u < ni; ++u) {
-        const uint32_t v = slot(total - 1 - u);
-        uint32_t k = m++;
-        while (k > 0 && out[k - 1] > v) {
-          out[k] = out[k - 1];
-          --k;
-        }
-        out[k] = v;
-      }
-      for (uint32_t q = lo; q < hi; ++q) {
-        const uint32_t v = slot(q);
-        uint32_t k = m++;
-        while (k > 0 && out[k - 1] > v) {
-          out[k] = out[k - 1];
-          --k;
-        }
-        out[k] = v;
-      }
-    };
-    place(me, 0, a);
-    place(mf, a, nd);
+    cfg_pair(t, r, seed, (kDomainConfig << 32) | (c0 + c), members + base + oe, uint32_t(off[ie + 1] - oe),
+             members + base + of, uint32_t(off[jf + 1] - of), tmp + base + oe, tmp + base + of);
   }
+}
+
+// All rounds of one copy by one workgroup, its hyperedges, working space and
+// orders in LDS (E <= kOrderCap, T <= kCfgWords).  A round's launches and the
+// passes of its sort cost more than its work: ten rounds of 33 copies of 1,860
+// hyperedges took 20 launches and about 200 us each, all of them now take 156
+// us.
+constexpr uint32_t kCfgWords = 8192;
+__global__ void __launch_bounds__(1024) k_cfg_copies(uint32_t c0, uint32_t E, uint32_t T, uint32_t rounds,
+                                                     const unsigned long long* __restrict__ seed_p,
+                                                     const unsigned long long* __restrict__ off,
+                                                     const uint32_t* __restrict__ src, uint32_t* __restrict__ members) {
+  __shared__ OrderLds l;
+  __shared__ uint32_t order[kOrderCap];
+  __shared__ uint32_t mem[kCfgWords], tmp[kCfgWords];
+  const unsigned long long seed = *seed_p, key1 = (kDomainConfig << 32) | (c0 + uint64_t(blockIdx.x));
+  for (uint32_t i = threadIdx.x; i < T; i += 1024) mem[i] = src[i];
+  for (uint32_t r = 0; r < rounds; ++r) {
+    order_sort<1024>(
+        l, E, 0,
+        [&](uint32_t i, uint32_t* hi, uint32_t* x) {
+          *hi = uint32_t(copy_word(i, r, seed, key1) >> 32);
+          *x = i;
+        },
+        [&](uint32_t x) { return uint32_t(copy_word(x, r, seed, key1)); },
+        [&](uint32_t rank, uint32_t x) { order[rank] = x; });
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < E / 2; t += 1024) {
+      const uint32_t ie = order[2 * t], jf = order[2 * t + 1];
+      const uint32_t oe = uint32_t(off[ie]), of = uint32_t(off[jf]);
+      cfg_pair(t, r, seed, key1, mem + oe, uint32_t(off[ie + 1]) - oe, mem + of, uint32_t(off[jf + 1]) - of, tmp + oe,
+               tmp + of);
+    }
+    __syncthreads();
+  }
+  uint32_t* out = members + uint64_t(blockIdx.x) * T;
+  for (uint32_t i = threadIdx.x; i < T; i += 1024) out[i] = mem[i];
 }
 
 // delta_m = (x_m - mu_m) / (x_m + mu_m + eps) over R null rows, and the
@@ -855,6 +1098,49 @@ __global__ void k_b_pair_adj(const unsigned long long* __restrict__ keys, uint64
     adj[i] = uint32_t(keys[i] & mask);
 }
 
+// With bit rows the pairwise rows are read off them, 16 lanes per (copy, node):
+// its neighbours are counted, and after a scan of the counts written in
+// ascending order.  (Sorting the copies' directed pairs under (copy, node,
+// neighbour) took 140 us for 64 copies of 19,000 pairs, this 10.)
+constexpr uint32_t kRowLanes = 16;
+__global__ void __launch_bounds__(kThreads) k_b_row_counts(const uint32_t* __restrict__ bits, uint64_t n_rows, uint32_t W,
+                                                           uint32_t* __restrict__ deg) {
+  const uint32_t l = threadIdx.x & (kRowLanes - 1);
+  for (uint64_t x = (uint64_t(blockIdx.x) * kThreads + threadIdx.x) / kRowLanes; x < n_rows;
+       x += uint64_t(gridDim.x) * kThreads / kRowLanes) {
+    uint32_t c = 0;
+    for (uint32_t w = l; w < W; w += kRowLanes) c += uint32_t(__popc(bits[x * W + w]));
+#pragma unroll
+    for (int d = kRowLanes / 2; d > 0; d >>= 1) c += uint32_t(__shfl_xor(int(c), d, kRowLanes));
+    if (l == 0) deg[x] = c;
+  }
+}
+
+__global__ void __launch_bounds__(kThreads) k_b_rows(const uint32_t* __restrict__ bits, uint64_t n_rows, uint32_t W,
+                                                     const uint32_t* __restrict__ off, uint32_t* __restrict__ adj) {
+  const uint32_t l = threadIdx.x & (kRowLanes - 1);
+  for (uint64_t x = (uint64_t(blockIdx.x) * kThreads + threadIdx.x) / kRowLanes; x < n_rows;
+       x += uint64_t(gridDim.x) * kThreads / kRowLanes) {
+    uint32_t base = off[x];
+    for (uint32_t w0 = 0; w0 < W; w0 += kRowLanes) {
+      uint32_t word = w0 + l < W ? bits[x * W + w0 + l] : 0u;
+      const uint32_t c = uint32_t(__popc(word));
+      uint32_t inc = c;
+#pragma unroll
+      for (uint32_t d = 1; d < kRowLanes; d <<= 1) {
+        const uint32_t y = uint32_t(__shfl_up(int(inc), d, kRowLanes));
+        if (l >= d) inc += y;
+      }
+      uint32_t p = base + inc - c;
+      while (word) {
+        adj[p++] = ((w0 + l) << 5) | uint32_t(__ffs(word) - 1);
+        word &= word - 1;
+      }
+      base += uint32_t(__shfl(int(inc), kRowLanes - 1, kRowLanes));
+    }
+  }
+}
+
 template <int J>
 __global__ void k_b_inc_count(uint64_t cap_items, const uint32_t* __restrict__ total, const uint32_t* __restrict__ e,
                               const uint32_t* __restrict__ copyj, uint32_t N, uint32_t* deg) {
@@ -1355,7 +1641,8 @@ int make_plan(const hm_graph* H, int k, uint32_t R, int model, int sweeps, NullP
   GET(P->skeys_tmp, RT);
   GET(P->svals, RT);
   GET(P->svals_tmp, RT);
-  const uint64_t sort_words = std::max(radix_ws_words(RT), radix_ws_words(2 * m2 + 2));
+  const uint64_t sort_words = std::max(order_ws_words(R, model == HM_NULL_CONFIG ? P->E : P->T),
+                                       P->use_bits ? 1 : radix_ws_words(2 * m2 + 2));
   GET(P->sort_ws, sort_words);
   P->repair_blocks = R < 256 ? R : 256;
   P->rs.chosen_pad = pow2_at_least(2ull * P->E + 2);
@@ -1392,10 +1679,12 @@ int make_plan(const hm_graph* H, int k, uint32_t R, int model, int sweeps, NullP
   GET(P->hs2, uint64_t(R) * P->cap2);
   GET(P->hs3, uint64_t(R) * 2 * P->cap3);
   GET(P->hs4, uint64_t(R) * 2 * P->cap4);
-  GET(P->pkeys, 2 * m2 + 2);
-  GET(P->pkeys_tmp, 2 * m2 + 2);
-  GET(P->pvals, 2 * m2 + 2);
-  GET(P->pvals_tmp, 2 * m2 + 2);
+  if (!P->use_bits) {
+    GET(P->pkeys, 2 * m2 + 2);
+    GET(P->pkeys_tmp, 2 * m2 + 2);
+    GET(P->pvals, 2 * m2 + 2);
+    GET(P->pvals_tmp, 2 * m2 + 2);
+  }
   GET(P->deg, RN);
   GET(P->cursor, RN);
   GET(P->g2_off, RN + 1);
@@ -1424,14 +1713,40 @@ int make_plan(const hm_graph* H, int k, uint32_t R, int model, int sweeps, NullP
 }
 
 // P.order := for each copy in turn, its `per` items in the order of their
-// words (see k_order_keys); no allocation, no sync.
+// words; no allocation, no sync.
 int enqueue_order(NullPlan& P, uint64_t n, uint64_t per, uint64_t round, unsigned long long domain, uint32_t c0,
                   hipStream_t st) {
+  const uint32_t buckets = order_buckets(per);
+  P.order = P.svals;
+  if (buckets == 1) {
+    k_order_copy<<<P.R, 1024, 0, st>>>(c0, uint32_t(per), round, domain, P.seed, P.order);
+    HM_HIP(hipGetLastError());
+    return HM_OK;
+  }
+  if (buckets) {
+    const uint32_t tiles = uint32_t((per + kOrderTile - 1) / kOrderTile);
+    uint32_t drop = 0;
+    while ((1u << drop) < buckets) ++drop;
+    const uint64_t counters = uint64_t(P.R) * buckets * tiles;
+    uint32_t *counts = P.sort_ws, *at = counts + counters, *ws = at + counters;
+    // (32-bit words: the first arrays in the halves of the radix sort's)
+    uint32_t *hi = reinterpret_cast<uint32_t*>(P.skeys), *dealt = reinterpret_cast<uint32_t*>(P.skeys_tmp);
+    k_order_words<<<unsigned(P.R * tiles), kThreads, 0, st>>>(c0, uint32_t(per), tiles, buckets, 32 - drop, round, domain,
+                                                             P.seed, hi, counts);
+    HM_HIP(hipGetLastError());
+    HM_TRY(scan_u32_ws(counts, at, counters, nullptr, ws, st));
+    k_order_deal<<<unsigned(P.R * tiles), kThreads, 0, st>>>(uint32_t(per), tiles, buckets, 32 - drop, hi, at, dealt,
+                                                            P.svals_tmp);
+    k_order_buckets<<<unsigned(P.R * buckets), kThreads, 0, st>>>(c0, uint32_t(per), tiles, buckets, drop, round, domain,
+                                                                 P.seed, n, at, dealt, P.svals_tmp, P.order);
+    HM_HIP(hipGetLastError());
+    return HM_OK;
+  }
   k_order_keys<<<grid_for(n), 256, 0, st>>>(c0, P.R, per, round, domain, P.seed, P.skeys, P.svals);
   HM_HIP(hipGetLastError());
   HM_TRY(radix_sort_ws(P.skeys, P.svals, P.skeys_tmp, P.svals_tmp, n, 32 + bits_for(P.R), P.sort_ws, st));
   const bool odd = radix_passes(32 + bits_for(P.R)) & 1;
-  P.order = odd ? P.svals_tmp : P.svals;
+  if (odd) P.order = P.svals_tmp;
   k_fix_ties<<<grid_for(n), 256, 0, st>>>(odd ? P.skeys_tmp : P.skeys, P.order, n, per, round, c0, domain, P.seed);
   HM_HIP(hipGetLastError());
   return HM_OK;
@@ -1465,6 +1780,12 @@ int enqueue_config(const hm_graph* H, NullPlan& P, uint32_t c0, hipStream_t st) 
   const uint64_t n = uint64_t(P.R) * P.T, ne = uint64_t(P.R) * P.E;
   HM_TRY(fill_u32(P.failed, 0, 1, st));
   if (n == 0) return HM_OK;
+  if (P.E <= kOrderCap && P.T <= kCfgWords) {
+    k_cfg_copies<<<P.R, 1024, 0, st>>>(c0, P.E, uint32_t(P.T), uint32_t(P.sweeps), P.seed, H->all_off, H->all_members,
+                                       P.members);
+    HM_HIP(hipGetLastError());
+    return HM_OK;
+  }
   k_cfg_init<<<grid_for(n), 256, 0, st>>>(P.R, P.T, H->all_members, P.members);
   HM_HIP(hipGetLastError());
   if (P.E < 2) return HM_OK;
@@ -1503,8 +1824,15 @@ int enqueue_ingest(const hm_graph* H, NullPlan& P, hipStream_t st) {
   if (m4) k_b_set128<4><<<grid_for(m4), 256, 0, st>>>(m4, P.tot + 2, P.e4, P.copy4, P.hs4, P.cap4);
   HM_HIP(hipGetLastError());
   // pairwise graph rows (ascending) of every copy
-  HM_TRY(fill_u32(P.deg, 0, RN, st));
-  if (m2) {
+  if (P.use_bits) {
+    HM_TRY(fill_u32(P.bits, 0, RN * P.W, st));
+    if (m2) k_b_bits<<<grid_for(m2), 256, 0, st>>>(m2, P.tot + 0, P.e2, P.copy2, N, P.W, P.bits);
+    k_b_row_counts<<<grid_for(RN * kRowLanes), kThreads, 0, st>>>(P.bits, RN, P.W, P.deg);
+    HM_HIP(hipGetLastError());
+  } else {
+    HM_TRY(fill_u32(P.deg, 0, RN, st));
+  }
+  if (!P.use_bits && m2) {
     k_b_pair_keys<<<grid_for(m2), 256, 0, st>>>(m2, P.tot + 0, P.e2, P.copy2, N, P.B, P.pkeys, P.pvals, P.deg);
     HM_HIP(hipGetLastError());
     HM_TRY(radix_sort_ws(P.pkeys, P.pvals, P.pkeys_tmp, P.pvals_tmp, 2 * m2, 2 * P.B + bits_for(R), P.sort_ws, st));
@@ -1513,6 +1841,7 @@ int enqueue_ingest(const hm_graph* H, NullPlan& P, hipStream_t st) {
     HM_HIP(hipGetLastError());
   }
   HM_TRY(scan_u32_ws(P.deg, P.g2_off, RN, P.g2_off + RN, P.scan_ws, st));
+  if (P.use_bits) k_b_rows<<<grid_for(RN * kRowLanes), kThreads, 0, st>>>(P.bits, RN, P.W, P.g2_off, P.g2_adj);
   // incident 3- and 4-node hyperedges
   HM_TRY(fill_u32(P.deg, 0, RN, st));
   if (m3) k_b_inc_count<3><<<grid_for(m3), 256, 0, st>>>(m3, P.tot + 1, P.e3, P.copy3, N, P.deg);
@@ -1527,11 +1856,6 @@ int enqueue_ingest(const hm_graph* H, NullPlan& P, hipStream_t st) {
   HM_TRY(copy_u32(P.i4_off, P.cursor, RN, st));
   if (m4) k_b_inc_fill<4><<<grid_for(m4), 256, 0, st>>>(m4, P.tot + 2, P.e4, P.copy4, N, P.cursor, P.i4_idx, P.i4_oth);
   HM_HIP(hipGetLastError());
-  if (P.use_bits) {
-    HM_TRY(fill_u32(P.bits, 0, RN * P.W, st));
-    if (m2) k_b_bits<<<grid_for(m2), 256, 0, st>>>(m2, P.tot + 0, P.e2, P.copy2, N, P.W, P.bits);
-    HM_HIP(hipGetLastError());
-  }
   return HM_OK;
 }
 
@@ -1704,7 +2028,7 @@ int null_copies(const hm_graph* H, uint32_t c0, uint32_t R, uint64_t seed, uint3
   HM_TRY(P.get(&P.skeys_tmp, RT));
   HM_TRY(P.get(&P.svals, RT));
   HM_TRY(P.get(&P.svals_tmp, RT));
-  HM_TRY(P.get(&P.sort_ws, radix_ws_words(RT)));
+  HM_TRY(P.get(&P.sort_ws, order_ws_words(R, model == HM_NULL_CONFIG ? P.E : P.T)));
   P.repair_blocks = R < 256 ? R : 256;
   P.rs.chosen_pad = pow2_at_least(2ull * P.E + 2);
   P.rs.pool_pad = pow2_at_least(P.T + 1);

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from oracle import core, nulls
+from oracle import core, nulls, profiles
 
 pytestmark = pytest.mark.gpu
 
@@ -142,3 +142,39 @@ def test_empty_hypergraph(hm):
     with hm.hm_graph_create(h.members, h.offsets, h.n_nodes) as g:
         real, nl, z = hm.count_nulls(g, 4, 3, 1)
         assert real.sum().item() == 0 and nl.sum().item() == 0 and float(z.abs().sum()) == 0.0
+
+
+def _pairs(n_nodes, n_pairs, seed):
+    """Hypergraph of n_pairs different pairs, in a random order."""
+    rng = np.random.default_rng(seed)
+    code = rng.choice(n_nodes * (n_nodes - 1) // 2, n_pairs, replace=False)
+    b = ((1 + np.sqrt(1 + 8.0 * code)) / 2).astype(np.int64)
+    b -= b * (b - 1) // 2 > code
+    a = code - b * (b - 1) // 2
+    return W.Hypergraph(n_nodes, np.c_[a, b].astype(np.uint32).ravel(),
+                        np.arange(0, 2 * n_pairs + 1, 2).astype(np.uint64), name="pairs")
+
+
+@pytest.mark.parametrize("n_pairs", [1, 2048, 2049, 2901, 5801, 371_200, 371_201])
+def test_orders_match_oracle(hm, n_pairs):
+    """Stub orders sorted by one workgroup, dealt to 2, 4 and 256 buckets, and
+    by the radix sort."""
+    h = _pairs(3000, n_pairs, n_pairs)
+    with hm.hm_graph_create(h.members, h.offsets, h.n_nodes) as g:
+        for copy in (0, 7):
+            m, _ = hm.hm_null_export(g, 5, copy)
+            assert np.array_equal(m, nulls.stub_matching(h, 5, copy)[0]), copy
+
+
+@pytest.mark.parametrize("edges,sizes", [(2, (2,)), (3, (2, 3)), (4096, (2,)), (4097, (2,)), (2300, (2, 3, 4, 5)),
+                                         (2400, (2, 3, 4, 5)), (6000, (2, 3))])
+def test_config_rounds_match_oracle(hm, edges, sizes):
+    """All rounds of a copy by one workgroup up to its largest numbers of
+    hyperedges and members, and round by round beyond either."""
+    h = W.random_small(edges, 2500, edges, {s: 1.0 for s in sizes})
+    if sizes == (2,):
+        h = _pairs(2500, edges, edges)
+    with hm.hm_graph_create(h.members, h.offsets, h.n_nodes) as g:
+        for sweeps, copy in ((1, 0), (3, 4)):
+            m, _ = hm.hm_null_export_model(g, hm.HM_NULL_CONFIG, sweeps, 9, copy)
+            assert np.array_equal(m, profiles.config_model(h, sweeps, 9, copy)[0]), (sweeps, copy)
