@@ -57,14 +57,16 @@ struct Ranked {
   const uint32_t* core_eid;  // position in e2 of the entry's pair
   const uint32_t* out_adj;
   const uint32_t* out_eid;
+  const uint32_t* degree;    // rank -> degree
   const uint32_t* weight;    // rank -> bound on the nodes marked and positions walked (degree >= kSmallDeg)
   const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg
   const uint32_t* facts;     // kLongestOut ..
 };
 
 // Words of Ranked::facts: the longest out row, the nodes with more than
-// 65,535 core neighbours, and the split walks' nodes and shares.
-enum : int { kLongestOut = 0, kManyCore = 1, kSplitNodes = 2, kSplitShares = 3, kFacts = 4 };
+// 65,535 core neighbours, the split walks' nodes and shares, and the core
+// rows' entries.
+enum : int { kLongestOut = 0, kManyCore = 1, kSplitNodes = 2, kSplitShares = 3, kCoreEntries = 4, kFacts = 5 };
 
 __global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, uint32_t* __restrict__ keys,
                             uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
@@ -140,12 +142,15 @@ __global__ void k_core_fill(const uint32_t* __restrict__ g2_adj, const uint32_t*
 __global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uint64_t m,
                             const uint32_t* __restrict__ node_of, const unsigned long long* __restrict__ flag,
                             const unsigned long long* __restrict__ pos, uint2* __restrict__ core,
-                            uint2* __restrict__ out, uint32_t* __restrict__ facts) {
+                            uint2* __restrict__ out, uint32_t* __restrict__ degree, uint32_t* __restrict__ facts) {
   uint32_t most = 0;
   auto at = [&](uint32_t i) { return i < m ? pos[i] : (m ? pos[m - 1] + flag[m - 1] : 0ull); };
+  if (blockIdx.x == 0 && threadIdx.x == 0) facts[kCoreEntries] = uint32_t(at(uint32_t(m)));
   for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
     const uint32_t x = node_of[r];
-    const unsigned long long b = at(g2_off[x]), e = at(g2_off[x + 1]);
+    const uint32_t g0 = g2_off[x], g1 = g2_off[x + 1];
+    degree[r] = g1 - g0;
+    const unsigned long long b = at(g0), e = at(g1);
     core[r] = make_uint2(uint32_t(b), uint32_t(e) - uint32_t(b));
     out[r] = make_uint2(uint32_t(b >> 32), uint32_t(e >> 32) - uint32_t(b >> 32));
     most = max(most, uint32_t(e >> 32) - uint32_t(b >> 32));
@@ -169,7 +174,7 @@ struct WalkArgs {
   // kSums: over the common neighbours w of the pair {a < b}: triangles of
   // {a, w}, of {b, w}, pairwise degrees of w
   unsigned long long *sum_a, *sum_b, *sum_d;
-  const uint32_t* g2_off;
+  const uint32_t* core_tri;         // kSums: per core entry, its pair's triangles
 };
 
 // A set of ranks with a value each, open addressing in LDS.
@@ -302,7 +307,7 @@ __device__ void walk_top(const WalkArgs& a, WalkLds<T * XPT, MODE>& S, const Tab
     for (uint32_t i = tid; i < ru.y; i += T) {
       const uint32_t w = g.core_adj[ru.x + i];
       if (!tab.covers(w)) continue;
-      if constexpr (MODE == kSums) tab.put(w, a.tri_e[g.core_eid[ru.x + i]] + 1u);
+      if constexpr (MODE == kSums) tab.put(w, a.core_tri[ru.x + i] + 1u);
       else tab.mark(w);
     }
   }
@@ -387,18 +392,43 @@ __device__ void walk_top(const WalkArgs& a, WalkLds<T * XPT, MODE>& S, const Tab
         }
 #pragma unroll
         for (uint32_t r = 0; r < L; ++r) w[r] = g.core_adj[q[r]];
+        if constexpr (MODE == kSums) {
+          // the common neighbours among them: both loads of each out before
+          // any is used; summed in registers as long as the row is the same
+          uint32_t t[L], tx[L], d[L];
+#pragma unroll
+          for (uint32_t r = 0; r < L; ++r) {
+            t[r] = p0 + r < total && w[r] != u && tab.covers(w[r]) ? tab.get(w[r]) : 0u;
+            tx[r] = t[r] ? a.core_tri[q[r]] : 0u;
+            d[r] = t[r] ? g.degree[w[r]] : 0u;
+          }
+          unsigned long long sx = 0, su = 0;
+          uint32_t sd = 0, at = k[0];   // (degrees add up to at most 2 |E2|, below 2^32)
+          auto add = [&]() {
+            if (!sd) return;
+            if (sx) atomicAdd(&S.sums[at], sx);
+            if (su) atomicAdd(&S.sums[XS + at], su);
+            atomicAdd(&S.sums[2 * XS + at], (unsigned long long)sd);
+          };
+#pragma unroll
+          for (uint32_t r = 0; r < L; ++r) {
+            if (k[r] != at) {
+              add();
+              sx = su = 0;
+              sd = 0;
+              at = k[r];
+            }
+            sx += tx[r];
+            su += t[r] ? t[r] - 1 : 0u;
+            sd += d[r];
+          }
+          add();
+          continue;
+        }
 #pragma unroll
         for (uint32_t r = 0; r < L; ++r) {
           if (p0 + r >= total || w[r] == u || !tab.covers(w[r])) continue;
-          if constexpr (MODE == kSums) {
-            const uint32_t t = tab.get(w[r]);
-            if (t) {
-              const uint32_t node = g.node_of[w[r]];
-              atomicAdd(&S.sums[k[r]], (unsigned long long)a.tri_e[g.core_eid[q[r]]]);
-              atomicAdd(&S.sums[XS + k[r]], (unsigned long long)(t - 1));
-              atomicAdd(&S.sums[2 * XS + k[r]], (unsigned long long)(a.g2_off[node + 1] - a.g2_off[node]));
-            }
-          } else if (pass == 0) {
+          if (pass == 0) {
             bool hit;
             if (MODE != kTri && w[r] < u) hit = tab.add(w[r]);
             else hit = tab.marked(w[r]);
@@ -917,9 +947,10 @@ int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_
   const uint64_t n2 = H->n_by_size[2], m = 2 * n2;
   unsigned long long *flag = nullptr, *pos = nullptr;
   uint32_t *core_adj = nullptr, *core_eid = nullptr, *out_adj = nullptr, *out_eid = nullptr, *weight = nullptr,
-           *facts = nullptr;
+           *degree = nullptr, *facts = nullptr;
   uint2 *core = nullptr, *rows = nullptr;
   HM_TRY(tmp.get(&weight, n));
+  HM_TRY(tmp.get(&degree, n));
   HM_TRY(tmp.get(&core, n));
   HM_TRY(tmp.get(&rows, n));
   HM_TRY(tmp.get(&facts, kFacts));
@@ -937,10 +968,10 @@ int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_
   HM_TRY(scan_exclusive_u64(flag, pos, m, st));
   k_core_fill<<<grid_of(m, 256, 4096), 256, 0, st>>>(H->g2_adj, H->g2_eid, m, H->rank_of, flag, pos, core_adj,
                                                      core_eid, out_adj, out_eid);
-  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, H->node_of, flag, pos, core, rows, facts);
+  k_core_rows<<<grid_of(n, 256, 1024), 256, 0, st>>>(H->g2_off, n, m, H->node_of, flag, pos, core, rows, degree, facts);
   HM_HIP(hipGetLastError());
-  *out = Ranked{n, H->rank_of, H->node_of, core, rows, core_adj, core_eid, out_adj, out_eid, weight, H->rank_bounds,
-                facts};
+  *out = Ranked{n, H->rank_of, H->node_of, core, rows, core_adj, core_eid, out_adj, out_eid, degree, weight,
+                H->rank_bounds, facts};
   if (most) {
     HM_HIP(hipMemcpyAsync(most, facts + kLongestOut, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HM_HIP(hipStreamSynchronize(st));
@@ -1073,6 +1104,14 @@ __global__ void k_es_widen(const uint32_t* __restrict__ t32, uint64_t n, unsigne
     t64[i] = t32[i];
 }
 
+// per core entry, its pair's triangles
+__global__ void k_core_tri(const uint32_t* __restrict__ core_eid, const uint32_t* __restrict__ tri_e,
+                           const uint32_t* __restrict__ facts, uint32_t* __restrict__ core_tri) {
+  const uint32_t n = facts[kCoreEntries];
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    core_tri[i] = tri_e[core_eid[i]];
+}
+
 // The per-pair statistics of hm_graph::es (6 x n2).
 int wedge_edge_stats(hm_graph* H, unsigned long long* es, hipStream_t st) {
   const uint64_t n2 = H->n_by_size[2];
@@ -1096,11 +1135,14 @@ int wedge_edge_stats(hm_graph* H, unsigned long long* es, hipStream_t st) {
   a.sum_a = es + 3 * n2;
   a.sum_b = es + 4 * n2;
   a.sum_d = es + 5 * n2;
-  a.g2_off = H->g2_off;
+  uint32_t* core_tri = nullptr;
+  HM_TRY(tmp.get(&core_tri, 2 * n2));
+  a.core_tri = core_tri;
   Split sp;
   HM_TRY(plan_split(g, tmp, &sp, st));
   HM_TRY(launch_walks<kPairCycles>(a, sp, "k_walk", st));
   k_es_widen<<<grid_of(n2, 256, 2048), 256, 0, st>>>(tri_e, n2, es);
+  k_core_tri<<<grid_of(2 * n2, 256, 4096), 256, 0, st>>>(g.core_eid, tri_e, g.facts, core_tri);
   HM_TRY(launch_walks<kSums>(a, sp, "k_walk_sums", st));
   HM_TRY(launch_cliques<true>(H, g, most, copies + kAccCopies, es + n2, st, tmp));
   return HM_OK;
