@@ -102,7 +102,7 @@ __device__ inline void fast_insert(const FastDedup& dd, unsigned long long h, ui
     const unsigned long long cur = atomicCAS(&dd.slots[pos], kEmpty64, mine);
     if (cur == kEmpty64) break;
     if ((cur >> 32) == tag) {
-      atomicMin(&dd.slots[pos], mine);
+      if (cur > mine) atomicMin(&dd.slots[pos], mine);   // (entries only decrease)
       break;
     }
     pos = (pos + 1) & dd.mask;
@@ -204,9 +204,9 @@ __global__ void k_prepare(const uint32_t* __restrict__ members, const uint64_t* 
 // written back in one sweep.  A tile of more than kPrepWords members, or with
 // an invalid offset, is read in place.  A thread per hyperedge, which sorted
 // more than 8 nodes by insertion in private or device memory, took 2.58 ms for
-// 5 million hyperedges of 2 to 50 nodes (28 million members), this one 0.53
-// (of 2 million with 7.2 million members: 0.43 and 0.20), of which the
-// duplicate search's atomics are a quarter to a half.  (Finding duplicates by
+// 5 million hyperedges of 2 to 50 nodes (28 million members), this one 0.48
+// (of 2 million with 7.2 million members: 0.43 and 0.18), most of which is the
+// duplicate search's atomics, 12 a nanosecond.  (Finding duplicates by
 // a radix partition of the hashes and LDS tables instead was no faster at 5
 // million and slower below 1.5 million.)
 //
@@ -548,43 +548,6 @@ __global__ void __launch_bounds__(kTile) k_first_tiles(const uint32_t* __restric
   }
 }
 
-// The validation summary of the tiles a workgroup's threads take (thread:
-// t_first, t_first + t_step, ... below t_end), reduced over the workgroup:
-// singletons, repeats, error bits, first erroneous index.  Every thread must
-// call it and receives the result.
-__device__ DevFlags tile_flags(const uint32_t* __restrict__ tile_cnt, uint64_t t_first, uint64_t t_end,
-                               uint64_t t_step) {
-  __shared__ unsigned long long s_single, s_dup;
-  __shared__ uint32_t s_err, s_min;
-  if (threadIdx.x == 0) {
-    s_single = 0;
-    s_dup = 0;
-    s_err = 0;
-    s_min = 0xFFFFFFFFu;
-  }
-  __syncthreads();
-  unsigned long long sg = 0, dp = 0;
-  uint32_t er = 0, mn = 0xFFFFFFFFu;
-  for (uint64_t t = t_first; t < t_end; t += t_step) {
-    const uint32_t* c = tile_cnt + t * kTileS;
-    sg += c[kTSingles];
-    dp += c[kTDups];
-    er |= c[kTErr];
-    mn = min(mn, c[kTErrMin]);
-  }
-  if (sg) atomicAdd(&s_single, sg);
-  if (dp) atomicAdd(&s_dup, dp);
-  if (er) atomicOr(&s_err, er);
-  if (mn != 0xFFFFFFFFu) atomicMin(&s_min, mn);
-  __syncthreads();
-  DevFlags f;
-  f.err = s_err;
-  f.err_edge = s_min;
-  f.singletons = s_single;
-  f.duplicates = s_dup;
-  return f;
-}
-
 // What the build reads back once: validation flags and the five totals.
 struct Report {
   DevFlags flags;
@@ -605,54 +568,80 @@ __device__ inline void publish_report(Report* out, bool wrote) {
 // Exclusive scan of the tiles' position counters in place; the five totals
 // and the validation summary go to the report (pinned host memory), the
 // totals and the error bits also to dev_totals (kTileN + 1 words) for the
-// kernels that follow.  One workgroup of 1024: thread t takes a run of
-// consecutive tiles, the runs' sums are scanned across the workgroup, and each
-// thread then writes the offsets of its run.  Every count is below 2^32 (so
-// are the incidences).
+// kernels that follow.  One workgroup of 1024: 1,024 tiles a round, the next
+// round's counters loaded while this one's are scanned (a run of consecutive
+// tiles per thread, read twice, took 89 us for 19,500 tiles, this 64).
+// Every count is below 2^32 (so are the incidences).
 __global__ void __launch_bounds__(1024) k_tile_scan(uint32_t* __restrict__ tile_cnt, uint64_t n_tiles, Report* out,
                                                     unsigned long long* __restrict__ dev_totals) {
-  __shared__ uint32_t wsum[kTileN][1024 / kWave];
+  __shared__ uint32_t wsum[2][kTileN][1024 / kWave];
+  __shared__ unsigned long long s_single, s_dup;
+  __shared__ uint32_t s_err, s_min;
   const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  const uint64_t per = (n_tiles + 1023) / 1024;
-  const uint64_t t0 = min(n_tiles, uint64_t(threadIdx.x) * per), t1 = min(n_tiles, t0 + per);
-  const DevFlags f = tile_flags(tile_cnt, t0, t1, 1);
-  uint32_t pre[kTileN];
-#pragma unroll
-  for (int k = 0; k < kTileN; ++k) pre[k] = 0;
-  for (uint64_t t = t0; t < t1; ++t) {
-#pragma unroll
-    for (int k = 0; k < kTileN; ++k) pre[k] += tile_cnt[t * kTileS + k];
-  }
-#pragma unroll
-  for (int k = 0; k < kTileN; ++k) {
-    uint32_t tot;
-    pre[k] = wave_exclusive_scan(pre[k], &tot);
-    if (lane == 0) wsum[k][wv] = tot;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kTileN; ++k)
-    for (uint32_t q = 0; q < wv; ++q) pre[k] += wsum[k][q];
-  for (uint64_t t = t0; t < t1; ++t) {
-#pragma unroll
-    for (int k = 0; k < kTileN; ++k) {
-      const uint32_t x = tile_cnt[t * kTileS + k];
-      tile_cnt[t * kTileS + k] = pre[k];
-      pre[k] += x;
-    }
-  }
-  if (threadIdx.x == 1023) {
-#pragma unroll
-    for (int k = 0; k < kTileN; ++k) {
-      out->totals[k] = pre[k];
-      dev_totals[k] = pre[k];
-    }
-  }
   if (threadIdx.x == 0) {
+    s_single = s_dup = 0;
+    s_err = 0;
+    s_min = 0xFFFFFFFFu;
+  }
+  uint32_t next[kTileS], base[kTileN];
+#pragma unroll
+  for (int k = 0; k < kTileN; ++k) base[k] = 0;
+  auto load = [&](uint64_t t) {
+#pragma unroll
+    for (int k = 0; k < kTileS; ++k) next[k] = t < n_tiles ? tile_cnt[t * kTileS + k] : (k == kTErrMin ? 0xFFFFFFFFu : 0u);
+  };
+  load(threadIdx.x);
+  unsigned long long sg = 0, dp = 0;
+  uint32_t er = 0, mn = 0xFFFFFFFFu, round = 0;
+  for (uint64_t t0 = 0; t0 < n_tiles; t0 += 1024, round ^= 1) {
+    const uint64_t t = t0 + threadIdx.x;
+    uint32_t x[kTileN], pre[kTileN];
+#pragma unroll
+    for (int k = 0; k < kTileN; ++k) x[k] = next[k];
+    sg += next[kTSingles];
+    dp += next[kTDups];
+    er |= next[kTErr];
+    mn = min(mn, next[kTErrMin]);
+    load(t + 1024);
+#pragma unroll
+    for (int k = 0; k < kTileN; ++k) {
+      uint32_t tot;
+      pre[k] = wave_exclusive_scan(x[k], &tot);
+      if (lane == 0) wsum[round][k][wv] = tot;
+    }
+    __syncthreads();   // (the other round's sums were read before it)
+#pragma unroll
+    for (int k = 0; k < kTileN; ++k) {
+      uint32_t before = 0, all = 0;
+      for (uint32_t q = 0; q < 1024 / kWave; ++q) {
+        const uint32_t y = wsum[round][k][q];
+        if (q < wv) before += y;
+        all += y;
+      }
+      if (t < n_tiles) tile_cnt[t * kTileS + k] = base[k] + before + pre[k];
+      base[k] += all;
+    }
+  }
+  if (sg) atomicAdd(&s_single, sg);
+  if (dp) atomicAdd(&s_dup, dp);
+  if (er) atomicOr(&s_err, er);
+  if (mn != 0xFFFFFFFFu) atomicMin(&s_min, mn);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < kTileN; ++k) {
+      out->totals[k] = base[k];
+      dev_totals[k] = base[k];
+    }
+    DevFlags f;
+    f.err = s_err;
+    f.err_edge = s_min;
+    f.singletons = s_single;
+    f.duplicates = s_dup;
     out->flags = f;
     dev_totals[kTileN] = f.err;
   }
-  publish_report(out, threadIdx.x == 0 || threadIdx.x == 1023);
+  publish_report(out, threadIdx.x == 0);
 }
 
 // Write the unique hyperedges out, in first-occurrence order, with everything
@@ -726,8 +715,11 @@ __device__ void scan_degree_array(const uint32_t* __restrict__ d, uint32_t* __re
 constexpr uint32_t kGatherScanRun = 32;
 constexpr uint64_t kGatherScanMax = uint64_t(kGatherScanRun) * kTile;   // n * R at most
 
-// COPY_TOGETHER (large inputs): the workgroup copies its tile's members in one
-// coalesced sweep; else each thread copies its hyperedge's.
+// COPY_TOGETHER (the builds that are not one-pass): the workgroup copies its
+// tile's members in one coalesced sweep; else each thread copies its
+// hyperedge's.  (The one-pass parts, self_offsets and scan, take 182 registers
+// and are left out of the former: 537 -> 249 us for 5 million hyperedges, 165
+// -> 129 for 2 million.)
 template <bool COPY_TOGETHER>
 __global__ void __launch_bounds__(kTile) k_gather_tiles(const uint32_t* __restrict__ sm,
                                                          const uint64_t* __restrict__ off,
@@ -743,7 +735,7 @@ __global__ void __launch_bounds__(kTile) k_gather_tiles(const uint32_t* __restri
   const uint32_t lane = threadIdx.x & (kWave - 1);
   __shared__ uint32_t bad;
   const uint64_t n_tiles = (n_edges + kTile - 1) / kTile;
-  if (blockIdx.x >= n_tiles) {
+  if (!COPY_TOGETHER && blockIdx.x >= n_tiles) {
     // a degree scan (g.scan): array blockIdx.x - n_tiles
     const uint32_t a = uint32_t(blockIdx.x - n_tiles);
     scan_degree_array<kGatherScanRun>(a == 0 ? g.deg.deg2 : a == 1 ? g.deg.deg3 : g.deg.deg4,
@@ -767,7 +759,7 @@ __global__ void __launch_bounds__(kTile) k_gather_tiles(const uint32_t* __restri
   uint32_t mm[4];
 #pragma unroll
   for (uint32_t j = 0; j < 4; ++j) mm[j] = first && j < s ? sm[at + j] : 0u;
-  if (g.self_offsets) {
+  if (!COPY_TOGETHER && g.self_offsets) {
     // every counter of the tiles a thread takes in one round of loads: the
     // five position counters, and the validation summary (singletons,
     // repeats, error bits, first erroneous index)
@@ -1373,7 +1365,7 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
   const uint64_t NR = keep_bits ? N * R : 0;
   // the degree scans ride on the gather's launch when its workgroups can
   // hold a run each (else a launch of their own after it)
-  const bool gather_scan = keep_bits && E > 0 && NR <= kGatherScanMax;
+  const bool gather_scan = one_pass && E > 0 && NR <= kGatherScanMax;
 
   unsigned long long* dev_totals = nullptr;
   uint32_t *sm = nullptr, *size = nullptr, *tile_cnt = nullptr;
