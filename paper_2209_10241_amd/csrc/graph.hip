@@ -1455,7 +1455,7 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
     own.add(&H->i4_off, N + 1);
     own.add(&H->i4_idx, 4 * n4);
     own.add(&H->hist, uint64_t(kHistCopies) * kExactHistStride);
-    own.add(&H->sample_hist, uint64_t(kHistCopies) * kSampleHistStride + 8);
+    own.add(&H->sample_hist, kSampleHistWords);
     std::vector<void*> blocks;
     const int rc = own.take(&blocks);
     // carved: the graph frees the one block; else every array is its own
@@ -1465,7 +1465,7 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
     fl.add(H->hs2.slot, c2, kEmpty64, 1);
     fl.add(H->hs3.slot, 2 * c3, kEmpty64, 1);
     fl.add(H->hs4.slot, 2 * c4, kEmpty64, 1);
-    fl.add(H->sample_hist, uint64_t(kHistCopies) * kSampleHistStride + 8, 0, 1);
+    fl.add(H->sample_hist, kSampleHistWords, 0, 1);
     fl.add(H->hist, uint64_t(kHistCopies) * kExactHistStride, 0, 1);
     if (keep_bits) fl.add(H->bits, N * H->words, 0, 0);
     fl.add(H->all_off, 1, 0, 1);   // all_off[0]; the rest is written by the gather
@@ -1631,7 +1631,7 @@ void release(hm_graph* H, hipStream_t st = nullptr, bool ordered = false) {
   // and those built later, on first use
   void* later[] = {H->g2_eid,  H->pl_keys,  H->pl_edge,  H->pl_slot,   H->pl_codeg, H->pl_third, H->pl_adj,
                    H->q_slot,  H->q_fourth, H->hub_rank, H->hub_bits, H->proj_bits,
-                   H->ns_tri,  H->ns_nbr,   H->ns_h3,    H->es,        H->e5,       H->hs5,   H->dense5,
+                   H->ns_tri,  H->ns_nbr,   H->ns_h3,    H->e3_pat, H->es,        H->e5,       H->hs5,   H->dense5,
                    H->rank_of, H->node_of, H->rank_bounds};
   std::vector<void*> ps(std::begin(later), std::end(later));
   if (H->arena)

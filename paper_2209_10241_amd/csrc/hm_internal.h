@@ -24,6 +24,11 @@ constexpr int kWave = 64;
 constexpr uint32_t kHistCopies = 16;
 constexpr uint32_t kExactHistStride = 1024;   // per copy: main, sub, G2 regions, 256 unused
 constexpr uint32_t kSampleHistStride = 256;
+// the pair sampler's work queue is kept in parts with counters of their own
+// (reserved and claimed entries), 128 bytes apart, after the counters
+constexpr uint32_t kQueueParts = 16;
+constexpr uint32_t kQueueStep = 16;
+constexpr uint64_t kSampleHistWords = uint64_t(kHistCopies) * kSampleHistStride + 2 * kQueueParts * kQueueStep;
 constexpr uint32_t kEmpty32 = 0xFFFFFFFFu;
 constexpr unsigned long long kEmpty64 = ~0ull;
 // adjacency bit rows are kept when the node count is at most this (the
@@ -348,6 +353,8 @@ struct hm_graph {
   unsigned long long* ns_tri = nullptr;
   unsigned long long* ns_nbr = nullptr;
   uint32_t* ns_h3 = nullptr;
+  // per 3-node hyperedge {a < b < c}: a~b, a~c, b~c (bits 0..2)
+  uint8_t* e3_pat = nullptr;
   // per pair of e2 (u < w), built on first use without bit rows, 6 x n2:
   // triangles, 4-cliques and 4-cycles through it; over its common neighbours
   // x: sum of t_{ux}, sum of t_{wx}, sum of deg x

@@ -87,7 +87,7 @@ __device__ void sample_j4(const View& v, const Draws& d, uint32_t part, uint32_t
 
 // Work chunks of heavy samples (without bit rows), drained by every
 // workgroup of a second launch so that one sample's work spreads over many.
-enum : uint32_t { kJobNone = 0, kJobPairT = 1, kJobPairR = 2, kJobTriple = 3, kJobPairS = 4, kJobPairQ = 5 };
+enum : uint32_t { kJobNone = 0, kJobPairT = 1, kJobPairR = 2, kJobTriple = 3, kJobPairS = 4, kJobPairQ = 5, kJobPairAll = 6 };
 // default chunk sizes (divided by the HM_OPT_SAMPLE_CHUNK_SCALE option).  A
 // chunk costs its claim and four or five dependent rounds of loads before its
 // first position, about 10 us, so it has to hold more work than that: with 4
@@ -98,7 +98,10 @@ enum : uint32_t { kJobNone = 0, kJobPairT = 1, kJobPairR = 2, kJobTriple = 3, kJ
 constexpr uint32_t kChunkT = 2;    // nodes of T per chunk (about 5,000 positions)
 constexpr uint32_t kChunkR = 64;   // correction items per chunk
 constexpr uint32_t kChunkX = 512;  // exception positions per chunk
-constexpr uint32_t kChunkH = 256;  // hyperedges at s (3-node) or holding e (4-node) per chunk
+constexpr uint32_t kChunkH = 1024;  // hyperedges at s (3-node) or holding e (4-node) per chunk
+// A sample of no more than this many chunks of each kind is one chunk of all
+// (2.12 ms with 1 or 4 where 2 takes 2.03).
+constexpr uint32_t kWholeChunks = 2;
 // queue entries per sample of strata 2 and 3 (times the chunk option), at
 // most kQueueMax in all; work that finds the queue full is done in place
 constexpr uint64_t kQueuePerSample = 2048;
@@ -107,12 +110,17 @@ constexpr uint64_t kQueuePerSample = 2048;
 constexpr uint64_t kInlineWork = 4096;
 constexpr uint64_t kQueueMax = 1ull << 26;
 
+// The queue is kept in kQueueParts parts, a workgroup's own (by its number) to
+// reserve in, and to claim from before the others': returning atomics on one
+// address take about 13 ns each, one after the other, which for 122,000 chunks
+// would be 1.6 ms.
 struct Queue {
   uint4* job;                   // {kind, sample, first, last}
-  unsigned long long cap;
-  unsigned long long* tail;     // reserved entries (may pass cap: those are done in place)
+  unsigned long long cap;       // entries of a part
+  unsigned long long* tail;     // per part (kQueueStep apart): reserved entries (may pass cap: those are done in place)
   unsigned long long* head;     // claimed entries
-  uint32_t* tcls;               // per pair sample: |T n A_q|, q = 1..3
+  uint4* info;                  // per pair sample: |T n A_q|, q = 1..3, and its position in e2
+  uint32_t* info3;              // per 3-node sample: its position in e3
   uint32_t ct, cr, cx, ch;      // chunk sizes: nodes of T, correction items, exception positions, hyperedges
   uint64_t inline_work;         // pair samples with a smaller bound on visited positions walk in place
 };
@@ -121,9 +129,11 @@ struct Queue {
 // caller then does the work in place; entries it reserved below cap are
 // marked empty).
 __device__ inline unsigned long long queue_reserve(const Queue& q, uint32_t n) {
-  const unsigned long long base = atomicAdd(q.tail, (unsigned long long)n);
-  if (base + n <= q.cap) return base;
-  for (unsigned long long e = base; e < q.cap && e < base + n; ++e) q.job[e] = make_uint4(kJobNone, 0, 0, 0);
+  const uint32_t part = blockIdx.x % kQueueParts;
+  const unsigned long long base = atomicAdd(q.tail + part * kQueueStep, (unsigned long long)n);
+  if (base + n <= q.cap) return part * q.cap + base;
+  for (unsigned long long e = base; e < q.cap && e < base + n; ++e)
+    q.job[part * q.cap + e] = make_uint4(kJobNone, 0, 0, 0);
   return ~0ull;
 }
 
@@ -173,7 +183,10 @@ __device__ void sample_j3_k4(const View& v, const PairLinks& pl, const Queue& q,
       const uint64_t jobs = (x.total + q.cx - 1) / q.cx;
       unsigned long long base = ~0ull;
       if (q.job && jobs > 1) {
-        if (lane == 0) base = queue_reserve(q, uint32_t(jobs));
+        if (lane == 0) {
+          base = queue_reserve(q, uint32_t(jobs));
+          q.info3[s] = uint32_t(i);
+        }
         base = __shfl(base, 0, kWave);
       }
       if (base == ~0ull) {
@@ -201,6 +214,7 @@ struct NodeStats {
   const unsigned long long* tri;   // triangles at the node
   const unsigned long long* nbr;   // sum of the neighbours' degrees
   const uint32_t* h3;              // 3-node hyperedges {x, y, z} at x by (x~y, x~z, y~z), y < z
+  const uint8_t* e3_pat;           // per 3-node hyperedge {a < b < c}: a~b, a~c, b~c (bits 0..2)
 };
 
 // j = 2 at order 4 without bit rows, for the sampled pair e = {s, o}, s the
@@ -224,62 +238,89 @@ struct NodeStats {
 //   holding e one by one.
 // One workgroup per sample; the walks over T and over the corrections of a
 // heavy sample go to the work queue in chunks.
+// Items of a flat walk at once.  (Held at 128, and the filters at 16,384 bits,
+// so that six workgroups of the drain fit a CU.)
+constexpr uint32_t kFlat = 128;
 struct J2SparseLds {
   uint32_t tcls[4];
   uint32_t tlo[4];   // nodes of T below s, by class
-  // flat walks over up to 256 items, each with up to three row segments
-  uint32_t pre[kThreads + 1];
+  // flat walks over up to kFlat items, each with up to three row segments
+  uint32_t pre[kFlat + 1];
   uint32_t wave_tot[kWavesPerBlock];
-  uint32_t item[kThreads];
-  uint32_t seg_base[kThreads][3];
-  uint32_t seg_len[kThreads][3];
-  uint32_t cnt[kThreads][11];
-  int row[kThreads];   // dense adjacency row of the item's node, or -1 (walk over T)
-  // the sorted lists the correction walk searches, when they fit (at most
-  // kHeldList entries): T and the pairwise row of s
-  uint32_t t_list[1024], s_list[1024];
+  uint32_t seg_base[kFlat][3];
+  uint32_t seg_len[kFlat][3];
+  uint32_t cnt[kFlat][11];
+  int row[kFlat];   // dense adjacency row of the item's node, or -1 (walk over T)
+  uint32_t node[kFlat], deg[kFlat];   // the item's node and its degree (walk over T)
+  // T and the pairwise row of s as filters (bit z mod kFilterBits): a node
+  // whose bit is clear is not in the set, which settles most of them
+  uint32_t t_set[512], s_set[512];
+  // counts of sets by pattern of their pairs (the sampled pair set), in copies
+  // by lane so that a wavefront's additions to few patterns do not queue up on
+  // one address (64-bit class counters did); j2_flush makes them class counts
+  uint32_t bins[32][32];
 };
-constexpr uint32_t kHeldList = 1024;
+constexpr uint32_t kFilterBits = 16384;
+constexpr uint32_t kFilterMost = 4096;   // entries of a set that is filtered
+// samples or jobs after which the 32-bit counts go to the class counters
+constexpr uint32_t kJobsPerFlush = 8;
 
-// Whether z is in the ascending list l[0, n) (LDS).
-__device__ inline bool lds_find(const uint32_t* l, uint32_t n, uint32_t z) {
-  uint32_t lo = 0, hi = n;
-  while (hi > lo) {
-    const uint32_t m = (lo + hi) >> 1;
-    const uint32_t y = l[m];
-    if (y == z) return true;
-    if (y < z) lo = m + 1; else hi = m;
-  }
-  return false;
+// n sets whose pattern of pairs is pat (bit 0 set, no larger hyperedge).
+__device__ inline void jadd(J2SparseLds& L, uint32_t pat, uint32_t n) {
+  const uint32_t i = ((pat >> 1) & 3u) | (((pat >> 4) & 3u) << 2) | (((pat >> 7) & 1u) << 4);
+  atomicAdd(&L.bins[i][threadIdx.x & 31u], n);
 }
 
-// Walk, for items [first, last) 256 at a time, the concatenated segments
+__device__ inline void j2_clear(J2SparseLds& L) {
+  for (uint32_t i = threadIdx.x; i < 32 * 32; i += kThreads) (&L.bins[0][0])[i] = 0;
+}
+
+// The counts of jadd (signed 32-bit sums) into the class counters; every
+// thread of the workgroup calls this, between barriers.
+__device__ inline void j2_flush(J2SparseLds& L, const uint8_t* lut, unsigned long long* h) {
+  const uint32_t i = threadIdx.x / 8, part = threadIdx.x % 8;
+  long long n = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) {
+    n += int32_t(L.bins[i][part * 4 + k]);
+    L.bins[i][part * 4 + k] = 0;
+  }
+#pragma unroll
+  for (int d = 4; d > 0; d >>= 1) n += __shfl_xor(n, d, kWave);
+  if (part == 0 && n) {
+    const uint8_t c = lut[1u | ((i & 3u) << 1) | (((i >> 2) & 3u) << 4) | ((i >> 4) << 7)];
+    if (c != 0xFF) atomicAdd(&h[c], (unsigned long long)n);
+  }
+}
+
+// Walk, for items [first, last) kFlat at a time, the concatenated segments
 // seg(i) defines (up to three, each a start and a length), as one flat range
 // over the workgroup: body(slot, segment, position) for every position; then
 // fin(slot, item) once per item.  Every thread must call it.
 template <typename Seg, typename Body, typename Fin>
 __device__ void block_flat(uint32_t first, uint32_t last, J2SparseLds& L, Seg seg, Body body, Fin fin) {
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-  for (uint32_t c0 = first; c0 < last; c0 += kThreads) {
+  for (uint32_t c0 = first; c0 < last; c0 += kFlat) {
     uint32_t len = 0;
-    L.seg_len[tid][0] = L.seg_len[tid][1] = L.seg_len[tid][2] = 0;
-    for (int q = 0; q < 11; ++q) L.cnt[tid][q] = 0;
-    if (c0 + tid < last) {
-      seg(c0 + tid, L.seg_base[tid], L.seg_len[tid]);
-      len = L.seg_len[tid][0] + L.seg_len[tid][1] + L.seg_len[tid][2];
+    if (tid < kFlat) {
+      L.seg_len[tid][0] = L.seg_len[tid][1] = L.seg_len[tid][2] = 0;
+      for (int q = 0; q < 11; ++q) L.cnt[tid][q] = 0;
+      if (c0 + tid < last) {
+        seg(c0 + tid, L.seg_base[tid], L.seg_len[tid]);
+        len = L.seg_len[tid][0] + L.seg_len[tid][1] + L.seg_len[tid][2];
+      }
     }
-    L.item[tid] = c0 + tid;
     uint32_t wtot;
     uint32_t off = wave_exclusive_scan(len, &wtot);
     if (lane == 0) L.wave_tot[wv] = wtot;
     __syncthreads();
     for (uint32_t q = 0; q < wv; ++q) off += L.wave_tot[q];
-    L.pre[tid] = off;
-    if (tid == kThreads - 1) L.pre[kThreads] = off + len;
+    if (tid < kFlat) L.pre[tid] = off;
+    if (tid == kFlat - 1) L.pre[kFlat] = off + len;
     __syncthreads();
-    const uint32_t work = L.pre[kThreads];
+    const uint32_t work = L.pre[kFlat];
     for (uint32_t t = tid; t < work; t += kThreads) {
-      uint32_t lo = 0, hi = kThreads;   // pre[lo] <= t < pre[hi]
+      uint32_t lo = 0, hi = kFlat;   // pre[lo] <= t < pre[hi]
       while (hi - lo > 1) {
         const uint32_t m = (lo + hi) >> 1;
         if (L.pre[m] <= t) lo = m; else hi = m;
@@ -292,13 +333,10 @@ __device__ void block_flat(uint32_t first, uint32_t last, J2SparseLds& L, Seg se
       body(lo, sg, L.seg_base[lo][sg] + k);
     }
     __syncthreads();
-    if (c0 + tid < last) fin(tid, c0 + tid);
+    if (tid < kFlat && c0 + tid < last) fin(tid, c0 + tid);
     __syncthreads();
   }
 }
-
-struct J2Ctx;
-__device__ inline void j2_hold_lists(const View& v, const PairLinks& pl, const J2Ctx& c, J2SparseLds& L);
 
 struct J2Ctx {
   uint32_t e0, s, o, ds, dO;
@@ -376,33 +414,53 @@ __device__ inline uint32_t j2_agg_pat_t(const J2Ctx& c, uint32_t t, uint32_t cls
 // |N(t) n N(s)| and |N(t) n N(s) n N(o)| (the shorter of the two rows walked)
 // and |N(t) n N(o)| (likewise); those inside T from the shorter of N(t) and T
 // (all of them, and those after t, which take each joined pair inside T once).
-// T (the run of {s, o}) and the row of s, both ascending, into LDS when they
-// have at most kHeldList entries.  Every thread of the workgroup calls this.
-__device__ inline void j2_hold_lists(const View& v, const PairLinks& pl, const J2Ctx& c, J2SparseLds& L) {
+// T (the run of {s, o}) and the row of s into their filters when they have at
+// most kFilterMost entries (the row only with_s).  Every thread of the
+// workgroup calls this.
+struct J2Sets {
+  bool t, s;   // filtered
+};
+__device__ inline J2Sets j2_sets(const View& v, const PairLinks& pl, const J2Ctx& c, J2SparseLds& L, bool with_s) {
   const uint32_t n_t = uint32_t(c.thi - c.tlo), sb = v.g2_off[c.s];
-  const bool hold_t = c.any_t && n_t <= kHeldList, hold_s = c.ds <= kHeldList;
-  for (uint32_t i = threadIdx.x; i < (hold_t ? n_t : 0u); i += kThreads) L.t_list[i] = pl.third[c.tlo + i];
-  for (uint32_t i = threadIdx.x; i < (hold_s ? c.ds : 0u); i += kThreads) L.s_list[i] = v.g2_adj[sb + i];
+  const J2Sets f{c.any_t && n_t <= kFilterMost, with_s && c.ds <= kFilterMost};
+  for (uint32_t i = threadIdx.x; i < (f.t ? kFilterBits / 32 : 0u); i += kThreads) L.t_set[i] = 0;
+  for (uint32_t i = threadIdx.x; i < (f.s ? kFilterBits / 32 : 0u); i += kThreads) L.s_set[i] = 0;
   __syncthreads();
+  for (uint32_t i = threadIdx.x; i < (f.t ? n_t : 0u); i += kThreads) {
+    const uint32_t z = pl.third[c.tlo + i] % kFilterBits;
+    atomicOr(&L.t_set[z >> 5], 1u << (z & 31));
+  }
+  for (uint32_t i = threadIdx.x; i < (f.s ? c.ds : 0u); i += kThreads) {
+    const uint32_t z = v.g2_adj[sb + i] % kFilterBits;
+    atomicOr(&L.s_set[z >> 5], 1u << (z & 31));
+  }
+  __syncthreads();
+  return f;
+}
+__device__ inline bool filter_has(const uint32_t* set, uint32_t z) {
+  return (set[(z % kFilterBits) >> 5] >> (z & 31)) & 1u;
+}
+// s ~ z, and z in T, by the filters first
+__device__ inline uint32_t j2_s_adj(const View& v, const PairLinks& pl, const J2Ctx& c, const J2SparseLds& L, J2Sets f,
+                                    uint32_t z) {
+  return f.s && !filter_has(L.s_set, z) ? 0u : j2_s_adj(v, pl, c, z);
+}
+__device__ inline uint32_t j2_in_t(const View& v, const J2Ctx& c, const J2SparseLds& L, J2Sets f, uint32_t z) {
+  return f.t && !filter_has(L.t_set, z) ? 0u : uint32_t(j2_in_t(v, c, z));
 }
 
-__device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t tc1, uint32_t tc2, uint32_t tc3,
+__device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, J2Sets f, uint32_t tc1, uint32_t tc2, uint32_t tc3,
                           uint32_t first, uint32_t last, J2SparseLds& L, const uint8_t* lut, unsigned long long* h) {
   const uint32_t n_t = uint32_t(c.thi - c.tlo);
-  j2_hold_lists(v, pl, c, L);
-  const bool hold_t = c.any_t && n_t <= kHeldList, hold_s = c.ds <= kHeldList;
-  auto s_adj = [&](uint32_t z) {
-    return hold_s ? uint32_t(lds_find(L.s_list, c.ds, z)) : j2_s_adj(v, pl, c, z);
-  };
-  auto in_t = [&](uint32_t y) {
-    return c.any_t && (hold_t ? lds_find(L.t_list, n_t, y) : has3(v.hs3, c.s, c.o, y));
-  };
+  auto s_adj = [&](uint32_t z) { return j2_s_adj(v, pl, c, L, f, z); };
   block_flat(
       first, last, L,
       [&](uint32_t j, uint32_t* base, uint32_t* len) {
         const uint32_t t = j2_t_node(v, pl, c, c.tlo + j);
         const uint32_t dt = deg2_of(v, t);
         L.row[threadIdx.x] = hub_of(pl, t);
+        L.node[threadIdx.x] = t;
+        L.deg[threadIdx.x] = dt;
         base[0] = dt <= c.ds ? v.g2_off[t] : v.g2_off[c.s];
         len[0] = dt <= c.ds ? dt : c.ds;
         base[1] = dt <= c.dO ? v.g2_off[t] : v.g2_off[c.o];
@@ -411,35 +469,48 @@ __device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, ui
         len[2] = dt <= n_t ? dt : n_t;
       },
       [&](uint32_t slot, uint32_t sg, uint32_t pos) {
-        const uint32_t t = j2_t_node(v, pl, c, c.tlo + L.item[slot]);
-        const uint32_t dt = deg2_of(v, t);
+        const uint32_t t = L.node[slot], dt = L.deg[slot];
         auto t_adj = [&](uint32_t z) {
           const int r = L.row[slot];
           return r >= 0 ? hub_adj(pl, r, z) : uint32_t(has2(v.hs2, t, z));
         };
+        uint32_t bump = 0;   // the item's counters that go up
         if (sg == 0) {
           const uint32_t z = v.g2_adj[pos];
-          const uint32_t hit = dt <= c.ds ? s_adj(z) : t_adj(z);
-          if (hit) {
-            atomicAdd(&L.cnt[slot][0], 1u);
-            if (j2_o_adj(v, pl, c, z)) atomicAdd(&L.cnt[slot][1], 1u);
-          }
+          if (dt <= c.ds ? s_adj(z) : t_adj(z)) bump = 1u | (j2_o_adj(v, pl, c, z) << 1);
         } else if (sg == 1) {
           const uint32_t z = v.g2_adj[pos];
-          if (dt <= c.dO ? j2_o_adj(v, pl, c, z) : t_adj(z)) atomicAdd(&L.cnt[slot][2], 1u);
+          if (dt <= c.dO ? j2_o_adj(v, pl, c, z) : t_adj(z)) bump = 1u << 2;
         } else {
-          uint32_t y, cy;
+          uint32_t y, cy = 0;
+          bool joined = false;
           if (dt <= n_t) {
             y = v.g2_adj[pos];
-            if (y == c.s || y == c.o || !in_t(y)) return;
-            cy = s_adj(y) | (j2_o_adj(v, pl, c, y) << 1);
+            joined = y != c.s && y != c.o && j2_in_t(v, c, L, f, y);
+            if (joined) cy = s_adj(y) | (j2_o_adj(v, pl, c, y) << 1);
           } else {
             y = j2_t_node(v, pl, c, pos);
-            if (y == t || !t_adj(y)) return;
-            cy = j2_t_cls(pl, c, pos);
+            joined = y != t && t_adj(y);
+            if (joined) cy = j2_t_cls(pl, c, pos);
           }
-          atomicAdd(&L.cnt[slot][3 + cy], 1u);
-          if (y > t) atomicAdd(&L.cnt[slot][7 + cy], 1u);
+          if (joined) bump = (1u << (3 + cy)) | (y > t ? 1u << (7 + cy) : 0u);
+        }
+        // (neighbouring positions mostly belong to one item: their counts are
+        // then added once)
+        const unsigned long long any = __ballot(bump != 0);
+        if (!any) return;
+        const uint32_t one = uint32_t(__builtin_amdgcn_readlane(int(slot), __ffsll(any) - 1));
+        if (__ballot(bump && slot != one)) {
+#pragma unroll
+          for (uint32_t k = 0; k < 11; ++k)
+            if ((bump >> k) & 1u) atomicAdd(&L.cnt[slot][k], 1u);
+        } else {
+#pragma unroll
+          for (uint32_t k = 0; k < 11; ++k) {
+            const unsigned long long m = __ballot((bump >> k) & 1u);
+            if (m && __ffsll(any) - 1 == int(threadIdx.x & (kWave - 1)))
+              atomicAdd(&L.cnt[one][k], uint32_t(__popcll(m)));
+          }
         }
       },
       [&](uint32_t slot, uint32_t j) {
@@ -489,12 +560,9 @@ __device__ void j2_walk_t(const View& v, const PairLinks& pl, const J2Ctx& c, ui
 // qualify).  What depends on y alone (y ~ s, y ~ o, y in T) is looked up once
 // per y and kept in the item's counters; each hyperedge then needs s ~ z,
 // o ~ z, y ~ z, z in T and whether {s, y, z} is a 3-node hyperedge.
-__device__ void j2_walk_r(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t first, uint32_t last,
-                          J2SparseLds& L, const uint8_t* lut, unsigned long long* h) {
+__device__ void j2_walk_r(const View& v, const PairLinks& pl, const J2Ctx& c, J2Sets f, uint32_t first, uint32_t last,
+                          J2SparseLds& L) {
   const uint32_t sb = v.g2_off[c.s];
-  const uint32_t n_t = uint32_t(c.thi - c.tlo);
-  j2_hold_lists(v, pl, c, L);
-  const bool hold_t = c.any_t && n_t <= kHeldList, hold_s = c.ds <= kHeldList;
   auto y_of = [&](uint32_t j) { return j < c.ds ? v.g2_adj[sb + j] : j2_t_node(v, pl, c, c.tlo + (j - c.ds)); };
   block_flat(
       first, last, L,
@@ -520,9 +588,7 @@ __device__ void j2_walk_r(const View& v, const PairLinks& pl, const J2Ctx& c, ui
         L.cnt[threadIdx.x][3] = slen;
         // y ~ s holds exactly for the first part of the list (a node of T
         // adjacent to s was taken there); y is in T in the second part
-        const uint32_t sy = j < c.ds,
-                       ty = j < c.ds ? uint32_t(c.any_t && (hold_t ? lds_find(L.t_list, n_t, y) : j2_in_t(v, c, y)))
-                                     : 1u;
+        const uint32_t sy = j < c.ds, ty = j < c.ds ? j2_in_t(v, c, L, f, y) : 1u;
         const uint32_t oy = j < c.ds ? j2_o_adj(v, pl, c, y) : (ycls >> 1);
         L.cnt[threadIdx.x][0] = y;
         L.cnt[threadIdx.x][1] = sy | (oy << 1) | (ty << 2);
@@ -537,77 +603,53 @@ __device__ void j2_walk_r(const View& v, const PairLinks& pl, const J2Ctx& c, ui
         const uint32_t oz = c.o < y ? (za & 1u) : (za >> 1), yz = c.o < y ? (za >> 1) : (za & 1u);
         // s ~ z; {s, o, z} a 3-node hyperedge exactly when z is in T, the run
         // of {s, o} (sorted by third node)
-        const uint32_t sz = hold_s ? uint32_t(lds_find(L.s_list, c.ds, z))
-                                   : (c.rs >= 0 ? hub_adj(pl, c.rs, z) : uint32_t(has2(v.hs2, c.s, z)));
-        const uint32_t tz = c.any_t && (hold_t ? lds_find(L.t_list, n_t, z) : run_find(pl, c.tlo, n_t, z) != ~0ull);
+        const uint32_t sz = j2_s_adj(v, pl, c, L, f, z), tz = j2_in_t(v, c, L, f, z);
         if (z < y && (sz | tz)) return;   // taken from z
         // as the histogram at o counts it (the smaller node first)
         const uint32_t olo = y < z ? oy : oz, ohi = y < z ? oz : oy;
-        hadd(lut, h, 1u | (olo << 2) | (ohi << 5) | (yz << 7), 1);
+        jadd(L, 1u | (olo << 2) | (ohi << 5) | (yz << 7), 1u);
         const uint32_t slen = L.cnt[slot][3];
         if (slen && run_find(pl, L.cnt[slot][2], slen, z) != ~0ull) return;   // removed at s
         // the pair {y, z} outside X whose set holds {o, y, z}, taken off
         if (ty | tz) return;
-        hsub(lut, h, 1u | (sy << 1) | (oy << 2) | (sz << 4) | (oz << 5) | (yz << 7), 1);
+        jadd(L, 1u | (sy << 1) | (oy << 2) | (sz << 4) | (oz << 5) | (yz << 7), ~0u);
       },
       [](uint32_t, uint32_t) {});
 }
 
-// The lookups of an item of the two passes below, for its two nodes y < z
-// outside e: their pairs with s and o and with each other, and whether
-// {s, o, y}, {s, o, z} are 3-node hyperedges.  The first slot of every probe
-// is loaded by start, so that they take one round of latency together.
-struct J2Item {
-  Probe64 psy, psz, poy, poz, pyz;
-  Probe128 pty, ptz;
-  uint32_t sy, sz, oy, oz, yz, ty, tz;
-  __device__ void start(const View& v, const J2Ctx& c, uint32_t y, uint32_t z) {
-    if (c.rs < 0) {
-      psy = probe2_start(v.hs2, c.s, y);
-      psz = probe2_start(v.hs2, c.s, z);
-    }
+// The 3-node hyperedges at s, entries [first, last) of its incidence row, one
+// by one (with the hyperedges at o that match one at s on the far side): the
+// pairs of a hyperedge {s, y, z} come with it (e3_pat), o ~ y and o ~ z are
+// looked up, T only where its filter has y or z, and {o, y, z} only when
+// neither is near s.
+__device__ void j2_pass_s(const View& v, const PairLinks& pl, const uint8_t* __restrict__ e3_pat, const J2Ctx& c,
+                          J2Sets f, uint32_t first, uint32_t last, J2SparseLds& L) {
+  const uint32_t row = v.i3_off[c.s];
+  for (uint32_t p = row + first + threadIdx.x; p < row + last; p += kThreads) {
+    const uint32_t i = v.i3_idx[p];
+    const uint32_t* m = v.e3 + 3ull * i;
+    const uint32_t f0 = m[0], f1 = m[1], f2 = m[2], pat = e3_pat[i];
+    if (f0 == c.o || f1 == c.o || f2 == c.o) continue;
+    const uint32_t y = f0 == c.s ? f1 : f0, z = f2 == c.s ? f1 : f2;
+    Probe64 poy, poz;
     if (c.ro < 0) {
       poy = probe2_start(v.hs2, c.o, y);
       poz = probe2_start(v.hs2, c.o, z);
     }
-    pyz = probe2_start(v.hs2, y, z);
-    if (c.any_t) {
-      pty = probe3_start(v.hs3, c.s, c.o, y);
-      ptz = probe3_start(v.hs3, c.s, c.o, z);
-    }
-  }
-  __device__ void end(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t y, uint32_t z) {
-    sy = c.rs >= 0 ? hub_adj(pl, c.rs, y) : uint32_t(probe64_end(v.hs2, psy));
-    sz = c.rs >= 0 ? hub_adj(pl, c.rs, z) : uint32_t(probe64_end(v.hs2, psz));
-    oy = c.ro >= 0 ? hub_adj(pl, c.ro, y) : uint32_t(probe64_end(v.hs2, poy));
-    oz = c.ro >= 0 ? hub_adj(pl, c.ro, z) : uint32_t(probe64_end(v.hs2, poz));
-    yz = probe64_end(v.hs2, pyz);
-    ty = c.any_t && probe128_end(v.hs3, pty);
-    tz = c.any_t && probe128_end(v.hs3, ptz);
-  }
-  // the pair {y, z} outside X whose set holds a larger hyperedge, taken off
-  __device__ void remove(const uint8_t* lut, unsigned long long* h) const {
-    if (!(ty | tz)) hsub(lut, h, 1u | (sy << 1) | (oy << 2) | (sz << 4) | (oz << 5) | (yz << 7), 1);
-  }
-};
-
-// The 3-node hyperedges at s, entries [first, last) of its incidence row, one
-// by one (with the hyperedges at o that match one at s on the far side).
-__device__ void j2_pass_s(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t first, uint32_t last,
-                          uint32_t lane, uint32_t stride, const uint8_t* lut, unsigned long long* h) {
-  for (uint32_t p = v.i3_off[c.s] + first + lane; p < v.i3_off[c.s] + last; p += stride) {
-    const uint32_t* f = v.e3 + 3ull * v.i3_idx[p];
-    const uint32_t f0 = f[0], f1 = f[1], f2 = f[2];
-    if (f0 == c.o || f1 == c.o || f2 == c.o) continue;
-    const uint32_t y = f0 == c.s ? f1 : f0, z = f2 == c.s ? f1 : f2;
-    J2Item it;
-    it.start(v, c, y, z);
-    const Probe128 po = probe3_start(v.hs3, c.o, y, z);
-    it.end(v, pl, c, y, z);
-    it.remove(lut, h);
+    // pat: bit 0 f0 ~ f1, bit 1 f0 ~ f2, bit 2 f1 ~ f2
+    const uint32_t ab = pat & 1u, ac = (pat >> 1) & 1u, bc = pat >> 2;
+    const uint32_t sy = f2 == c.s ? ac : ab, sz = f0 == c.s ? ac : bc;
+    const uint32_t yz = f0 == c.s ? bc : (f1 == c.s ? ac : ab);
+    const uint32_t ty = j2_in_t(v, c, L, f, y), tz = j2_in_t(v, c, L, f, z);
+    const bool far = !(sy | ty | sz | tz);
+    Probe128 po;
+    if (far) po = probe3_start(v.hs3, c.o, y, z);
+    const uint32_t oy = c.ro >= 0 ? hub_adj(pl, c.ro, y) : uint32_t(probe64_end(v.hs2, poy));
+    const uint32_t oz = c.ro >= 0 ? hub_adj(pl, c.ro, z) : uint32_t(probe64_end(v.hs2, poz));
+    // the pair {y, z} outside X whose set holds the hyperedge, taken off
+    if (!(ty | tz)) jadd(L, 1u | (sy << 1) | (oy << 2) | (sz << 4) | (oz << 5) | (yz << 7), ~0u);
     // a 3-node hyperedge {o, y, z} away from s, as the histogram at o counts it
-    if (!(it.sy | it.ty | it.sz | it.tz) && probe128_end(v.hs3, po))
-      hadd(lut, h, 1u | (it.oy << 2) | (it.oz << 5) | (it.yz << 7), 1);
+    if (far && probe128_end(v.hs3, po)) jadd(L, 1u | (oy << 2) | (oz << 5) | (yz << 7), 1u);
   }
 }
 
@@ -618,9 +660,9 @@ __device__ inline uint32_t j2_q_node(const View& v, const J2Ctx& c) {
   return fs <= fo ? c.s : c.o;
 }
 __device__ void j2_pass_q(const View& v, const PairLinks& pl, const J2Ctx& c, uint32_t first, uint32_t last,
-                          uint32_t lane, uint32_t stride, const uint8_t* lut, unsigned long long* h) {
+                          J2SparseLds& L) {
   const uint32_t a = j2_q_node(v, c), other = a == c.s ? c.o : c.s;
-  for (uint32_t p = v.i4_off[a] + first + lane; p < v.i4_off[a] + last; p += stride) {
+  for (uint32_t p = v.i4_off[a] + first + threadIdx.x; p < v.i4_off[a] + last; p += kThreads) {
     const uint32_t* f = v.e4 + 4ull * v.i4_idx[p];
     const uint32_t g0 = f[0], g1 = f[1], g2 = f[2], g3 = f[3];
     if (g0 != other && g1 != other && g2 != other && g3 != other) continue;
@@ -629,13 +671,26 @@ __device__ void j2_pass_q(const View& v, const PairLinks& pl, const J2Ctx& c, ui
       if (m == c.s || m == c.o) continue;
       if (x == 0xFFFFFFFFu) x = m; else y = m;
     }
-    J2Item it;
-    it.start(v, c, x, y);
     const Probe128 ps = probe3_start(v.hs3, c.s, x, y), po = probe3_start(v.hs3, c.o, x, y);
-    it.end(v, pl, c, x, y);
+    const Probe64 pxy = probe2_start(v.hs2, x, y);
     if (probe128_end(v.hs3, ps) || probe128_end(v.hs3, po)) continue;   // removed with a 3-node hyperedge
-    it.remove(lut, h);
+    if (j2_in_t(v, c, x) || j2_in_t(v, c, y)) continue;                // not outside X
+    const uint32_t cx = j2_cls(v, pl, c, x), cy = j2_cls(v, pl, c, y);
+    jadd(L, j2_pat(cx, cy, uint32_t(probe64_end(v.hs2, pxy))), ~0u);
   }
+}
+
+// All walks and passes of a sampled pair.  Every thread of the workgroup calls
+// this.
+__device__ void j2_whole(const View& v, const PairLinks& pl, const uint8_t* __restrict__ e3_pat, const J2Ctx& c,
+                         uint32_t tc1, uint32_t tc2, uint32_t tc3, J2SparseLds& L, const uint8_t* lut,
+                         unsigned long long* h) {
+  const J2Sets f = j2_sets(v, pl, c, L, true);
+  const uint32_t n_t = uint32_t(c.thi - c.tlo), q = j2_q_node(v, c);
+  j2_pass_s(v, pl, e3_pat, c, f, 0, v.i3_off[c.s + 1] - v.i3_off[c.s], L);
+  j2_pass_q(v, pl, c, 0, v.i4_off[q + 1] - v.i4_off[q], L);
+  if (n_t) j2_walk_t(v, pl, c, f, tc1, tc2, tc3, 0, n_t, L, lut, h);
+  j2_walk_r(v, pl, c, f, 0, c.ds + n_t, L);
 }
 
 __device__ void sample_j2_k4_sparse(const View& v, const PairLinks& pl, const NodeStats& ns,
@@ -644,6 +699,9 @@ __device__ void sample_j2_k4_sparse(const View& v, const PairLinks& pl, const No
                                     unsigned long long* h_lds, unsigned long long* rows) {
   const uint32_t tid = threadIdx.x;
   __shared__ unsigned long long q_base;
+  uint32_t done = 0;
+  j2_clear(L);
+  __syncthreads();
   for (uint64_t smp = part; smp < d.S[2]; smp += n_parts) {
     const uint64_t i = d.at(2, smp);
     if (i >= d.n[2]) continue;
@@ -742,7 +800,8 @@ __device__ void sample_j2_k4_sparse(const View& v, const PairLinks& pl, const No
     const uint32_t qn = j2_q_node(v, c), n_q = v.i4_off[qn + 1] - v.i4_off[qn];
     const uint32_t jobs_t = (n_t + q.ct - 1) / q.ct, jobs_r = (n_r + q.cr - 1) / q.cr;
     const uint32_t jobs_s = (n_s + q.ch - 1) / q.ch, jobs_q = (n_q + q.ch - 1) / q.ch;
-    const uint32_t jobs = jobs_t + jobs_r + jobs_s + jobs_q;
+    const bool whole = max(max(jobs_t, jobs_r), max(jobs_s, jobs_q)) <= kWholeChunks;
+    const uint32_t jobs = whole ? 1u : jobs_t + jobs_r + jobs_s + jobs_q;
     // the walks stay here only when a bound on the positions they visit is
     // small (the correction walk meets at most one run of 3-node hyperedges
     // at o per item); otherwise they go to the queue, whose claiming
@@ -753,18 +812,17 @@ __device__ void sample_j2_k4_sparse(const View& v, const PairLinks& pl, const No
     if (!here) {
       if (tid == 0) {
         q_base = queue_reserve(q, jobs);
-        if (q_base != ~0ull) {
-          q.tcls[3 * smp] = tc1;
-          q.tcls[3 * smp + 1] = tc2;
-          q.tcls[3 * smp + 2] = tc3;
-        }
+        if (q_base != ~0ull) q.info[smp] = make_uint4(tc1, tc2, tc3, uint32_t(i));
       }
       __syncthreads();
       here = q_base == ~0ull;
       if (!here) {
         for (uint32_t k = tid; k < jobs; k += kThreads) {
           uint32_t kind, first, last;
-          if (k < jobs_t) {
+          if (whole) {
+            kind = kJobPairAll;
+            first = last = 0;
+          } else if (k < jobs_t) {
             kind = kJobPairT;
             first = k * q.ct;
             last = min(first + q.ct, n_t);
@@ -785,18 +843,19 @@ __device__ void sample_j2_k4_sparse(const View& v, const PairLinks& pl, const No
         }
       }
     }
-    if (here) {
-      j2_pass_s(v, pl, c, 0, n_s, tid, kThreads, lut, h);
-      j2_pass_q(v, pl, c, 0, n_q, tid, kThreads, lut, h);
-      j2_walk_t(v, pl, c, tc1, tc2, tc3, 0, n_t, L, lut, h);
-      j2_walk_r(v, pl, c, 0, n_r, L, lut, h);
-    }
+    if (here) j2_whole(v, pl, ns.e3_pat, c, tc1, tc2, tc3, L, lut, h);
     __syncthreads();
     if (rows) {
+      j2_flush(L, lut, h);
+      __syncthreads();
       flush_row(h_lds, rows + smp * 256, tid, kThreads);
+      __syncthreads();
+    } else if (++done % kJobsPerFlush == 0) {
+      j2_flush(L, lut, h);
       __syncthreads();
     }
   }
+  j2_flush(L, lut, h_lds);
 }
 
 // j = 2 at order 4 with adjacency bit rows.  The kept sets for the sampled
@@ -1115,9 +1174,9 @@ __global__ void __launch_bounds__(kThreads) k_finish_sampled(SampledArgs a, Scal
     a.est[c] = float(e);
     if (a.raw) a.raw[c] = int64_t(r);
   }
-  if (c == 0) {
-    *a.q.tail = 0;
-    *a.q.head = 0;
+  if (c < int(kQueueParts)) {
+    a.q.tail[c * kQueueStep] = 0;
+    a.q.head[c * kQueueStep] = 0;
   }
 }
 
@@ -1125,8 +1184,10 @@ __global__ void __launch_bounds__(kThreads) k_finish_sampled(SampledArgs a, Scal
 // workgroups for the sampled pairs, then a.blocks[3] for the 3-node and
 // a.blocks[4] for the 4-node hyperedges.  Each workgroup adds its LDS counts to
 // a.hist (k_finish_sampled scales them).
+// (without bit rows: held to the registers of six wavefronts per SIMD, 0.51 ->
+// 0.46 ms on the communication graph at 2%)
 template <int K, bool BITS>
-__global__ void __launch_bounds__(kThreads) k_sampled(SampledArgs a) {
+__global__ void __launch_bounds__(kThreads, K == 4 && !BITS ? 6 : 1) k_sampled(SampledArgs a) {
   constexpr int kLut = K == 4 ? 2048 : 16;
   __shared__ uint8_t lut[kLut];
   __shared__ unsigned long long h_lds[256];
@@ -1164,22 +1225,41 @@ __global__ void __launch_bounds__(kThreads) k_sampled(SampledArgs a) {
 }
 
 // Drain the work queue that k_sampled filled (without bit rows).  Its jobs are
-// chains of dependent lookups: held to the registers of four wavefronts per
-// SIMD (4.07 -> 3.48 ms per estimate on the communication graph at 2%).
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) k_sampled_drain(SampledArgs a) {
+// chains of dependent lookups, so what counts is how many are under way: held
+// to the registers (with some scratch) and LDS of six workgroups a CU, the next
+// job claimed while one is done.  2.85 -> 2.03 ms on the communication graph at
+// 2% (106,000 jobs); the same with four workgroups a CU 2.57.
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) k_sampled_drain(SampledArgs a) {
   __shared__ uint8_t lut[2048];
   __shared__ unsigned long long h_lds[256];
   __shared__ J2SparseLds L;
   __shared__ uint4 job;
-  __shared__ uint32_t tcls[3];
   load_lut(lut, a.lut, 2048);
   h_lds[threadIdx.x] = 0;
-  const unsigned long long n_jobs = min(__hip_atomic_load(a.q.tail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), a.q.cap);
+  j2_clear(L);
+  uint32_t done = 0;
+  // (thread 0: the part it claims from, the part's jobs, and the next job's
+  // claim, which is on its way while the workgroup does the job before)
+  uint32_t tried = 0, part = blockIdx.x % kQueueParts;
+  unsigned long long n_jobs = 0, k = 0;
+  auto jobs_of = [&](uint32_t q) {
+    return min(__hip_atomic_load(a.q.tail + q * kQueueStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), a.q.cap);
+  };
+  if (threadIdx.x == 0) {
+    n_jobs = jobs_of(part);
+    if (n_jobs) k = atomicAdd(a.q.head + part * kQueueStep, 1ull);
+  }
   for (;;) {
     __syncthreads();
     if (threadIdx.x == 0) {
-      const unsigned long long k = atomicAdd(a.q.head, 1ull);
-      job = k < n_jobs ? a.q.job[k] : make_uint4(0xFFFFFFFFu, 0, 0, 0);
+      while (k >= n_jobs && ++tried < kQueueParts) {
+        part = (blockIdx.x + tried) % kQueueParts;
+        n_jobs = jobs_of(part);
+        if (n_jobs) k = atomicAdd(a.q.head + part * kQueueStep, 1ull);
+      }
+      const bool got = k < n_jobs;
+      job = got ? a.q.job[part * a.q.cap + k] : make_uint4(0xFFFFFFFFu, 0, 0, 0);
+      if (got) k = atomicAdd(a.q.head + part * kQueueStep, 1ull);
     }
     __syncthreads();
     const uint4 jb = job;
@@ -1189,32 +1269,40 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     unsigned long long* h = h_lds;
     unsigned long long* row = nullptr;
     if (jb.x == kJobPairS || jb.x == kJobPairQ) {
-      const J2Ctx c = j2_ctx(a.v, a.pl, a.es, a.d.n[2], a.d.at(2, jb.y));
+      const J2Ctx c = j2_ctx(a.v, a.pl, a.es, a.d.n[2], a.q.info[jb.y].w);
       if (a.rows[2]) row = a.rows[2] + uint64_t(jb.y) * 256;
-      if (jb.x == kJobPairS) j2_pass_s(a.v, a.pl, c, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
-      else j2_pass_q(a.v, a.pl, c, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
-    } else if (jb.x == kJobPairT || jb.x == kJobPairR) {
-      const uint64_t i = a.d.at(2, jb.y);
-      const J2Ctx c = j2_ctx(a.v, a.pl, a.es, a.d.n[2], i);
+      if (jb.x == kJobPairS) j2_pass_s(a.v, a.pl, a.ns.e3_pat, c, j2_sets(a.v, a.pl, c, L, false), jb.z, jb.w, L);
+      else j2_pass_q(a.v, a.pl, c, jb.z, jb.w, L);
+    } else if (jb.x == kJobPairT || jb.x == kJobPairR || jb.x == kJobPairAll) {
+      const uint4 info = a.q.info[jb.y];
+      const J2Ctx c = j2_ctx(a.v, a.pl, a.es, a.d.n[2], info.w);
       if (a.rows[2]) row = a.rows[2] + uint64_t(jb.y) * 256;
-      if (jb.x == kJobPairT) {
-        if (threadIdx.x < 3) tcls[threadIdx.x] = a.q.tcls[3ull * jb.y + threadIdx.x];
-        __syncthreads();
-        j2_walk_t(a.v, a.pl, c, tcls[0], tcls[1], tcls[2], jb.z, jb.w, L, lut, h);
+      if (jb.x == kJobPairAll) {
+        j2_whole(a.v, a.pl, a.ns.e3_pat, c, info.x, info.y, info.z, L, lut, h);
+      } else if (jb.x == kJobPairT) {
+        const J2Sets f = j2_sets(a.v, a.pl, c, L, true);
+        j2_walk_t(a.v, a.pl, c, f, info.x, info.y, info.z, jb.z, jb.w, L, lut, h);
       } else {
-        j2_walk_r(a.v, a.pl, c, jb.z, jb.w, L, lut, h);
+        j2_walk_r(a.v, a.pl, c, j2_sets(a.v, a.pl, c, L, true), jb.z, jb.w, L);
       }
     } else if (jb.x == kJobTriple) {
-      const uint64_t i = a.d.at(3, jb.y);
+      const uint64_t i = a.q.info3[jb.y];
       const B4Ctx x = b4_ctx(a.v, a.pl, a.v.e3[3 * i], a.v.e3[3 * i + 1], a.v.e3[3 * i + 2]);
       if (a.rows[3]) row = a.rows[3] + uint64_t(jb.y) * 256;
       j3_exceptions(a.v, a.pl, x, jb.z, jb.w, threadIdx.x, kThreads, lut, h);
+    }
+    ++done;
+    if (row || done % kJobsPerFlush == 0) {
+      __syncthreads();
+      j2_flush(L, lut, h);
     }
     if (row) {
       __syncthreads();
       flush_row(h_lds, row, threadIdx.x, kThreads);
     }
   }
+  __syncthreads();
+  j2_flush(L, lut, h_lds);
   __syncthreads();
   flush(h_lds, hist_copy(a.hist, kSampleHistStride), 256);
 }
@@ -1272,6 +1360,7 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   a.ns.tri = H->ns_tri;
   a.ns.nbr = H->ns_nbr;
   a.ns.h3 = H->ns_h3;
+  a.ns.e3_pat = H->e3_pat;
   a.es = H->es;
   for (int j = 0; j < 5; ++j) {
     const bool in = j >= 2 && j <= k;
@@ -1315,9 +1404,10 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   // once an event recorded on st after the drain and the finish has completed
   a.q.job = nullptr;
   a.q.cap = 0;
-  a.q.tail = H->sample_hist + uint64_t(kHistCopies) * kSampleHistStride + 1;
-  a.q.head = H->sample_hist + uint64_t(kHistCopies) * kSampleHistStride + 2;
-  a.q.tcls = nullptr;
+  a.q.tail = H->sample_hist + uint64_t(kHistCopies) * kSampleHistStride;
+  a.q.head = a.q.tail + kQueueParts * kQueueStep;
+  a.q.info = nullptr;
+  a.q.info3 = nullptr;
   const uint32_t scale = sample_chunk_scale();
   a.q.ct = std::max<uint32_t>(1, kChunkT / scale);
   a.q.cr = std::max<uint32_t>(1, kChunkR / scale);
@@ -1325,16 +1415,19 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   a.q.ch = std::max<uint32_t>(1, kChunkH / scale);
   a.q.inline_work = kInlineWork / scale;
   struct Release {
-    void* p[2] = {nullptr, nullptr};
+    void* p[3] = {nullptr, nullptr, nullptr};
     hipStream_t st;
-    ~Release() { dfree_on(p, 2, st); }
-  } rel{{nullptr, nullptr}, st};
+    ~Release() { dfree_on(p, 3, st); }
+  } rel{{nullptr, nullptr, nullptr}, st};
   if (k == 4 && !bits) {
-    a.q.cap = std::min<uint64_t>(kQueuePerSample * scale * (a.d.S[2] + a.d.S[3]) + 65536, kQueueMax);
-    HM_TRY(dalloc(&rel.p[0], a.q.cap * sizeof(uint4)));
-    HM_TRY(dalloc(&rel.p[1], (3 * a.d.S[2] + 1) * sizeof(uint32_t)));
+    a.q.cap = std::min<uint64_t>(kQueuePerSample * scale * (a.d.S[2] + a.d.S[3]) / kQueueParts + 65536,
+                                 kQueueMax / kQueueParts);
+    HM_TRY(dalloc(&rel.p[0], kQueueParts * a.q.cap * sizeof(uint4)));
+    HM_TRY(dalloc(&rel.p[1], (a.d.S[2] + 1) * sizeof(uint4)));
+    HM_TRY(dalloc(&rel.p[2], (a.d.S[3] + 1) * sizeof(uint32_t)));
     a.q.job = static_cast<uint4*>(rel.p[0]);
-    a.q.tcls = static_cast<uint32_t*>(rel.p[1]);
+    a.q.info = static_cast<uint4*>(rel.p[1]);
+    a.q.info3 = static_cast<uint32_t*>(rel.p[2]);
   }
   ProfileScope pscope("k_sampled", st);
   if (k == 4 && bits)
@@ -1345,7 +1438,7 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
     k_sampled<3, false><<<grid, kThreads, 0, st>>>(a);
   HM_HIP(hipGetLastError());
   if (a.q.job) {
-    k_sampled_drain<<<1024, kThreads, 0, st>>>(a);
+    k_sampled_drain<<<1536, kThreads, 0, st>>>(a);
     HM_HIP(hipGetLastError());
   }
   k_finish_sampled<<<1, kThreads, 0, st>>>(a, sc);

@@ -318,3 +318,38 @@ def test_queue_buffers_outlive_the_call(hm, queued):
     assert np.array_equal(raw.cpu().numpy(), want_raw)
     assert np.array_equal(est.cpu().numpy(), want_est)
     assert np.array_equal(got_b.cpu().numpy(), want_b)
+
+
+@pytest.mark.parametrize("n,third,degree", [(300, 3, 40), (300, 150, 200), (8000, 4096, 4096), (8000, 4200, 6000)])
+def test_pair_sets_match_bit_rows(hm, n, third, degree):
+    """Samples of pairs whose third nodes T and pairwise rows are few, many and
+    more than are held as filters, taken together and chunk by chunk, without
+    bit rows against the bit-row path."""
+    rng = np.random.default_rng(n + third)
+    t = rng.choice(np.arange(2, n), third, replace=False)
+    rows = [np.c_[np.full(degree - 1, x), rng.choice(np.arange(2, n), degree - 1, replace=False)] for x in (0, 1)]
+    e2 = np.concatenate([[[0, 1]], *rows, np.sort(rng.choice(n, (2 * n, 2)), axis=1)])
+    e3 = np.r_[np.sort(np.c_[np.zeros(third, int), np.ones(third, int), t], axis=1),
+               np.sort(np.c_[np.zeros(n, int), rng.choice(np.arange(1, n), (n, 2))], axis=1),
+               np.sort(np.c_[np.ones(n, int), rng.choice(np.arange(2, n), (n, 2))], axis=1),
+               np.sort(rng.choice(n, (n, 3)), axis=1)]
+    e4 = np.r_[np.sort(np.c_[np.zeros(60, int), np.ones(60, int), rng.choice(np.arange(2, n), (60, 2))], axis=1),
+               np.sort(rng.choice(n, (n // 2, 4)), axis=1)]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in (e2, e3, e4)]
+    members = np.concatenate([e.ravel() for e in parts]).astype(np.uint32)
+    offsets = np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))].astype(np.uint64)
+    got = {}
+    try:
+        for bits in (8192, 0):
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+            with hm.hm_graph_create(members, offsets, n) as g:
+                st = g.stats()
+                idx = {2: np.r_[0, 1, rng.integers(0, st["n2"], 40)] if not got else idx[2],
+                       3: rng.integers(0, st["n3"], 40) if not got else idx[3]}
+                for scale in (1, 64):
+                    hm.hm_set_option(hm.HM_OPT_SAMPLE_CHUNK_SCALE, scale)
+                    got[bits, scale] = hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy()
+    finally:
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+        hm.hm_set_option(hm.HM_OPT_SAMPLE_CHUNK_SCALE, 1)
+    assert len({x.tobytes() for x in got.values()}) == 1
