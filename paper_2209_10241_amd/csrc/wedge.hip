@@ -38,6 +38,7 @@ constexpr uint32_t kSmallSlots = 1024;    // 23 x 23 paths and 23 neighbours: lo
 constexpr uint32_t kMidSlots = 4096;
 constexpr uint32_t kMidMost = 3072;
 constexpr uint32_t kRankBits = 8;
+constexpr uint32_t kNarrowDeg = 16;       // degrees below: path counts of 4 bits
 
 // Class of a degree: itself below 64, then eight classes per octave.
 __device__ inline uint32_t degree_class(uint32_t d) {
@@ -60,7 +61,7 @@ struct Ranked {
   const uint32_t* out_eid;
   const uint32_t* degree;    // rank -> degree
   const uint32_t* weight;    // rank -> bound on the nodes marked and positions walked (degree >= kSmallDeg)
-  const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg
+  const uint32_t* bounds;    // first rank of degree >= 2, of degree >= kSmallDeg, of degree >= 16
   const uint32_t* facts;     // kLongestOut ..
 };
 
@@ -71,7 +72,7 @@ enum : int { kLongestOut = 0, kManyCore = 1, kSplitNodes = 2, kSplitShares = 3, 
 
 __global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, uint32_t* __restrict__ keys,
                             uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
-  if (blockIdx.x == 0 && threadIdx.x < 2) bounds[threadIdx.x] = n;
+  if (blockIdx.x == 0 && threadIdx.x < 3) bounds[threadIdx.x] = n;
   for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
     keys[x] = degree_class(g2_off[x + 1] - g2_off[x]);
     vals[x] = x;
@@ -85,6 +86,7 @@ __global__ void k_rank_assign(const uint32_t* __restrict__ keys, const uint32_t*
     const uint32_t k = keys[r], before = r ? keys[r - 1] : 0u;
     if (k >= 2 && (r == 0 || before < 2)) bounds[0] = r;
     if (k >= kSmallDeg && (r == 0 || before < kSmallDeg)) bounds[1] = r;
+    if (k >= kNarrowDeg && (r == 0 || before < kNarrowDeg)) bounds[2] = r;
   }
 }
 
@@ -238,42 +240,56 @@ struct HashTab {
   __device__ void end() const {}
 };
 
-// Values by rank for the ranks [lo, lo + n): path counts of 16 bits beside a
-// mark bit each (or, `wide`, of 32 bits for half as many ranks), or mark bits
-// alone for kTri.  All zero between walks.
+// Values by rank for the ranks [lo, lo + n): path counts of 1 << lg bits
+// beside a mark bit each, or mark bits alone for kTri.  All zero between
+// walks.  A count holds every path u - x - w when w, or u, has no more core
+// neighbours than it can: 4 bits for the ranks of degree below 16 (most), 16
+// bits for the others, and 32 when u has more than 65,535 as well as another
+// node.  Each range walks the same positions: 16 bits for all took 9 ranges for
+// a coauthorship graph's 458,000 ranks, this four.  k_walk_large<2> there: 896
+// -> 380 us; k_walk_large<1> on one a tenth as dense: 391 -> 180 us.
 constexpr uint32_t kDirectRanks = 51200;   // 16-bit counts: 100 KB, marks 6.25 KB
 constexpr uint32_t kDirectWords = kDirectRanks / 2;
 constexpr uint32_t kDirectMarks = kDirectRanks / 32;
+constexpr uint32_t kNarrowRanks = 163840;   // 4-bit counts: 80 KB, and their marks in the next 20
+constexpr uint32_t kNarrowWords = kNarrowRanks / 8;
+static_assert(kNarrowWords + kNarrowRanks / 32 == kDirectWords, "both in the same words");
 struct DirectTab {
   uint32_t *cnt, *bits;
-  uint32_t lo, n;
-  bool wide;
+  uint32_t lo, n, lg;
   __device__ bool covers(uint32_t w) const { return w - lo < n; }
   __device__ void mark(uint32_t w) const { atomicOr(&bits[(w - lo) >> 5], 1u << ((w - lo) & 31)); }
   __device__ bool marked(uint32_t w) const { return (bits[(w - lo) >> 5] >> ((w - lo) & 31)) & 1u; }
   __device__ bool add(uint32_t w) const {
-    const uint32_t i = w - lo;
-    if (wide) atomicAdd(&cnt[i], 1u);
-    else atomicAdd(&cnt[i >> 1], 1u << (16 * (i & 1)));
+    const uint32_t i = (w - lo) << lg;   // (the count's first bit)
+    atomicAdd(&cnt[(w - lo) >> (5 - lg)], 1u << (i & 31));
     return marked(w);
   }
   __device__ uint32_t paths(uint32_t w) const {
-    const uint32_t i = w - lo;
-    return wide ? cnt[i] : (cnt[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+    const uint32_t v = cnt[(w - lo) >> (5 - lg)] >> (((w - lo) << lg) & 31);
+    return lg == 5 ? v : v & ((1u << (1u << lg)) - 1u);
   }
-  __device__ uint32_t words() const { return wide ? n : (n + 1) / 2; }
+  __device__ uint32_t words() const { return (n + (32u >> lg) - 1) >> (5 - lg); }
+  // the pairs of paths a word of counts of 1 << lg bits holds
+  static __device__ unsigned long long pairs_of(uint32_t v, uint32_t lg) {
+    if (lg == 5) {
+      const unsigned long long c = v;
+      return c * (c - (c > 0)) / 2;
+    }
+    if (lg == 4) {
+      const uint32_t a = v & 0xFFFFu, b = v >> 16;
+      return (unsigned long long)(a * (a - (a > 0)) / 2) + b * (b - (b > 0)) / 2;
+    }
+    uint32_t s = 0;
+    for (; v; v >>= 4) {
+      const uint32_t c = v & 15u;
+      s += c * (c - (c > 0)) / 2;
+    }
+    return s;
+  }
   __device__ unsigned long long pairs() const {
     unsigned long long s = 0;
-    for (uint32_t i = threadIdx.x; i < words(); i += blockDim.x) {
-      const uint32_t v = cnt[i];
-      if (wide) {
-        const unsigned long long c = v;
-        s += c * (c - (c > 0)) / 2;
-      } else {
-        const uint32_t a = v & 0xFFFFu, b = v >> 16;
-        s += (a * (a - (a > 0)) / 2) + (b * (b - (b > 0)) / 2);
-      }
-    }
+    for (uint32_t i = threadIdx.x; i < words(); i += blockDim.x) s += pairs_of(cnt[i], lg);
     return s;
   }
 };
@@ -697,13 +713,41 @@ __global__ void __launch_bounds__(1024) k_split_plan(Ranked g, uint32_t* __restr
   }
 }
 
-// Ranks a direct table holds in this mode, and threads' neighbours per chunk
-// (the LDS beside it).
+// Threads' neighbours per chunk (the LDS beside the table).
 template <int MODE>
-struct DirectMode {
-  static constexpr uint32_t kRanks = MODE == kTri ? kDirectWords * 32 : MODE == kSums ? kBitRanks : kDirectRanks;
-  static constexpr uint32_t kXpt = MODE == kSums ? 1 : 2;
+constexpr uint32_t direct_xpt() { return MODE == kSums ? 1 : 2; }
+
+// Range `part` of the ranks a mode's table holds at once, from the first of
+// degree 2; empty past the last.  kTri and kSums take ranges of one size.  The
+// modes that count paths take the ranks of degree below 16 by kNarrowRanks (lg
+// 2) and the others by kDirectRanks (lg 4) where that makes fewer ranges, for
+// each one walks every position again, and otherwise all by kDirectRanks: the
+// communication graph's 50,000 ranks fit one, and as two ranges k_walk_large
+// took 422 us in place of 141.
+struct RankRange {
+  uint32_t first, size, lg;
 };
+template <int MODE>
+__device__ inline RankRange range_of(const Ranked& g, uint32_t part) {
+  uint32_t first = g.bounds[0], end = g.n, step = MODE == kTri ? kDirectWords * 32 : kBitRanks, lg = 0;
+  if (counts_paths(MODE)) {
+    auto ranges = [](uint32_t ranks, uint32_t r) { return ranks / r + (ranks % r != 0); };
+    const uint32_t mid = g.bounds[2], narrow = ranges(mid - first, kNarrowRanks);
+    const bool both = narrow + ranges(end - mid, kDirectRanks) < ranges(end - first, kDirectRanks);
+    step = kDirectRanks;
+    lg = 4;
+    if (both && part < narrow) {
+      end = mid;
+      step = kNarrowRanks;
+      lg = 2;
+    } else if (both) {
+      first = mid;
+      part -= narrow;
+    }
+  }
+  const uint64_t at = first + uint64_t(part) * step;
+  return at < end ? RankRange{uint32_t(at), min(step, end - uint32_t(at)), lg} : RankRange{0, 0, lg};
+}
 
 // kSums over the ranks [first, first + size) for u's entries [e0, e1).
 template <uint32_t XPT>
@@ -725,7 +769,7 @@ __device__ void walk_sums(const WalkArgs& a, WalkLds<1024 * XPT, kSums>& S, uint
 
 template <int MODE>
 __global__ void __launch_bounds__(1024) k_walk_large(WalkArgs a, uint32_t parts) {
-  constexpr uint32_t R = DirectMode<MODE>::kRanks, XPT = DirectMode<MODE>::kXpt;
+  constexpr uint32_t XPT = direct_xpt<MODE>();
   __shared__ WalkLds<1024 * XPT, MODE> S;
   __shared__ uint32_t words[kDirectWords];
   __shared__ uint32_t marks[MODE == kTri || MODE == kSums ? 1 : kDirectMarks];
@@ -734,36 +778,33 @@ __global__ void __launch_bounds__(1024) k_walk_large(WalkArgs a, uint32_t parts)
   if (MODE != kTri && MODE != kSums)
     for (uint32_t i = threadIdx.x; i < kDirectMarks; i += 1024) marks[i] = 0;
   unsigned long long cycles = 0;
-  const uint32_t n = a.g.n, r0 = a.g.bounds[0], r1 = a.g.bounds[1];
+  const uint32_t n = a.g.n, r1 = a.g.bounds[1];
   for_candidates<1024>(
       uint64_t(n - r1) * parts, list, &n_list,
       [&](uint64_t c) {
-        const uint32_t part = uint32_t(c % parts);
         const uint32_t w = a.g.weight[n - 1 - uint32_t(c / parts)];
-        return uint64_t(r0) + uint64_t(part) * R < n && w > kMidMost && w != kSplitWalk;
+        return w > kMidMost && w != kSplitWalk && range_of<MODE>(a.g, uint32_t(c % parts)).size;
       },
       [&](uint64_t c) {
-        const uint32_t u = n - 1 - uint32_t(c / parts), part = uint32_t(c % parts);
-        const uint32_t first = r0 + part * R, size = min(R, n - first);
+        const uint32_t u = n - 1 - uint32_t(c / parts);
+        const RankRange q = range_of<MODE>(a.g, uint32_t(c % parts));
         if constexpr (MODE == kSums) {
-          walk_sums<XPT>(a, S, words, u, first, size, 0, a.g.core[u].y);
-          return;
-        }
-        const bool wide = counts_paths(MODE) && wide_counts(a.g, u);
-        for (uint32_t half = 0; half < (wide ? 2u : 1u); ++half) {
-          const uint32_t step = wide ? R / 2 : R;
-          if (half * step >= size) break;
-          DirectTab tab{words, MODE == kTri ? words : marks, first + half * step,
-                         size - half * step < step ? size - half * step : step, wide};
-          __syncthreads();
-          if constexpr (MODE != kSums)
+          walk_sums<XPT>(a, S, words, u, q.first, q.size, 0, a.g.core[u].y);
+        } else {
+          const bool narrow = counts_paths(MODE) && q.lg == 2u;
+          const bool wide = counts_paths(MODE) && !narrow && wide_counts(a.g, u);
+          const uint32_t step = wide ? kDirectRanks / 2 : q.size;
+          for (uint32_t at = 0; at < q.size; at += step) {
+            DirectTab tab{words, MODE == kTri ? words : narrow ? words + kNarrowWords : marks, q.first + at,
+                          q.size - at < step ? q.size - at : step, wide ? 5u : q.lg};
+            __syncthreads();
             walk_top<1024, XPT, 8, MODE>(a, S, tab, u, 0, a.g.core[u].y, 0, passes_of(MODE), parts > 1 || wide);
-          if (counts_paths(MODE)) cycles += tab.pairs();
-          __syncthreads();
-          const uint32_t used = MODE == kTri ? (tab.n + 31) / 32 : tab.words();
-          for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = 0;
-          if (MODE != kTri && MODE != kSums)
-            for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) marks[i] = 0;
+            if (counts_paths(MODE)) cycles += tab.pairs();
+            __syncthreads();
+            if (counts_paths(MODE))
+              for (uint32_t i = threadIdx.x; i < tab.words(); i += 1024) words[i] = 0;
+            for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) tab.bits[i] = 0;
+          }
         }
       });
   if (counts_paths(MODE)) add_copies<1024>(cycles, a.cycles);
@@ -775,15 +816,15 @@ __global__ void __launch_bounds__(1024) k_walk_large(WalkArgs a, uint32_t parts)
 template <int MODE, bool SECOND>
 __global__ void __launch_bounds__(1024) k_walk_split(WalkArgs a, const SplitNode* __restrict__ nodes, uint32_t parts,
                                                      uint32_t* __restrict__ dump) {
-  constexpr uint32_t R = DirectMode<MODE>::kRanks, XPT = DirectMode<MODE>::kXpt;
+  constexpr uint32_t XPT = direct_xpt<MODE>();
   __shared__ WalkLds<1024 * XPT, MODE> S;
   __shared__ uint32_t words[kDirectWords];
   __shared__ uint32_t marks[MODE == kSums ? 1 : kDirectMarks];
-  const uint32_t n = a.g.n, r0 = a.g.bounds[0];
   const uint32_t n_nodes = a.g.facts[kSplitNodes], n_shares = a.g.facts[kSplitShares];
   for (uint64_t t = blockIdx.x; t < uint64_t(n_shares) * parts; t += gridDim.x) {
     const uint32_t share = uint32_t(t / parts), part = uint32_t(t % parts);
-    if (uint64_t(r0) + uint64_t(part) * R >= n) continue;
+    const RankRange q = range_of<MODE>(a.g, part);
+    if (!q.size) continue;
     uint32_t lo = 0, hi = n_nodes;   // nodes[lo].first <= share < nodes[hi].first
     while (hi - lo > 1) {
       const uint32_t m = (lo + hi) >> 1;
@@ -792,51 +833,47 @@ __global__ void __launch_bounds__(1024) k_walk_split(WalkArgs a, const SplitNode
     const SplitNode node = nodes[lo];
     const uint32_t s = share - node.first, len = a.g.core[node.u].y;
     const uint32_t e0 = uint32_t(uint64_t(len) * s / node.shares), e1 = uint32_t(uint64_t(len) * (s + 1) / node.shares);
-    const uint32_t first = r0 + part * R;
     if constexpr (MODE == kSums) {
-      walk_sums<XPT>(a, S, words, node.u, first, min(R, n - first), e0, e1);
-      continue;
-    }
-    DirectTab tab{words, marks, first, min(R, n - first), false};
-    __syncthreads();   // the previous task's tables are no longer read
-    const uint32_t used = tab.words();
-    if (SECOND) {
-      const uint32_t* summed = dump + (uint64_t(node.first) * parts + part) * kDirectWords;
-      for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = summed[i];
+      walk_sums<XPT>(a, S, words, node.u, q.first, q.size, e0, e1);
     } else {
-      for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = 0;
-      if (MODE != kSums)
-        for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) marks[i] = 0;
-    }
-    __syncthreads();
-    if constexpr (MODE != kSums)
+      DirectTab tab{words, q.lg == 2 ? words + kNarrowWords : marks, q.first, q.size, q.lg};
+      __syncthreads();   // the previous task's tables are no longer read
+      const uint32_t used = tab.words();
+      if (SECOND) {
+        const uint32_t* summed = dump + (uint64_t(node.first) * parts + part) * kDirectWords;
+        for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = summed[i];
+      } else {
+        for (uint32_t i = threadIdx.x; i < used; i += 1024) words[i] = 0;
+        for (uint32_t i = threadIdx.x; i < (tab.n + 31) / 32; i += 1024) tab.bits[i] = 0;
+      }
+      __syncthreads();
       walk_top<1024, XPT, 8, MODE>(a, S, tab, node.u, e0, e1, SECOND ? 1 : 0, SECOND ? 2 : 1, true);
-    if (counts_paths(MODE) && !SECOND) {
-      uint32_t* out = dump + t * kDirectWords;
-      for (uint32_t i = threadIdx.x; i < used; i += 1024) out[i] = words[i];
+      if (!SECOND) {
+        uint32_t* out = dump + t * kDirectWords;
+        for (uint32_t i = threadIdx.x; i < used; i += 1024) out[i] = words[i];
+      }
     }
   }
 }
 
 // The counts of each split node's shares summed into its first share's, and
-// the 4-cycles they close.  (Two 16-bit counts per word: neither half's sum
-// passes 65,535, see wide_counts.)
+// the 4-cycles they close.  (Several counts per word: no count's sum over the
+// shares passes its bits, see DirectTab.)
 __global__ void __launch_bounds__(1024) k_split_sum(Ranked g, const SplitNode* __restrict__ nodes, uint32_t parts,
                                                     uint32_t* __restrict__ dump, unsigned long long* __restrict__ out) {
-  const uint32_t n = g.n, r0 = g.bounds[0], n_nodes = g.facts[kSplitNodes];
+  const uint32_t n_nodes = g.facts[kSplitNodes];
   unsigned long long cycles = 0;
   for (uint64_t t = blockIdx.x; t < uint64_t(n_nodes) * parts; t += gridDim.x) {
     const SplitNode node = nodes[t / parts];
     const uint32_t part = uint32_t(t % parts);
-    if (uint64_t(r0) + uint64_t(part) * kDirectRanks >= n) continue;
-    const uint32_t words = (min(kDirectRanks, n - (r0 + part * kDirectRanks)) + 1) / 2;
+    const RankRange q = range_of<kCycles>(g, part);
+    const uint32_t words = q.size ? (q.size + (32u >> q.lg) - 1) >> (5 - q.lg) : 0u;
     uint32_t* base = dump + (uint64_t(node.first) * parts + part) * kDirectWords;
     for (uint32_t i = threadIdx.x; i < words; i += 1024) {
       uint32_t v = 0;
       for (uint32_t s = 0; s < node.shares; ++s) v += base[uint64_t(s) * parts * kDirectWords + i];
       base[i] = v;
-      const unsigned long long a = v & 0xFFFFu, b = v >> 16;
-      cycles += a * (a - (a > 0)) / 2 + b * (b - (b > 0)) / 2;
+      cycles += DirectTab::pairs_of(v, q.lg);
     }
   }
   add_copies<1024>(cycles, out);
@@ -1090,16 +1127,20 @@ struct Split {
   uint32_t parts = 0;   // ranges of ranks of the counting modes
 };
 
+// Ranges of ranks of a mode (an upper bound; see range_of): at most n2 / 8
+// nodes have 16 neighbours.
 template <int MODE>
-uint32_t parts_of(uint32_t n) {
-  constexpr uint64_t r = DirectMode<MODE>::kRanks;
-  return uint32_t(std::max<uint64_t>(1, (n + r - 1) / r));
+uint32_t parts_of(uint32_t n, uint64_t n2) {
+  auto ranges = [](uint64_t ranks, uint64_t r) { return uint32_t(std::max<uint64_t>(1, (ranks + r - 1) / r)); };
+  if (!counts_paths(MODE)) return ranges(n, MODE == kTri ? kDirectWords * 32 : kBitRanks);
+  return std::min(ranges(n, kDirectRanks),
+                  ranges(n, kNarrowRanks) + ranges(std::min<uint64_t>(n, n2 / 8), kDirectRanks));
 }
 
 // Plans the split walks (marking their nodes in g.weight), with counters for
 // 1,024 (share, range) tasks (100 MB).
-int plan_split(const Ranked& g, Scratch& tmp, Split* sp, hipStream_t st) {
-  sp->parts = parts_of<kCycles>(g.n);
+int plan_split(const Ranked& g, uint64_t n2, Scratch& tmp, Split* sp, hipStream_t st) {
+  sp->parts = parts_of<kCycles>(g.n, n2);
   const uint32_t capacity = 1024 / sp->parts;
   HM_TRY(tmp.get(&sp->nodes, kSplitRanks));
   HM_TRY(tmp.get(&sp->dump, uint64_t(std::max<uint32_t>(capacity, 1)) * sp->parts * kDirectWords));
@@ -1111,9 +1152,9 @@ int plan_split(const Ranked& g, Scratch& tmp, Split* sp, hipStream_t st) {
 
 // The walk launches of one mode, the longest walks first.
 template <int MODE>
-int launch_walks(const WalkArgs& a, const Split& sp, const char* name, hipStream_t st) {
+int launch_walks(const WalkArgs& a, uint64_t n2, const Split& sp, const char* name, hipStream_t st) {
   ProfileScope ps(name, st);
-  const uint32_t parts = parts_of<MODE>(a.g.n);
+  const uint32_t parts = parts_of<MODE>(a.g.n, n2);
   if constexpr (MODE != kTri) {
     k_walk_split<MODE, false><<<256, 1024, 0, st>>>(a, sp.nodes, parts, sp.dump);
     if constexpr (counts_paths(MODE)) k_split_sum<<<256, 1024, 0, st>>>(a.g, sp.nodes, parts, sp.dump, a.cycles);
@@ -1162,7 +1203,7 @@ int ensure_ranks(hm_graph* H, hipStream_t st) {
   HM_TRY(kept.get(&rank_of, n));
   HM_TRY(kept.get(&node_of, n));
   HM_TRY(kept.get(&vals_tmp, n));
-  HM_TRY(kept.get(&bounds, 2));
+  HM_TRY(kept.get(&bounds, 3));
   k_rank_keys<<<grid_of(n, 256, 2048), 256, 0, st>>>(H->g2_off, n, keys, node_of, bounds);
   HM_HIP(hipGetLastError());
   HM_TRY(radix_sort_pairs(keys, node_of, keys_tmp, vals_tmp, n, kRankBits, st));
@@ -1193,9 +1234,9 @@ int wedge_counts(hm_graph* H, int k, uint32_t* tri_e, unsigned long long* n_cycl
   a.tri_e = tri_e;
   a.cycles = copies;
   Split sp;
-  if (k == 3) return launch_walks<kTri>(a, sp, "k_walk", st);
-  HM_TRY(plan_split(g, tmp, &sp, st));
-  HM_TRY(launch_walks<kCycles>(a, sp, "k_walk", st));
+  if (k == 3) return launch_walks<kTri>(a, n2, sp, "k_walk", st);
+  HM_TRY(plan_split(g, n2, tmp, &sp, st));
+  HM_TRY(launch_walks<kCycles>(a, n2, sp, "k_walk", st));
   HM_TRY(launch_cliques<false>(H, g, most, copies + kAccCopies, nullptr, st, tmp));
   k_sum_copies<<<1, kWave, 0, st>>>(copies, n_cycles);
   k_sum_copies<<<1, kWave, 0, st>>>(copies + kAccCopies, n_cliques);
@@ -1244,11 +1285,11 @@ int wedge_edge_stats(hm_graph* H, unsigned long long* es, hipStream_t st) {
   a.core_tri = core_tri;
   HM_TRY(tmp.get(&a.vals, uint64_t(256) * kBitWide));
   Split sp;
-  HM_TRY(plan_split(g, tmp, &sp, st));
-  HM_TRY(launch_walks<kPairCycles>(a, sp, "k_walk", st));
+  HM_TRY(plan_split(g, n2, tmp, &sp, st));
+  HM_TRY(launch_walks<kPairCycles>(a, n2, sp, "k_walk", st));
   k_es_widen<<<grid_of(n2, 256, 2048), 256, 0, st>>>(tri_e, n2, es);
   k_core_tri<<<grid_of(2 * n2, 256, 4096), 256, 0, st>>>(g.core_eid, tri_e, g.facts, core_tri);
-  HM_TRY(launch_walks<kSums>(a, sp, "k_walk_sums", st));
+  HM_TRY(launch_walks<kSums>(a, n2, sp, "k_walk_sums", st));
   HM_TRY(launch_cliques<true>(H, g, most, copies + kAccCopies, es + n2, st, tmp));
   return HM_OK;
 }

@@ -663,6 +663,28 @@ def test_walks_over_several_rank_ranges(hm):
     assert k4 >= 1 and got.sum() == path + star + cycle + paw + dia + k4
 
 
+@pytest.mark.parametrize("degree", [14, 15, 16, 17])
+def test_paths_of_every_neighbour(hm, degree):
+    """Nodes whose every neighbour is the hub's too, of degrees around the 15
+    paths that a count of four bits holds, among more than 51,200 others:
+    4-cycles against matrix products."""
+    n, spokes, ends = 110_000, 3400, 300
+    rng = np.random.default_rng(degree)
+    x = 1 + np.arange(spokes)
+    w = spokes + 1 + np.arange(ends)
+    ring = np.arange(w[-1] + 1, n)
+    pairs = [np.stack([np.zeros(spokes, int), x], 1), np.stack([ring[:-1], ring[1:]], 1), [[ring[0], ring[-1]]]]
+    pairs += [np.stack([rng.choice(x, degree, replace=False), np.full(degree, v)], 1) for v in w]
+    e = np.sort(np.concatenate(pairs), axis=1)
+    want = _pair_shape_counts(hm, e, n)
+    with hm.hm_graph_create(e.astype(np.uint32).ravel(), np.arange(0, 2 * len(e) + 1, 2, dtype=np.uint64), n) as g:
+        got = hm.count_exact(g, 4).cpu().numpy()
+        raw = hm.count_sampled_indices(g, 4, {2: np.arange(len(e))})[1].cpu().numpy()
+    cls = lambda *bits: hm.hm_pattern_class(4, sum(1 << b for b in bits))
+    assert want["tri"] == 0 and got[cls(0, 2, 7, 4)] == want["cyc"] > ends * degree * (degree - 1) // 2 - 1
+    assert raw[cls(0, 2, 7, 4)] == 4 * want["cyc"]   # (each of its pairs finds a cycle)
+
+
 @pytest.mark.parametrize("n,hubs,hub_degree,ring,clique", [
     (200, 0, 0, True, 0), (4000, 40, 3700, True, 0), (3000, 3, 2900, True, 0), (3000, 40, 700, True, 66), (1500, 0, 0, False, 24),
     (2000, 2, 500, True, 120), (2500, 0, 0, True, 700)])
