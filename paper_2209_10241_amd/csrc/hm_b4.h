@@ -18,16 +18,21 @@ namespace hm {
 
 constexpr uint32_t kMaxWordsB = kBitsetMaxNodes / 32;
 constexpr int kB4Batch = 4;   // incidence entries a lane loads at once
-// LDS words one wavefront needs for rows of W words: T_ab, T_ac, T_bc, Q and
-// a list of kWave candidate nodes
-__host__ __device__ constexpr uint32_t b4_set_words(uint32_t W) { return 4 * W + kWave; }
+// Rows of at most 32 words take a 3-node hyperedge per half of the wavefront.
+__host__ __device__ constexpr uint32_t b4_per_wave(uint32_t W) { return W <= 32 ? 2 : 1; }
+// LDS words one group of lanes needs for rows of W words (T_ab, T_ac, T_bc, Q
+// and a list of as many candidate nodes as it has lanes), and one wavefront
+__host__ __device__ constexpr uint32_t b4_group_words(uint32_t W, uint32_t lanes) { return 4 * W + lanes; }
+__host__ __device__ constexpr uint32_t b4_set_words(uint32_t W) { return 4 * W * b4_per_wave(W) + kWave; }
 
-__device__ inline void count_class(const uint8_t* lut, unsigned long long* h_main, unsigned long long* h_sub,
-                                   uint32_t pattern, uint32_t pair_bits) {
-  atomicAdd(&h_main[lut[pattern]], 1ull);
+// (T: the width of the counters in LDS)
+template <typename T>
+__device__ inline void count_class(const uint8_t* lut, T* h_main, T* h_sub, uint32_t pattern, uint32_t pair_bits,
+                                   T n = 1) {
+  atomicAdd(&h_main[lut[pattern]], n);
   if (h_sub) {
     const uint8_t g = lut[pattern & pair_bits];
-    if (g != 0xFF) atomicAdd(&h_sub[g], 1ull);
+    if (g != 0xFF) atomicAdd(&h_sub[g], n);
   }
 }
 
@@ -36,12 +41,12 @@ __device__ inline void count_class(const uint8_t* lut, unsigned long long* h_mai
 // nodes with e, reached from the row of the smaller shared node (witness 3
 // for {a,b}, 4 for {a,c}, 5 for {b,c}).  An instance counts only when no
 // witness ahead of its own exists, so each v is taken once.
-template <bool OWN>
+template <bool OWN, typename T>
 __device__ void b4_edge_hash(uint32_t a, uint32_t b, uint32_t c, const uint32_t* __restrict__ e3,
                              const uint32_t* __restrict__ g2_off, const uint32_t* __restrict__ g2_adj,
                              const uint32_t* __restrict__ i3_off, const uint32_t* __restrict__ i3_idx,
                              const Set64& hs2, const Set128& hs3, const Set128& hs4, const uint8_t* lut,
-                             unsigned long long* h_main, unsigned long long* h_sub) {
+                             T* h_main, T* h_sub) {
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t pab = has2(hs2, a, b), pac = has2(hs2, a, c), pbc = has2(hs2, b, c);
   const uint32_t base_p = pab | (pac << 1) | (pbc << 2) | (1u << 3);
@@ -104,8 +109,10 @@ __device__ void b4_edge_hash(uint32_t a, uint32_t b, uint32_t c, const uint32_t*
   }
 }
 
-// Bit-row version, counting instead of listing.  The wavefront builds, in
-// LDS (sets: b4_set_words(W) words), bit sets of the nodes v with {a,b,v}, {a,c,v} or
+// Bit-row version, counting instead of listing, by a group of G lanes (the
+// wavefront, or half of it: a row of 13 words keeps 13 lanes busy either way,
+// and what bounds an item is its chain of loads, LDS accesses and moves).  The
+// group builds, in LDS (sets: b4_group_words(W, G) words), bit sets of the nodes v with {a,b,v}, {a,c,v} or
 // {b,c,v} a 3-node hyperedge (T_ab, T_ac, T_bc, from the incident 3-node
 // hyperedges of the two members with the fewest) and with e u {v} a 4-node
 // hyperedge (Q, from those of the member with the fewest).  The incidence
@@ -113,14 +120,16 @@ __device__ void b4_edge_hash(uint32_t a, uint32_t b, uint32_t c, const uint32_t*
 // each is one load.  Any other v leaves e the only hyperedge of size >= 3 in
 // e u {v}, so those v are counted per pairwise combination (av, bv, cv) with
 // popcounts over the rows of a, b, c.  The nodes that lie in a T set and
-// outside Q are listed in LDS and classified one per lane.
-template <bool OWN>
+// outside Q are listed in LDS and classified one per lane; the seven pairwise
+// combinations are counted by a lane each.  (Whole wavefronts, and lane 0 for
+// the combinations, with 64-bit counters there: k_null_count_lds on 64 copies
+// of 400 nodes 657 us; halves 419; the pairs by halves too, see id_edges, 392.)
+template <bool OWN, int G, typename T>
 __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uint32_t* __restrict__ i3_off,
                                    const uint32_t* __restrict__ i3_oth, const uint32_t* __restrict__ i4_off,
                                    const unsigned long long* __restrict__ i4_oth, const uint32_t* __restrict__ bits,
-                                   uint32_t W, uint32_t* sets, const uint8_t* lut, unsigned long long* h_main,
-                                   unsigned long long* h_sub) {
-  const int lane = threadIdx.x & (kWave - 1);
+                                   uint32_t W, uint32_t* sets, const uint8_t* lut, T* h_main, T* h_sub) {
+  const int lane = threadIdx.x & (G - 1);
   uint32_t* Tab = sets;
   uint32_t* Tac = sets + W;
   uint32_t* Tbc = sets + 2 * W;
@@ -128,7 +137,7 @@ __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uin
   const uint32_t* Ra = bits + uint64_t(a) * W;
   const uint32_t* Rb = bits + uint64_t(b) * W;
   const uint32_t* Rc = bits + uint64_t(c) * W;
-  for (uint32_t w = lane; w < 4 * W; w += kWave) sets[w] = 0;
+  for (uint32_t w = lane; w < 4 * W; w += G) sets[w] = 0;
   // 3-node hyperedges sharing two nodes with e: each holds one of any two
   // members of e, so the lists of the two members with the fewest are read
   // (one found twice sets its bit twice)
@@ -146,22 +155,22 @@ __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uin
   wave_sync();
   // the entries of both walks are loaded kB4Batch per lane at a time before
   // any is used, so that their latencies overlap
-  // (batch q: 3-node entries [q * kB4Batch * kWave, (q + 1) * kB4Batch * kWave),
-  // 4-node entries [q * kWave, (q + 1) * kWave))
+  // (batch q: 3-node entries [q * kB4Batch * G, (q + 1) * kB4Batch * G),
+  // 4-node entries [q * G, (q + 1) * G))
   const uint32_t l3 = l1 + l2;
-  for (uint32_t q = 0; q * (kB4Batch * kWave) < l3 || q * kWave < l4; ++q) {
-    const uint32_t t0 = q * (kB4Batch * kWave);
+  for (uint32_t q = 0; q * (kB4Batch * G) < l3 || q * G < l4; ++q) {
+    const uint32_t t0 = q * (kB4Batch * G);
     uint32_t o3[kB4Batch];
 #pragma unroll
     for (int u = 0; u < kB4Batch; ++u) {
-      const uint32_t t = t0 + u * kWave + lane;
+      const uint32_t t = t0 + u * G + lane;
       o3[u] = t < l3 ? i3_oth[t < l1 ? pa + t : pb + (t - l1)] : 0u;
     }
-    const uint32_t t4 = q * kWave + lane;
+    const uint32_t t4 = q * G + lane;
     const unsigned long long o4 = t4 < l4 ? i4_oth[p4 + t4] : 0ull;
 #pragma unroll
     for (int u = 0; u < kB4Batch; ++u) {
-      const uint32_t t = t0 + u * kWave + lane;
+      const uint32_t t = t0 + u * G + lane;
       if (t >= l3) continue;
       const uint32_t p = t < l1 ? o1 : o2;   // the list's node; the hyperedge is {p, y, z}
       const uint32_t y = o3[u] & 0xFFFFu, z = o3[u] >> 16;
@@ -169,8 +178,8 @@ __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uin
       if (hy == hz) continue;                // e itself, or only p shared
       const uint32_t v = hy ? z : y, w = hy ? y : z;   // shared pair {p, w}
       const bool ha = p == a || w == a, hb = p == b || w == b;
-      uint32_t* T = (ha && hb) ? Tab : (ha ? Tac : Tbc);
-      atomicOr(&T[v >> 5], 1u << (v & 31));
+      uint32_t* set = (ha && hb) ? Tab : (ha ? Tac : Tbc);
+      atomicOr(&set[v >> 5], 1u << (v & 31));
     }
     if (t4 < l4) {   // the hyperedge is {m4, x, y, z}
       const uint32_t x = uint32_t(o4) & 0xFFFFu, y = uint32_t(o4 >> 16) & 0xFFFFu, z = uint32_t(o4 >> 32) & 0xFFFFu;
@@ -186,8 +195,8 @@ __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uin
                  pbc = (Rb[c >> 5] >> (c & 31)) & 1u;
   const uint32_t base_p = pab | (pac << 1) | (pbc << 2) | (1u << 3);
   uint32_t n1 = 0, n2 = 0, n3 = 0, n4 = 0, n5 = 0, n6 = 0, n7 = 0;
-  uint32_t* list = sets + 4 * W;   // kWave candidate nodes
-  for (uint32_t w0 = 0; w0 < W; w0 += kWave) {
+  uint32_t* list = sets + 4 * W;   // G candidate nodes
+  for (uint32_t w0 = 0; w0 < W; w0 += G) {
     const uint32_t w = w0 + lane;
     uint32_t cw = 0;
     if (w < W) {
@@ -209,11 +218,11 @@ __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uin
       // the fourth nodes on another 3-node hyperedge (not on a 4-node one)
       cw = (tab_w | tac_w | tbc_w) & ~(q_w | self);
     }
-    // which are listed in order, kWave at a time, and classified one per lane
-    uint32_t tot;
-    uint32_t at = wave_exclusive_scan(__popc(cw), &tot);
-    for (uint32_t base = 0; base < tot; base += kWave) {
-      while (cw && at < base + kWave) {
+    // which are listed in order, G at a time, and classified one per lane
+    const uint32_t upto = group_scan<G>(__popc(cw)), tot = group_last<G>(upto);
+    uint32_t at = upto - __popc(cw);
+    for (uint32_t base = 0; base < tot; base += G) {
+      while (cw && at < base + G) {
         list[at - base] = (w << 5) | uint32_t(__ffs(cw) - 1);
         cw &= cw - 1;
         ++at;
@@ -227,34 +236,24 @@ __device__ void b4_edge_bits_count(uint32_t a, uint32_t b, uint32_t c, const uin
           const uint32_t qa = (Ra[vw] >> vb) & 1u, qb = (Rb[vw] >> vb) & 1u, qc = (Rc[vw] >> vb) & 1u;
           // local positions a=0, b=1, c=2, v=3
           const uint32_t pt = base_p | (qa << 4) | (qb << 5) | (tab << 6) | (qc << 7) | (tac << 8) | (tbc << 9);
-          count_class(lut, h_main, h_sub, pt, kPairBits4);
+          count_class<T>(lut, h_main, h_sub, pt, kPairBits4);
         }
       }
       wave_sync();
     }
   }
-  // Reduce over the wavefront (lanes without words hold zeros); a
-  // combination's total over the wavefront is below the node count, at most
-  // 8192, so two of them share a 32-bit word.
-  uint32_t pk[4] = {n1 | (n2 << 16), n3 | (n4 << 16), n5 | (n6 << 16), n7};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) pk[k] = wave_sum_u32(pk[k]);
-  uint32_t n[8];
-  n[1] = pk[0] & 0xFFFFu; n[2] = pk[0] >> 16; n[3] = pk[1] & 0xFFFFu; n[4] = pk[1] >> 16;
-  n[5] = pk[2] & 0xFFFFu; n[6] = pk[2] >> 16; n[7] = pk[3];
-  if (lane == 0) {
-#pragma unroll
-    for (uint32_t cmb = 1; cmb < 8; ++cmb) {
-      if (!n[cmb]) continue;
-      const uint32_t pt = base_p | ((cmb & 1u) << 4) | (((cmb >> 1) & 1u) << 5) | ((cmb >> 2) << 7);
-      atomicAdd(&h_main[lut[pt]], (unsigned long long)n[cmb]);
-      if (h_sub) {
-        const uint8_t g = lut[pt & kPairBits4];
-        if (g != 0xFF) atomicAdd(&h_sub[g], (unsigned long long)n[cmb]);
-      }
-    }
+  // Sums over the group (lanes without words hold zeros); a combination's
+  // total is below the node count, at most 8192, so two of them share a 32-bit
+  // word.  Lane cmb then counts combination cmb.
+  const uint32_t s12 = group_last<G>(group_scan<G>(n1 | (n2 << 16))), s34 = group_last<G>(group_scan<G>(n3 | (n4 << 16))),
+                 s56 = group_last<G>(group_scan<G>(n5 | (n6 << 16))), s7 = group_last<G>(group_scan<G>(n7));
+  const uint32_t cmb = lane, two = cmb < 3 ? s12 : (cmb < 5 ? s34 : (cmb < 7 ? s56 : s7));
+  const uint32_t n = (cmb & 1u) ? two & 0xFFFFu : two >> 16;
+  if (cmb - 1u < 7u && n) {
+    const uint32_t pt = base_p | ((cmb & 1u) << 4) | (((cmb >> 1) & 1u) << 5) | ((cmb >> 2) << 7);
+    count_class<T>(lut, h_main, h_sub, pt, kPairBits4, T(n));
   }
-  wave_sync();   // the sets are rewritten by the wavefront's next 3-node hyperedge
+  wave_sync();   // the sets are rewritten by the group's next 3-node hyperedge
 }
 
 }  // namespace hm

@@ -207,6 +207,28 @@ __device__ inline uint32_t wave_exclusive_scan(uint32_t v, uint32_t* total) {
   return x - v;
 }
 
+// The same over groups of G = 32 or 64 lanes, a group's lanes all active: no
+// move crosses the halves but the last broadcast.
+template <int G>
+__device__ __forceinline__ uint32_t group_scan(uint32_t x) {
+  static_assert(G == 32 || G == kWave, "halves or whole wavefronts");
+  x += dpp::mov<dpp::kRowShr1, 0xF>(x);
+  x += dpp::mov<dpp::kRowShr2, 0xF>(x);
+  x += dpp::mov<dpp::kRowShr4, 0xF>(x);
+  x += dpp::mov<dpp::kRowShr8, 0xF>(x);
+  x += dpp::mov<dpp::kRowBcast15, 0xA>(x);
+  if (G == kWave) x += dpp::mov<dpp::kRowBcast31, 0xC>(x);
+  return x;
+}
+// The value of a group's last lane.
+template <int G>
+__device__ __forceinline__ uint32_t group_last(uint32_t x) {
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(x), kWave - 1));
+  if (G == kWave) return hi;
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(x), 31));
+  return (threadIdx.x & 32u) ? hi : lo;
+}
+
 __device__ inline void load_lut(uint8_t* lut, const uint8_t* g, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) lut[i] = g[i];
 }

@@ -95,13 +95,25 @@ __device__ inline uint32_t a3_pattern(const View& v, uint32_t a, uint32_t b, uin
          (pair_bit(v.hs2, v.bits, v.W, b, c) << 2);
 }
 
-// (b) at order 4 for the 3-node hyperedge at position i of v.e3
-__device__ inline void b4_item(const View& v, uint64_t i, uint32_t* sets, const uint8_t* lut, unsigned long long* h_main,
-                               unsigned long long* h_sub) {
+// (b) at order 4 for the 3-node hyperedges that a wavefront takes at once (with
+// bit rows b4_per_wave(v.W), else one) from position i of v.e3, below `last`
+template <typename T>
+__device__ inline void b4_item(const View& v, uint64_t i, uint64_t last, uint32_t* sets, const uint8_t* lut, T* h_main,
+                               T* h_sub) {
+  const uint32_t half = v.bits && b4_per_wave(v.W) == 2 ? (threadIdx.x >> 5) & 1u : 0u;
+  const bool in = i + half < last;
+  if (in) i += half;   // (a lane of no hyperedge loads another's)
   const uint32_t a = v.e3[3 * i], b = v.e3[3 * i + 1], c = v.e3[3 * i + 2];
-  if (v.bits)
-    b4_edge_bits_count<true>(a, b, c, v.i3_off, v.i3_oth, v.i4_off, v.i4_oth, v.bits, v.W, sets, lut, h_main, h_sub);
-  else
+  if (v.bits) {
+    if (b4_per_wave(v.W) == 2) {
+      if (in)
+        b4_edge_bits_count<true, 32>(a, b, c, v.i3_off, v.i3_oth, v.i4_off, v.i4_oth, v.bits, v.W,
+                                     sets + half * b4_group_words(v.W, 32), lut, h_main, h_sub);
+    } else {
+      b4_edge_bits_count<true, kWave>(a, b, c, v.i3_off, v.i3_oth, v.i4_off, v.i4_oth, v.bits, v.W, sets, lut, h_main,
+                                      h_sub);
+    }
+  } else
     b4_edge_hash<true>(a, b, c, v.e3, v.g2_off, v.g2_adj, v.i3_off, v.i3_idx, v.hs2, v.hs3, v.hs4, lut, h_main, h_sub);
 }
 
@@ -138,14 +150,15 @@ struct C4Lanes {
   bool on;
 };
 
-__device__ inline C4Lanes c4_lanes(uint32_t W) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const bool grouped = W <= uint32_t(kWave);
+// (over `lanes` lanes: the wavefront, or a half of it)
+__device__ inline C4Lanes c4_lanes(uint32_t W, uint32_t lanes = kWave) {
+  const int lane = threadIdx.x & (lanes - 1);
+  const bool grouped = W <= lanes;
   C4Lanes L;
-  L.G = grouped ? uint32_t(kWave) / W : 1u;
+  L.G = grouped ? lanes / W : 1u;
   L.g = grouped ? uint32_t(lane) / W : 0u;
   L.w0 = grouped ? uint32_t(lane) % W : uint32_t(lane);
-  L.wstep = grouped ? W : uint32_t(kWave);
+  L.wstep = grouped ? W : lanes;
   L.on = grouped ? (L.g < L.G) : true;
   return L;
 }
@@ -340,23 +353,24 @@ __device__ inline void id_k4_list(const View& v, const uint32_t* Ru, const uint3
   }
 }
 
-// One wavefront per edge {u < x}; ys: 64 words of wavefront-private LDS.
-// The common neighbours above x, C', are listed in ys (each lane writing the
-// set bits of its word at its offset in a wavefront scan) when they number
-// at most 64, else taken one set bit per lane per round.
+// A group of G lanes per edge {u < x} (see id_edges); ys: G words of its own
+// LDS.  The common neighbours above x, C', are listed in ys (each lane writing
+// the set bits of its word at its offset in a scan over the group) when they
+// number at most G, else taken one set bit per lane per round.
+template <int G>
 __device__ inline void id_edge_item(const View& v, uint32_t u, uint32_t x, const C4Lanes& L, uint32_t* ys,
                                     IdAcc& acc) {
-  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t lane = threadIdx.x & (G - 1), half = (threadIdx.x & (kWave - 1)) & ~uint32_t(G - 1);
   const uint32_t W = v.W;
   const uint32_t* Ru = v.bits + uint64_t(u) * W;
   const uint32_t* Rx = v.bits + uint64_t(x) * W;
   uint32_t t_lane = 0, c_word = 0;
-  for (uint32_t w = lane; w < W; w += kWave) {
+  for (uint32_t w = lane; w < W; w += G) {
     const uint32_t cn = Ru[w] & Rx[w];
     t_lane += __popc(cn);
-    if (w < uint32_t(kWave)) c_word = cn & mask_gt(x, w);
+    if (w < uint32_t(G)) c_word = cn & mask_gt(x, w);
   }
-  const uint32_t t = wave_sum_u32(t_lane);
+  const uint32_t t = group_last<G>(group_scan<G>(t_lane));
   if (lane == 0) {
     const unsigned long long du = g2_degree(v, u), dx = g2_degree(v, x), tt = t;
     acc.t3 += tt;
@@ -365,10 +379,10 @@ __device__ inline void id_edge_item(const View& v, uint32_t u, uint32_t x, const
     if (tt) acc.paw2 += tt * (du + dx - 4);   // then du, dx >= t + 1 >= 2
   }
   if (t < 2) return;   // a 4-clique on {u, x} needs two common neighbours
-  if (W <= uint32_t(kWave)) {
-    uint32_t total;
-    uint32_t off = wave_exclusive_scan(__popc(c_word), &total);
-    if (total <= uint32_t(kWave)) {
+  if (W <= uint32_t(G)) {
+    const uint32_t upto = group_scan<G>(__popc(c_word)), total = group_last<G>(upto);
+    uint32_t off = upto - __popc(c_word);
+    if (total <= uint32_t(G)) {
       for (uint32_t b = c_word; b; b &= b - 1) ys[off++] = (lane << 5) | uint32_t(__ffs(b) - 1);
       wave_sync();
       id_k4_list(v, Ru, Rx, x, L, ys, total, acc);
@@ -376,12 +390,16 @@ __device__ inline void id_edge_item(const View& v, uint32_t u, uint32_t x, const
       return;
     }
   }
-  for (uint32_t w0 = 0; w0 < W; w0 += kWave) {
+  auto group_ballot = [half](bool p) {
+    const unsigned long long m = __ballot(p);
+    return G == kWave ? m : (m >> half) & 0xFFFFFFFFull;
+  };
+  for (uint32_t w0 = 0; w0 < W; w0 += G) {
     const uint32_t w = w0 + lane;
     uint32_t word = w < W ? (Ru[w] & Rx[w] & mask_gt(x, w)) : 0u;
-    while (__ballot(word != 0)) {
+    while (group_ballot(word != 0)) {
       const bool has = word != 0;
-      const unsigned long long m = __ballot(has);
+      const unsigned long long m = group_ballot(has);
       if (has) {
         ys[__popcll(m & ((1ull << lane) - 1ull))] = (w << 5) | uint32_t(__ffs(word) - 1);
         word &= word - 1;
@@ -390,6 +408,20 @@ __device__ inline void id_edge_item(const View& v, uint32_t u, uint32_t x, const
       id_k4_list(v, Ru, Rx, x, L, ys, uint32_t(__popcll(m)), acc);
       wave_sync();
     }
+  }
+}
+
+// The edges [i, last) of e2 that a wavefront takes at once: one per half for
+// rows of at most 32 words (b4_per_wave), else one.  L: c4_lanes(W, kWave /
+// b4_per_wave(W)); ys: 64 words of wavefront-private LDS.
+__device__ inline void id_edges(const View& v, const uint32_t* e2, uint64_t i, uint64_t last, const C4Lanes& L, uint32_t* ys,
+                                IdAcc& acc) {
+  if (b4_per_wave(v.W) == 2) {
+    const uint32_t half = (threadIdx.x >> 5) & 1u;
+    i += half;
+    if (i < last) id_edge_item<32>(v, e2[2 * i], e2[2 * i + 1], L, ys + 32 * half, acc);
+  } else {
+    id_edge_item<kWave>(v, e2[2 * i], e2[2 * i + 1], L, ys, acc);
   }
 }
 

@@ -1268,7 +1268,8 @@ __global__ void __launch_bounds__(kThreads) k_null_count(BatchView b, uint32_t R
   unsigned long long* h_main = wh[wv];
   unsigned long long* h_sub = wh[wv] + 256;
   const uint32_t total = tile_prefix[3 * R];
-  const C4Lanes L = c4_lanes(b.W);
+  const bool id = batch_ident(b, k);
+  const C4Lanes L = c4_lanes(b.W, id ? kWave / b4_per_wave(b.W) : uint32_t(kWave));
   while (true) {
     uint32_t t = 0;
     if (lane == 0) t = atomicAdd(counter, 1u);
@@ -1287,25 +1288,21 @@ __global__ void __launch_bounds__(kThreads) k_null_count(BatchView b, uint32_t R
     for (uint32_t i = lane; i < 512; i += kWave) wh[wv][i] = 0;
     wave_sync();
     if (ph == 0) {
-      const uint32_t n = b.base3[c + 1] - b.base3[c];
+      const uint32_t n = b.base3[c + 1] - b.base3[c], per = v.bits ? b4_per_wave(v.W) : 1u;
       const uint32_t last = min(n, first + ch.per_tile[0]);
-      for (uint32_t j = first; j < last; ++j) b4_item(v, b.base3[c] + j, b4_sets + wv * b4_set_words(b.W), lut, h_main, h_sub);
+      for (uint32_t j = first; j < last; j += per)
+        b4_item(v, b.base3[c] + j, b.base3[c] + last, b4_sets + wv * b4_set_words(b.W), lut, h_main, h_sub);
     } else if (ph == 1) {
       const uint32_t n2c = b.base2[c + 1] - b.base2[c];
-      const bool id = batch_ident(b, k);
       const uint32_t n = n2c + (id ? b.N : 0u);
       const uint32_t last = min(n, first + ch.per_tile[1]);
       if (id) {
         IdAcc acc;
         id_zero(acc);
-        for (uint32_t j = first; j < last; ++j) {
-          if (j < n2c) {
-            const uint64_t q = b.base2[c] + j;
-            id_edge_item(v, b.e2[2 * q], b.e2[2 * q + 1], L, ylist[wv], acc);
-          } else {
-            id_node_item(v, j - n2c, acc);
-          }
-        }
+        const uint32_t per = b4_per_wave(v.W), edges = min(last, n2c);
+        for (uint32_t j = first; j < edges; j += per)
+          id_edges(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
+        for (uint32_t j = max(first, n2c); j < last; ++j) id_node_item(v, j - n2c, acc);
         id_flush(acc, hc + kIdAcc);
       } else if (k == 4) {
         if (v.bits) {
@@ -1387,22 +1384,22 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
                                                              const uint8_t* __restrict__ lut_g,
                                                              unsigned long long* __restrict__ hist_all) {
   __shared__ uint8_t lut[2048];
-  __shared__ unsigned long long wh[kWavesPerBlock][512];
+  __shared__ uint32_t wh[kWavesPerBlock][512];   // (a tile adds at most its items times the nodes, below 2^20)
   extern __shared__ uint32_t dyn_lds[];
   __shared__ uint32_t ylist[kWavesPerBlock][kWave];
   __shared__ uint32_t s_tile;
   load_lut(lut, lut_g, 2048);
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = threadIdx.x / kWave;
-  unsigned long long* h_main = wh[wv];
-  unsigned long long* h_sub = wh[wv] + 256;
+  uint32_t* h_main = wh[wv];
+  uint32_t* h_sub = wh[wv] + 256;
   uint32_t* sets = dyn_lds + wv * b4_set_words(b.W);
   uint32_t* rows = dyn_lds + kWavesPerBlock * b4_set_words(b.W);
   const uint32_t nw = b.N * b.W;
   uint32_t* offs = rows + nw;
   const uint32_t total = tile_prefix[3 * R];
-  const C4Lanes L = c4_lanes(b.W);
   const bool id = batch_ident(b, 4);
+  const C4Lanes L = c4_lanes(b.W, id ? kWave / b4_per_wave(b.W) : uint32_t(kWave));
   uint32_t loaded = 0xFFFFFFFFu;
   while (true) {
     __syncthreads();   // the previous tile is done with s_tile and the LDS tables
@@ -1440,9 +1437,10 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
     for (uint32_t i = lane; i < 512; i += kWave) wh[wv][i] = 0;
     wave_sync();
     if (ph == 0) {
-      const uint32_t n = b.base3[c + 1] - b.base3[c];
+      const uint32_t n = b.base3[c + 1] - b.base3[c], per = b4_per_wave(v.W);
       const uint32_t last = min(n, first + ch.per_tile[0]);
-      for (uint32_t j = first + wv; j < last; j += kWavesPerBlock) b4_item(v, b.base3[c] + j, sets, lut, h_main, h_sub);
+      for (uint32_t j = first + wv * per; j < last; j += kWavesPerBlock * per)
+        b4_item(v, b.base3[c] + j, b.base3[c] + last, sets, lut, h_main, h_sub);
     } else if (ph == 1) {
       const uint32_t n2c = b.base2[c + 1] - b.base2[c];
       const uint32_t n = n2c + (id ? b.N : 0u);
@@ -1450,14 +1448,10 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
       if (id) {
         IdAcc acc;
         id_zero(acc);
-        for (uint32_t j = first + wv; j < last; j += kWavesPerBlock) {
-          if (j < n2c) {
-            const uint64_t q = b.base2[c] + j;
-            id_edge_item(v, b.e2[2 * q], b.e2[2 * q + 1], L, ylist[wv], acc);
-          } else {
-            id_node_item(v, j - n2c, acc);
-          }
-        }
+        const uint32_t per = b4_per_wave(v.W), edges = min(last, n2c);
+        for (uint32_t j = first + wv * per; j < edges; j += kWavesPerBlock * per)
+          id_edges(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
+        for (uint32_t j = max(first, n2c) + wv; j < last; j += kWavesPerBlock) id_node_item(v, j - n2c, acc);
         id_flush(acc, hc + kIdAcc);
       } else {
         C4Acc acc;
@@ -1479,8 +1473,8 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
     }
     wave_sync();
     for (uint32_t i = lane; i < 512; i += kWave) {
-      const unsigned long long x = wh[wv][i];
-      if (x) atomicAdd(hc + i, x);   // kMain = 0, kSub = 256
+      const uint32_t x = wh[wv][i];
+      if (x) atomicAdd(hc + i, (unsigned long long)x);   // kMain = 0, kSub = 256
     }
   }
 }

@@ -178,3 +178,33 @@ def test_config_rounds_match_oracle(hm, edges, sizes):
         for sweeps, copy in ((1, 0), (3, 4)):
             m, _ = hm.hm_null_export_model(g, hm.HM_NULL_CONFIG, sweeps, 9, copy)
             assert np.array_equal(m, profiles.config_model(h, sweeps, 9, copy)[0]), (sweeps, copy)
+
+
+@pytest.mark.parametrize("n,clique", [(33, 0), (500, 45), (900, 33), (1024, 40), (1025, 70)])
+def test_half_wavefront_rows_match_hash(hm, n, clique):
+    """Bit rows of up to 32 words, counted by halves of a wavefront, and the
+    first beyond them: odd numbers of pairs and 3-node hyperedges, pairs with
+    more common neighbours than a half has lanes; the hypergraph's counts and
+    its copies' against the paths without bit rows."""
+    rng = np.random.default_rng(n)
+    rows = [tuple(p) for p in np.stack(np.triu_indices(clique, 1), 1)]
+    for size, count in ((2, 3 * n), (3, 2 * n), (4, n // 2)):
+        rows += [tuple(sorted(rng.choice(n // 2 if j % 2 else n, size, replace=False))) for j in range(count)]
+    rows = sorted(set(rows))
+    for size in (2, 3):
+        if sum(len(r) == size for r in rows) % 2 == 0:
+            rows.remove(next(r for r in rows if len(r) == size))
+    members = np.concatenate([np.array(r, np.uint32) for r in rows])
+    offsets = np.cumsum([0] + [len(r) for r in rows]).astype(np.uint64)
+    got = {}
+    for bits in (8192, 0):
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+        try:
+            with hm.hm_graph_create(members, offsets, n) as g:
+                real, nl, _ = hm.count_nulls(g, 4, 3, 2)
+                got[bits] = (hm.count_exact(g, 4).cpu().numpy(), real.cpu().numpy(), nl.cpu().numpy())
+        finally:
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+    assert np.array_equal(got[8192][0], got[8192][1])
+    for b, h in zip(got[8192], got[0]):
+        assert np.array_equal(b, h)
