@@ -208,3 +208,28 @@ def test_half_wavefront_rows_match_hash(hm, n, clique):
     assert np.array_equal(got[8192][0], got[8192][1])
     for b, h in zip(got[8192], got[0]):
         assert np.array_equal(b, h)
+
+
+@pytest.mark.parametrize("k", [3, 4])
+@pytest.mark.parametrize("n", [1, 2048, 2049, 2700])
+def test_copy_rows_match_hash(hm, n, k):
+    """Copies whose incidence lists one workgroup makes (bit rows of up to 2^17
+    words), the first beyond, and rows that are read as lists as well, against
+    the path without bit rows."""
+    rng = np.random.default_rng(n)
+    sizes = [j for j, m in ((1, 3), (2, 2001), (3, 1500), (4, 700), (6, 30)) for _ in range(m) if j <= n]
+    rows = [np.sort(rng.choice(min(n, 400), j, replace=False)) for j in sizes]
+    rows[-1] = np.sort(n - 1 - np.arange(len(rows[-1])))
+    members = np.concatenate(rows).astype(np.uint32)
+    offsets = np.cumsum([0] + sizes).astype(np.uint64)
+    got = {}
+    for bits in (8192, 0):
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+        try:
+            with hm.hm_graph_create(members, offsets, n) as g:
+                real, nl, _ = hm.count_nulls(g, k, 5, 3)
+                got[bits] = (real.cpu().numpy(), nl.cpu().numpy())
+        finally:
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+    for b, h in zip(got[8192], got[0]):
+        assert np.array_equal(b, h)
