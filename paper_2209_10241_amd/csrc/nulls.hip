@@ -1006,13 +1006,23 @@ __global__ void k_b_first(uint32_t R, uint32_t E, uint64_t T, const unsigned lon
   }
 }
 
-__global__ void k_b_bases(uint32_t R, uint32_t E, const uint32_t* __restrict__ p2, const uint32_t* __restrict__ p3,
-                          const uint32_t* __restrict__ p4, const uint32_t* __restrict__ tot, uint32_t* base2,
+// The flags f2, f3, f4 and their prefix sums p2, p3, p4 each stand one behind
+// the other (R x E words each), scanned in one go: a size's positions are its
+// sums less the one at its first word.  (tot[3]: all sizes)
+__global__ void k_b_bases(uint32_t R, uint32_t E, const uint32_t* __restrict__ p2, uint32_t* tot, uint32_t* base2,
                           uint32_t* base3, uint32_t* base4) {
+  const uint64_t n = uint64_t(R) * E;
+  const uint32_t first3 = n ? p2[n] : 0u, first4 = n ? p2[2 * n] : 0u, all = tot[3];
   for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= R; c += gridDim.x * blockDim.x) {
-    base2[c] = c < R ? p2[uint64_t(c) * E] : tot[0];
-    base3[c] = c < R ? p3[uint64_t(c) * E] : tot[1];
-    base4[c] = c < R ? p4[uint64_t(c) * E] : tot[2];
+    const uint64_t at = uint64_t(c) * E;
+    base2[c] = c < R && n ? p2[at] : first3;
+    base3[c] = (c < R && n ? p2[n + at] : first4) - first3;
+    base4[c] = (c < R && n ? p2[2 * n + at] : all) - first4;
+    if (c == 0) {
+      tot[0] = first3;
+      tot[1] = first4 - first3;
+      tot[2] = all - first4;
+    }
   }
 }
 
@@ -1032,11 +1042,11 @@ __global__ void k_b_gather(uint32_t R, uint32_t E, uint64_t T, const unsigned lo
       e2[2 * q + 1] = m[1];
       copy2[q] = uint32_t(c);
     } else if (f3[idx]) {
-      const uint64_t q = p3[idx];
+      const uint64_t q = p3[idx] - p3[0];
       for (int j = 0; j < 3; ++j) e3[3 * q + j] = m[j];
       copy3[q] = uint32_t(c);
     } else if (f4[idx]) {
-      const uint64_t q = p4[idx];
+      const uint64_t q = p4[idx] - p4[0];
       for (int j = 0; j < 4; ++j) e4[4 * q + j] = m[j];
       copy4[q] = uint32_t(c);
     }
@@ -1741,14 +1751,14 @@ int make_plan(const hm_graph* H, int k, uint32_t R, int model, int sweeps, NullP
   GET(P->failed, 1);
   GET(P->hash, RE);
   GET(P->dtab, uint64_t(R) * P->capD);
-  GET(P->f2, RE);
-  GET(P->f3, RE);
-  GET(P->f4, RE);
-  GET(P->p2, RE);
-  GET(P->p3, RE);
-  GET(P->p4, RE);
+  GET(P->f2, 3 * RE);
+  P->f3 = P->f2 + RE;
+  P->f4 = P->f3 + RE;
+  GET(P->p2, 3 * RE);
+  P->p3 = P->p2 + RE;
+  P->p4 = P->p3 + RE;
   GET(P->tot, 4);
-  GET(P->scan_ws, std::max(scan_ws_words(RE), scan_ws_words(RN + 1)) + scan_ws_words(3ull * R + 1));
+  GET(P->scan_ws, std::max(scan_ws_words(3 * RE), scan_ws_words(RN + 1)) + scan_ws_words(3ull * R + 1));
   GET(P->base2, uint64_t(R) + 1);
   GET(P->base3, uint64_t(R) + 1);
   GET(P->base4, uint64_t(R) + 1);
@@ -1891,10 +1901,8 @@ int enqueue_ingest(const hm_graph* H, NullPlan& P, hipStream_t st) {
   k_b_first<<<grid_for(RE), 256, 0, st>>>(R, E, P.T, H->all_off, P.members, P.hash, P.dtab, P.capD, P.f2, P.f3,
                                           P.f4);
   HM_HIP(hipGetLastError());
-  HM_TRY(scan_u32_ws(P.f2, P.p2, RE, P.tot + 0, P.scan_ws, st));
-  HM_TRY(scan_u32_ws(P.f3, P.p3, RE, P.tot + 1, P.scan_ws, st));
-  HM_TRY(scan_u32_ws(P.f4, P.p4, RE, P.tot + 2, P.scan_ws, st));
-  k_b_bases<<<grid_for(R + 1), 256, 0, st>>>(R, E, P.p2, P.p3, P.p4, P.tot, P.base2, P.base3, P.base4);
+  HM_TRY(scan_u32_ws(P.f2, P.p2, 3 * RE, P.tot + 3, P.scan_ws, st));
+  k_b_bases<<<grid_for(R + 1), 256, 0, st>>>(R, E, P.p2, P.tot, P.base2, P.base3, P.base4);
   k_b_gather<<<grid_for(RE), 256, 0, st>>>(R, E, P.T, H->all_off, P.members, P.f2, P.f3, P.f4, P.p2, P.p3, P.p4, P.e2,
                                            P.e3, P.e4, P.copy2, P.copy3, P.copy4);
   HM_HIP(hipGetLastError());
