@@ -541,13 +541,16 @@ __global__ void k_profile_quality(const double* __restrict__ a, const double* __
 }
 
 // ---------------------------------------------------------------- block helpers
+// (of the repair: a copy's few hundred hyperedges are one workgroup's, whose
+// time is its chain of steps, so it has the threads of one sort pass)
+constexpr uint32_t kRepairThreads = 512, kRepairWaves = kRepairThreads / kWave;
 __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const uint32_t x = wave_inclusive_scan(v);
   if (lane == kWave - 1) wsum[wave] = x;
   __syncthreads();
   uint32_t before = 0, all = 0;
-  for (int w = 0; w < kWavesPerBlock; ++w) {
+  for (int w = 0; w < int(kRepairWaves); ++w) {
     if (w < wave) before += wsum[w];
     all += wsum[w];
   }
@@ -558,12 +561,12 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint
 
 // Stable compaction of the indices i < n with flag(i) into out (ascending).
 // Each thread takes kCompactRun consecutive indices per round, so that one
-// workgroup scan serves kThreads * kCompactRun of them.
+// workgroup scan serves kRepairThreads * kCompactRun of them.
 constexpr uint32_t kCompactRun = 4;
 template <typename F>
 __device__ uint32_t block_compact(uint32_t n, F flag, uint32_t* out, uint32_t* wsum) {
   uint32_t count = 0;
-  for (uint32_t base = 0; base < n; base += kThreads * kCompactRun) {
+  for (uint32_t base = 0; base < n; base += kRepairThreads * kCompactRun) {
     const uint32_t i0 = base + threadIdx.x * kCompactRun;
     uint32_t bits = 0;
 #pragma unroll
@@ -580,73 +583,63 @@ __device__ uint32_t block_compact(uint32_t n, F flag, uint32_t* out, uint32_t* w
   return count;
 }
 
-// Ascending bitonic sort of n_pad (a power of two) (key, aux) pairs in
-// device memory by one workgroup; ties are broken by aux.  Up to
-// kLdsBitonic entries the sort runs on copies in LDS (lk, la, lv).
+// Ascending bitonic sort of n_pad (a power of two) (key, aux) pairs by one
+// workgroup, a compared pair per thread and pass; ties are broken by aux.  Up
+// to kLdsBitonic entries the sort runs on copies in LDS (lk, la, lv; key, aux
+// and val may be these), where a pass of a distance up to a wavefront's pairs
+// stays among 128 entries that one wavefront has to itself: passes of greater
+// distance alone wait for the workgroup.  (A wait after each of the 55 passes
+// over 1,024 entries by 256 threads, half of them idle: k_null_repair on 64
+// copies of 30,000 hyperedges 206 us, this 111.)
 constexpr uint32_t kLdsBitonic = 2048;
-__device__ void block_bitonic(unsigned long long* key, uint32_t* aux, uint32_t* val, uint32_t n_pad,
-                              unsigned long long* lk, uint32_t* la, uint32_t* lv) {
-  if (n_pad <= kLdsBitonic) {
-    for (uint32_t i = threadIdx.x; i < n_pad; i += kThreads) {
-      lk[i] = key[i];
-      la[i] = aux[i];
-      if (val) lv[i] = val[i];
-    }
-    __syncthreads();
-    for (uint32_t k = 2; k <= n_pad; k <<= 1)
-      for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-        for (uint32_t i = threadIdx.x; i < n_pad; i += kThreads) {
-          const uint32_t l = i ^ j;
-          if (l <= i) continue;
-          const bool asc = (i & k) == 0;
-          const bool greater = lk[i] > lk[l] || (lk[i] == lk[l] && la[i] > la[l]);
-          if (greater == asc) {
-            const unsigned long long tk = lk[i];
-            lk[i] = lk[l];
-            lk[l] = tk;
-            const uint32_t ta = la[i];
-            la[i] = la[l];
-            la[l] = ta;
-            if (val) {
-              const uint32_t tv = lv[i];
-              lv[i] = lv[l];
-              lv[l] = tv;
-            }
-          }
-        }
-        __syncthreads();
-      }
-    for (uint32_t i = threadIdx.x; i < n_pad; i += kThreads) {
-      key[i] = lk[i];
-      aux[i] = la[i];
-      if (val) val[i] = lv[i];
-    }
-    __syncthreads();
-    return;
-  }
+template <bool LDS>
+__device__ inline void bitonic_passes(unsigned long long* key, uint32_t* aux, uint32_t* val, uint32_t n_pad) {
   for (uint32_t k = 2; k <= n_pad; k <<= 1)
     for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-      for (uint32_t i = threadIdx.x; i < n_pad; i += kThreads) {
-        const uint32_t l = i ^ j;
-        if (l <= i) continue;
-        const bool asc = (i & k) == 0;
-        const bool greater = key[i] > key[l] || (key[i] == key[l] && aux[i] > aux[l]);
-        if (greater == asc) {
-          const unsigned long long tk = key[i];
-          key[i] = key[l];
-          key[l] = tk;
-          const uint32_t ta = aux[i];
-          aux[i] = aux[l];
-          aux[l] = ta;
-          if (val) {
-            const uint32_t tv = val[i];
-            val[i] = val[l];
-            val[l] = tv;
-          }
+      for (uint32_t t = threadIdx.x; t < n_pad / 2; t += kRepairThreads) {
+        const uint32_t i = 2 * t - (t & (j - 1)), l = i + j;
+        const unsigned long long ki = key[i], kl = key[l];
+        const uint32_t ai = aux[i], al = aux[l];
+        if ((ki > kl || (ki == kl && ai > al)) != ((i & k) == 0)) continue;
+        key[i] = kl;
+        key[l] = ki;
+        aux[i] = al;
+        aux[l] = ai;
+        if (val) {
+          const uint32_t tv = val[i];
+          val[i] = val[l];
+          val[l] = tv;
         }
       }
-      __syncthreads();
+      // (the next pass: distance j / 2, or after the last k)
+      if (LDS && (j > 1 ? j / 2 : k) <= uint32_t(kWave) && j <= uint32_t(kWave)) wave_sync();
+      else __syncthreads();
     }
+  if (LDS) __syncthreads();
+}
+__device__ void block_bitonic(unsigned long long* key, uint32_t* aux, uint32_t* val, uint32_t n_pad,
+                              unsigned long long* lk, uint32_t* la, uint32_t* lv) {
+  if (n_pad > kLdsBitonic) {
+    bitonic_passes<false>(key, aux, val, n_pad);
+    return;
+  }
+  if (key == lk) {   // (then aux and val are theirs too)
+    bitonic_passes<true>(lk, la, val ? lv : nullptr, n_pad);
+    return;
+  }
+  for (uint32_t i = threadIdx.x; i < n_pad; i += kRepairThreads) {
+    lk[i] = key[i];
+    la[i] = aux[i];
+    if (val) lv[i] = val[i];
+  }
+  __syncthreads();
+  bitonic_passes<true>(lk, la, val ? lv : nullptr, n_pad);
+  for (uint32_t i = threadIdx.x; i < n_pad; i += kRepairThreads) {
+    key[i] = lk[i];
+    aux[i] = la[i];
+    if (val) val[i] = lv[i];
+  }
+  __syncthreads();
 }
 
 __device__ inline bool repeats_node(const uint32_t* m, uint32_t s) {
@@ -707,12 +700,12 @@ __global__ void k_null_deal(uint32_t R, uint32_t E, uint64_t T, const unsigned l
 // sort (2 n_bad <= kLdsBitonic) keeps the list, the pool offsets and, when
 // the pool fits too, the pool and its keys in LDS; larger rounds use the
 // scratch arrays in device memory (the sort works on either).
-__global__ void __launch_bounds__(kThreads) k_null_repair(uint32_t c0, uint32_t R, uint32_t E, uint64_t T,
+__global__ void __launch_bounds__(kRepairThreads) k_null_repair(uint32_t c0, uint32_t R, uint32_t E, uint64_t T,
                                                           const unsigned long long* __restrict__ off,
                                                           uint32_t* __restrict__ members,
                                                           const unsigned long long* __restrict__ seed_p,
                                                           RepairScratch sc, bool pre, uint32_t* __restrict__ failed) {
-  __shared__ uint32_t wsum[kWavesPerBlock];
+  __shared__ uint32_t wsum[kRepairWaves];
   __shared__ uint32_t lstart[kBadLists + 1];
   __shared__ unsigned long long lk[kLdsBitonic];
   __shared__ uint32_t la[kLdsBitonic], lv[kLdsBitonic];
@@ -742,11 +735,11 @@ __global__ void __launch_bounds__(kThreads) k_null_repair(uint32_t c0, uint32_t 
       }
       __syncthreads();
       n_bad = lstart[kBadLists];
-      for (uint32_t k = threadIdx.x / kWave; k < kBadLists; k += kWavesPerBlock)
+      for (uint32_t k = threadIdx.x / kWave; k < kBadLists; k += kRepairWaves)
         for (uint32_t j = lstart[k] + (threadIdx.x & (kWave - 1)); j < lstart[k + 1]; j += kWave)
           g_chosen[j] = bad[k * sc.bad_cap + (j - lstart[k])];
       __syncthreads();
-      for (uint32_t q = threadIdx.x; q < n_bad; q += kThreads) bad[q] = g_chosen[q];
+      for (uint32_t q = threadIdx.x; q < n_bad; q += kRepairThreads) bad[q] = g_chosen[q];
       __syncthreads();
     } else {
       n_bad = block_compact(E, [&](uint32_t i) {
@@ -764,31 +757,31 @@ __global__ void __launch_bounds__(kThreads) k_null_repair(uint32_t c0, uint32_t 
       uint32_t* aux = small ? la : g_aux;
       uint32_t* tmp = small ? lv : bad;   // (bad is not read again in the round once copied)
       // partners, then the ascending union of bad and partners
-      for (uint32_t q = threadIdx.x; q < 2 * n_bad; q += kThreads)
+      for (uint32_t q = threadIdx.x; q < 2 * n_bad; q += kRepairThreads)
         chosen[q] = q < n_bad ? bad[q]
                               : uint32_t(bounded64(philox4x64_10(q - n_bad, uint64_t(r), 1, 0, seed, k1).v[0], E));
-      for (uint32_t q = 2 * n_bad + threadIdx.x; q < pad; q += kThreads) chosen[q] = 0xFFFFFFFFu;
+      for (uint32_t q = 2 * n_bad + threadIdx.x; q < pad; q += kRepairThreads) chosen[q] = 0xFFFFFFFFu;
       __syncthreads();
       // sort the 32-bit list with the key and aux arrays (key = value)
-      for (uint32_t q = threadIdx.x; q < pad; q += kThreads) {
+      for (uint32_t q = threadIdx.x; q < pad; q += kRepairThreads) {
         key[q] = chosen[q];
         aux[q] = 0;
       }
       __syncthreads();
       block_bitonic(key, aux, nullptr, pad, lk, la, lv);
-      for (uint32_t q = threadIdx.x; q < pad; q += kThreads) chosen[q] = uint32_t(key[q]);
+      for (uint32_t q = threadIdx.x; q < pad; q += kRepairThreads) chosen[q] = uint32_t(key[q]);
       __syncthreads();
       const uint32_t n_ch = block_compact(2 * n_bad, [&](uint32_t q) {
         return q == 0 || chosen[q] != chosen[q - 1];
       }, aux, wsum);
       // aux[0..n_ch) = positions of first copies; gather them (ascending, unique)
-      for (uint32_t q = threadIdx.x; q < n_ch; q += kThreads) tmp[q] = chosen[aux[q]];
+      for (uint32_t q = threadIdx.x; q < n_ch; q += kRepairThreads) tmp[q] = chosen[aux[q]];
       __syncthreads();
-      for (uint32_t q = threadIdx.x; q < n_ch; q += kThreads) chosen[q] = tmp[q];
+      for (uint32_t q = threadIdx.x; q < n_ch; q += kRepairThreads) chosen[q] = tmp[q];
       __syncthreads();
       // pool offsets and gather
       uint32_t pool = 0;
-      for (uint32_t base = 0; base < n_ch; base += kThreads) {
+      for (uint32_t base = 0; base < n_ch; base += kRepairThreads) {
         const uint32_t q = base + threadIdx.x;
         const uint32_t s = q < n_ch ? uint32_t(off[chosen[q] + 1] - off[chosen[q]]) : 0u;
         uint32_t tot;
@@ -807,13 +800,13 @@ __global__ void __launch_bounds__(kThreads) k_null_repair(uint32_t c0, uint32_t 
       unsigned long long* pkey = pool_small ? lk : g_key;
       uint32_t* paux = pool_small ? la : g_aux;
       uint32_t* pval = pool_small ? lv : g_val;
-      for (uint32_t q = threadIdx.x; q < n_ch; q += kThreads) {
+      for (uint32_t q = threadIdx.x; q < n_ch; q += kRepairThreads) {
         const unsigned long long b = off[chosen[q]];
         const uint32_t s = uint32_t(off[chosen[q] + 1] - b);
         for (uint32_t t = 0; t < s; ++t) pval[poff[q] + t] = m[b + t];
       }
       __syncthreads();
-      for (uint32_t t = threadIdx.x; t < ppad; t += kThreads) {
+      for (uint32_t t = threadIdx.x; t < ppad; t += kRepairThreads) {
         if (t < pool) {
           pkey[t] = philox4x64_10(t, uint64_t(r), 0, 0, seed, k1).v[0];
           paux[t] = t;
@@ -826,7 +819,7 @@ __global__ void __launch_bounds__(kThreads) k_null_repair(uint32_t c0, uint32_t 
       __syncthreads();
       block_bitonic(pkey, paux, pval, ppad, lk, la, lv);
       // deal back and find the hyperedges that still repeat a node
-      for (uint32_t q = threadIdx.x; q < n_ch; q += kThreads) {
+      for (uint32_t q = threadIdx.x; q < n_ch; q += kRepairThreads) {
         const unsigned long long b = off[chosen[q]];
         const uint32_t s = uint32_t(off[chosen[q] + 1] - b);
         for (uint32_t t = 0; t < s; ++t) m[b + t] = pval[poff[q] + t];
@@ -836,7 +829,7 @@ __global__ void __launch_bounds__(kThreads) k_null_repair(uint32_t c0, uint32_t 
         const unsigned long long b = off[chosen[q]];
         return repeats_node(m + b, uint32_t(off[chosen[q] + 1] - b));
       }, paux, wsum);
-      for (uint32_t q = threadIdx.x; q < n_bad; q += kThreads) bad[q] = chosen[paux[q]];
+      for (uint32_t q = threadIdx.x; q < n_bad; q += kRepairThreads) bad[q] = chosen[paux[q]];
       __syncthreads();
     }
     if (n_bad > 0 && threadIdx.x == 0) atomicOr(failed, 1u);
@@ -1859,7 +1852,7 @@ int enqueue_stubs(const hm_graph* H, NullPlan& P, uint32_t c0, hipStream_t st) {
     k_null_gather<<<grid_for(n), 256, 0, st>>>(P.order, n, P.T, H->all_members, P.members);
   }
   HM_HIP(hipGetLastError());
-  k_null_repair<<<P.repair_blocks, kThreads, 0, st>>>(c0, P.R, P.E, P.T, H->all_off, P.members, P.seed, P.rs, pre,
+  k_null_repair<<<P.repair_blocks, kRepairThreads, 0, st>>>(c0, P.R, P.E, P.T, H->all_off, P.members, P.seed, P.rs, pre,
                                                       P.failed);
   HM_HIP(hipGetLastError());
   return HM_OK;

@@ -233,3 +233,15 @@ def test_copy_rows_match_hash(hm, n, k):
             hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
     for b, h in zip(got[8192], got[0]):
         assert np.array_equal(b, h)
+
+
+@pytest.mark.parametrize("edges", [4, 60, 300, 700, 1500, 6000])
+def test_repairs_of_every_size_match_oracle(hm, edges):
+    """Repairs whose lists are sorted within a wavefront, by the workgroup in
+    LDS and in device memory."""
+    h = W.random_small(5400 + edges, 25, edges, {2: 0.5, 3: 0.3, 4: 0.15, 5: 0.05}, allow_dups=True)
+    with hm.hm_graph_create(h.members, h.offsets, h.n_nodes) as g:
+        for copy in (0, 3):
+            m, o = hm.hm_null_export(g, 21, copy)
+            wm, wo = nulls.stub_matching(h, 21, copy)
+            assert np.array_equal(o, wo) and np.array_equal(m, wm), copy
