@@ -353,3 +353,31 @@ def test_pair_sets_match_bit_rows(hm, n, third, degree):
         hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
         hm.hm_set_option(hm.HM_OPT_SAMPLE_CHUNK_SCALE, 1)
     assert len({x.tobytes() for x in got.values()}) == 1
+
+
+@pytest.mark.parametrize("samples", [1, 20, 100, 500, 4000])
+def test_queue_sizes_match_bit_rows(hm, samples):
+    """Queues of no job, of fewer and of more than a part has workgroups, and
+    of thousands in all, against the bit-row path."""
+    n = 400
+    rng = np.random.default_rng(samples)
+    hub = np.sort(np.c_[np.zeros(2 * n, int), rng.integers(1, n, (2 * n, 2))], axis=1)
+    parts = [np.sort(rng.integers(0, n, (6 * n, 2)), axis=1), np.c_[np.zeros(n - 1, int), np.arange(1, n)], hub,
+             np.sort(rng.integers(0, n, (n, 4)), axis=1)]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in parts]
+    members = np.concatenate([e.ravel() for e in parts]).astype(np.uint32)
+    offsets = np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))].astype(np.uint64)
+    got = []
+    try:
+        for bits, scales in ((8192, (1,)), (0, (1, 4, 16, 64))):
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+            with hm.hm_graph_create(members, offsets, n) as g:
+                st = g.stats()
+                idx = {j: np.random.default_rng(j).integers(0, st["n%d" % j], samples) for j in (2, 3)}
+                for scale in scales:
+                    hm.hm_set_option(hm.HM_OPT_SAMPLE_CHUNK_SCALE, scale)
+                    got.append(hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy())
+    finally:
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+        hm.hm_set_option(hm.HM_OPT_SAMPLE_CHUNK_SCALE, 1)
+    assert len({x.tobytes() for x in got}) == 1
