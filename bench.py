@@ -72,14 +72,16 @@ def _unit_counts(e2: np.ndarray, e3: np.ndarray, n_nodes: int, words: int) -> di
 
 def _b4_positions(e2: np.ndarray, e3: np.ndarray, e4: np.ndarray, n_nodes: int) -> dict:
     """Work of the 3-node-hyperedge step without bit rows, counted from the
-    strata as its two kernels walk it.  k_sp_b4, per 3-node hyperedge
-    e = {a<b<c}: the shortest pairwise row among a, b, c (each entry tested
-    against the other two members) and the 4-node hyperedges holding e.
-    k_sp_b4_runs, per entry of the pair index (a pair P of e with the third
-    node t) whose run holds L >= 2 entries: the other L - 1 entries of the
-    run when L - 1 <= d(t) + L(P0, t) + L(P1, t) + (4-node hyperedges holding
-    e), else those lists.  Each position is a few lookups (a third node, a
-    membership test against a list in LDS, a dense-row word or a hash probe)."""
+    strata as a walk of every set around every hyperedge meets it (k_tri_items
+    and k_run_items look at about half of the second kind: a run's pairs of
+    entries once each, and 4-node hyperedges not at all).  Per 3-node
+    hyperedge e = {a<b<c}: the shortest pairwise row among a, b, c (each entry
+    tested against the other two members) and the 4-node hyperedges holding e.
+    Per entry of the pair index (a pair P of e with the third node t) whose
+    run holds L >= 2 entries: the other L - 1 entries of the run when L - 1 <=
+    d(t) + L(P0, t) + L(P1, t) + (4-node hyperedges holding e), else those
+    lists.  Each position is a few lookups (a third node, a search in a short
+    list, a dense-row word or a hash probe)."""
     n = np.int64(n_nodes)
     if len(e3) == 0:
         return {"positions_b4": 0, "positions_runs": 0, "hyperedges": 0, "entries": 0, "entries_active": 0}
@@ -160,8 +162,8 @@ def measured_valu_issue():
     return float(frac)
 
 
-LOOKUP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_lookup_k_sp_b4_heavy_tailed.md")
-LOOKUP_SOURCES = ("sparse.hip", "hm_sparse.h", "hm_device.h", "hm_internal.h", "prims.hip")
+LOOKUP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_lookup_k_run_items_heavy_tailed.md")
+LOOKUP_SOURCES = ("triples.hip", "hm_sparse.h", "hm_device.h", "hm_internal.h", "prims.hip")
 
 
 def lookup_source_digest() -> str:
@@ -174,7 +176,7 @@ def lookup_source_digest() -> str:
 
 
 def measured_lookup_traffic() -> dict:
-    """HBM bytes per count of k_sp_b4 plus k_sp_b4_runs (FETCH_SIZE + WRITE_SIZE,
+    """HBM bytes per count of k_tri_items plus k_run_items (FETCH_SIZE + WRITE_SIZE,
     copy-calibrated) by workload, if the profile is still current."""
     try:
         lines = open(LOOKUP_TRAFFIC_FILE).read().splitlines()
@@ -248,9 +250,9 @@ def large_workloads(hm, W, torch, seeds: int = 32, exact_only: bool = False) -> 
         kernels = {k: {"launches": n, "avg_ms": ms / max(n, 1)} for k, (n, ms) in prof.items()}
         model = _b4_positions(g.export(2), g.export(3), g.export(4), h.n_nodes)
         lookup = None
-        if "k_sp_b4" in kernels and "k_sp_b4_runs" in kernels:
-            ms = kernels["k_sp_b4"]["avg_ms"] + kernels["k_sp_b4_runs"]["avg_ms"]
-            lookup = {"kernels": ["k_sp_b4", "k_sp_b4_runs"], "ms": ms,
+        if "k_tri_items" in kernels and "k_run_items" in kernels:
+            ms = kernels["k_tri_items"]["avg_ms"] + kernels["k_run_items"]["avg_ms"]
+            lookup = {"kernels": ["k_tri_items", "k_run_items"], "ms": ms,
                       "positions_per_s": (model["positions_b4"] + model["positions_runs"]) / (ms / 1e3), **model}
             # HBM bytes of the two kernels from the committed counter runs
             # (FETCH_SIZE + WRITE_SIZE per launch), while the sources match
