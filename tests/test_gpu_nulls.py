@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from oracle import core, nulls, profiles
+from oracle import core, nulls
 
 pytestmark = pytest.mark.gpu
 
@@ -171,6 +171,7 @@ def test_orders_match_oracle(hm, n_pairs):
 def test_config_rounds_match_oracle(hm, edges, sizes):
     """All rounds of a copy by one workgroup up to its largest numbers of
     hyperedges and members, and round by round beyond either."""
+    from oracle import profiles
     h = W.random_small(edges, 2500, edges, {s: 1.0 for s in sizes})
     if sizes == (2,):
         h = _pairs(2500, edges, edges)
