@@ -416,6 +416,67 @@ int noalloc_scratch(int dev, unsigned long long** out) {
 
 }  // namespace
 
+// Sum of d^2 over the n nodes (one workgroup of 1024).
+__global__ void __launch_bounds__(1024) k_degree_squares(const uint32_t* __restrict__ g2_off, uint32_t n,
+                                                         unsigned long long* __restrict__ out) {
+  __shared__ unsigned long long sums[1024 / kWave];
+  unsigned long long s = 0;
+  for (uint32_t x = threadIdx.x; x < n; x += 1024) {
+    const unsigned long long d = g2_off[x + 1] - g2_off[x];
+    s += d * d;
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) sums[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s = 0;
+    for (uint32_t w = 0; w < 1024 / kWave; ++w) s += sums[w];
+    *out = s;
+  }
+}
+
+// Whether the host may wait for st and allocate: not while it is captured.
+static bool may_wait(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(st, &status);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess && status == hipStreamCaptureStatusNone;
+}
+
+// Whether a graph with bit rows counts order 4 as one without them (by ranked
+// walks and pair runs).  Off the identity route (above 2,574 nodes) case (c)
+// enumerates: for each pair the rows of both ends, a word of every bit row at a
+// time, sum of d^2 x W words in all.  That takes about 0.9 us per million; the
+// runs take 0.65 ms for the smallest graphs and grow slowly (with the build:
+// 65,000 pairs of even degrees on 2,600 nodes, 5.8e8 words, 0.55 ms against
+// 0.85; 97,000 on 8,000, 1.2e9, 1.11 against 0.88; heavy-tailed degrees on 2,600,
+// 5,000 and 8,000 nodes, 2.4e9 to 5.8e10, 3.6, 12.2 and 55.5 ms against 1.3, 1.8
+// and 2.3).  So the line is 2^30 words.  With all degrees alike the sum is
+// 4 n2^2 / N, its least; where that is within a factor of four of the line the
+// degrees themselves are asked, once per graph (35 us).  The runs need scratch memory and wait once: a stream that is being
+// captured keeps the bit rows, as does a device without the memory.
+static int prefers_runs(const hm_graph* H, hipStream_t st, bool* runs) {
+  *runs = false;
+  if (use_identities(H->n_nodes, H->words) || H->n_nodes == 0) return HM_OK;
+  constexpr unsigned long long kLine = 1ull << 30;
+  const unsigned long long n2 = H->n_by_size[2], least = 4 * n2 * n2 / H->n_nodes * H->words;
+  if (least < kLine / 4 || !may_wait(st)) return HM_OK;
+  if (least < kLine && !H->degree_squares_known) {
+    Scratch tmp(st);
+    unsigned long long* sum = nullptr;
+    const int rc = tmp.get(&sum, 1);
+    if (rc == HM_ENOMEM) return HM_OK;
+    HM_TRY(rc);
+    k_degree_squares<<<1, 1024, 0, st>>>(H->g2_off, H->n_nodes, sum);
+    HM_HIP(hipGetLastError());
+    HM_HIP(hipMemcpyAsync(&H->degree_squares, sum, sizeof(*sum), hipMemcpyDeviceToHost, st));
+    HM_HIP(hipStreamSynchronize(st));
+    H->degree_squares_known = true;
+  }
+  *runs = least >= kLine || H->degree_squares * H->words >= kLine;
+  return HM_OK;
+}
+
 int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) {
   note_use(H, st);
   const uint8_t *lut4 = nullptr, *lut3 = nullptr;
@@ -438,7 +499,10 @@ int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) 
   const uint64_t n3 = H->n_by_size[3], n4 = H->n_by_size[4];
   const View v = view_of(H);
   bool id = false;
-  if (v.bits) {
+  bool runs = !v.bits;
+  if (!runs && k == 4) HM_TRY(prefers_runs(H, st, &runs));
+  const bool by_bits = !runs;
+  if (by_bits) {
     id = launch_bits_count(H, k, k == 4 ? lut4 : lut3, H->hist, st);
   } else {
     if (k == 4 && n4) {
@@ -450,7 +514,14 @@ int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) 
       k_case_a3<<<grid_threads(n3), kThreads, 0, st>>>(v, n3, lut3, H->hist);
     }
     HM_HIP(hipGetLastError());
-    HM_TRY(count_sparse(H, k, st));
+    int rc = v.bits ? ensure_pair_positions(const_cast<hm_graph*>(H), st) : HM_OK;
+    if (rc == HM_OK) rc = count_sparse(H, k, st);
+    if (rc == HM_ENOMEM && v.bits) {
+      HM_TRY(fill_u64(H->hist, 0, uint64_t(kHistCopies) * kExactHistStride, st));
+      id = launch_bits_count(H, k, lut4, H->hist, st);
+      rc = HM_OK;
+    }
+    HM_TRY(rc);
   }
   HM_HIP(hipGetLastError());
   k_combine<<<1, 256, 0, st>>>(H->hist, t.n_classes[k], pairs_only, counts, id_shapes(id));

@@ -1620,6 +1620,25 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
   return HM_OK;
 }
 
+// g2_eid of a graph with bit rows, whose neighbour rows were read off them.
+template <typename K>
+int sorted_pair_positions(hm_graph* H, Temps& tmp, hipStream_t st) {
+  const uint64_t n2 = H->n_by_size[2], m = 2 * n2;
+  const int B = node_bits(H->n_nodes);
+  K *keys, *keys_tmp;
+  uint32_t *eid, *eid_tmp;
+  HM_TRY(tmp.get(&keys, m));
+  HM_TRY(tmp.get(&keys_tmp, m));
+  HM_TRY(tmp.get(&eid, m));
+  HM_TRY(tmp.get(&eid_tmp, m));
+  k_pair_keys<K><<<grid_for(n2), 256, 0, st>>>(H->e2, n2, B, keys, eid);
+  HM_HIP(hipGetLastError());
+  HM_TRY(radix_sort_pairs(keys, eid, keys_tmp, eid_tmp, m, 2 * B, st));
+  tmp.ptrs.erase(std::find(tmp.ptrs.begin(), tmp.ptrs.end(), static_cast<void*>(eid)));
+  H->g2_eid = eid;
+  return HM_OK;
+}
+
 // Device memory of a graph.  With a stream, it returns to the cache once the
 // work enqueued on that stream so far has run; without, at once (its users
 // have been synchronised).
@@ -1650,6 +1669,16 @@ void release(hm_graph* H, hipStream_t st = nullptr, bool ordered = false) {
 }
 
 }  // namespace
+
+// The position in e2 of each neighbour row's entry, built on first use where
+// the build did not need it.
+int ensure_pair_positions(hm_graph* H, hipStream_t st) {
+  if (H->g2_eid || H->n_by_size[2] == 0) return HM_OK;
+  Temps tmp(st);
+  if (2 * node_bits(H->n_nodes) <= 32) return sorted_pair_positions<uint32_t>(H, tmp, st);
+  return sorted_pair_positions<unsigned long long>(H, tmp, st);
+}
+
 }  // namespace hm
 
 extern "C" {

@@ -250,6 +250,7 @@ int ensure_pair_links(hm_graph* H, hipStream_t st);
 int ensure_quad_index(hm_graph* H, hipStream_t st);
 int ensure_hub_rows(hm_graph* H, hipStream_t st);
 int ensure_ranks(hm_graph* H, hipStream_t st);
+int ensure_pair_positions(hm_graph* H, hipStream_t st);
 int ensure_node_stats(hm_graph* H, hipStream_t st);
 int ensure_edge_stats(hm_graph* H, hipStream_t st);
 
@@ -302,6 +303,10 @@ struct hm_graph {
   // adjacency bit rows of the pairwise graph (n_nodes x words), when kept
   uint32_t* bits = nullptr;
   uint32_t words = 0;
+  // sum of the squared degrees of the pairwise graph (order-4 counts, on first
+  // need; see prefers_runs)
+  mutable unsigned long long degree_squares = 0;
+  mutable bool degree_squares_known = false;
 
   // histogram scratch, reused by the counting calls (serialised per graph):
   // kHistCopies copies of main, sub and G2 regions of 256 counters (and 256

@@ -816,3 +816,39 @@ def test_large_build(hm, tag_bits):
             hm.hm_graph_create(members, offsets, n)
     finally:
         hm.hm_set_option(hm.HM_OPT_DEDUP_TAG_BITS, 32)
+
+
+@pytest.mark.parametrize("n,pairs,hubs", [(2574, 100_000, 0), (2575, 40_000, 0), (2575, 60_000, 0), (2575, 60_000, 6),
+                                          (2575, 100_000, 0), (8192, 30_000, 10)])
+def test_count_beyond_identities_matches_noalloc(hm, n, pairs, hubs):
+    """Graphs with bit rows on both sides of the identity route's end, of few
+    pairs, of more with even degrees and with hubs, and of many: count_exact,
+    by either way, against the count that always takes the bit rows, on a first
+    call, a second one and after samples."""
+    rng = np.random.default_rng(n + pairs + hubs)
+    e2 = np.r_[rng.integers(0, n, (pairs, 2)), np.c_[np.arange(hubs * (n // 2)) % max(hubs, 1), rng.integers(1, n, hubs * (n // 2))]]
+    e3 = np.r_[rng.integers(0, n, (n, 3)), np.c_[rng.integers(0, 12, (n, 2)), rng.integers(0, n, n)]]
+    e4 = np.r_[rng.integers(0, n, (n // 2, 4)), np.c_[rng.integers(0, 12, (n // 4, 3)), rng.integers(0, n, n // 4)]]
+    parts = [np.sort(e, axis=1) for e in (e2, e3, e4)]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in parts]
+    members = np.concatenate([e.ravel() for e in parts]).astype(np.uint32)
+    offsets = np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))].astype(np.uint64)
+
+    def by_bit_rows(g):
+        import ctypes
+        import torch
+        out = torch.empty(hm.hm_num_classes(4), dtype=torch.int64, device="cuda")
+        assert hm.lib().count_exact_noalloc(g.handle, 4, ctypes.c_void_p(out.data_ptr()), None) == 0
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    with hm.hm_graph_create(members, offsets, n) as g:
+        want = by_bit_rows(g)
+        first = hm.count_exact(g, 4).cpu().numpy()
+        idx = {j: rng.integers(0, g.stats()["n%d" % j], 50) for j in (2, 3, 4)}
+        raw = hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy()
+        second = hm.count_exact(g, 4).cpu().numpy()
+        third = by_bit_rows(g)
+        assert np.array_equal(raw, hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy())
+    for got in (first, second, third):
+        assert np.array_equal(got, want)
