@@ -455,13 +455,13 @@ static bool may_wait(hipStream_t st) {
 // 4 n2^2 / N, its least; where that is within a factor of four of the line the
 // degrees themselves are asked, once per graph (35 us).  The runs need scratch memory and wait once: a stream that is being
 // captured keeps the bit rows, as does a device without the memory.
-static int prefers_runs(const hm_graph* H, hipStream_t st, bool* runs) {
+int prefers_runs(const hm_graph* H, hipStream_t st, bool* runs) {
   *runs = false;
   if (use_identities(H->n_nodes, H->words) || H->n_nodes == 0) return HM_OK;
   constexpr unsigned long long kLine = 1ull << 30;
   const unsigned long long n2 = H->n_by_size[2], least = 4 * n2 * n2 / H->n_nodes * H->words;
   if (least < kLine / 4 || !may_wait(st)) return HM_OK;
-  if (least < kLine && !H->degree_squares_known) {
+  if (!H->degree_squares_known) {   // (the samplers' rule reads the sum as well)
     Scratch tmp(st);
     unsigned long long* sum = nullptr;
     const int rc = tmp.get(&sum, 1);

@@ -250,6 +250,7 @@ int ensure_pair_links(hm_graph* H, hipStream_t st);
 int ensure_quad_index(hm_graph* H, hipStream_t st);
 int ensure_hub_rows(hm_graph* H, hipStream_t st);
 int ensure_ranks(hm_graph* H, hipStream_t st);
+int prefers_runs(const hm_graph* H, hipStream_t st, bool* runs);
 int ensure_pair_positions(hm_graph* H, hipStream_t st);
 int ensure_node_stats(hm_graph* H, hipStream_t st);
 int ensure_edge_stats(hm_graph* H, hipStream_t st);
@@ -307,6 +308,8 @@ struct hm_graph {
   // need; see prefers_runs)
   mutable unsigned long long degree_squares = 0;
   mutable bool degree_squares_known = false;
+  // order-4 pair samples that calls before asked for (see walks_samples)
+  mutable uint64_t sampled_pairs = 0;
 
   // histogram scratch, reused by the counting calls (serialised per graph):
   // kHistCopies copies of main, sub and G2 regions of 256 counters (and 256

@@ -1332,6 +1332,34 @@ uint32_t blocks_for(uint64_t items, uint64_t per_block, uint32_t cap) {
   return uint32_t(std::min<uint64_t>((items + per_block - 1) / per_block, cap));
 }
 
+// Whether samples of a graph with bit rows are taken as without them.  A pair
+// sample reads a bit row for each neighbour of its ends; the walks need the pair
+// statistics and links first, 1.6 ms once per graph, and then take 0.15 to 0.32
+// ms where the bit rows take 1.1 to 7.1 (heavy-tailed graphs of 5,000 and 8,000
+// nodes at 0.5 and 2%).  A graph's first call cannot know that others follow
+// and keeps the bit rows.  On graphs whose exact count leaves them
+// (prefers_runs) a later call turns to the walks when the samples of all calls
+// so far have read 2^27 words, about as much time as the indices take.
+int walks_samples(const hm_graph* H, uint64_t S2, hipStream_t st, bool* walks) {
+  *walks = false;
+  const uint64_t before = H->sampled_pairs, n2 = std::max<uint64_t>(H->n_by_size[2], 1);
+  H->sampled_pairs += S2;
+  bool runs = false;
+  if (before) HM_TRY(prefers_runs(H, st, &runs));
+  *walks = runs && double(before + S2) * double(H->degree_squares) * H->words / double(n2) >= double(1ull << 27);
+  return HM_OK;
+}
+
+// What the samplers of graphs without bit rows look up, built on first use.
+int ensure_sample_indices(hm_graph* H, hipStream_t st) {
+  HM_TRY(ensure_pair_positions(H, st));
+  HM_TRY(ensure_pair_links(H, st));
+  HM_TRY(ensure_quad_index(H, st));
+  HM_TRY(ensure_edge_stats(H, st));
+  HM_TRY(ensure_node_stats(H, st));
+  return ensure_hub_rows(H, st);
+}
+
 // Launch the sampler over every stratum: explicit indices (idx[j] non-null)
 // or draws of the stratum's stream under `seed`.  rows != null: sample s of
 // stratum j adds to row rows[row0[j] + s] and nothing is scaled; otherwise
@@ -1341,17 +1369,19 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   note_use(H, st);
   const uint8_t *lut4 = nullptr, *lut3 = nullptr;
   HM_TRY(device_luts(H->device, &lut4, &lut3));
-  const bool bits = H->bits != nullptr;
+  bool bits = H->bits != nullptr;
   if (k == 4 && bits && H->words > kMaxWordsJ2) {
     set_error("bit rows of %u words exceed the sampler's %u", H->words, kMaxWordsJ2);
     return HM_EINTERNAL;
   }
-  if (k == 4 && !bits) {
-    HM_TRY(ensure_pair_links(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_quad_index(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_edge_stats(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_node_stats(const_cast<hm_graph*>(H), st));
-    HM_TRY(ensure_hub_rows(const_cast<hm_graph*>(H), st));
+  if (k == 4) {
+    bool walks = !bits;
+    if (bits) HM_TRY(walks_samples(H, S[2], st, &walks));
+    if (walks) {
+      const int rc = ensure_sample_indices(const_cast<hm_graph*>(H), st);
+      if (rc != HM_ENOMEM || !bits) HM_TRY(rc);
+      bits = rc != HM_OK;   // (without the memory, the bit rows)
+    }
   }
   SampledArgs a;
   a.v = view_of(H);
@@ -1435,12 +1465,18 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   if (k == 4 && !bits) {
     a.q.cap = std::min<uint64_t>(kQueuePerSample * scale * (a.d.S[2] + a.d.S[3]) / kQueueParts + 65536,
                                  kQueueMax / kQueueParts);
-    HM_TRY(dalloc(&rel.p[0], kQueueParts * a.q.cap * sizeof(uint4)));
-    HM_TRY(dalloc(&rel.p[1], (a.d.S[2] + 1) * sizeof(uint4)));
-    HM_TRY(dalloc(&rel.p[2], (a.d.S[3] + 1) * sizeof(uint32_t)));
-    a.q.job = static_cast<uint4*>(rel.p[0]);
-    a.q.info = static_cast<uint4*>(rel.p[1]);
-    a.q.info3 = static_cast<uint32_t*>(rel.p[2]);
+    int rc = dalloc(&rel.p[0], kQueueParts * a.q.cap * sizeof(uint4));
+    if (rc == HM_OK) rc = dalloc(&rel.p[1], (a.d.S[2] + 1) * sizeof(uint4));
+    if (rc == HM_OK) rc = dalloc(&rel.p[2], (a.d.S[3] + 1) * sizeof(uint32_t));
+    if (rc != HM_ENOMEM || !H->bits) HM_TRY(rc);
+    if (rc == HM_OK) {
+      a.q.job = static_cast<uint4*>(rel.p[0]);
+      a.q.info = static_cast<uint4*>(rel.p[1]);
+      a.q.info3 = static_cast<uint32_t*>(rel.p[2]);
+    } else {
+      bits = true;
+      a.q.cap = 0;
+    }
   }
   ProfileScope pscope("k_sampled", st);
   if (k == 4 && bits)

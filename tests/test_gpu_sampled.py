@@ -381,3 +381,36 @@ def test_queue_sizes_match_bit_rows(hm, samples):
         hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
         hm.hm_set_option(hm.HM_OPT_SAMPLE_CHUNK_SCALE, 1)
     assert len({x.tobytes() for x in got}) == 1
+
+
+@pytest.mark.parametrize("n,samples", [(2574, 60), (2575, 60), (4000, 3), (8192, 40)])
+def test_samples_beyond_identities_match_hash(hm, n, samples):
+    """Graphs with bit rows and hubs whose samples turn from the rows to the
+    walks: each of several calls, an exact count between them, and drawn
+    estimates against the graph without bit rows."""
+    rng = np.random.default_rng(n)
+    hub = np.c_[np.arange(8 * 1200) % 8, rng.integers(8, n, 8 * 1200)]
+    parts = [np.r_[rng.integers(0, n, (40_000, 2)), hub], np.r_[rng.integers(0, n, (n, 3)), np.c_[hub, rng.integers(8, n, len(hub))]],
+             rng.integers(0, n, (n // 2, 4))]
+    parts = [np.sort(e, axis=1) for e in parts]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in parts]
+    members = np.concatenate([e.ravel() for e in parts]).astype(np.uint32)
+    offsets = np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))].astype(np.uint64)
+    got = {}
+    for bits in (8192, 0):
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, bits)
+        try:
+            with hm.hm_graph_create(members, offsets, n) as g:
+                st, out = g.stats(), []
+                for call in range(4):
+                    draw = np.random.default_rng(call)
+                    idx = {j: draw.integers(0, st["n%d" % j], samples << (2 * call)) for j in (2, 3, 4)}
+                    out.append(hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy())
+                    if call == 1:
+                        out.append(hm.count_exact(g, 4).cpu().numpy())
+                out += [x.cpu().numpy() for x in hm.count_sampled(g, 4, 0.02, 5)]
+                got[bits] = out
+        finally:
+            hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+    for b, h in zip(got[8192], got[0]):
+        assert np.array_equal(b, h)
