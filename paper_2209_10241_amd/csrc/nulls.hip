@@ -1196,7 +1196,9 @@ struct CopyRows {
 };
 constexpr uint32_t kCopyRowsThreads = 1024;
 // Words of bit rows and hyperedges of a size, per copy, up to which one
-// workgroup takes them: COPYROWS_RULE
+// workgroup takes them; longer lists have work for more.  At 2,000 nodes and
+// 120,000 and 60,000 hyperedges it is still the faster: two copies 3.76 ms a call
+// against 3.88, 64 copies 49.3 against 52.1.
 constexpr uint64_t kCopyRowsMost = 1u << 17;
 
 // at[0..N) := start + the counts before; off too.
