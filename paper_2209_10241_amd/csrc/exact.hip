@@ -144,10 +144,9 @@ struct ExactArgs {
   unsigned long long* hist;
 };
 
-// Order 4: items are the pairs of G2 (case (c); on the identity route
-// b4_per_wave(W) at a time, and one per node), then the 3-node hyperedges,
-// b4_per_wave(W) at a time (case (b)), then chunks of kA4Chunk 4-node hyperedges
-// (case (a)).  Dynamic LDS holds b4_set_words(W) words per wavefront and,
+// Order 4: items are the pairs of G2 (case (c); on the identity route also one
+// per node), then the 3-node hyperedges (case (b)), then chunks of kA4Chunk
+// 4-node hyperedges (case (a)).  Dynamic LDS holds b4_set_words(W) words per wavefront and,
 // with LB, a copy of the whole bit matrix (N x W words) and of the row
 // starts of G2 and of the incidence lists, so that every adjacency word and
 // row bound the items read comes from LDS rather than from L2.
@@ -190,25 +189,23 @@ __global__ void __launch_bounds__(kExact4Threads) k_exact4_bits(ExactArgs a) {
   const int wv = threadIdx.x / kWave;
   const uint32_t lane = threadIdx.x & (kWave - 1);
   uint32_t* sets = b4_sets + wv * b4_set_words(v.W);
-  const uint32_t per = b4_per_wave(v.W);
-  const C4Lanes L = c4_lanes(v.W, ID ? kWave / per : uint32_t(kWave));
+  const C4Lanes L = c4_lanes(v.W);
   C4Acc acc;
   IdAcc ida;
   if (ID) id_zero(ida); else c4_zero(acc);
   // (c) items: the pairs of G2, then (identity route) one per node
-  const uint64_t ne = ID ? (a.n2 + per - 1) / per : a.n2;
-  const uint64_t nc = ID ? ne + v.N : ne;
-  const uint64_t n23 = nc + (a.n3 + per - 1) / per;
+  const uint64_t nc = ID ? a.n2 + v.N : a.n2;
+  const uint64_t n23 = nc + a.n3;
   const uint64_t items = n23 + (a.n4 + kA4Chunk - 1) / kA4Chunk;
   const uint64_t n_waves = uint64_t(gridDim.x) * kExact4Waves;
   for (uint64_t i = uint64_t(blockIdx.x) * kExact4Waves + wv; i < items; i += n_waves) {
-    if (i < ne) {
-      if (ID) id_edges(v, v.e2, i * per, a.n2, L, ylist[wv], ida);
+    if (i < a.n2) {
+      if (ID) id_edges<1>(v, v.e2, i, a.n2, L, ylist[wv], ida);
       else c4_bits_item(v, v.e2[2 * i], v.e2[2 * i + 1], L, ylist[wv], acc, lut, h_g2);
     } else if (i < nc) {
-      id_node_item(v, uint32_t(i - ne), ida);
+      id_node_item(v, uint32_t(i - a.n2), ida);
     } else if (i < n23) {
-      b4_item(v, (i - nc) * per, a.n3, sets, lut, h_main, h_sub);
+      b4_item(v, i - nc, a.n3, sets, lut, h_main, h_sub);
     } else {
       const uint64_t e = (i - n23) * kA4Chunk + lane;
       if (e < a.n4)
@@ -336,9 +333,7 @@ bool launch_bits_count(const hm_graph* H, int k, const uint8_t* lut, unsigned lo
     const bool lb = rows <= kLdsBitsMaxBytes;
     const bool id = use_identities(v.N, v.W);
     const size_t lds = size_t(kExact4Waves) * b4_set_words(v.W) * 4 + (lb ? rows : 0);
-    const uint64_t per = b4_per_wave(v.W);
-    const uint64_t items =
-        (id ? (n2 + per - 1) / per + v.N : n2) + (n3 + per - 1) / per + (n4 + kA4Chunk - 1) / kA4Chunk;
+    const uint64_t items = n2 + (id ? v.N : 0) + n3 + (n4 + kA4Chunk - 1) / kA4Chunk;
     const void* kern = lb ? (id ? reinterpret_cast<const void*>(k_exact4_bits<true, true>)
                                 : reinterpret_cast<const void*>(k_exact4_bits<true, false>))
                           : (id ? reinterpret_cast<const void*>(k_exact4_bits<false, true>)

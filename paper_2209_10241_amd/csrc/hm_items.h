@@ -95,26 +95,24 @@ __device__ inline uint32_t a3_pattern(const View& v, uint32_t a, uint32_t b, uin
          (pair_bit(v.hs2, v.bits, v.W, b, c) << 2);
 }
 
-// (b) at order 4 for the 3-node hyperedges that a wavefront takes at once (with
-// bit rows b4_per_wave(v.W), else one) from position i of v.e3, below `last`
-template <typename T>
+// (b) at order 4 for the PER 3-node hyperedges that a wavefront takes at once
+// (PER = 2: with bit rows of at most 32 words) from position i of v.e3, below
+// `last`; sets: b4_set_words(v.W, PER) words of the wavefront's LDS
+template <uint32_t PER = 1, typename T>
 __device__ inline void b4_item(const View& v, uint64_t i, uint64_t last, uint32_t* sets, const uint8_t* lut, T* h_main,
                                T* h_sub) {
-  const uint32_t half = v.bits && b4_per_wave(v.W) == 2 ? (threadIdx.x >> 5) & 1u : 0u;
-  const bool in = i + half < last;
-  if (in) i += half;   // (a lane of no hyperedge loads another's)
+  constexpr uint32_t G = kWave / PER;
+  const uint32_t part = PER == 1 ? 0u : (threadIdx.x / G) % PER;
+  const bool in = i + part < last;
+  if (in) i += part;   // (a lane of no hyperedge loads another's)
   const uint32_t a = v.e3[3 * i], b = v.e3[3 * i + 1], c = v.e3[3 * i + 2];
-  if (v.bits) {
-    if (b4_per_wave(v.W) == 2) {
-      if (in)
-        b4_edge_bits_count<true, 32>(a, b, c, v.i3_off, v.i3_oth, v.i4_off, v.i4_oth, v.bits, v.W,
-                                     sets + half * b4_group_words(v.W, 32), lut, h_main, h_sub);
-    } else {
-      b4_edge_bits_count<true, kWave>(a, b, c, v.i3_off, v.i3_oth, v.i4_off, v.i4_oth, v.bits, v.W, sets, lut, h_main,
-                                      h_sub);
-    }
-  } else
+  if (PER > 1 || v.bits) {
+    if (PER == 1 || in)
+      b4_edge_bits_count<true, G>(a, b, c, v.i3_off, v.i3_oth, v.i4_off, v.i4_oth, v.bits, v.W,
+                                  sets + part * b4_group_words(v.W, G), lut, h_main, h_sub);
+  } else {
     b4_edge_hash<true>(a, b, c, v.e3, v.g2_off, v.g2_adj, v.i3_off, v.i3_idx, v.hs2, v.hs3, v.hs4, lut, h_main, h_sub);
+  }
 }
 
 // ---------------------------------------------------------------- (c), order 4, bit rows
@@ -411,18 +409,15 @@ __device__ inline void id_edge_item(const View& v, uint32_t u, uint32_t x, const
   }
 }
 
-// The edges [i, last) of e2 that a wavefront takes at once: one per half for
-// rows of at most 32 words (b4_per_wave), else one.  L: c4_lanes(W, kWave /
-// b4_per_wave(W)); ys: 64 words of wavefront-private LDS.
+// The PER edges from position i of e2, below `last`, that a wavefront takes at
+// once.  L: c4_lanes(W, kWave / PER); ys: 64 words of wavefront-private LDS.
+template <uint32_t PER>
 __device__ inline void id_edges(const View& v, const uint32_t* e2, uint64_t i, uint64_t last, const C4Lanes& L, uint32_t* ys,
                                 IdAcc& acc) {
-  if (b4_per_wave(v.W) == 2) {
-    const uint32_t half = (threadIdx.x >> 5) & 1u;
-    i += half;
-    if (i < last) id_edge_item<32>(v, e2[2 * i], e2[2 * i + 1], L, ys + 32 * half, acc);
-  } else {
-    id_edge_item<kWave>(v, e2[2 * i], e2[2 * i + 1], L, ys, acc);
-  }
+  constexpr uint32_t G = kWave / PER;
+  const uint32_t part = PER == 1 ? 0u : (threadIdx.x / G) % PER;
+  i += part;
+  if (i < last) id_edge_item<G>(v, e2[2 * i], e2[2 * i + 1], L, ys + part * G, acc);
 }
 
 // One wavefront per node u: C(d_u, 3), and C(|N(u) n N(w)|, 2) for every

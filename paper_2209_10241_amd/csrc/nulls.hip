@@ -1362,7 +1362,8 @@ __global__ void __launch_bounds__(kThreads) k_null_count(BatchView b, uint32_t R
   unsigned long long* h_sub = wh[wv] + 256;
   const uint32_t total = tile_prefix[3 * R];
   const bool id = batch_ident(b, k);
-  const C4Lanes L = c4_lanes(b.W, id ? kWave / b4_per_wave(b.W) : uint32_t(kWave));
+  const uint32_t per = b.bits ? b4_per_wave(b.W) : 1u;
+  const C4Lanes L = c4_lanes(b.W, id ? kWave / per : uint32_t(kWave));
   while (true) {
     uint32_t t = 0;
     if (lane == 0) t = atomicAdd(counter, 1u);
@@ -1381,10 +1382,13 @@ __global__ void __launch_bounds__(kThreads) k_null_count(BatchView b, uint32_t R
     for (uint32_t i = lane; i < 512; i += kWave) wh[wv][i] = 0;
     wave_sync();
     if (ph == 0) {
-      const uint32_t n = b.base3[c + 1] - b.base3[c], per = v.bits ? b4_per_wave(v.W) : 1u;
+      const uint32_t n = b.base3[c + 1] - b.base3[c];
       const uint32_t last = min(n, first + ch.per_tile[0]);
-      for (uint32_t j = first; j < last; j += per)
-        b4_item(v, b.base3[c] + j, b.base3[c] + last, b4_sets + wv * b4_set_words(b.W), lut, h_main, h_sub);
+      uint32_t* sets = b4_sets + wv * b4_set_words(b.W, per);
+      if (per == 2)
+        for (uint32_t j = first; j < last; j += 2) b4_item<2>(v, b.base3[c] + j, b.base3[c] + last, sets, lut, h_main, h_sub);
+      else
+        for (uint32_t j = first; j < last; ++j) b4_item(v, b.base3[c] + j, b.base3[c] + last, sets, lut, h_main, h_sub);
     } else if (ph == 1) {
       const uint32_t n2c = b.base2[c + 1] - b.base2[c];
       const uint32_t n = n2c + (id ? b.N : 0u);
@@ -1392,9 +1396,11 @@ __global__ void __launch_bounds__(kThreads) k_null_count(BatchView b, uint32_t R
       if (id) {
         IdAcc acc;
         id_zero(acc);
-        const uint32_t per = b4_per_wave(v.W), edges = min(last, n2c);
-        for (uint32_t j = first; j < edges; j += per)
-          id_edges(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
+        const uint32_t edges = min(last, n2c);
+        if (per == 2)
+          for (uint32_t j = first; j < edges; j += 2) id_edges<2>(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
+        else
+          for (uint32_t j = first; j < edges; ++j) id_edges<1>(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
         for (uint32_t j = max(first, n2c); j < last; ++j) id_node_item(v, j - n2c, acc);
         id_flush(acc, hc + kIdAcc);
       } else if (k == 4) {
@@ -1471,6 +1477,11 @@ __global__ void __launch_bounds__(kThreads) k_null_count(BatchView b, uint32_t R
 __host__ __device__ inline size_t null_lds_table_words(uint32_t N, uint32_t W) {
   return size_t(N) * W + 3 * (size_t(N) + 1);
 }
+// items of phases 0 and 1 a wavefront takes at once: tables of at most
+// kNullLdsMaxBytes have rows of fewer than 32 words
+constexpr size_t kNullLdsMaxBytes = 48 * 1024;
+constexpr uint32_t kNullLdsPer = 2;
+static_assert(32 * 32 * 32 * 4 > kNullLdsMaxBytes && b4_per_wave(32) == kNullLdsPer, "rows of at most 32 words");
 __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32_t R,
                                                              const uint32_t* __restrict__ tile_prefix,
                                                              uint32_t* __restrict__ counter, Chunks ch,
@@ -1486,13 +1497,13 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
   const int wv = threadIdx.x / kWave;
   uint32_t* h_main = wh[wv];
   uint32_t* h_sub = wh[wv] + 256;
-  uint32_t* sets = dyn_lds + wv * b4_set_words(b.W);
-  uint32_t* rows = dyn_lds + kWavesPerBlock * b4_set_words(b.W);
+  uint32_t* sets = dyn_lds + wv * b4_set_words(b.W, kNullLdsPer);
+  uint32_t* rows = dyn_lds + kWavesPerBlock * b4_set_words(b.W, kNullLdsPer);
   const uint32_t nw = b.N * b.W;
   uint32_t* offs = rows + nw;
   const uint32_t total = tile_prefix[3 * R];
   const bool id = batch_ident(b, 4);
-  const C4Lanes L = c4_lanes(b.W, id ? kWave / b4_per_wave(b.W) : uint32_t(kWave));
+  const C4Lanes L = c4_lanes(b.W, id ? kWave / kNullLdsPer : uint32_t(kWave));
   uint32_t loaded = 0xFFFFFFFFu;
   while (true) {
     __syncthreads();   // the previous tile is done with s_tile and the LDS tables
@@ -1530,10 +1541,10 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
     for (uint32_t i = lane; i < 512; i += kWave) wh[wv][i] = 0;
     wave_sync();
     if (ph == 0) {
-      const uint32_t n = b.base3[c + 1] - b.base3[c], per = b4_per_wave(v.W);
+      const uint32_t n = b.base3[c + 1] - b.base3[c], per = kNullLdsPer;
       const uint32_t last = min(n, first + ch.per_tile[0]);
       for (uint32_t j = first + wv * per; j < last; j += kWavesPerBlock * per)
-        b4_item(v, b.base3[c] + j, b.base3[c] + last, sets, lut, h_main, h_sub);
+        b4_item<kNullLdsPer>(v, b.base3[c] + j, b.base3[c] + last, sets, lut, h_main, h_sub);
     } else if (ph == 1) {
       const uint32_t n2c = b.base2[c + 1] - b.base2[c];
       const uint32_t n = n2c + (id ? b.N : 0u);
@@ -1541,9 +1552,9 @@ __global__ void __launch_bounds__(kThreads) k_null_count_lds(BatchView b, uint32
       if (id) {
         IdAcc acc;
         id_zero(acc);
-        const uint32_t per = b4_per_wave(v.W), edges = min(last, n2c);
+        const uint32_t per = kNullLdsPer, edges = min(last, n2c);
         for (uint32_t j = first + wv * per; j < edges; j += kWavesPerBlock * per)
-          id_edges(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
+          id_edges<kNullLdsPer>(v, b.e2, b.base2[c] + j, b.base2[c] + edges, L, ylist[wv], acc);
         for (uint32_t j = max(first, n2c) + wv; j < last; j += kWavesPerBlock) id_node_item(v, j - n2c, acc);
         id_flush(acc, hc + kIdAcc);
       } else {
@@ -1997,12 +2008,11 @@ unsigned persistent_grid_lds(size_t lds) {
 
 // Whether the batch counts with k_null_count_lds (order 4, bit rows, a copy's
 // tables in at most kNullLdsMaxBytes), and its dynamic LDS.
-constexpr size_t kNullLdsMaxBytes = 48 * 1024;
 bool null_lds(const NullPlan& P) {
   return P.k == 4 && P.use_bits && null_lds_table_words(P.N, P.W) * 4 <= kNullLdsMaxBytes;
 }
 size_t null_lds_bytes(const NullPlan& P) {
-  return (size_t(kWavesPerBlock) * b4_set_words(P.W) + null_lds_table_words(P.N, P.W)) * 4;
+  return (size_t(kWavesPerBlock) * b4_set_words(P.W, kNullLdsPer) + null_lds_table_words(P.N, P.W)) * 4;
 }
 
 int enqueue_count(const hm_graph* H, NullPlan& P, const Chunks& ch, hipStream_t st) {
@@ -2020,7 +2030,7 @@ int enqueue_count(const hm_graph* H, NullPlan& P, const Chunks& ch, hipStream_t 
     k_null_count_lds<<<persistent_grid_lds(lds), kThreads, lds, st>>>(bv, R, P.tile_prefix, P.tile_counter, ch, lut4,
                                                                       P.hist_all);
   } else {
-    const size_t lds = (P.k == 4 && bv.bits) ? size_t(kWavesPerBlock) * b4_set_words(bv.W) * 4 : 0;
+    const size_t lds = (P.k == 4 && bv.bits) ? size_t(kWavesPerBlock) * b4_set_words(bv.W, b4_per_wave(bv.W)) * 4 : 0;
     k_null_count<<<persistent_grid(lds), kThreads, lds, st>>>(bv, R, P.k, P.tile_prefix, P.tile_counter, ch,
                                                          P.k == 4 ? lut4 : lut3, P.hist_all);
   }

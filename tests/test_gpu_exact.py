@@ -852,3 +852,25 @@ def test_count_beyond_identities_matches_noalloc(hm, n, pairs, hubs):
         assert np.array_equal(raw, hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy())
     for got in (first, second, third):
         assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n,missing", [(34, 0.0), (67, 0.0), (90, 0.2)])
+def test_dense_pairs_match_oracle(hm, n, missing):
+    """Pairs with up to more common neighbours than a wavefront, or half of
+    one, has lanes, beside 3- and 4-node hyperedges: one graph's count and the
+    count of configuration copies (whose real counts take the same kernels)
+    against the oracle."""
+    rng = np.random.default_rng(n)
+    a, b = np.triu_indices(n, 1)
+    keep = rng.random(len(a)) >= missing
+    parts = [np.c_[a, b][keep], rng.integers(0, n, (3 * n, 3)), rng.integers(0, n, (n, 4))]
+    parts = [np.sort(e, axis=1) for e in parts]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in parts]
+    members = np.concatenate([e.ravel() for e in parts]).astype(np.uint32)
+    offsets = np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))].astype(np.uint64)
+    want = core.count_exact(W.Hypergraph(n, members, offsets), 4)
+    with hm.hm_graph_create(members, offsets, n) as g:
+        assert np.array_equal(hm.count_exact(g, 4).cpu().numpy(), want)
+        nulls = hm.count_nulls_model(g, 4, 2, hm.HM_NULL_CONFIG, 1, 9)[1].cpu().numpy()
+        m, o = hm.hm_null_export_model(g, hm.HM_NULL_CONFIG, 1, 9, 1)
+        assert np.array_equal(nulls[1], core.count_exact(W.Hypergraph(n, m, o), 4))
