@@ -488,14 +488,17 @@ int count_sampled_weighted_indices(const hm_graph* H, int k, const uint32_t* idx
  *                            probes everywhere.
  *   HM_OPT_SAMPLE_CHUNK_SCALE the sampled counts of graphs without bit rows
  *                            hand the long walks of heavy samples to a work
- *                            queue in chunks (2 nodes of T, 64 correction
- *                            items, 512 exception positions, 256 hyperedges;
- *                            pair samples with a bound above 4096 visited
- *                            positions); every chunk size and that bound
+ *                            queue in chunks (with 4096 samples or more, 2
+ *                            nodes of T, 64 correction items, 512 exception
+ *                            positions, 1024 hyperedges; pair samples with a
+ *                            bound above 4096 visited positions; smaller with
+ *                            fewer samples); every chunk size and that bound
  *                            are divided by this value
  *                            (default 1, range 1..1024), so larger values
  *                            route more of the work through the queue.  The
- *                            results do not depend on it.
+ *                            results do not depend on it.  (So do the later
+ *                            sampled calls of a graph with bit rows of more
+ *                            than 2574 nodes once they are taken as without.)
  *   HM_OPT_ONE_PASS_MAX_EDGES graphs that keep bit rows and have at most this
  *                            many input hyperedges (default and maximum
  *                            2^20) are built in one pass: buffers are sized

@@ -93,8 +93,8 @@ enum : uint32_t { kJobNone = 0, kJobPairT = 1, kJobPairR = 2, kJobTriple = 3, kJ
 // first position, about 10 us, so it has to hold more work than that: with 4
 // correction items per chunk 656,000 of them held 108 positions each on the
 // communication graph (2% of every stratum, 10.1 ms; 64 items 4.1 ms, 256 no
-// better, and at 0.1%, where a few heavy samples are the tail, 0.80, 0.60 and
-// 1.00 ms).
+// better).  With few samples the chunks of the heaviest are the tail: see
+// chunk_divisor.
 constexpr uint32_t kChunkT = 2;    // nodes of T per chunk (about 5,000 positions)
 constexpr uint32_t kChunkR = 64;   // correction items per chunk
 constexpr uint32_t kChunkX = 512;  // exception positions per chunk
@@ -102,6 +102,16 @@ constexpr uint32_t kChunkH = 1024;  // hyperedges at s (3-node) or holding e (4-
 // A sample of no more than this many chunks of each kind is one chunk of all
 // (2.12 ms with 1 or 4 where 2 takes 2.03).
 constexpr uint32_t kWholeChunks = 2;
+// What chunk sizes (and the bound of work done in place) are divided by for
+// `samples` pair or 3-node samples: few samples leave most workgroups waiting
+// for the chunks of the heaviest, many pay for each chunk's own cost.
+// Communication recipe, us by divisor 1, 2, 4, 8: 8,460 nodes, 89 samples 190,
+// 140, 130, 112; 178: 195, 152, 149, 135; 893: 250, 215, 208, 208; 3,572: 388,
+// 370, 406, 510.  47,000 nodes: 1,044: 585, 460, 470, 450; 2,088: 690, 583,
+// 612, 680; 5,222: 945, 953, 1,080; 20,889: 2,530, 2,760, 3,430.
+// Co-authorship recipe, 95,000 and 950,000 nodes: 1 to 8 within a tenth of each
+// other up to 504 and 1,016 samples, 1 and 2 alike from there.
+inline uint32_t chunk_divisor(uint64_t samples) { return samples < 256 ? 8 : samples < 1024 ? 4 : samples < 4096 ? 2 : 1; }
 // queue entries per sample of strata 2 and 3 (times the chunk option), at
 // most kQueueMax in all; work that finds the queue full is done in place
 constexpr uint64_t kQueuePerSample = 2048;
@@ -1451,7 +1461,7 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   a.q.head = a.q.tail + kQueueParts * kQueueStep;
   a.q.info = nullptr;
   a.q.info3 = nullptr;
-  const uint32_t scale = sample_chunk_scale();
+  const uint32_t scale = sample_chunk_scale() * chunk_divisor(std::max(a.d.S[2], a.d.S[3]));
   a.q.ct = std::max<uint32_t>(1, kChunkT / scale);
   a.q.cr = std::max<uint32_t>(1, kChunkR / scale);
   a.q.cx = std::max<uint32_t>(1, kChunkX / scale);

@@ -414,3 +414,23 @@ def test_samples_beyond_identities_match_hash(hm, n, samples):
             hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
     for b, h in zip(got[8192], got[0]):
         assert np.array_equal(b, h)
+
+
+def test_chunk_sizes_by_samples_match_bit_rows(hm):
+    """Work queue chunks on both sides of every number of samples at which
+    their size changes (heavy pairs: their walks go through the queue), without
+    bit rows against the bit-row sampler."""
+    rng = np.random.default_rng(3)
+    n = 1500
+    hub = np.c_[rng.integers(0, 6, 6000), rng.integers(6, n, 6000)]
+    parts = [np.r_[hub, rng.integers(0, n, (6000, 2))], np.r_[np.c_[hub[:3000], rng.integers(0, n, 3000)], rng.integers(0, n, (2000, 3))],
+             np.c_[hub[:1000], rng.integers(0, n, (1000, 2))]]
+    parts = [np.sort(e, axis=1) for e in parts]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in parts]
+    h = W.Hypergraph(n, np.concatenate([e.ravel() for e in parts]),
+                     np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))])
+    with _graph(hm, h) as g, _graph(hm, h, bit_rows=False) as f:
+        for s2, s3 in [(1, 1), (255, 255), (256, 100), (100, 256), (1023, 10), (1024, 10), (4095, 10), (4096, 10)]:
+            idx = {2: rng.integers(0, g.stats()["n2"], s2), 3: rng.integers(0, g.stats()["n3"], s3)}
+            want = hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy()
+            assert np.array_equal(hm.count_sampled_indices(f, 4, idx)[1].cpu().numpy(), want), (s2, s3)
