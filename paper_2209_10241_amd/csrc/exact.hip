@@ -411,31 +411,11 @@ int noalloc_scratch(int dev, unsigned long long** out) {
 
 }  // namespace
 
-// Sum of d^2 over the n nodes (one workgroup of 1024).
-__global__ void __launch_bounds__(1024) k_degree_squares(const uint32_t* __restrict__ g2_off, uint32_t n,
-                                                         unsigned long long* __restrict__ out) {
-  __shared__ unsigned long long sums[1024 / kWave];
-  unsigned long long s = 0;
-  for (uint32_t x = threadIdx.x; x < n; x += 1024) {
-    const unsigned long long d = g2_off[x + 1] - g2_off[x];
-    s += d * d;
-  }
-  s = wave_sum(s);
-  if ((threadIdx.x & (kWave - 1)) == 0) sums[threadIdx.x / kWave] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    s = 0;
-    for (uint32_t w = 0; w < 1024 / kWave; ++w) s += sums[w];
-    *out = s;
-  }
-}
-
-// Whether the host may wait for st and allocate: not while it is captured.
-static bool may_wait(hipStream_t st) {
+bool being_captured(hipStream_t st) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   const hipError_t e = hipStreamIsCapturing(st, &status);
   if (e != hipSuccess) (void)hipGetLastError();
-  return e == hipSuccess && status == hipStreamCaptureStatusNone;
+  return e != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
 // Whether a graph with bit rows counts order 4 as one without them (by ranked
@@ -446,30 +426,14 @@ static bool may_wait(hipStream_t st) {
 // 65,000 pairs of even degrees on 2,600 nodes, 5.8e8 words, 0.55 ms against
 // 0.85; 97,000 on 8,000, 1.2e9, 1.11 against 0.88; heavy-tailed degrees on 2,600,
 // 5,000 and 8,000 nodes, 2.4e9 to 5.8e10, 3.6, 12.2 and 55.5 ms against 1.3, 1.8
-// and 2.3).  So the line is 2^30 words.  With all degrees alike the sum is
-// 4 n2^2 / N, its least; where that is within a factor of four of the line the
-// degrees themselves are asked, once per graph (35 us).  The runs need scratch memory and wait once: a stream that is being
+// and 2.3; one and five hubs of 7,900 pairs among 4,000 others on 8,000 nodes,
+// 1.6e10 and 7.8e10, 18.3 and 76.5 against 0.68 and 0.85).  So the line is 2^30
+// words.  The build sums the squares (k_degree_squares in graph.hip).  The runs
+// need scratch memory and indices built on first use: a stream that is being
 // captured keeps the bit rows, as does a device without the memory.
-int prefers_runs(const hm_graph* H, hipStream_t st, bool* runs) {
-  *runs = false;
-  if (use_identities(H->n_nodes, H->words) || H->n_nodes == 0) return HM_OK;
-  constexpr unsigned long long kLine = 1ull << 30;
-  const unsigned long long n2 = H->n_by_size[2], least = 4 * n2 * n2 / H->n_nodes * H->words;
-  if (least < kLine / 4 || !may_wait(st)) return HM_OK;
-  if (!H->degree_squares_known) {   // (the samplers' rule reads the sum as well)
-    Scratch tmp(st);
-    unsigned long long* sum = nullptr;
-    const int rc = tmp.get(&sum, 1);
-    if (rc == HM_ENOMEM) return HM_OK;
-    HM_TRY(rc);
-    k_degree_squares<<<1, 1024, 0, st>>>(H->g2_off, H->n_nodes, sum);
-    HM_HIP(hipGetLastError());
-    HM_HIP(hipMemcpyAsync(&H->degree_squares, sum, sizeof(*sum), hipMemcpyDeviceToHost, st));
-    HM_HIP(hipStreamSynchronize(st));
-    H->degree_squares_known = true;
-  }
-  *runs = least >= kLine || H->degree_squares * H->words >= kLine;
-  return HM_OK;
+bool prefers_runs(const hm_graph* H, hipStream_t st) {
+  if (use_identities(H->n_nodes, H->words)) return false;
+  return H->degree_squares * H->words >= 1ull << 30 && !being_captured(st);
 }
 
 int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) {
@@ -495,7 +459,7 @@ int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) 
   const View v = view_of(H);
   bool id = false;
   bool runs = !v.bits;
-  if (!runs && k == 4) HM_TRY(prefers_runs(H, st, &runs));
+  if (!runs && k == 4) runs = prefers_runs(H, st);
   const bool by_bits = !runs;
   if (by_bits) {
     id = launch_bits_count(H, k, k == 4 ? lut4 : lut3, H->hist, st);

@@ -548,10 +548,14 @@ __global__ void __launch_bounds__(kTile) k_first_tiles(const uint32_t* __restric
   }
 }
 
-// What the build reads back once: validation flags and the five totals.
+constexpr uint32_t kDegreeParts = 16;
+
+// What the build reads back once: validation flags, the five totals and the
+// squared degrees.
 struct Report {
   DevFlags flags;
   unsigned long long totals[kTileN];
+  unsigned long long degree_squares[kDegreeParts];   // (k_degree_squares, a launch before)
   uint32_t ready;   // set to 1 (after the fields above) by the kernel that writes them
   uint32_t pad;
 };
@@ -563,6 +567,28 @@ __device__ inline void publish_report(Report* out, bool wrote) {
   if (wrote) __threadfence_system();
   __syncthreads();
   if (threadIdx.x == 0) __hip_atomic_store(&out->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Sum of the squared pairwise degrees of the first occurrences (counted by
+// k_first_tiles, R copies of each node's counter), a part per workgroup, for
+// the rule of prefers_runs (exact.hip): before the launch that publishes the
+// report, so that no call has to wait for it.
+__global__ void __launch_bounds__(256) k_degree_squares(const uint32_t* __restrict__ deg, uint32_t n, uint32_t R,
+                                                        Report* out) {
+  __shared__ unsigned long long part[256 / kWave];
+  unsigned long long s = 0;
+  for (uint32_t x = blockIdx.x * 256 + threadIdx.x; x < n; x += gridDim.x * 256) {
+    unsigned long long d = 0;
+    for (uint32_t c = 0; c < R; ++c) d += deg[uint64_t(x) * R + c];
+    s += d * d;
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out->degree_squares[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+    __threadfence_system();
+  }
 }
 
 // Exclusive scan of the tiles' position counters in place; the five totals
@@ -1363,6 +1389,7 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
   // (degrees are counted for the fills beside bit rows only)
   const uint32_t R = degree_copies(N);
   const uint64_t NR = keep_bits ? N * R : 0;
+  const bool squares = keep_bits && E > 0 && !use_identities(uint32_t(N), uint32_t((N + 31) / 32));
   // the degree scans ride on the gather's launch when its workgroups can
   // hold a run each (else a launch of their own after it)
   const bool gather_scan = one_pass && E > 0 && NR <= kGatherScanMax;
@@ -1504,6 +1531,7 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
       k_dedup_insert<<<grid_for(E), 256, 0, st>>>(sm, offsets, size, hash, E, slots, cap - 1, slot_of);
     k_first_tiles<<<unsigned(n_tiles), kTile, 0, st>>>(size, E, slots, slot_of, ecode, first, tile_cnt, fast_dedup,
                                                         sm, offsets, hash, Degrees{deg2, deg3, deg4, R});
+    if (squares) k_degree_squares<<<kDegreeParts, 256, 0, st>>>(deg2, uint32_t(N), R, rep_dev);
     // in one pass with few tiles the gather sums the tile counts itself
     if (!self_offsets) k_tile_scan<<<1, 1024, 0, st>>>(tile_cnt, n_tiles, rep_dev, dev_totals);
     rep.st = st;
@@ -1534,6 +1562,8 @@ int build(hm_graph* H, const uint32_t* members_in, const uint64_t* offsets_in, u
     H->n_singletons = got.singletons;
     H->n_duplicates = got.duplicates;
     H->n_unique_members = tot[4];
+    H->degree_squares = 0;
+    for (uint32_t p = 0; squares && p < kDegreeParts; ++p) H->degree_squares += rep.p->degree_squares[p];
     return HM_OK;
   };
   // host-side bounds of the unique counts for grid sizes: exact after the

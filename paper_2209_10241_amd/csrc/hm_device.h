@@ -14,6 +14,15 @@ constexpr uint32_t kPairBits4 = (1u << 0) | (1u << 1) | (1u << 2) | (1u << 4) | 
 constexpr uint32_t kTripleBits4 = (1u << 3) | (1u << 6) | (1u << 8) | (1u << 9);
 constexpr uint32_t kPairBits3 = 0x7u;
 
+// Order 4 with bit rows takes the identity route (hm_items.h) while the node
+// items' codegrees (every node pair, W words each) stay within this many word
+// operations.
+constexpr uint64_t kIdPairWordsMax = 1ull << 28;
+
+__host__ __device__ inline bool use_identities(uint32_t N, uint32_t W) {
+  return uint64_t(N) * N * W / 2 <= kIdPairWordsMax;
+}
+
 __device__ inline bool has2(const Set64& s, uint32_t u, uint32_t v) {
   return set64_has(s, u < v ? key2(u, v) : key2(v, u));
 }

@@ -250,7 +250,9 @@ int ensure_pair_links(hm_graph* H, hipStream_t st);
 int ensure_quad_index(hm_graph* H, hipStream_t st);
 int ensure_hub_rows(hm_graph* H, hipStream_t st);
 int ensure_ranks(hm_graph* H, hipStream_t st);
-int prefers_runs(const hm_graph* H, hipStream_t st, bool* runs);
+bool prefers_runs(const hm_graph* H, hipStream_t st);
+// Whether st is being captured (or that cannot be told).
+bool being_captured(hipStream_t st);
 int ensure_pair_positions(hm_graph* H, hipStream_t st);
 int ensure_node_stats(hm_graph* H, hipStream_t st);
 int ensure_edge_stats(hm_graph* H, hipStream_t st);
@@ -304,10 +306,9 @@ struct hm_graph {
   // adjacency bit rows of the pairwise graph (n_nodes x words), when kept
   uint32_t* bits = nullptr;
   uint32_t words = 0;
-  // sum of the squared degrees of the pairwise graph (order-4 counts, on first
-  // need; see prefers_runs)
-  mutable unsigned long long degree_squares = 0;
-  mutable bool degree_squares_known = false;
+  // sum of the squared degrees of the pairwise graph, from the build (graphs
+  // with bit rows beyond the identity route; see prefers_runs)
+  unsigned long long degree_squares = 0;
   // order-4 pair samples that calls before asked for (see walks_samples)
   mutable uint64_t sampled_pairs = 0;
 

@@ -439,14 +439,6 @@ __device__ inline void id_node_item(const View& v, uint32_t u, IdAcc& acc) {
   }
 }
 
-// The identity route runs while the node items' codegrees (every node pair,
-// W words each) stay within this many word operations.
-constexpr uint64_t kIdPairWordsMax = 1ull << 28;
-
-__host__ __device__ inline bool use_identities(uint32_t N, uint32_t W) {
-  return uint64_t(N) * N * W / 2 <= kIdPairWordsMax;
-}
-
 // Classes of the six connected 4-node graphs; with `on`, their G2 counts come
 // from the seven identity sums rather than from the G2 region.
 struct IdShapes {

@@ -1350,14 +1350,11 @@ uint32_t blocks_for(uint64_t items, uint64_t per_block, uint32_t cap) {
 // and keeps the bit rows.  On graphs whose exact count leaves them
 // (prefers_runs) a later call turns to the walks when the samples of all calls
 // so far have read 2^27 words, about as much time as the indices take.
-int walks_samples(const hm_graph* H, uint64_t S2, hipStream_t st, bool* walks) {
-  *walks = false;
+bool walks_samples(const hm_graph* H, uint64_t S2, hipStream_t st) {
   const uint64_t before = H->sampled_pairs, n2 = std::max<uint64_t>(H->n_by_size[2], 1);
   H->sampled_pairs += S2;
-  bool runs = false;
-  if (before) HM_TRY(prefers_runs(H, st, &runs));
-  *walks = runs && double(before + S2) * double(H->degree_squares) * H->words / double(n2) >= double(1ull << 27);
-  return HM_OK;
+  return before && prefers_runs(H, st) &&
+         double(before + S2) * double(H->degree_squares) * H->words / double(n2) >= double(1ull << 27);
 }
 
 // What the samplers of graphs without bit rows look up, built on first use.
@@ -1385,9 +1382,7 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
     return HM_EINTERNAL;
   }
   if (k == 4) {
-    bool walks = !bits;
-    if (bits) HM_TRY(walks_samples(H, S[2], st, &walks));
-    if (walks) {
+    if (!bits || walks_samples(H, S[2], st)) {
       const int rc = ensure_sample_indices(const_cast<hm_graph*>(H), st);
       if (rc != HM_ENOMEM || !bits) HM_TRY(rc);
       bits = rc != HM_OK;   // (without the memory, the bit rows)

@@ -1,0 +1,68 @@
+"""Graphs with bit rows of more nodes than the identity route takes: order 4
+is counted by bit rows or, where the squared degrees say so, by the walks and
+runs of graphs without them.  Each way against one that shares no code with
+it, and what both owe the caller's stream."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hm():
+    import torch
+    import paper_2209_10241_amd as hm
+    assert torch.cuda.is_available()
+    return hm
+
+
+def _hubs(n, hubs, degree, pairs, seed=0):
+    """(members, offsets): `hubs` nodes of `degree` pairs each, other pairs, n 3-node and n / 4 4-node hyperedges."""
+    rng = np.random.default_rng(seed + n + hubs)
+    parts = [np.c_[np.full(degree, h), rng.choice(n, degree, replace=False)] for h in range(hubs)]
+    parts += [rng.integers(0, n, (pairs, 2))]
+    parts = [np.concatenate(parts), rng.integers(0, n, (n, 3)), rng.integers(0, n, (n // 4, 4))]
+    parts = [np.sort(e, axis=1) for e in parts]
+    parts = [e[(e[:, 1:] > e[:, :-1]).all(axis=1)] for e in parts]
+    members = np.concatenate([e.ravel() for e in parts]).astype(np.uint32)
+    offsets = np.r_[0, np.cumsum(np.concatenate([np.full(len(e), e.shape[1]) for e in parts]))].astype(np.uint64)
+    return members, offsets
+
+
+def _by_bit_rows(hm, g):
+    """Order-4 counts by the entry point that always takes the bit rows."""
+    import torch
+    out = torch.empty(hm.hm_num_classes(4), dtype=torch.int64, device="cuda")
+    assert hm.lib().count_exact_noalloc(g.handle, 4, ctypes.c_void_p(out.data_ptr()), None) == 0
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("one_pass", [True, False])
+@pytest.mark.parametrize("n,hubs,degree,pairs,runs", [
+    (8000, 5, 7900, 4000, True), (8000, 1, 7900, 10, True), (4097, 3, 4000, 0, True), (8000, 1, 1800, 4000, False),
+    (2600, 1, 300, 2000, False)])
+def test_few_hubs_decide_the_route(hm, n, hubs, degree, pairs, runs, one_pass):
+    """A few hubs among few pairs outweigh the line between bit rows and runs
+    (2^30 words) though the number of pairs alone lies far below it; in either
+    kind of build, which sums the squared degrees."""
+    members, offsets = _hubs(n, hubs, degree, pairs)
+    keep = hm.hm_get_option(hm.HM_OPT_ONE_PASS_MAX_EDGES)
+    hm.hm_set_option(hm.HM_OPT_ONE_PASS_MAX_EDGES, keep if one_pass else 0)
+    try:
+        g = hm.hm_graph_create(members, offsets, n)
+    finally:
+        hm.hm_set_option(hm.HM_OPT_ONE_PASS_MAX_EDGES, keep)
+    with g:
+        hm.hm_profile_enable(True)
+        hm.hm_profile_reset()
+        try:
+            got = hm.count_exact(g, 4).cpu().numpy()
+            names = hm.hm_profile_read()
+        finally:
+            hm.hm_profile_enable(False)
+            hm.hm_profile_reset()
+        assert ("k_walk" in names) == runs and ("k_exact4_bits" in names) != runs
+        assert np.array_equal(got, _by_bit_rows(hm, g))
