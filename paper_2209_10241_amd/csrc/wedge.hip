@@ -24,6 +24,7 @@
 // most 3,072 nodes marked and met), or one of 1,024 threads with counters
 // addressed by rank, a range of ranks at a time.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "hm_sparse.h"
@@ -903,6 +904,7 @@ __global__ void __launch_bounds__(T) k_clique(Ranked g, uint32_t least, unsigned
   constexpr uint32_t DPT = CAP / T, STRIDE = Lds::kWords + 1, SLOTS = 2 * CAP, L = 4;
   __shared__ Lds S;
   __shared__ uint32_t list[T], n_list;
+  if (g.facts[kLongestOut] < least) return;   // (launched on a bound of it)
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   unsigned long long cliques = 0;
   const uint32_t r0 = g.bounds[0];
@@ -1016,6 +1018,7 @@ __global__ void __launch_bounds__(1024) k_clique_wide(Ranked g, View v, uint32_t
                                                       unsigned long long* __restrict__ acc,
                                                       unsigned long long* __restrict__ k4e,
                                                       const uint32_t* __restrict__ g2_eid) {
+  if (g.facts[kLongestOut] < least) return;
   const uint32_t cap_words = (cap + 31) / 32;
   uint32_t* M = matrix + uint64_t(blockIdx.x) * cap * cap_words;
   unsigned long long cliques = 0;
@@ -1080,8 +1083,13 @@ unsigned grid_of(uint64_t items, uint64_t per_block, unsigned cap) {
   return unsigned(std::max<uint64_t>(1, std::min<uint64_t>((items + per_block - 1) / per_block, cap)));
 }
 
-// H's pairwise graph in rank space, in buffers of tmp; *most receives the
-// largest out row (one host read-back) when asked for.
+// H's pairwise graph in rank space, in buffers of tmp; *most receives, when
+// asked for, the largest out row (one host read-back) or, for a graph with bit
+// rows, a bound on it, as calls on those do not wait for the stream.  (The
+// bound: an out row of m entries belongs to a node of m neighbours or more, and
+// its entries are of the same class of degrees or a later one, whose degrees
+// are more than 8/9 of the node's.  So 8/9 m^2 is at most the sum of all
+// degrees, 2 n2.)
 int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_t* most) {
   HM_TRY(ensure_ranks(H, st));
   const uint32_t n = H->n_nodes;
@@ -1113,7 +1121,9 @@ int ranked_graph(hm_graph* H, hipStream_t st, Scratch& tmp, Ranked* out, uint32_
   HM_HIP(hipGetLastError());
   *out = Ranked{n, H->rank_of, H->node_of, core, rows, core_adj, core_eid, out_adj, out_eid, degree, weight,
                 H->rank_bounds, facts};
-  if (most) {
+  if (most && H->bits) {
+    *most = uint32_t(std::min<double>(n, 1.5 * std::sqrt(double(n2)) + 1.0));
+  } else if (most) {
     HM_HIP(hipMemcpyAsync(most, facts + kLongestOut, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HM_HIP(hipStreamSynchronize(st));
   }

@@ -66,3 +66,33 @@ def test_few_hubs_decide_the_route(hm, n, hubs, degree, pairs, runs, one_pass):
             hm.hm_profile_reset()
         assert ("k_walk" in names) == runs and ("k_exact4_bits" in names) != runs
         assert np.array_equal(got, _by_bit_rows(hm, g))
+
+
+@pytest.mark.parametrize("n,hubs,degree,pairs", [(8000, 5, 7900, 4000), (2600, 0, 1, 120_000)])
+def test_calls_do_not_wait(hm, n, hubs, degree, pairs):
+    """Counts and samples of these graphs are enqueued on the stream, as the
+    header says: behind work that keeps the stream busy they return before it
+    ends, on a handle's first call too, and give what they give otherwise."""
+    import torch
+    members, offsets = _hubs(n, hubs, degree, pairs)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    torch.cuda._sleep(1_000_000)
+    b.record()
+    b.synchronize()
+    cycles = int(1_000_000 * 400 / a.elapsed_time(b))   # about 0.4 s
+    calls = [lambda g: hm.count_exact(g, 4)] + [lambda g: hm.count_sampled(g, 4, 0.05, 7)[1]] * 4
+    with hm.hm_graph_create(members, offsets, n) as g:
+        want = [f(g) for f in calls]   # (also leaves the memory that the calls need in the library's cache)
+        torch.cuda.synchronize()
+    with hm.hm_graph_create(members, offsets, n) as g:
+        torch.cuda.synchronize()
+        torch.cuda._sleep(cycles)
+        after = torch.cuda.Event()
+        after.record()
+        got = [f(g) for f in calls]
+        waited = after.query()
+        torch.cuda.synchronize()
+    assert not waited
+    for w, x in zip(want, got):
+        assert torch.equal(w, x)
