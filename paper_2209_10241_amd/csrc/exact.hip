@@ -418,6 +418,13 @@ bool being_captured(hipStream_t st) {
   return e != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
+int refuse_capture(hipStream_t st) {
+  if (!being_captured(st)) return HM_OK;
+  set_error("this call builds indices of the graph or waits for the stream, which a capture does not allow: "
+            "make it once outside");
+  return HM_EDEVICE;
+}
+
 // Whether a graph with bit rows counts order 4 as one without them (by ranked
 // walks and pair runs).  Off the identity route (above 2,574 nodes) case (c)
 // enumerates: for each pair the rows of both ends, a word of every bit row at a
@@ -442,6 +449,8 @@ int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) 
   HM_TRY(device_luts(H->device, &lut4, &lut3));
   const ClassTables& t = class_tables();
   const ClassMask pairs_only = pairs_only_mask(k);
+  const View v = view_of(H);
+  if (!v.bits) HM_TRY(refuse_capture(st));
   // H->hist is zero between calls; a call that fails part-way clears it on
   // the next call
   if (H->hist_dirty) {
@@ -456,12 +465,8 @@ int count_exact_impl(const hm_graph* H, int k, int64_t* counts, hipStream_t st) 
     }
   } guard{H};
   const uint64_t n3 = H->n_by_size[3], n4 = H->n_by_size[4];
-  const View v = view_of(H);
   bool id = false;
-  bool runs = !v.bits;
-  if (!runs && k == 4) runs = prefers_runs(H, st);
-  const bool by_bits = !runs;
-  if (by_bits) {
+  if (v.bits && !(k == 4 && prefers_runs(H, st))) {
     id = launch_bits_count(H, k, k == 4 ? lut4 : lut3, H->hist, st);
   } else {
     if (k == 4 && n4) {

@@ -1704,6 +1704,7 @@ void release(hm_graph* H, hipStream_t st = nullptr, bool ordered = false) {
 // the build did not need it.
 int ensure_pair_positions(hm_graph* H, hipStream_t st) {
   if (H->g2_eid || H->n_by_size[2] == 0) return HM_OK;
+  HM_TRY(refuse_capture(st));
   Temps tmp(st);
   if (2 * node_bits(H->n_nodes) <= 32) return sorted_pair_positions<uint32_t>(H, tmp, st);
   return sorted_pair_positions<unsigned long long>(H, tmp, st);

@@ -253,6 +253,10 @@ int ensure_ranks(hm_graph* H, hipStream_t st);
 bool prefers_runs(const hm_graph* H, hipStream_t st);
 // Whether st is being captured (or that cannot be told).
 bool being_captured(hipStream_t st);
+// HM_EDEVICE with a message while st is being captured.  What a call builds on
+// a graph for later ones (ensure_*) must not be recorded instead of run: the
+// handle would keep it as built.
+int refuse_capture(hipStream_t st);
 int ensure_pair_positions(hm_graph* H, hipStream_t st);
 int ensure_node_stats(hm_graph* H, hipStream_t st);
 int ensure_edge_stats(hm_graph* H, hipStream_t st);

@@ -1072,6 +1072,7 @@ unsigned grid5(uint64_t n) {
 // E_5 and its hash set, on first use.
 int ensure_order5(hm_graph* H, hipStream_t st) {
   if (H->order5_built) return HM_OK;
+  HM_TRY(refuse_capture(st));
   note_use(H, st);
   const uint64_t n = H->n_unique;
   std::vector<void*> tmp;
@@ -1131,6 +1132,7 @@ int ensure_order5(hm_graph* H, hipStream_t st) {
 // hypergraph does not take that path or the memory is not there.
 int ensure_dense5(hm_graph* H, hipStream_t st) {
   if (H->dense5 || !H->bits || H->n_nodes > kDense5MaxNodes) return HM_OK;
+  HM_TRY(refuse_capture(st));
   const uint64_t words = uint64_t(H->n_nodes) * H->n_nodes * H->words;
   void* p = nullptr;
   if (dalloc(&p, 3 * words * sizeof(uint32_t)) != HM_OK) return HM_OK;

@@ -365,6 +365,7 @@ __global__ void k_ns_h3(View v, uint64_t m, const uint8_t* __restrict__ pat, uin
 int ensure_edge_stats(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->es) return HM_OK;
+  HM_TRY(refuse_capture(st));
   void* es = nullptr;
   HM_TRY(dalloc(&es, 6 * std::max<uint64_t>(H->n_by_size[2], 1) * sizeof(unsigned long long)));
   const int rc = wedge_edge_stats(H, static_cast<unsigned long long*>(es), st);
@@ -382,6 +383,7 @@ int ensure_edge_stats(hm_graph* H, hipStream_t st) {
 int ensure_node_stats(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->ns_tri) return HM_OK;
+  HM_TRY(refuse_capture(st));
   HM_TRY(ensure_edge_stats(H, st));
   const View v = view_of(H);
   const uint64_t n2 = H->n_by_size[2], n3 = H->n_by_size[3], N = H->n_nodes;
@@ -448,6 +450,7 @@ T* keep(Scratch& tmp, T* p) {
 int ensure_quad_index(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->q_done) return HM_OK;
+  HM_TRY(refuse_capture(st));
   const uint64_t n4 = H->n_by_size[4];
   int bits = 1;
   while (bits < 32 && (1ull << bits) < H->n_nodes) ++bits;
@@ -501,6 +504,7 @@ int sort_by_pair(const hm_graph* H, uint64_t n, int bits, uint32_t*& e, uint32_t
 int ensure_pair_links(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->pl_keys || H->n_by_size[3] == 0) return HM_OK;
+  HM_TRY(refuse_capture(st));
   HM_TRY(ensure_hub_rows(H, st));
   const uint64_t n = 3 * H->n_by_size[3];
   int bits = 1;
@@ -610,6 +614,7 @@ __global__ void __launch_bounds__(1024) k_hub_rows(const uint32_t* __restrict__ 
 int ensure_hub_rows(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->hub_built) return HM_OK;
+  HM_TRY(refuse_capture(st));
   const uint32_t n = H->n_nodes, min_deg = hub_min_degree();
   const uint32_t words = (n + 31) / 32;
   uint64_t rows = 0;

@@ -1200,6 +1200,7 @@ int launch_cliques(const hm_graph* H, const Ranked& g, uint32_t most, unsigned l
 // H->rank_of, node_of and rank_bounds, on first use.
 int ensure_ranks(hm_graph* H, hipStream_t st) {
   if (H->rank_of) return HM_OK;
+  HM_TRY(refuse_capture(st));
   note_use(H, st);
   const uint32_t n = H->n_nodes;
   Scratch tmp(st);

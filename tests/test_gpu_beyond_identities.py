@@ -96,3 +96,51 @@ def test_calls_do_not_wait(hm, n, hubs, degree, pairs):
     assert not waited
     for w, x in zip(want, got):
         assert torch.equal(w, x)
+
+
+def test_first_calls_refuse_a_capture(hm):
+    """On a stream that is being captured, calls that would build a graph's
+    indices are refused (a handle must not keep what was only recorded), leave
+    the capture and the handle as they were, and work afterwards; graphs with
+    bit rows are captured by them, whichever way they count otherwise, and
+    replay."""
+    import torch
+    members, offsets = _hubs(3000, 3, 2500, 3000)
+    keep = hm.hm_get_option(hm.HM_OPT_BITSET_MAX_NODES)
+    hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 0)
+    try:
+        bare = hm.hm_graph_create(members, offsets, 3000)
+    finally:
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, keep)
+    with bare, hm.hm_graph_create(members, offsets, 3000) as g, hm.hm_graph_create(members, offsets, 3000) as ref:
+        want = {k: hm.count_exact(ref, k).clone() for k in (3, 4)}
+        sampled = [hm.count_sampled(ref, 4, 0.05, s)[1].clone() for s in (1, 2)]
+        out = torch.zeros(hm.hm_num_classes(4), dtype=torch.int64, device="cuda")
+        est, raw = torch.zeros(out.numel(), device="cuda"), torch.zeros_like(out)
+        torch.cuda.synchronize()
+        stream, graph, errors = torch.cuda.Stream(), torch.cuda.CUDAGraph(), []
+        with torch.cuda.stream(stream):
+            graph.capture_begin(capture_error_mode="thread_local")
+            for call in (lambda: hm.count_exact(bare, 3, out=out), lambda: hm.count_exact(bare, 4, out=out),
+                         lambda: hm.count_sampled(bare, 4, 0.05, 1, est=est, raw=raw)):
+                try:
+                    call()
+                except hm.HMError as e:
+                    errors.append(e.code)
+            hm.count_exact(g, 4, out=out)
+            for s in (1, 2):
+                hm.count_sampled(g, 4, 0.05, s, est=est, raw=raw)
+            graph.capture_end()
+        assert errors == [hm.binding.HM_EDEVICE] * 3
+        for _ in range(3):
+            out.zero_()
+            raw.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want[4]) and torch.equal(raw, sampled[1])
+        del graph
+        for k in (3, 4):
+            assert torch.equal(hm.count_exact(bare, k), want[k])
+            assert torch.equal(hm.count_exact(g, k), want[k])
+        for s in (1, 2):
+            assert torch.equal(hm.count_sampled(bare, 4, 0.05, s)[1], sampled[s - 1])
