@@ -63,8 +63,8 @@ __global__ void __launch_bounds__(kThreads) k_sp_pairs(View v, uint64_t n2, cons
 // Per node: C(d,3) (3-stars), C(d,2) (wedges).
 __global__ void __launch_bounds__(kThreads) k_sp_nodes(View v, unsigned long long* __restrict__ acc) {
   unsigned long long s3 = 0, s2 = 0;
-  for (uint32_t x = blockIdx.x * kThreads + threadIdx.x; x < v.N; x += gridDim.x * kThreads) {
-    const unsigned long long d = deg2_of(v, x);
+  for (uint64_t x = blockIdx.x * kThreads + threadIdx.x; x < v.N; x += gridDim.x * kThreads) {
+    const unsigned long long d = v.g2_off[x + 1] - v.g2_off[x];
     if (d >= 2) s2 += d * (d - 1) / 2;
     if (d >= 3) s3 += d * (d - 1) / 2 * (d - 2) / 3;
   }
@@ -308,7 +308,7 @@ __global__ void k_ns_rows(View v, uint64_t m, const uint32_t* __restrict__ eid, 
 }
 
 __global__ void k_ns_half(unsigned long long* __restrict__ tri, uint32_t n) {
-  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) tri[x] /= 2;
+  for (uint64_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) tri[x] /= 2;
 }
 
 // per 3-node hyperedge {a < b < c}: a ~ b, a ~ c, b ~ c (bits 0..2)
@@ -360,11 +360,19 @@ __global__ void k_ns_h3(View v, uint64_t m, const uint8_t* __restrict__ pat, uin
 
 }  // namespace
 
+// HM_EUNSUPPORTED for a pairwise graph over more than 2^31 nodes at order 4.
+static int within_node_range(const hm_graph* H) {
+  if (H->n_nodes <= 1u << 31 || H->n_by_size[2] == 0) return HM_OK;
+  set_error("order 4 supports at most 2^31 nodes with pairwise hyperedges, not %u", H->n_nodes);
+  return HM_EUNSUPPORTED;
+}
+
 // Per-pair statistics of H for the pair sampler without bit rows (layout in
 // hm_graph::es), built on first use.
 int ensure_edge_stats(hm_graph* H, hipStream_t st) {
   note_use(H, st);
   if (H->es) return HM_OK;
+  HM_TRY(within_node_range(H));
   HM_TRY(refuse_capture(st));
   void* es = nullptr;
   HM_TRY(dalloc(&es, 6 * std::max<uint64_t>(H->n_by_size[2], 1) * sizeof(unsigned long long)));
@@ -571,7 +579,7 @@ PairLinks pair_links_of(const hm_graph* H) {
 // least min_deg pairwise neighbours.
 __global__ void k_hub_ranks(const uint32_t* __restrict__ g2_off, const uint32_t* __restrict__ rank_of, uint32_t n,
                             uint32_t n_rows, uint32_t min_deg, int32_t* __restrict__ hub_rank) {
-  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
+  for (uint64_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
     const uint32_t i = n - 1 - rank_of[x];
     hub_rank[x] = i < n_rows && g2_off[x + 1] - g2_off[x] >= min_deg ? int32_t(i) : -1;
   }
@@ -649,6 +657,7 @@ int ensure_hub_rows(hm_graph* H, hipStream_t st) {
 // Fills the main, sub and G2 regions of H->hist (zeroed by the caller) except
 // case (a), which the caller counts.
 int count_sparse(const hm_graph* H, int k, hipStream_t st) {
+  if (k == 4) HM_TRY(within_node_range(H));
   note_use(H, st);
   const uint8_t *lut4 = nullptr, *lut3 = nullptr;
   HM_TRY(device_luts(H->device, &lut4, &lut3));

@@ -74,15 +74,16 @@ enum : int { kLongestOut = 0, kManyCore = 1, kSplitNodes = 2, kSplitShares = 3, 
 __global__ void k_rank_keys(const uint32_t* __restrict__ g2_off, uint32_t n, uint32_t* __restrict__ keys,
                             uint32_t* __restrict__ vals, uint32_t* __restrict__ bounds) {
   if (blockIdx.x == 0 && threadIdx.x < 3) bounds[threadIdx.x] = n;
-  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
+  for (uint64_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
     keys[x] = degree_class(g2_off[x + 1] - g2_off[x]);
-    vals[x] = x;
+    vals[x] = uint32_t(x);
   }
 }
 
 __global__ void k_rank_assign(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ node_of,
                               uint32_t n, uint32_t* __restrict__ rank_of, uint32_t* __restrict__ bounds) {
-  for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+  for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const uint32_t r = uint32_t(i);
     rank_of[node_of[r]] = r;
     const uint32_t k = keys[r], before = r ? keys[r - 1] : 0u;
     if (k >= 2 && (r == 0 || before < 2)) bounds[0] = r;
@@ -150,8 +151,8 @@ __global__ void k_core_rows(const uint32_t* __restrict__ g2_off, uint32_t n, uin
   uint32_t most = 0;
   auto at = [&](uint32_t i) { return i < m ? pos[i] : (m ? pos[m - 1] + flag[m - 1] : 0ull); };
   if (blockIdx.x == 0 && threadIdx.x == 0) facts[kCoreEntries] = uint32_t(at(uint32_t(m)));
-  for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-    const uint32_t x = node_of[r];
+  for (uint64_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+    const uint64_t x = node_of[r];
     const uint32_t g0 = g2_off[x], g1 = g2_off[x + 1];
     degree[r] = g1 - g0;
     const unsigned long long b = at(g0), e = at(g1);
@@ -584,7 +585,8 @@ __global__ void __launch_bounds__(kWave) k_walk_small(WalkArgs a) {
   HashTab<kSmallSlots> tab{key, val, 0};
   unsigned long long cycles = 0;
   const uint32_t r0 = a.g.bounds[0], r1 = a.g.bounds[1];
-  for (uint32_t u = r0 + blockIdx.x; u < r1; u += gridDim.x) {
+  for (uint64_t at = uint64_t(r0) + blockIdx.x; at < r1; at += gridDim.x) {
+    const uint32_t u = uint32_t(at);
     const uint2 row = a.g.core[u];
     if (row.y < 2) continue;   // one neighbour of degree 2 or more closes nothing
     // what the walk may meet: every path, when the table holds paths
@@ -1264,7 +1266,7 @@ __global__ void k_es_widen(const uint32_t* __restrict__ t32, uint64_t n, unsigne
 __global__ void k_core_tri(const uint32_t* __restrict__ core_eid, const uint32_t* __restrict__ tri_e,
                            const uint32_t* __restrict__ facts, uint32_t* __restrict__ core_tri) {
   const uint32_t n = facts[kCoreEntries];
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+  for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     core_tri[i] = tri_e[core_eid[i]];
 }
 

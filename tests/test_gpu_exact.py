@@ -874,3 +874,19 @@ def test_dense_pairs_match_oracle(hm, n, missing):
         nulls = hm.count_nulls_model(g, 4, 2, hm.HM_NULL_CONFIG, 1, 9)[1].cpu().numpy()
         m, o = hm.hm_null_export_model(g, hm.HM_NULL_CONFIG, 1, 9, 1)
         assert np.array_equal(nulls[1], core.count_exact(W.Hypergraph(n, m, o), 4))
+
+
+def test_order4_node_range(hm):
+    """A pairwise graph over more than 2^31 nodes is refused at order 4, exact
+    and sampled."""
+    import torch
+    if torch.cuda.mem_get_info()[0] < 96 << 30:
+        pytest.skip("needs 96 GiB of free device memory")
+    n = 2**31 + 1
+    members = np.array([0, 1, 1, n - 1, 0, 5, n - 1], dtype=np.uint32)
+    offsets = np.array([0, 2, 4, 7], dtype=np.uint64)
+    with hm.hm_graph_create(members, offsets, n) as g:
+        for call in (lambda: hm.count_exact(g, 4), lambda: hm.count_sampled(g, 4, 1.0, 1)):
+            with pytest.raises(hm.HMError, match="2\\^31") as e:
+                call()
+            assert e.value.code == hm.binding.HM_EUNSUPPORTED
