@@ -60,6 +60,71 @@ __global__ void __launch_bounds__(kThreads) k_sp_pairs(View v, uint64_t n2, cons
   block_add(sw, acc + kAccPaw2);
 }
 
+// Triangles for order 3 (3 x, as the sum over the pairs) by probes: a wavefront
+// takes kProbePairs pairs, lays the shorter row of each out flat, four positions
+// per lane and round, and looks every entry up beside the pair's other node.
+// One launch, where the walks of wedge.hip rank the nodes and copy the rows
+// first; the probes go to memory, where the walks' lookups stay in LDS, so
+// they are the better up to a number of pairs, and of pairs times degrees
+// (probes_order3).  Order 3 on kept graphs, us by probes and by walks (a
+// wavefront per pair in brackets): 5,000 pairs on 10,000 nodes 42, 80 (63);
+// co-authorship recipe, 9,900, 201,000 and 609,000 pairs 46, 107 (109); 173,
+// 250 (291); 433, 515 (612); 1.02 million 1046, 857 (1512).  Communication
+// recipe, 199,000 pairs on 9,400 nodes 344, 414 (367); 356,000 on 16,450 556,
+// 670 (576); 620,000 on 28,200 1253, 1095 (1225).  (4 or 64 pairs a wavefront:
+// 303 and 829 at 199,000; 50 and 54 at 9,900; 274 and 134 at a million pairs
+// of degree 2, where 8 take 200.)
+constexpr uint32_t kProbePairs = 8;
+bool probes_order3(uint64_t n2, uint64_t nodes) { return n2 < 3u << 18 && 2 * n2 * n2 / nodes <= 1u << 24; }
+
+__global__ void __launch_bounds__(kThreads) k_sp_pair_probes(View v, uint64_t n2, unsigned long long* __restrict__ acc) {
+  constexpr uint32_t L = 4, per = kProbePairs;
+  __shared__ uint32_t s_pos[kWavesPerBlock][per + 1], s_row[kWavesPerBlock][per], s_other[kWavesPerBlock][per];
+  const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  uint32_t *pos = s_pos[wv], *row = s_row[wv], *other = s_other[wv];
+  const uint64_t n_waves = uint64_t(gridDim.x) * kWavesPerBlock;
+  unsigned long long hits = 0;
+  for (uint64_t e0 = (uint64_t(blockIdx.x) * kWavesPerBlock + wv) * per; e0 < n2; e0 += n_waves * per) {
+    uint32_t len = 0;
+    if (lane < per && e0 + lane < n2) {
+      const uint32_t a = v.e2[2 * (e0 + lane)], b = v.e2[2 * (e0 + lane) + 1];
+      const uint32_t ab = v.g2_off[a], da = v.g2_off[a + 1] - ab, bb = v.g2_off[b], db = v.g2_off[b + 1] - bb;
+      len = min(da, db);
+      if (len < 2) len = 0;   // (the pair itself)
+      row[lane] = da <= db ? ab : bb;
+      other[lane] = da <= db ? b : a;
+    }
+    uint32_t total;
+    const uint32_t at = wave_exclusive_scan(len, &total);
+    if (lane < per) pos[lane] = at;
+    if (lane == 0) pos[per] = total;
+    wave_sync();
+    for (uint64_t t0 = lane * L; t0 < total; t0 += kWave * L) {
+      uint32_t lo = 0, hi = per;   // pos[lo] <= t0 < pos[hi]
+      while (hi - lo > 1) {
+        const uint32_t m = (lo + hi) >> 1;
+        if (pos[m] <= t0) lo = m; else hi = m;
+      }
+      Probe64 pr[L];
+      uint32_t z[L], o[L];
+#pragma unroll
+      for (uint32_t r = 0; r < L; ++r) {
+        const uint32_t t = uint32_t(min<uint64_t>(t0 + r, total - 1));
+        while (pos[lo + 1] <= t) ++lo;   // (pairs without a row)
+        o[r] = other[lo];
+        z[r] = v.g2_adj[row[lo] + (t - pos[lo])];
+      }
+#pragma unroll
+      for (uint32_t r = 0; r < L; ++r) pr[r] = probe2_start(v.hs2, o[r], z[r]);
+#pragma unroll
+      for (uint32_t r = 0; r < L; ++r)
+        if (probe64_end(v.hs2, pr[r]) && t0 + r < total) ++hits;
+    }
+    wave_sync();   // (the next pairs' rows)
+  }
+  block_add(hits, acc + kAccT3);
+}
+
 // Per node: C(d,3) (3-stars), C(d,2) (wedges).
 __global__ void __launch_bounds__(kThreads) k_sp_nodes(View v, unsigned long long* __restrict__ acc) {
   unsigned long long s3 = 0, s2 = 0;
@@ -667,9 +732,12 @@ int count_sparse(const hm_graph* H, int k, hipStream_t st) {
   unsigned long long* acc = nullptr;
   uint32_t* tri_e = nullptr;
   HM_TRY(tmp.get(&acc, kAccN));
-  HM_TRY(tmp.get(&tri_e, n2));
   HM_TRY(fill_u64(acc, 0, kAccN, st));
-  if (n2) {
+  if (n2 && k == 3 && probes_order3(n2, H->n_nodes)) {
+    ProfileScope ps("k_sp_pair_probes", st);
+    k_sp_pair_probes<<<grid_cap(n2, kWavesPerBlock * kProbePairs, 2048), kThreads, 0, st>>>(v, n2, acc);
+  } else if (n2) {
+    HM_TRY(tmp.get(&tri_e, n2));
     HM_TRY(wedge_counts(const_cast<hm_graph*>(H), k, tri_e, acc + kAccC4, acc + kAccK4, st));
     ProfileScope ps("k_sp_pairs", st);
     k_sp_pairs<<<grid_cap(n2, kThreads, 512), kThreads, 0, st>>>(v, n2, tri_e, acc);

@@ -890,3 +890,37 @@ def test_order4_node_range(hm):
             with pytest.raises(hm.HMError, match="2\\^31") as e:
                 call()
             assert e.value.code == hm.binding.HM_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("n,pairs,probes", [(2, 1, True), (10, 20, True), (3000, 150_000, True), (3000, 175_000, False),
+                                            (300_000, 786_000, True), (300_000, 787_000, False)])
+def test_order3_by_probes_and_walks(hm, n, pairs, probes):
+    """Order 3 without bit rows on both sides of the lines between probes and
+    walks (pairs, and pairs times degrees), and on a pair alone: the triangles
+    and the paths against matrix products."""
+    rng = np.random.default_rng(n)
+    e = np.sort(rng.integers(0, n, (pairs + pairs // 3 + 40, 2)), axis=1)
+    e = np.unique(e[e[:, 0] < e[:, 1]], axis=0)
+    if n > 3000:   # closing some wedges of a hub
+        e = np.unique(np.r_[np.c_[np.zeros(5000, int), 1 + np.arange(5000)], np.c_[1 + np.arange(4999), 2 + np.arange(4999)], e], axis=0)
+    e = np.concatenate([e[:1] * 0 + [0, 1], e]) if n == 2 else e
+    e = np.unique(e, axis=0)
+    e = e[np.sort(rng.permutation(len(e))[:pairs])]
+    d = np.bincount(e.ravel(), minlength=n)
+    import scipy.sparse as sp
+    A = sp.csr_matrix((np.ones(2 * len(e), np.int64), (np.r_[e[:, 0], e[:, 1]], np.r_[e[:, 1], e[:, 0]])), shape=(n, n))
+    tri = int((A @ A).multiply(A).sum()) // 6
+    hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 0)
+    try:
+        with hm.hm_graph_create(e.astype(np.uint32).ravel(), np.arange(0, 2 * len(e) + 1, 2, dtype=np.uint64), n) as g:
+            hm.hm_profile_enable(True)
+            hm.hm_profile_reset()
+            got = hm.count_exact(g, 3).cpu().numpy()
+            names = hm.hm_profile_read()
+    finally:
+        hm.hm_profile_enable(False)
+        hm.hm_profile_reset()
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 8192)
+    assert ("k_sp_pair_probes" in names) == probes and ("k_walk" in names) != probes
+    assert got[hm.hm_pattern_class(3, 7)] == tri and got[hm.hm_pattern_class(3, 3)] == int((d * (d - 1) // 2).sum()) - 3 * tri
+    assert n < 100 or tri > 0
