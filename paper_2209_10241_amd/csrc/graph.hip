@@ -200,8 +200,8 @@ __global__ void k_prepare(const uint32_t* __restrict__ members, const uint64_t* 
 // The builds of large inputs (every build but the one-pass one) prepare tiles
 // of 256 hyperedges per workgroup: the tile's members are loaded into LDS in
 // one coalesced sweep, sorted there (up to 8 nodes by one thread's network; 9
-// to 16 by ranks among 16 lanes; up to 64 by ranks among a wavefront) and
-// written back in one sweep.  A tile of more than kPrepWords members, or with
+// to 16 by ranks among 16 lanes; up to 64 by ranks among a wavefront; longer
+// ones, rare, see the end of the kernel) and written back in one sweep.  A tile of more than kPrepWords members, or with
 // an invalid offset, is read in place.  A thread per hyperedge, which sorted
 // more than 8 nodes by insertion in private or device memory, took 2.58 ms for
 // 5 million hyperedges of 2 to 50 nodes (28 million members), this one 0.48
@@ -217,6 +217,72 @@ constexpr uint32_t kPrepWords = 6144;
 
 __device__ inline unsigned long long tuple_term(uint32_t x, uint32_t i) {
   return mix64(x + 0x9e3779b97f4a7c15ull * (i + 1));
+}
+
+// A hyperedge of so > kRankMost nodes by the workgroup: src's members ascending
+// to out, its hash and error bits to *hash and *err.  They are copied to a (src
+// itself, or out) and, unless they are ascending, sorted there by Batcher's
+// merge exchange (Knuth, The Art of Computer Programming, volume 3, 5.2.2,
+// algorithm M), about log2(so)^2 / 2 passes of disjoint exchanges for any so.
+// (Ranking every node among all, as wavefronts do with fewer, is as many
+// comparisons as the square: 20,000 nodes of which two were swapped took 570
+// ms a build, a thread's insertion sort before it 9.5, this 0.8.)
+constexpr uint32_t kRankMost = 512;
+__device__ void prepare_long(const uint32_t* src, uint32_t* a, uint32_t* out, uint32_t so, uint32_t n_nodes,
+                             unsigned long long* hash, uint32_t* err) {
+  __shared__ uint32_t unsorted;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t n = so;
+  if (tid == 0) {
+    unsorted = 0;
+    *hash = 0;
+    *err = 0;
+  }
+  __syncthreads();
+  bool up = true;
+  for (uint64_t k = tid; k < n; k += kPrepTile) {
+    const uint32_t x = src[k];
+    if (k) up &= src[k - 1] < x;
+    if (a != src) a[k] = x;
+  }
+  if (!up) atomicOr(&unsorted, 1u);
+  __syncthreads();
+  if (unsorted) {
+    uint64_t top = 1;
+    while (2 * top < n) top *= 2;   // the largest power of two below n
+    for (uint64_t p = top; p; p >>= 1) {
+      uint64_t d = p, r = 0;
+      for (uint64_t q = top;; q >>= 1) {
+        // the i below n - d whose bit p is that of r
+        for (uint64_t u = tid;; u += kPrepTile) {
+          const uint64_t i = ((u & ~(p - 1)) << 1) | (u & (p - 1)) | r;
+          if (i >= n - d) break;
+          const uint32_t x = a[i], y = a[i + d];
+          if (x > y) {
+            a[i] = y;
+            a[i + d] = x;
+          }
+        }
+        __syncthreads();
+        if (q == p) break;
+        d = q - p;
+        r = p;
+      }
+    }
+  }
+  unsigned long long t = 0;
+  uint32_t eo = 0;
+  for (uint64_t k = tid; k < n; k += kPrepTile) {
+    const uint32_t x = a[k];
+    if (x >= n_nodes) eo |= kErrBadId;
+    if (k && a[k - 1] == x) eo |= kErrRepeat;
+    if (a != out) out[k] = x;
+    t += tuple_term(x, uint32_t(k));
+  }
+  atomicAdd(hash, t);
+  if (eo) atomicOr(err, eo);
+  __syncthreads();
+  if (tid == 0) *hash = mix64(tuple_hash_start(so) ^ *hash);
 }
 
 __global__ void __launch_bounds__(kPrepTile) k_prepare_tiles(
@@ -338,34 +404,34 @@ __global__ void __launch_bounds__(kPrepTile) k_prepare_tiles(
   __syncthreads();
   for (uint32_t w = tid; w < words; w += kPrepTile) sm[t0 + w] = mem[w];
   if (n_long) {
-    // more than 64 nodes: a wavefront each, whose lanes rank the nodes among
-    // all (one check finds members that are ascending already), from the
-    // unsorted members in LDS or in the input
+    // more than 64 nodes, up to kRankMost: a wavefront each, whose lanes rank
+    // the nodes among all (one check finds members that are ascending already),
+    // from the unsorted members in LDS or in the input
     __syncthreads();   // (the sweep has written their places)
     for (uint32_t q = tid / kWave; q < n_wide; q += kPrepTile / kWave) {
       const uint32_t o = wide[q], so = s_size[o];
-      if (so <= uint32_t(kWave)) continue;
+      if (so <= uint32_t(kWave) || so > kRankMost) continue;
       const uint64_t bo = s_at[o];
       const uint32_t* src = in_lds ? mem + uint32_t(bo - t0) : members + bo;
       bool up = true;
-      for (uint64_t k = uint64_t(lane) + 1; k < so; k += kWave) up &= src[k - 1] < src[k];
+      for (uint32_t k = lane + 1; k < so; k += kWave) up &= src[k - 1] < src[k];
       const bool sorted = __ballot(!up) == 0;
       unsigned long long t = 0;
       uint32_t eo = 0;
-      for (uint64_t k = lane; k < so; k += kWave) {
+      for (uint32_t k = lane; k < so; k += kWave) {
         const uint32_t x = src[k];
         if (x >= n_nodes) eo |= kErrBadId;
-        uint64_t rank = k;
+        uint32_t rank = k;
         if (!sorted) {
           rank = 0;
-          for (uint64_t j = 0; j < so; ++j) {
+          for (uint32_t j = 0; j < so; ++j) {
             const uint32_t y = src[j];
-            rank += uint64_t(y < x || (y == x && j < k));
+            rank += uint32_t(y < x || (y == x && j < k));
             if (y == x && j != k) eo |= kErrRepeat;
           }
         }
         sm[bo + rank] = x;
-        t += tuple_term(x, uint32_t(rank));
+        t += tuple_term(x, rank);
       }
       t = wave_sum(t);
 #pragma unroll
@@ -374,6 +440,17 @@ __global__ void __launch_bounds__(kPrepTile) k_prepare_tiles(
         s_hash[o] = mix64(tuple_hash_start(so) ^ t);
         s_err[o] = eo;
       }
+    }
+    __syncthreads();
+    // more: the workgroup together, one after another
+    for (uint32_t q = 0; q < n_wide; ++q) {
+      const uint32_t o = wide[q], so = s_size[o];
+      if (so <= kRankMost) continue;
+      const uint64_t bo = s_at[o];
+      if (in_lds)
+        prepare_long(mem + uint32_t(bo - t0), mem + uint32_t(bo - t0), sm + bo, so, n_nodes, &s_hash[o], &s_err[o]);
+      else
+        prepare_long(members + bo, sm + bo, sm + bo, so, n_nodes, &s_hash[o], &s_err[o]);
     }
     __syncthreads();
   }

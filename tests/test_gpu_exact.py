@@ -924,3 +924,52 @@ def test_order3_by_probes_and_walks(hm, n, pairs, probes):
     assert ("k_sp_pair_probes" in names) == probes and ("k_walk" in names) != probes
     assert got[hm.hm_pattern_class(3, 7)] == tri and got[hm.hm_pattern_class(3, 3)] == int((d * (d - 1) // 2).sum()) - 3 * tri
     assert n < 100 or tri > 0
+
+
+@pytest.mark.parametrize("sizes", [(65, 511, 512), (513, 700, 1025), (2048, 2049, 6000), (6145, 70), (20_000, 513)])
+def test_long_hyperedges_of_large_builds(hm, sizes):
+    """Hyperedges of more than 64 nodes where graphs are built without bit
+    rows, in LDS and beyond it: any order of a hyperedge's members is the same
+    hyperedge, a changed member another one, and repeats and ids out of range
+    are found wherever they stand.  A nearly ascending one is not much slower
+    than an ascending one."""
+    import time
+    import torch
+    n = 30_000
+    rng = np.random.default_rng(sizes[0])
+    edges, unique = [], 0
+    for s in sizes:
+        e = np.sort(rng.permutation(n - 1)[:s])
+        swapped = e.copy()
+        swapped[[s // 2, s // 2 + 1]] = swapped[[s // 2 + 1, s // 2]]
+        other = e.copy()
+        other[-1] = n - 1
+        edges += [e, swapped, e[::-1], np.r_[e[-1], e[:-1]], np.r_[e[1:], e[0]], rng.permutation(e), other, rng.permutation(other)]
+        unique += 2
+
+    def build(edges):
+        offsets = np.r_[0, np.cumsum([len(e) for e in edges])].astype(np.uint64)
+        return hm.hm_graph_create(np.concatenate(edges).astype(np.uint32), offsets, n)
+
+    for order in (range(len(edges)), rng.permutation(len(edges))):
+        with build([edges[i] for i in order] + [np.array([0, 1])]) as g:
+            st = g.stats()
+            assert (st["n_unique"], st["duplicates"]) == (unique + 1, len(edges) - unique)
+            assert st["n_unique_members"] == 2 * sum(sizes) + 2
+    s = sizes[0]
+    for at in (0, s // 2, s - 1):
+        for value, message in ((edges[0][(at + 7) % s], "repeated"), (n, "node id")):
+            bad = rng.permutation(edges[0])
+            bad[at] = value if value == n else bad[(at + 7) % s]
+            with pytest.raises(hm.HMError, match=message):
+                build([edges[1], bad])
+    took = {}
+    for name, e in (("ascending", edges[0]), ("nearly", edges[1])):
+        build([e, np.array([0, 1])])
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(3):
+            build([e, np.array([0, 1])])
+        torch.cuda.synchronize()
+        took[name] = (time.perf_counter() - t) / 3
+    assert took["nearly"] < took["ascending"] + 0.05, took
