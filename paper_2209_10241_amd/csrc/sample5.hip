@@ -12,7 +12,8 @@
 // and classify it.
 //
 // That is the general path.  Hypergraphs of at most kDense5MaxNodes nodes
-// with adjacency bit rows take the dense path instead (k_dense5): with the
+// with adjacency bit rows take the dense path instead (k_dense5), unless a call's
+// samples can meet few sets (dense5_pays): with the
 // 3-node hyperedges also kept as bit rows, one row of z per node pair, the
 // sets around a sampled pair are counted 32 at a time by popcounts.
 //
@@ -522,9 +523,8 @@ __global__ void __launch_bounds__(kThreads5) k_sampled5(Sampled5Args a, Tables5 
 struct Dense5 {
   uint32_t *t3, *f4, *f5;
 };
-// 3 N^2 W words: 3.4 MB at N = 200, 400 MB at the limit (about 0.15 ms to
-// clear, once per hypergraph; one pair sample of the general path at 1,000
-// nodes within reach takes longer).
+// 3 N^2 W words: 3.4 MB at N = 200, 402 MB at the limit, kept with the graph
+// (see dense5_pays).
 constexpr uint32_t kDense5MaxNodes = 1024;
 constexpr uint32_t kDense5MaxWords = kDense5MaxNodes / 32;
 
@@ -1128,10 +1128,28 @@ int ensure_order5(hm_graph* H, hipStream_t st) {
   return HM_OK;
 }
 
+// Whether a call's samples S[2..5] are worth the dense path's bit tensors on a
+// graph that has none yet.  Clearing them costs what the general path needs for
+// about a candidate set per 96 words (some 10^10 sets a second, 0.08 ms for the
+// 10^8 words of 1,024 nodes).  The sets are bounded by the choices among the
+// nodes that any pair (or 3- or 4-node hyperedge) could bring within reach: far
+// too many mostly, so that the general path is left to samples of hypergraphs
+// with a few hyperedges among many nodes.  First calls there, 1,024 nodes, one
+// sample: 50 pairs 143 us by the general path, 220 with the tensors; 50 4-node
+// hyperedges 148 and 195; but 400 pairs and 50 3-node hyperedges, 23 samples,
+// 661 and 558; 2,000 and 100, 2 samples, 3,160 and 340.
+bool dense5_pays(const hm_graph* H, const uint64_t S[6]) {
+  const double N = H->n_nodes, words = 3.0 * N * N * H->words;
+  const double r2 = std::min(N, 2.0 * H->n_by_size[2]), r3 = std::min(N, r2 + 3.0 * H->n_by_size[3]),
+               r4 = std::min(N, r3 + 4.0 * H->n_by_size[4]);
+  const double sets = double(S[2]) * r2 * r2 * r2 / 6 + double(S[3]) * r3 * r3 / 2 + double(S[4]) * r4;
+  return 96 * sets >= words;
+}
+
 // The dense path's bit tensors, on first use; H->dense5 stays null when the
 // hypergraph does not take that path or the memory is not there.
-int ensure_dense5(hm_graph* H, hipStream_t st) {
-  if (H->dense5 || !H->bits || H->n_nodes > kDense5MaxNodes) return HM_OK;
+int ensure_dense5(hm_graph* H, const uint64_t S[6], hipStream_t st) {
+  if (H->dense5 || !H->bits || H->n_nodes > kDense5MaxNodes || !dense5_pays(H, S)) return HM_OK;
   HM_TRY(refuse_capture(st));
   const uint64_t words = uint64_t(H->n_nodes) * H->n_nodes * H->words;
   void* p = nullptr;
@@ -1175,7 +1193,7 @@ int sampled5(hm_graph* H, const uint32_t* const idx[6], const uint64_t S[6], uin
     total += a.S[j];
   }
   a.seed = seed;
-  if (total) HM_TRY(ensure_dense5(H, st));
+  if (total) HM_TRY(ensure_dense5(H, a.S, st));
   // the device class table: at most one class per candidate set, bounded by
   // the 2^26 patterns; sized for the output capacity at load 1/2
   const unsigned long long tcap = pow2_capacity(std::min<uint64_t>(std::max<uint64_t>(capacity, 1024), 1ull << 26));

@@ -129,3 +129,36 @@ def test_order5_errors(hm):
             hm.count_sampled5(g, 1.0, 1, capacity=1)
         with pytest.raises(hm.HMError):
             hm.count_sampled5_indices(g, {2: [nh.count(2)]})
+
+
+@pytest.mark.parametrize("mix,few", [({2: 1.0}, {2: [3]}), ({2: 0.8, 3: 0.2}, {2: [0], 3: [1]}), ({4: 1.0}, {4: [0, 1]}),
+                                     ({5: 0.9, 2: 0.1}, {5: [0], 2: [0]})])
+def test_few_sets_leave_the_bit_tensors(hm, mix, few):
+    """Samples of a hypergraph of a few hyperedges among many nodes take the
+    general path, which needs no bit tensors; with the tensors there (after a
+    call that pays for them) the same samples give the same classes."""
+    h = W.random_small(9950 + len(mix), 1000, 60, mix)
+    nh = core.normalise(h)
+    many = {j: np.tile(np.arange(nh.count(j)), 400) for j in (2, 3, 4) if nh.count(j)}
+
+    def route(g, samples):
+        hm.hm_profile_enable(True)
+        hm.hm_profile_reset()
+        try:
+            out = hm.count_sampled5_indices(g, samples)
+            names = hm.hm_profile_read()
+        finally:
+            hm.hm_profile_enable(False)
+            hm.hm_profile_reset()
+        assert ("k_dense5" in names) != ("k_sampled5" in names)
+        return "k_dense5" in names, out
+
+    with hm.hm_graph_create(h.members, h.offsets, h.n_nodes) as g:
+        dense, general = route(g, few)
+        assert not dense
+        pays, _ = route(g, many)
+        dense, again = route(g, few)
+        assert dense == pays
+        for x, y in zip(general, again):
+            assert np.array_equal(x, y)
+    assert pays or 4 in mix or 5 in mix
