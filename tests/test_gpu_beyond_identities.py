@@ -144,3 +144,42 @@ def test_first_calls_refuse_a_capture(hm):
             assert torch.equal(hm.count_exact(g, k), want[k])
         for s in (1, 2):
             assert torch.equal(hm.count_sampled(bare, 4, 0.05, s)[1], sampled[s - 1])
+
+
+@pytest.mark.parametrize("n,hubs,degree,pairs", [(4000, 40, 3700, 8000), (3000, 3, 2900, 6000), (8000, 5, 7900, 4000)])
+def test_walks_match_the_bit_rows(hm, n, hubs, degree, pairs):
+    """The walks and runs (walks split into shares among them) against the
+    bit rows: a graph without bit rows and one that turns to the walks against
+    count_exact_noalloc, and samples of every stratum, on handles that have
+    turned to the walks, against a handle's first call, which has not."""
+    members, offsets = _hubs(n, hubs, degree, pairs)
+    keep = hm.hm_get_option(hm.HM_OPT_BITSET_MAX_NODES)
+    hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, 0)
+    try:
+        bare = hm.hm_graph_create(members, offsets, n)
+    finally:
+        hm.hm_set_option(hm.HM_OPT_BITSET_MAX_NODES, keep)
+    rng = np.random.default_rng(n)
+
+    def profiled(call):
+        hm.hm_profile_enable(True)
+        hm.hm_profile_reset()
+        try:
+            return call().cpu().numpy(), hm.hm_profile_read()
+        finally:
+            hm.hm_profile_enable(False)
+            hm.hm_profile_reset()
+
+    with bare, hm.hm_graph_create(members, offsets, n) as turned:
+        want = _by_bit_rows(hm, turned)
+        got, names = profiled(lambda: hm.count_exact(turned, 4))
+        assert "k_walk" in names and np.array_equal(got, want)
+        assert np.array_equal(hm.count_exact(bare, 4).cpu().numpy(), want)
+        for _ in range(4):   # enough words read for the later calls to turn
+            hm.count_sampled(turned, 4, 0.2, 1)
+        for size in (1, 40, 700):
+            idx = {j: rng.integers(0, turned.stats()["n%d" % j], size) for j in (2, 3, 4)}
+            with hm.hm_graph_create(members, offsets, n) as fresh:
+                first = hm.count_sampled_indices(fresh, 4, idx)[1].cpu().numpy()
+            assert np.array_equal(hm.count_sampled_indices(turned, 4, idx)[1].cpu().numpy(), first), size
+            assert np.array_equal(hm.count_sampled_indices(bare, 4, idx)[1].cpu().numpy(), first), size

@@ -973,3 +973,47 @@ def test_long_hyperedges_of_large_builds(hm, sizes):
         torch.cuda.synchronize()
         took[name] = (time.perf_counter() - t) / 3
     assert took["nearly"] < took["ascending"] + 0.05, took
+
+
+@pytest.mark.parametrize("leaves", [65_535, 65_536, 70_000])
+def test_walks_beyond_every_table(hm, leaves):
+    """Three hubs over the same tens of thousands of nodes of a ring of
+    900,000: 4-cycle counts around the 65,535 paths that 16 bits hold, more
+    ranks than one range of any table, more marked values than one window.
+    Exact counts at orders 3 and 4 and the sampled pairs of a hub in closed
+    form."""
+    ring, hubs = 900_000, 3
+    n = ring + hubs
+    v = np.arange(ring)
+    leaf = 12 * np.arange(leaves)
+    chord = np.arange(850_000, 890_000, 5)   # (each closes one triangle with the ring)
+    e = np.concatenate([np.stack([v, (v + 1) % ring], 1), np.stack([chord, chord + 2], 1)] +
+                       [np.stack([leaf, np.full(leaves, ring + h)], 1) for h in range(hubs)])
+    e = np.sort(e, axis=1)
+    d = np.bincount(e.ravel(), minlength=n).astype(np.int64)
+    du, dv = d[e[:, 0]], d[e[:, 1]]
+    in_tri = np.zeros(len(e), bool)
+    in_tri[chord] = in_tri[chord + 1] = in_tri[ring:ring + len(chord)] = True
+    tri = len(chord)
+    pairs = lambda x: x * (x - 1) // 2
+    cyc = hubs * (hubs - 1) // 2 * pairs(leaves)
+    paw = int((du + dv - 4)[in_tri].sum()) // 2
+    star = int((d * (d - 1) * (d - 2) // 6).sum()) - paw
+    path = int(((du - 1) * (dv - 1)).sum()) - 3 * tri - 4 * cyc - 2 * paw
+    cls = lambda *bits: hm.hm_pattern_class(4, sum(1 << b for b in bits))
+    want = np.zeros(hm.hm_num_classes(4), np.int64)
+    want[cls(0, 2, 7)], want[cls(0, 1, 4)], want[cls(0, 2, 7, 4)], want[cls(0, 1, 2, 4)] = path, star, cyc, paw
+    rng = np.random.default_rng(leaves)
+    sample = ring + len(chord) + rng.integers(0, hubs * leaves, 200)   # pairs of a hub and a leaf
+    one = np.zeros_like(want)
+    one[cls(0, 2, 7, 4)] = (hubs - 1) * (leaves - 1)
+    one[cls(0, 1, 4)] = pairs(leaves - 1) + pairs(hubs - 1 + 2)
+    one[cls(0, 2, 7)] = 2 * (leaves - 1) + 2 + 2 * (leaves - 1)
+    with hm.hm_graph_create(e.astype(np.uint32).ravel(), np.arange(0, 2 * len(e) + 1, 2, dtype=np.uint64), n) as g:
+        got3 = hm.count_exact(g, 3).cpu().numpy()
+        got4 = hm.count_exact(g, 4).cpu().numpy()
+        raw = hm.count_sampled_indices(g, 4, {2: sample})[1].cpu().numpy()
+    assert got3[hm.hm_pattern_class(3, 7)] == tri
+    assert got3[hm.hm_pattern_class(3, 3)] == int(pairs(d).sum()) - 3 * tri
+    assert np.array_equal(got4, want)
+    assert np.array_equal(raw, 200 * one)
