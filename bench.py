@@ -71,17 +71,16 @@ def _unit_counts(e2: np.ndarray, e3: np.ndarray, n_nodes: int, words: int) -> di
 
 
 def _b4_positions(e2: np.ndarray, e3: np.ndarray, e4: np.ndarray, n_nodes: int) -> dict:
-    """Work of the 3-node-hyperedge step without bit rows, counted from the
-    strata as a walk of every set around every hyperedge meets it (k_tri_items
-    and k_run_items look at about half of the second kind: a run's pairs of
-    entries once each, and 4-node hyperedges not at all).  Per 3-node
+    """Positions that a walk of every set around every 3-node hyperedge meets,
+    counted from the strata: work equivalent to the 3-node-hyperedge step
+    without bit rows, whatever way it goes (what its kernels look at:
+    _item_counts).  Per 3-node
     hyperedge e = {a<b<c}: the shortest pairwise row among a, b, c (each entry
     tested against the other two members) and the 4-node hyperedges holding e.
     Per entry of the pair index (a pair P of e with the third node t) whose
     run holds L >= 2 entries: the other L - 1 entries of the run when L - 1 <=
     d(t) + L(P0, t) + L(P1, t) + (4-node hyperedges holding e), else those
-    lists.  Each position is a few lookups (a third node, a search in a short
-    list, a dense-row word or a hash probe)."""
+    lists."""
     n = np.int64(n_nodes)
     if len(e3) == 0:
         return {"positions_b4": 0, "positions_runs": 0, "hyperedges": 0, "entries": 0, "entries_active": 0}
@@ -117,6 +116,74 @@ def _b4_positions(e2: np.ndarray, e3: np.ndarray, e4: np.ndarray, n_nodes: int) 
         runs += int(np.where(on, np.where(L - 1 <= listed, L - 1, listed), 0).sum())
     return {"positions_b4": int((dmin + holding).sum()), "positions_runs": runs, "hyperedges": int(len(t)),
             "entries": 3 * int(len(t)), "entries_active": active}
+
+
+HUB_MIN_DEGREE = 256      # pairwise neighbours from which a node has a dense row
+HUB_ROW_BYTES = 32 << 20   # of all dense rows
+
+
+def _common_neighbour(e2: np.ndarray, pairs: np.ndarray, n_nodes: int) -> np.ndarray:
+    """Whether the nodes of each pair share a pairwise neighbour."""
+    n = np.int64(n_nodes)
+    both = np.concatenate([e2, e2[:, ::-1]]).astype(np.int64) if len(e2) else np.zeros((0, 2), np.int64)
+    keys = np.sort(both[:, 0] * n + both[:, 1])
+    if len(keys) == 0:
+        return np.zeros(len(pairs), bool)
+    adj, off = keys % n, np.searchsorted(keys, np.arange(n_nodes + 1, dtype=np.int64) * n)
+    deg = np.diff(off)
+    x, y = pairs[:, 0].astype(np.int64), pairs[:, 1].astype(np.int64)
+    short, other = np.where(deg[x] <= deg[y], x, y), np.where(deg[x] <= deg[y], y, x)
+    found = np.zeros(len(pairs), bool)
+    left = np.flatnonzero(deg[short] > 0)
+    step = 0
+    while len(left):   # (most pairs that share one find it within a few entries)
+        k = other[left] * n + adj[off[short[left]] + step]
+        at = np.minimum(np.searchsorted(keys, k), len(keys) - 1)
+        found[left] = keys[at] == k
+        step += 1
+        left = left[~found[left] & (deg[short[left]] > step)]
+    return found
+
+
+def _item_counts(e2: np.ndarray, e3: np.ndarray, n_nodes: int) -> dict:
+    """Items that k_tri_items and k_run_items take, from the strata by the
+    rules of their plans.  Per 3-node hyperedge whose three pairs each have
+    common neighbours: the shortest row of its members, or, where all three
+    have dense rows of fewer words than that, those words.  Per entry (the pair
+    {x, y} with the third node t) but the last of a run, unless nothing is
+    related to t: the later entries of the run, or, where they are more, t's
+    pairwise neighbours and the entries of the runs of {x, t} and {y, t}, those
+    above t of each."""
+    n = np.int64(n_nodes)
+    if len(e3) == 0:
+        return {"tri_items": 0, "run_items": 0}
+    deg = np.bincount(e2.reshape(-1).astype(np.int64), minlength=n_nodes) if len(e2) else np.zeros(n_nodes, np.int64)
+    above = np.bincount(e2[:, 0].astype(np.int64), minlength=n_nodes) if len(e2) else np.zeros(n_nodes, np.int64)
+    t = e3.astype(np.int64)
+    a, b, c = t[:, 0], t[:, 1], t[:, 2]
+    pk = np.concatenate([a * n + b, a * n + c, b * n + c])
+    third = np.concatenate([c, b, a])
+    uk, inv, cnt = np.unique(pk, return_inverse=True, return_counts=True)
+    shared = _common_neighbour(e2, np.stack([uk // n, uk % n], 1), n_nodes)[inv].reshape(3, -1).all(axis=0)
+    dmin = np.minimum(np.minimum(deg[a], deg[b]), deg[c])
+    words = (n_nodes + 31) // 32
+    rows = min(HUB_ROW_BYTES // (4 * words), 2 * len(e2) // HUB_MIN_DEGREE, n_nodes)
+    least = max(HUB_MIN_DEGREE, int(np.sort(deg)[-rows]) if rows else n_nodes)
+    tri = np.where((dmin >= least) & (dmin > words), words, dmin)[shared].sum()
+    order = np.lexsort((third, inv))
+    run, node = inv[order], third[order]
+    first = np.cumsum(cnt) - cnt
+    later = first[run] + cnt[run] - 1 - np.arange(len(run))
+    place = run * n + node   # ascending
+
+    def listed(x, z):   # entries of the run of {x, z}, and those above z
+        i = np.searchsorted(uk, np.minimum(x, z) * n + np.maximum(x, z))
+        return cnt[i], first[i] + cnt[i] - np.searchsorted(place, i * n + z, side="right")
+
+    lx, ax = listed(uk[run] // n, node)
+    ly, ay = listed(uk[run] % n, node)
+    items = np.where(later > deg[node] + lx + ly, above[node] + ax + ay, later)
+    return {"tri_items": int(tri), "run_items": int(items[(deg[node] > 0) | (lx > 1) | (ly > 1)].sum())}
 
 
 def exact_source_digest() -> str:
@@ -248,12 +315,14 @@ def large_workloads(hm, W, torch, seeds: int = 32, exact_only: bool = False) -> 
         prof = hm.hm_profile_read()
         hm.hm_profile_enable(False)
         kernels = {k: {"launches": n, "avg_ms": ms / max(n, 1)} for k, (n, ms) in prof.items()}
-        model = _b4_positions(g.export(2), g.export(3), g.export(4), h.n_nodes)
+        walked = _b4_positions(g.export(2), g.export(3), g.export(4), h.n_nodes)
+        items = _item_counts(g.export(2), g.export(3), h.n_nodes)
         lookup = None
         if "k_tri_items" in kernels and "k_run_items" in kernels:
             ms = kernels["k_tri_items"]["avg_ms"] + kernels["k_run_items"]["avg_ms"]
-            lookup = {"kernels": ["k_tri_items", "k_run_items"], "ms": ms,
-                      "positions_per_s": (model["positions_b4"] + model["positions_runs"]) / (ms / 1e3), **model}
+            lookup = {"kernels": ["k_tri_items", "k_run_items"], "ms": ms, **items,
+                      "positions_per_s": (items["tri_items"] + items["run_items"]) / (ms / 1e3),
+                      "equivalent_work": walked}
             # HBM bytes of the two kernels from the committed counter runs
             # (FETCH_SIZE + WRITE_SIZE per launch), while the sources match
             meas = measured_lookup_traffic().get(name)

@@ -70,3 +70,45 @@ def test_b4_positions_match_loop(seed, n, sizes):
 def test_b4_positions_empty():
     e = np.zeros((0, 3), np.uint32)
     assert bench._b4_positions(np.zeros((0, 2), np.uint32), e, np.zeros((0, 4), np.uint32), 10)["positions_b4"] == 0
+
+
+def _loop_items(e2, e3, n):
+    adj = [set() for _ in range(n)]
+    for x, y in e2.tolist():
+        adj[x].add(y)
+        adj[y].add(x)
+    run = {}
+    for t in e3.tolist():
+        for i, j in ((0, 1), (0, 2), (1, 2)):
+            run.setdefault((t[i], t[j]), []).append(t[3 - i - j])
+    words = (n + 31) // 32
+    tri = runs = 0
+    for e in e3.tolist():
+        if all(adj[e[i]] & adj[e[j]] for i, j in ((0, 1), (0, 2), (1, 2))):
+            d = min(len(adj[v]) for v in e)
+            tri += words if d >= bench.HUB_MIN_DEGREE and d > words else d
+    for (x, y), thirds in run.items():
+        thirds.sort()
+        for i, t in enumerate(thirds[:-1]):
+            xt, yt = run[min(x, t), max(x, t)], run[min(y, t), max(y, t)]
+            if not adj[t] and len(xt) < 2 and len(yt) < 2:
+                continue
+            later = len(thirds) - 1 - i
+            lists = (adj[t], xt, yt)
+            runs += sum(z > t for l in lists for z in l) if later > sum(map(len, lists)) else later
+    return {"tri_items": tri, "run_items": runs}
+
+
+@pytest.mark.parametrize("seed,n,sizes", [(5, 60, (200, 400, 200)), (7, 120, (900, 700, 500)), (9, 16, (40, 150, 80)),
+                                          (11, 700, (2500, 900, 10)), (13, 50, (1, 300, 1))])
+def test_item_counts_match_loop(seed, n, sizes, monkeypatch):
+    e2, e3, _ = _hub_strata(seed, n, *sizes)
+    assert bench._item_counts(e2, e3, n) == _loop_items(e2, e3, n)
+    monkeypatch.setattr(bench, "HUB_MIN_DEGREE", 12)   # (dense rows among these too)
+    assert bench._item_counts(e2, e3, n) == _loop_items(e2, e3, n)
+
+
+def test_item_counts_empty():
+    e3 = np.zeros((0, 3), np.uint32)
+    assert bench._item_counts(np.array([[0, 1]], np.uint32), e3, 10) == {"tri_items": 0, "run_items": 0}
+    assert bench._item_counts(np.zeros((0, 2), np.uint32), np.array([[0, 1, 2]], np.uint32), 10) == {"tri_items": 0, "run_items": 0}
