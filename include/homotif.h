@@ -133,7 +133,15 @@ int hm_graph_export(const hm_graph* H, int j, uint32_t* out);
 
 /* Exact counts of every order-k motif (k = 3: Algorithm 2; k = 4:
  * Algorithm 3).  counts: device int64 array of hm_num_classes(k) values,
- * overwritten.  Asynchronous on `stream`. */
+ * overwritten.  Asynchronous on `stream` for graphs with adjacency bit rows
+ * (HM_OPT_BITSET_MAX_NODES).  Order 4 without them waits for the stream once,
+ * supports at most 2^31 nodes with pairwise hyperedges (HM_EUNSUPPORTED past
+ * that), and its first call builds indices that stay with the graph (8 bytes
+ * per node, dense rows of at most 32 MiB, 57 to 97 bytes per pair inside a
+ * 3-node hyperedge).  Graphs with bit rows of more than 2574 nodes whose squared
+ * pairwise degrees add up to 2^30 / ceil(n_nodes / 32) or more count order 4
+ * the same way, without the wait.  While `stream` is captured the bit rows
+ * are used; without them the call returns HM_EDEVICE. */
 int count_exact(const hm_graph* H, int k, int64_t* counts, void* stream);
 
 /* Exact counts of every order-k motif (k = 3 or 4, as count_exact) of each
@@ -250,7 +258,10 @@ int count_sampled_sizes(const hm_graph* H, int k, uint64_t s2, uint64_t s3, uint
  * Outputs (device, `capacity` entries): canon (uint32), raw (int64), est
  * (float), the classes found in ascending canonical order; *n_classes (host)
  * receives their number.  Synchronous.  The first call on a graph builds its
- * list and hash set of 5-node hyperedges (kept with the graph).
+ * list and hash set of 5-node hyperedges (kept with the graph).  On graphs with
+ * bit rows of at most 1024 nodes a call whose samples can meet many sets also
+ * builds bit tensors of 3 n_nodes^2 ceil(n_nodes / 32) words, 402 MB at 1024
+ * nodes, kept with the graph.
  * Limits: each sampled hyperedge may have at most 4096 nodes within
  * 5 - |e| hops and fewer than 2^32 candidate sets (HM_EUNSUPPORTED past
  * that: the enumeration is meant for the sparse or small hypergraphs the
@@ -287,7 +298,12 @@ int hm_sample_draw(const hm_graph* H, int k, double fraction, uint64_t seed, int
  * fp32.
  *   est  device float array of hm_num_classes(k) values (required)
  *   raw  device int64 array of the unscaled counts, or NULL
- * fraction in (0, 1]; HM_EINVAL otherwise.  Asynchronous on `stream`. */
+ * fraction in (0, 1]; HM_EINVAL otherwise.  Asynchronous on `stream`, but for
+ * the first order-4 call on a graph without bit rows, which builds the indices
+ * of count_exact, statistics (48 bytes per pair and per node) and an index of
+ * the 4-node hyperedges (36 to 68 bytes per 3-node subset) that stay with the
+ * graph, waits once, and returns HM_EDEVICE while `stream` is captured.  (Repeated calls on the graphs with bit rows that count_exact
+ * counts as without them come to do the same, without a wait.) */
 int count_sampled(const hm_graph* H, int k, double fraction, uint64_t seed, int allocation, float* est,
                   int64_t* raw, void* stream);
 

@@ -384,8 +384,8 @@ struct hm_graph {
   // first use on small hypergraphs with bit rows
   uint32_t* dense5 = nullptr;
   // raw counters of the sampled counting calls (kHistCopies copies of 256),
-  // then the tail and head of their work queue (the two words after one
-  // unused); zero between calls
+  // then the tails and the heads of their work queue's kQueueParts parts,
+  // kQueueStep words apart; zero between calls
   unsigned long long* sample_hist = nullptr;
   // buffers and captured HIP graph of the batched null-model pipeline
   hm::NullPlan* null_plan = nullptr;

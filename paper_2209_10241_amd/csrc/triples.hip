@@ -556,8 +556,8 @@ __global__ void __launch_bounds__(kThreads) k_run_plan(View v, PairLinks pl, con
 
 // The related t, z are counted by their nine bits (x ~ y, class of t, class
 // of z, t ~ z, {x, t, z}, {y, t, z}, whether {x, y, t} and {x, y, z} are the
-// two smallest 3-node hyperedges of the set), one set of counters per
-// wavefront, which become class counts at the end.
+// two smallest 3-node hyperedges of the set), in two sets of counters that the
+// wavefronts share by pairs, which become class counts at the end.
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6,6))) k_run_items(View v, PairLinks pl, uint64_t m,
                                                         const RunRec* __restrict__ rec,
                                                         const unsigned long long* __restrict__ pre,
