@@ -145,22 +145,40 @@ struct ExactArgs {
 };
 
 // Order 4: items are the pairs of G2 (case (c); on the identity route also one
-// per node), then the 3-node hyperedges (case (b)), then chunks of kA4Chunk
-// 4-node hyperedges (case (a)).  Dynamic LDS holds b4_set_words(W) words per wavefront and,
+// per node), then the 3-node hyperedges, one or two at a time (case (b)), then
+// chunks of kA4Chunk 4-node hyperedges (case (a)).  Dynamic LDS holds b4_set_words(W, b4_per_wave(W)) words per wavefront and,
 // with LB, a copy of the whole bit matrix (N x W words) and of the row
 // starts of G2 and of the incidence lists, so that every adjacency word and
 // row bound the items read comes from LDS rather than from L2.
+//
+// 3-node hyperedges by half wavefronts (rows of at most 32 words): where the
+// nodes are in about as many each, the count is bound by how many items are
+// under way, and halves are the better; where a few nodes are in most, the
+// launch ends with the chain of the items there, which halves make longer.  So
+// they are taken when no node is in more than kEvenMost of them, or kEvenRatio
+// times the mean (which the launch finds in 0.5 us).  Repeated counts, us by
+// wavefronts, by halves and by this rule: even graphs of 400 nodes with 7,200
+// of them (a node is in 79 at most, 54 on average) 22.6, 19.5 and 20.5, 300
+// with 30,000 48.1, 39.3 and 40.3; a communication recipe's of 300 with 23,900
+// (6,385 and 239) 102, 132 and 104, of 470 with 7,800 (2,493 and 50) 33.1, 49
+// and 33.8.  (Pairs by halves too: 22.8 at 400 nodes, 140 at 300.)
+constexpr uint32_t kEvenMost = 128, kEvenRatio = 4;
 template <bool LB, bool ID>
 __global__ void __launch_bounds__(kExact4Threads) k_exact4_bits(ExactArgs a) {
   __shared__ uint8_t lut[2048];
+  __shared__ uint32_t most_of[kExact4Waves];   // 3-node hyperedges at a node, the most
   __shared__ unsigned long long h_main[256], h_sub[256], h_g2[256], h_id[8];
   __shared__ uint32_t ylist[kExact4Waves][kWave];
   extern __shared__ uint32_t dyn_lds[];
   View v = a.v;
   uint32_t* b4_sets = dyn_lds;
+  const bool may_halve = b4_per_wave(v.W) == 2;
+  // (at most 1,024 nodes: one each, on its way while the rows are copied)
+  uint32_t at_node = 0;
+  if (may_halve && threadIdx.x < v.N) at_node = v.i3_off[threadIdx.x + 1] - v.i3_off[threadIdx.x];
   if (LB) {
-    // the rows start 16 * (4 * W + 64) words in: 16-byte aligned
-    uint32_t* rows = dyn_lds + kExact4Waves * b4_set_words(v.W);
+    // the rows start a multiple of 16 words in: 16-byte aligned
+    uint32_t* rows = dyn_lds + kExact4Waves * b4_set_words(v.W, b4_per_wave(v.W));
     const uint32_t n = v.N * v.W, n4 = n / 4;
     const uint4* src = reinterpret_cast<const uint4*>(v.bits);
     uint4* dst = reinterpret_cast<uint4*>(rows);
@@ -185,17 +203,24 @@ __global__ void __launch_bounds__(kExact4Threads) k_exact4_bits(ExactArgs a) {
     h_g2[threadIdx.x] = 0;
   }
   if (threadIdx.x < 8) h_id[threadIdx.x] = 0;
-  __syncthreads();
   const int wv = threadIdx.x / kWave;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  uint32_t* sets = b4_sets + wv * b4_set_words(v.W);
+  for (int d = 1; d < kWave; d <<= 1) at_node = max(at_node, uint32_t(__shfl_xor(int(at_node), d, kWave)));
+  if (lane == 0) most_of[wv] = at_node;
+  __syncthreads();
+  uint32_t most = most_of[lane % kExact4Waves];
+  for (uint32_t d = 1; d < kExact4Waves; d <<= 1) most = max(most, uint32_t(__shfl_xor(int(most), int(d), kWave)));
+  most = uint32_t(__builtin_amdgcn_readfirstlane(int(most)));
+  uint32_t* sets = b4_sets + wv * b4_set_words(v.W, b4_per_wave(v.W));
+  const bool halves =
+      may_halve && (most <= kEvenMost || uint64_t(most) * v.N <= uint64_t(kEvenRatio) * 3 * a.n3);
   const C4Lanes L = c4_lanes(v.W);
   C4Acc acc;
   IdAcc ida;
   if (ID) id_zero(ida); else c4_zero(acc);
   // (c) items: the pairs of G2, then (identity route) one per node
   const uint64_t nc = ID ? a.n2 + v.N : a.n2;
-  const uint64_t n23 = nc + a.n3;
+  const uint64_t n23 = nc + (halves ? (a.n3 + 1) / 2 : a.n3);
   const uint64_t items = n23 + (a.n4 + kA4Chunk - 1) / kA4Chunk;
   const uint64_t n_waves = uint64_t(gridDim.x) * kExact4Waves;
   for (uint64_t i = uint64_t(blockIdx.x) * kExact4Waves + wv; i < items; i += n_waves) {
@@ -205,7 +230,8 @@ __global__ void __launch_bounds__(kExact4Threads) k_exact4_bits(ExactArgs a) {
     } else if (i < nc) {
       id_node_item(v, uint32_t(i - a.n2), ida);
     } else if (i < n23) {
-      b4_item(v, i - nc, a.n3, sets, lut, h_main, h_sub);
+      if (halves) b4_item<2>(v, 2 * (i - nc), a.n3, sets, lut, h_main, h_sub);
+      else b4_item(v, i - nc, a.n3, sets, lut, h_main, h_sub);
     } else {
       const uint64_t e = (i - n23) * kA4Chunk + lane;
       if (e < a.n4)
@@ -332,7 +358,7 @@ bool launch_bits_count(const hm_graph* H, int k, const uint8_t* lut, unsigned lo
     const size_t rows = (size_t(v.N) * v.W + 3 * (size_t(v.N) + 1)) * 4;
     const bool lb = rows <= kLdsBitsMaxBytes;
     const bool id = use_identities(v.N, v.W);
-    const size_t lds = size_t(kExact4Waves) * b4_set_words(v.W) * 4 + (lb ? rows : 0);
+    const size_t lds = size_t(kExact4Waves) * b4_set_words(v.W, b4_per_wave(v.W)) * 4 + (lb ? rows : 0);
     const uint64_t items = n2 + (id ? v.N : 0) + n3 + (n4 + kA4Chunk - 1) / kA4Chunk;
     const void* kern = lb ? (id ? reinterpret_cast<const void*>(k_exact4_bits<true, true>)
                                 : reinterpret_cast<const void*>(k_exact4_bits<true, false>))

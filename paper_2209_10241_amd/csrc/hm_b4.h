@@ -21,10 +21,7 @@ constexpr int kB4Batch = 4;   // incidence entries a lane loads at once
 // Rows of at most 32 words may take an item (a 3-node hyperedge, or a pair of
 // the identity route) per half of the wavefront.  The copies of a null batch
 // do: their count is bound by how many items are under way.  One graph's count
-// does not: it ends with the chain of its longest items, which half a
-// wavefront makes longer: 121 us a call by wavefronts and 160 by halves for
-// 300 nodes with 15,000 pairs and 24,000 3-node hyperedges, 442 and 530 for
-// 1,000 nodes with 48,000 and 56,000.
+// does where its items are alike (see k_exact4_bits).
 __host__ __device__ constexpr uint32_t b4_per_wave(uint32_t W) { return W <= 32 ? 2 : 1; }
 // LDS words one group of lanes needs for rows of W words (T_ab, T_ac, T_bc, Q
 // and a list of as many candidate nodes as it has lanes), and a wavefront of
