@@ -192,7 +192,11 @@ int device_luts(int device, const uint8_t** lut4, const uint8_t** lut3) {
 // block released with dfree is assumed idle (its users were synchronised);
 // one released with dfree_on stays pending until an event recorded on the
 // given stream after its last use has completed, so it is never handed out
-// while work enqueued before the release may still touch it.
+// while work enqueued before the release may still touch it, except to the
+// same stream (dalloc_on): calls enqueued one behind another then share their
+// temporaries, where each took its own, which a full cache gave back one by one
+// to the runtime while the GPU was busy (40 sampled calls of 1 GiB each took 2.7
+// to 54 ms a call, 1.7 one at a time).
 namespace {
 struct BlockInfo {
   int device;
@@ -203,6 +207,8 @@ struct BlockInfo {
 struct Pending {
   hipEvent_t ev;
   int device;
+  hipStream_t st;   // the event's stream
+  bool captured;    // the release was recorded into a graph, whose replays use the blocks
   std::vector<std::pair<void*, BlockInfo>> blocks;
 };
 std::mutex g_pool_mu;
@@ -283,9 +289,32 @@ void* take_cached(int dev, size_t cls, bool filled = false) {
   g_live[p] = BlockInfo{dev, cls};
   return p;
 }
-}  // namespace
 
-int dalloc(void** p, size_t bytes) {
+// caller holds g_pool_mu: a block of (dev, cls) still pending on st, which is
+// made to wait for its release, or null.  (A stream's later work would run
+// after the release anyway; the wait also holds when the handle has come to
+// name another stream.)  Not while st is captured: a replay would not wait.
+void* take_pending(int dev, size_t cls, hipStream_t st) {
+  for (Pending& q : g_pending) {
+    if (q.captured || q.st != st || q.device != dev) continue;
+    for (size_t i = 0; i < q.blocks.size(); ++i) {
+      if (q.blocks[i].second.bytes != cls || q.blocks[i].second.filled) continue;
+      if (being_captured(st)) return nullptr;
+      if (hipStreamWaitEvent(st, q.ev, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      void* p = q.blocks[i].first;
+      q.blocks[i] = q.blocks.back();
+      q.blocks.pop_back();
+      g_live[p] = BlockInfo{dev, cls};
+      return p;
+    }
+  }
+  return nullptr;
+}
+
+int alloc_block(void** p, size_t bytes, bool on_stream, hipStream_t st) {
   *p = nullptr;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
@@ -300,6 +329,7 @@ int dalloc(void** p, size_t bytes) {
     if (!*p && !g_pending.empty()) {
       reap_pending();
       *p = take_cached(dev, cls);
+      if (!*p && on_stream) *p = take_pending(dev, cls, st);
     }
     if (*p) return HM_OK;
   }
@@ -314,6 +344,11 @@ int dalloc(void** p, size_t bytes) {
   g_live[*p] = BlockInfo{dev, cls};
   return HM_OK;
 }
+
+}  // namespace
+
+int dalloc(void** p, size_t bytes) { return alloc_block(p, bytes, false, nullptr); }
+int dalloc_on(void** p, size_t bytes, hipStream_t st) { return alloc_block(p, bytes, true, st); }
 
 int dalloc_filled(void** p, size_t bytes, bool* filled) {
   *p = nullptr;
@@ -366,6 +401,7 @@ void dfree_on(void* const* ps, size_t n, hipStream_t st) {
     g_live.erase(it);
   }
   if (blocks.empty()) return;
+  const bool captured = being_captured(st);
   // one event for the batch, shared by its blocks
   const int dev = blocks.front().second.device;
   hipEvent_t ev = nullptr;
@@ -385,7 +421,7 @@ void dfree_on(void* const* ps, size_t n, hipStream_t st) {
     for (auto& b : blocks) cache_block(b.first, b.second);
     return;
   }
-  g_pending.push_back(Pending{ev, dev, std::move(blocks)});
+  g_pending.push_back(Pending{ev, dev, st, captured, std::move(blocks)});
 }
 
 void dfree_on(void* p, hipStream_t st) { dfree_on(&p, 1, st); }

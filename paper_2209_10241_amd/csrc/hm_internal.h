@@ -211,6 +211,8 @@ class ProfileScope {
 
 // ----------------------------------------------------------------- device allocations
 int dalloc(void** p, size_t bytes);
+// a block that st alone uses first: also one whose release on st is pending
+int dalloc_on(void** p, size_t bytes, hipStream_t st);
 // release a block whose users are synchronised
 void dfree(void* p);
 // release blocks that work already enqueued on st may still use (one event

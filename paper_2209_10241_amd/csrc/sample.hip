@@ -1448,8 +1448,9 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
     sc.countmax[c] = c < t.n_classes[k] ? t.countmax[k][c] : 1;
   }
   // work queue of heavy samples (order 4 without bit rows); its buffers are
-  // released in stream order: the caching allocator hands them out again only
-  // once an event recorded on st after the drain and the finish has completed
+  // released in stream order: the caching allocator hands them to the next call
+  // on st at once, and to others once an event recorded on st after the drain
+  // and the finish has completed
   a.q.job = nullptr;
   a.q.cap = 0;
   a.q.tail = H->sample_hist + uint64_t(kHistCopies) * kSampleHistStride;
@@ -1470,9 +1471,9 @@ int launch_sampled(const hm_graph* H, int k, const uint32_t* const idx[5], const
   if (k == 4 && !bits) {
     a.q.cap = std::min<uint64_t>(kQueuePerSample * scale * (a.d.S[2] + a.d.S[3]) / kQueueParts + 65536,
                                  kQueueMax / kQueueParts);
-    int rc = dalloc(&rel.p[0], kQueueParts * a.q.cap * sizeof(uint4));
-    if (rc == HM_OK) rc = dalloc(&rel.p[1], (a.d.S[2] + 1) * sizeof(uint4));
-    if (rc == HM_OK) rc = dalloc(&rel.p[2], (a.d.S[3] + 1) * sizeof(uint32_t));
+    int rc = dalloc_on(&rel.p[0], kQueueParts * a.q.cap * sizeof(uint4), st);
+    if (rc == HM_OK) rc = dalloc_on(&rel.p[1], (a.d.S[2] + 1) * sizeof(uint4), st);
+    if (rc == HM_OK) rc = dalloc_on(&rel.p[2], (a.d.S[3] + 1) * sizeof(uint32_t), st);
     if (rc != HM_ENOMEM || !H->bits) HM_TRY(rc);
     if (rc == HM_OK) {
       a.q.job = static_cast<uint4*>(rel.p[0]);

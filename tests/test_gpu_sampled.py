@@ -434,3 +434,29 @@ def test_chunk_sizes_by_samples_match_bit_rows(hm):
             idx = {2: rng.integers(0, g.stats()["n2"], s2), 3: rng.integers(0, g.stats()["n3"], s3)}
             want = hm.count_sampled_indices(g, 4, idx)[1].cpu().numpy()
             assert np.array_equal(hm.count_sampled_indices(f, 4, idx)[1].cpu().numpy(), want), (s2, s3)
+
+
+def test_enqueued_calls_share_their_queue(hm):
+    """Calls enqueued one behind another on a stream, none of them waited for,
+    take one work queue between them: the device's free memory falls by one
+    queue (at most 1 GiB, as a power of two) and the small blocks, not by one
+    queue a call, and every call counts what it counts alone."""
+    import torch
+    h = W.random_small(3, 3000, 30000, {2: 0.6, 3: 0.27, 4: 0.13})
+    with _graph(hm, h, bit_rows=False) as g:
+        want = [hm.count_sampled(g, 4, 0.6, seed)[1].cpu() for seed in range(24)]
+        raw = [torch.zeros(len(want[0]), dtype=torch.int64, device="cuda") for _ in want]
+        est = torch.zeros(len(want[0]), dtype=torch.float32, device="cuda")
+        x = torch.ones(8192, 8192, device="cuda")
+        y = x @ x
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        for _ in range(8):   # tens of milliseconds of work for the calls to pile up behind
+            torch.mm(x, x, out=y)
+        for seed in range(24):
+            hm.count_sampled(g, 4, 0.6, seed, est=est, raw=raw[seed])
+        taken = free - torch.cuda.mem_get_info()[0]
+        torch.cuda.synchronize()
+        assert taken <= 2 << 30
+        for seed in range(24):
+            assert torch.equal(raw[seed].cpu(), want[seed]), seed
