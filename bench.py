@@ -28,11 +28,11 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_exact_k4_facetoface_N
 # hardware counters is only reported while these are unchanged
 EXACT_SOURCES = ("exact.hip", "hm_items.h", "hm_b4.h", "hm_device.h", "hm_internal.h")
 HBM_PEAK_GBS = 8000.0
-# integer VALU issue rate: 256 CUs x 64 lanes per cycle x 2.4 GHz
 # worker threads (one stream each) of the count_exact_many call that the
 # headline measurement makes: 3 gave 36 us per hypergraph, 7 or 8 about 31.5,
 # 10 to 16 no better
 PIPELINE = 8
+# integer VALU issue rate: 256 CUs x 64 lanes per cycle x 2.4 GHz
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 
 

@@ -843,11 +843,13 @@ __device__ void quad_sets5(LdsDense5& L, const Sampled5Args& s, const Dense5& d,
 // Every sample of the call.  Tasks: the 3-node samples in nc3 shares each,
 // the pair samples in nc2, then one per 4-node sample, then the 5-node
 // samples 256 at a time.  A pair sample is N^2/2 node pairs of W words at about 75
-// operations a word, bound by integer issue: on the communication recipe at
-// N = 200 (1.3e6 candidate sets a pair sample, 5% of every stratum drawn)
-// this launch takes 0.21 ms where the general path's k_sampled5, which fills
-// in and classifies every set, took 53.3 ms; the 3-node samples' shares come
-// first, since one workgroup a sample left a tail (0.40 ms).
+// operations a word.  On the communication recipe at N = 200 (1.3e6 candidate
+// sets a pair sample, 5% of every stratum drawn) this launch takes 0.21 ms where
+// the general path's k_sampled5, which fills in and classifies every set, took
+// 53.3 ms; the 3-node samples' shares come first, since one workgroup a sample
+// left a tail (0.40 ms).  What bounds it is latency with few wavefronts in
+// flight, six a CU: 60% of their cycles wait, 29% of the VALU issue rate is
+// used.
 __global__ void __launch_bounds__(kThreads5) k_dense5(Sampled5Args a, Dense5 d, Tables5 tables, uint32_t nc2,
                                                       uint32_t nc3,
                                                       unsigned long long* __restrict__ pair_bins) {
