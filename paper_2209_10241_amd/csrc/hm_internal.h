@@ -228,8 +228,8 @@ void dfree_on(void* const* ps, size_t n, hipStream_t st);
 int dalloc_filled(void** p, size_t bytes, bool* filled);
 void mark_filled(void* p);
 
-// Temporaries of one call, released in stream order (see dfree_on), also
-// when the call returns early on an error.
+// Temporaries of one call, used on st alone and released in its order (see
+// dalloc_on, dfree_on), also when the call returns early on an error.
 struct Scratch {
   std::vector<void*> ptrs;
   hipStream_t st;
@@ -238,7 +238,7 @@ struct Scratch {
   template <typename T>
   int get(T** p, uint64_t n) {
     void* q = nullptr;
-    HM_TRY(dalloc(&q, size_t(n ? n : 1) * sizeof(T)));
+    HM_TRY(dalloc_on(&q, size_t(n ? n : 1) * sizeof(T), st));
     ptrs.push_back(q);
     *p = static_cast<T*>(q);
     return HM_OK;

@@ -183,3 +183,30 @@ def test_walks_match_the_bit_rows(hm, n, hubs, degree, pairs):
                 first = hm.count_sampled_indices(fresh, 4, idx)[1].cpu().numpy()
             assert np.array_equal(hm.count_sampled_indices(turned, 4, idx)[1].cpu().numpy(), first), size
             assert np.array_equal(hm.count_sampled_indices(bare, 4, idx)[1].cpu().numpy(), first), size
+
+
+def test_enqueued_counts_share_their_temporaries(hm):
+    """Counts by the walks enqueued one behind another, none of them waited
+    for, take the temporaries of one: a hundred of them take no more of the
+    device's free memory than two would, and count what one counts alone."""
+    import torch
+    members, offsets = _hubs(8000, 5, 7900, 4000)
+    outs = [torch.zeros(hm.hm_num_classes(4), dtype=torch.int64, device="cuda") for _ in range(100)]
+    with hm.hm_graph_create(members, offsets, 8000) as g:
+        want = hm.count_exact(g, 4).clone()
+        x = torch.ones(8192, 8192, device="cuda")
+        y = x @ x
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        for _ in range(8):   # tens of milliseconds of work for the counts to pile up behind
+            torch.mm(x, x, out=y)
+        hm.count_exact(g, 4, out=outs[0])
+        hm.count_exact(g, 4, out=outs[1])
+        two = free - torch.cuda.mem_get_info()[0]
+        for out in outs[2:]:
+            hm.count_exact(g, 4, out=out)
+        taken = free - torch.cuda.mem_get_info()[0]
+        torch.cuda.synchronize()
+        assert taken <= two + (8 << 20)   # (the runtime's own queues and events may grow)
+        for out in outs:
+            assert torch.equal(out, want)
